@@ -137,6 +137,7 @@ class Plan:
     def __init__(self, handle: ctypes.c_void_p):
         self._h = handle
         self._shapes = None
+        self._spec = None
 
     def shapes(self):
         """(out_shape, a_shape, b_shape), computed once (a plan's shapes never change)."""
@@ -144,6 +145,11 @@ class Plan:
             d = self.desc()
             self._shapes = (self.out_shape(), tuple(d.a.shape[:d.a.ndim]), tuple(d.b.shape[:d.b.ndim]))
         return self._shapes
+
+    def _new_spec(self):
+        """What the native calls take in place of this object (handle and shapes)."""
+        self._spec = _native().spec(self.handle.value, *self.shapes())
+        return self._spec
 
     @property
     def handle(self):
@@ -153,6 +159,7 @@ class Plan:
 
     def destroy(self):
         if self._h:
+            self._spec = None
             lib().merit_plan_destroy(self._h)
             self._h = None
 
@@ -270,7 +277,42 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+# The operations of csrc/torch_calls.cpp, in its order.
+(_CONV2D, _CONV2D_PACKED, _RESIDUAL, _POOL2D, _SAD, _DEPTHWISE, _SEPFILTER, _BILATERAL, _CORRELATION) = range(9)
+_calls = None
+
+
+def _native():
+    """The module built from csrc/torch_calls.cpp (built here only if there is none)."""
+    global _calls
+    if _calls is None:
+        import importlib.util
+
+        import torch  # noqa: F401  (its libraries, before the module that uses them)
+        lib()
+        if not os.path.exists(_build.CALLS_PATH):
+            _build.build_torch_calls()
+        spec = importlib.util.spec_from_file_location(__package__ + "._torch_calls", _build.CALLS_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _calls = module
+    return _calls
+
+
+def _ordinary(where, op, plan, *args):
+    """The call natively if it is of the ordinary form (see csrc/torch_calls.cpp), else None."""
+    spec = plan._spec or plan._new_spec()
+    r = _calls.call(op, spec, *args)
+    if r.__class__ is int:
+        raise MeritError(r, where)
+    return r
+
+
 def merit_conv2d(plan: Plan, x, w, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_conv2d", _CONV2D, plan, x, w)
+        if r is not None:
+            return r
     import torch
     out_shape, a_shape, b_shape = plan.shapes()
     if y is None:
@@ -306,6 +348,10 @@ def merit_conv2d_pack_weights(plan: Plan, w, packed=None, stream=None):
 
 
 def merit_conv2d_packed(plan: Plan, x, packed, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_conv2d_packed", _CONV2D_PACKED, plan, x, packed)
+        if r is not None:
+            return r
     import torch
     out_shape, a_shape, _ = plan.shapes()
     if y is None:
@@ -333,6 +379,10 @@ def merit_conv2d_packed_noalloc(plan: Plan, x, w, y, stream=None):
 
 
 def merit_conv2d_residual(plan: Plan, x, w, r, y=None, stream=None):
+    if y is None and stream is None:
+        out = _ordinary("merit_conv2d_residual", _RESIDUAL, plan, x, w, r)
+        if out is not None:
+            return out
     import torch
     out_shape, a_shape, b_shape = plan.shapes()
     if y is None:
@@ -348,6 +398,10 @@ def merit_conv2d_residual(plan: Plan, x, w, r, y=None, stream=None):
 
 
 def merit_pool2d(plan: Plan, x, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_pool2d", _POOL2D, plan, x)
+        if r is not None:
+            return r
     import torch
     out_shape, a_shape, _ = plan.shapes()
     if y is None:
@@ -362,6 +416,10 @@ def merit_pool2d(plan: Plan, x, y=None, stream=None):
 
 
 def merit_sad_search(plan: Plan, cur, ref, sad=None, mv=None, stream=None):
+    if sad is None and mv is None and stream is None:
+        r = _ordinary("merit_sad_search", _SAD, plan, cur, ref)
+        if r is not None:
+            return r
     import torch
     (nby, nbx), a_shape, b_shape = plan.shapes()
     if sad is None:
@@ -386,6 +444,10 @@ def merit_plan_conv2d_depthwise(N, C, H, W, kh, kw, sh, sw, ph, pw) -> Plan:
 
 
 def merit_conv2d_depthwise(plan: Plan, x, w, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_conv2d_depthwise", _DEPTHWISE, plan, x, w)
+        if r is not None:
+            return r
     import torch
     out_shape, a_shape, b_shape = plan.shapes()
     if y is None:
@@ -414,6 +476,10 @@ def _sep_args(plan, x, kx, ky, y, stream):
 
 
 def merit_sepfilter(plan: Plan, x, kx, ky, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_sepfilter", _SEPFILTER, plan, x, kx, ky)
+        if r is not None:
+            return r
     import torch
     if y is None:
         y = torch.empty(plan.out_shape(), dtype=torch.float32, device=x.device)
@@ -444,6 +510,10 @@ def _bilateral_args(plan, x, gx, gy, norm, y, stream):
 
 
 def merit_bilateral(plan: Plan, x, gx, gy, norm, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_bilateral", _BILATERAL, plan, x, gx, gy, norm)
+        if r is not None:
+            return r
     import torch
     if y is None:
         y = torch.empty(plan.out_shape(), dtype=torch.float32, device=x.device)
@@ -483,6 +553,10 @@ def merit_plan_correlation(N, C, H, W, R, sd=1) -> Plan:
 
 
 def merit_correlation(plan: Plan, x1, x2, y=None, stream=None):
+    if y is None and stream is None:
+        r = _ordinary("merit_correlation", _CORRELATION, plan, x1, x2)
+        if r is not None:
+            return r
     import torch
     out_shape, a_shape, b_shape = plan.shapes()
     if y is None:

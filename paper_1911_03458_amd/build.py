@@ -1,4 +1,4 @@
-"""Build libmerit.so (HIP kernels + C ABI) in-tree with hipcc for gfx950."""
+"""Build libmerit.so (HIP kernels + C ABI) in-tree with hipcc for gfx950, and _torch_calls.so beside it."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libmerit.so")
+CALLS_SRC = os.path.join(CSRC, "torch_calls.cpp")
+CALLS_PATH = os.path.join(_HERE, "_torch_calls.so")      # a Python module over libmerit.so and PyTorch
 
 SOURCES = ["merit_plan.cpp", "pool2d.hip", "sad_search.hip", "conv2d.hip", "conv2d_chws.hip", "maxpool_f16.hip", "generic.hip", "corr.hip", "dwconv.hip", "sepfilter.hip", "bilateral.hip", "probe.hip"]
 HEADERS = [os.path.join(CSRC, "merit_internal.h"), os.path.join(ROOT, "include", "merit.h"),
@@ -56,7 +58,33 @@ def build_library(force: bool = True, extra_flags=()) -> str:
     proc = subprocess.run(common + ["-shared", "-o", LIB_PATH] + objs, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc (link) failed:\n" + proc.stdout + proc.stderr)
+    build_torch_calls(force=True)
     return LIB_PATH
+
+
+def build_torch_calls(force: bool = True) -> str:
+    """Compile csrc/torch_calls.cpp (host code, no kernels) against PyTorch and the built library."""
+    if not force and os.path.exists(CALLS_PATH) and os.path.getmtime(CALLS_PATH) >= os.path.getmtime(CALLS_SRC):
+        return CALLS_PATH
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    libs = ext.library_paths()
+    tmp = CALLS_PATH + ".%d.tmp" % os.getpid()      # (never a half-written module in the way of another process)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), CALLS_SRC, "-o", tmp,
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+    cmd += ["-isystem" + d for d in ext.include_paths() + [os.path.join(rocm, "include")]]
+    cmd += ["-L" + _HERE, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"] + ["-L" + d for d in libs]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10"]
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ (torch_calls) failed:\n" + proc.stdout + proc.stderr)
+    os.replace(tmp, CALLS_PATH)
+    return CALLS_PATH
 
 
 def build_host_check(sanitizer: str = "address,undefined") -> str:
