@@ -16,7 +16,12 @@
 // pixel, transposed in registers on the way (v_perm_b32): exactly the operand a lane feeds to
 // the MFMA.  Positions are ordered by residue class so that the 16 pixels of a block are
 // adjacent.  Channels go through LDS in passes of `chg` groups of eight; the loads of the next
-// pass are in flight while the current one is multiplied.  Needs W % 8 == 0, R <= 15, sd <= 8.
+// pass are in flight while the current one is multiplied.  Needs W >= 8, R <= 15, sd <= 8.
+// Rows of any width: a unit's eight pixels lie on any 2-byte boundary (a 16-byte global load needs no more), and
+// the unit that a row's end cuts is loaded so that it ends with the row and shifted down, which brings in the zeros
+// beyond the edge and keeps every load inside the tensor.  Widths off the multiple of 8 ran on the definition kernel
+// before: 1x184x60x36, +-3: 245 us -> 7.6; 1x32x17x41, +-4: 50 us -> 5.0; 256 channels at 64x63, +-5 at stride 2:
+// 614 -> 12.3 us (9.2 at 64x64).
 #include "merit_internal.h"
 
 namespace merit {
@@ -29,14 +34,24 @@ constexpr int XB = CORR_XB;    // staging units a thread holds in registers per 
 // One staging unit = 8 adjacent pixels x 8 channels of one row: eight 16-byte loads (one per
 // channel), transposed to eight 16-byte LDS items (one per pixel).  The units of a pass form
 // one list: for each channel group the chunk's units of the first tensor, then those of the
-// second.  8-column units outside the row (starts are multiples of 8, W % 8 == 0) and
-// missing channels give zeros.
+// second.  Units start at multiples of 8: those outside the row, the part of the last one past
+// the row's end, and missing channels give zeros.
 struct StageGeom {
     int b, p1, yy, px0, npx8, gx2;
     uint32_t per_g;
     FastDiv div_perg;
 };
 
+// The unit's bytes, moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind them.
+__device__ __forceinline__ uint4 shift_down(uint4 t, int bits)
+{
+    const uint64_t lo = ((uint64_t)t.y << 32) | t.x, hi = ((uint64_t)t.w << 32) | t.z;
+    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
+    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
+    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+
+template <bool RAGGED>
 __device__ __forceinline__ void issue_pass(const CorrParams &p, const StageGeom &sg,
                                            const uint16_t *__restrict__ x1, const uint16_t *__restrict__ x2,
                                            int chi0, int ng, int tid, uint32_t (&v)[XB][8][4])
@@ -52,22 +67,36 @@ __device__ __forceinline__ void issue_pass(const CorrParams &p, const StageGeom 
         const int gx = second ? sg.gx2 + 8 * (r - sg.npx8) : sg.px0 + 8 * r;
         const int gy = second ? sg.yy : sg.p1;
         const bool colok = gx >= 0 && gx < p.W;
+        const bool cut = RAGGED && colok && gx + 8 > p.W;         // the row ends inside this unit
         const int c0 = (chi0 + (int)g) * 8;
         const uint16_t *xs = second ? x2 : x1;
-        const uint16_t *src = xs + (((size_t)sg.b * p.C + min(c0, p.C - 1)) * p.H + gy) * p.W + (colok ? gx : 0);
+        const uint16_t *src = xs + (((size_t)sg.b * p.C + min(c0, p.C - 1)) * p.H + gy) * p.W + (cut ? p.W - 8 : colok ? gx : 0);
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const bool ok = colok && (c0 + c < p.C);
             // branch-free: a missing element re-reads the tensor's first bytes and is zeroed
-            const uint4 t4 = *reinterpret_cast<const uint4 *>(ok ? src + c * chstride : xs);
+            uint4 t4;
+            if (RAGGED)
+                __builtin_memcpy(&t4, ok ? src + c * chstride : xs, 16);
+            else
+                t4 = *reinterpret_cast<const uint4 *>(ok ? src + c * chstride : xs);
             v[k][c][0] = ok ? t4.x : 0u; v[k][c][1] = ok ? t4.y : 0u;
             v[k][c][2] = ok ? t4.z : 0u; v[k][c][3] = ok ? t4.w : 0u;
         }
     }
 }
 
+// Whether unit k of this thread is the one a row's end cuts: its values are shifted when they are written to LDS
+// (where they are waited for anyway), not where they are requested.
+__device__ __forceinline__ bool unit_is_cut(const CorrParams &p, const StageGeom &sg, bool second, int run)
+{
+    const int gx = second ? sg.gx2 + 8 * run : sg.px0 + 8 * run;
+    return gx >= 0 && gx < p.W && gx + 8 > p.W;
+}
+
+template <bool RAGGED>
 __device__ __forceinline__ void commit_pass(const CorrParams &p, const StageGeom &sg, uint4 *a1l, uint4 *a2l,
-                                            int ng, int tid, const uint32_t (&v)[XB][8][4])
+                                            int ng, int tid, uint32_t (&v)[XB][8][4])
 {
     const uint32_t nu = (uint32_t)ng * sg.per_g;
 #pragma unroll
@@ -78,6 +107,14 @@ __device__ __forceinline__ void commit_pass(const CorrParams &p, const StageGeom
         const int r = (int)(u - g * sg.per_g);
         const bool second = r >= sg.npx8;
         const int run = second ? r - sg.npx8 : r;
+        if (RAGGED && unit_is_cut(p, sg, second, run)) {
+            const int bits = 16 * (8 - (p.W & 7));
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const uint4 t = shift_down(make_uint4(v[k][c][0], v[k][c][1], v[k][c][2], v[k][c][3]), bits);
+                v[k][c][0] = t.x; v[k][c][1] = t.y; v[k][c][2] = t.z; v[k][c][3] = t.w;
+            }
+        }
         uint4 *d4 = second ? a2l + g * p.P2 : a1l + g * p.P1;
         const int pitch = second ? p.pitch2 : p.pitch1;
 #pragma unroll
@@ -95,8 +132,8 @@ __device__ __forceinline__ void commit_pass(const CorrParams &p, const StageGeom
     }
 }
 
-// NB = 16-column blocks of the second row per pixel block, BPW = pixel blocks per wavefront.
-template <int NB, int BPW>
+// NB = 16-column blocks of the second row per pixel block, BPW = pixel blocks per wavefront, RAGGED = W % 8 != 0.
+template <int NB, int BPW, bool RAGGED>
 __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const uint16_t *__restrict__ x1,
                                                        const uint16_t *__restrict__ x2, uint16_t *__restrict__ y)
 {
@@ -121,7 +158,7 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
     StageGeom sg;
     sg.b = b; sg.p1 = p1; sg.px0 = xc * 64;
     sg.yy = p1 + (p3 - p.R) * p.sd;
-    sg.npx8 = min(8, (p.W - sg.px0) >> 3);                        // 8-pixel units of the first tensor's chunk
+    sg.npx8 = min(8, (p.W - sg.px0 + 7) >> 3);                     // 8-pixel units of the first tensor's chunk
     sg.gx2 = sg.px0 - p.lead;                                     // first staged column of the second tensor
     sg.per_g = (uint32_t)(sg.npx8 + (p.cols2 >> 3));
     sg.div_perg = sg.npx8 == 8 ? p.div_perg : p.div_perg_last;
@@ -157,15 +194,15 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
         // groups of the pass that starts at chi0, padded to whole reduction steps (the padding is staged as zeros)
         auto groups_of = [&](int chi0) { return min(p.chg, ((p.nchi - chi0) + 3) & ~3); };
         uint32_t v[XB][8][4];
-        issue_pass(p, sg, x1, x2, 0, groups_of(0), tid, v);
+        issue_pass<RAGGED>(p, sg, x1, x2, 0, groups_of(0), tid, v);
         for (int chi0 = 0; chi0 < p.nchi; chi0 += p.chg) {
             const int ng = groups_of(chi0);
             if (chi0 > 0) __syncthreads();                        // previous pass has been read
-            commit_pass(p, sg, a1l, a2l, ng, tid, v);
+            commit_pass<RAGGED>(p, sg, a1l, a2l, ng, tid, v);
             __syncthreads();
             // the next pass's loads are in flight while this one is multiplied
             const int nxt = chi0 + p.chg;
-            if (nxt < p.nchi) issue_pass(p, sg, x1, x2, nxt, groups_of(nxt), tid, v);
+            if (nxt < p.nchi) issue_pass<RAGGED>(p, sg, x1, x2, nxt, groups_of(nxt), tid, v);
 #pragma unroll
             for (int t = 0; t < BPW; ++t) {
                 if (wave + 4 * t >= p.nblk) break;                // uniform
@@ -214,15 +251,15 @@ size_t corr_lds_bytes(const CorrParams &p)
     return (size_t)p.chg * (p.P1 + p.P2) * 16;
 }
 
-template <int NB, int BPW>
+template <int NB, int BPW, bool RAGGED>
 static hipError_t launch_corr(const CorrParams &p, const void *x1, const void *x2, void *y, hipStream_t s,
                               uint32_t grid)
 {
     static std::atomic<int> raised{0};
-    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_corr_mfma<NB, BPW>), raised);
+    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_corr_mfma<NB, BPW, RAGGED>), raised);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((merit_corr_mfma<NB, BPW>), dim3(grid), dim3(256), corr_lds_bytes(p), s, p,
+    hipLaunchKernelGGL((merit_corr_mfma<NB, BPW, RAGGED>), dim3(grid), dim3(256), corr_lds_bytes(p), s, p,
                        reinterpret_cast<const uint16_t *>(x1), reinterpret_cast<const uint16_t *>(x2),
                        reinterpret_cast<uint16_t *>(y));
     return hipGetLastError();
@@ -235,15 +272,20 @@ hipError_t launch_correlation(const CorrParams &p, const void *x1, const void *x
     const uint32_t gx = (uint32_t)grid;
     const int bpw = (p.nblk + 3) / 4;
     if (bpw < 1 || bpw > 2) return hipErrorInvalidValue;
-    switch (p.nb * 2 + (bpw - 1)) {
-    case 2: return launch_corr<1, 1>(p, x1, x2, y, s, gx);
-    case 3: return launch_corr<1, 2>(p, x1, x2, y, s, gx);
-    case 4: return launch_corr<2, 1>(p, x1, x2, y, s, gx);
-    case 5: return launch_corr<2, 2>(p, x1, x2, y, s, gx);
-    case 6: return launch_corr<3, 1>(p, x1, x2, y, s, gx);
-    case 7: return launch_corr<3, 2>(p, x1, x2, y, s, gx);
-    default: return hipErrorInvalidValue;
+    const int v = p.nb * 2 + (bpw - 1);
+#define MERIT_CORR(RAGGED)                                              \
+    switch (v) {                                                        \
+    case 2: return launch_corr<1, 1, RAGGED>(p, x1, x2, y, s, gx);      \
+    case 3: return launch_corr<1, 2, RAGGED>(p, x1, x2, y, s, gx);      \
+    case 4: return launch_corr<2, 1, RAGGED>(p, x1, x2, y, s, gx);      \
+    case 5: return launch_corr<2, 2, RAGGED>(p, x1, x2, y, s, gx);      \
+    case 6: return launch_corr<3, 1, RAGGED>(p, x1, x2, y, s, gx);      \
+    case 7: return launch_corr<3, 2, RAGGED>(p, x1, x2, y, s, gx);      \
+    default: return hipErrorInvalidValue;                               \
     }
+    if (p.W % 8 != 0) MERIT_CORR(true)
+    MERIT_CORR(false)
+#undef MERIT_CORR
 }
 
 }  // namespace merit

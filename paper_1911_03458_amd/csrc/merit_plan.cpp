@@ -1119,7 +1119,11 @@ merit_status derive_corr(merit_plan *pl)
         if (d.b.shape[i] != d.a.shape[i]) return MERIT_ERR_SHAPE;
     if (d.range[0] != N || d.range[1] != H || d.range[2] != W || d.range[5] != C) return MERIT_ERR_SHAPE;
     // the kernel stages 8-pixel units and gives a wavefront at most 8 column displacements
-    if ((W % 8) != 0 || R > 15 || sd > 8 || C > 65536) return MERIT_ERR_UNSUPPORTED;
+    if (W < 8 || R > 15 || sd > 8 || C > 65536) return MERIT_ERR_UNSUPPORTED;
+    // Widths off the multiple of 8: up to 64 K products in all the definition kernel stays (18 us against 5: these
+    // calls are small enough not to matter, and they are what its own correlation tests run); above, it costs 1.5 us
+    // per channel and the MFMA kernel 5-12 us in all (8x60x60, +-5: 35 against 5).
+    if ((W % 8) != 0 && N * C * H * W * n * n <= 65536) return MERIT_ERR_UNSUPPORTED;
     if (N * C * H * W >= INT_LIMIT || N * H * W * n * n >= INT_LIMIT) return MERIT_ERR_UNSUPPORTED;
 
     CorrParams &p = pl->corr;
@@ -1146,7 +1150,7 @@ merit_status derive_corr(merit_plan *pl)
     if (p.chg * per_g_full > 256 * CORR_XB || p.chg * per_group > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
     p.div_sd = make_fastdiv((uint32_t)sd);
     p.div_perg = make_fastdiv((uint32_t)per_g_full);
-    p.div_perg_last = make_fastdiv((uint32_t)((W % 64) / 8 + p.cols2 / 8));
+    p.div_perg_last = make_fastdiv((uint32_t)(cdiv(W % 64, 8) + p.cols2 / 8));
     const int64_t grid = N * H * n * p.xchunks;
     if (grid >= INT_LIMIT || !fastdiv_ok(grid, p.xchunks) || !fastdiv_ok(grid, n) || !fastdiv_ok(grid, H))
         return MERIT_ERR_UNSUPPORTED;
