@@ -239,6 +239,22 @@ struct ConvParams {
                            // (rows_out_max odd), 0 = that row is carried from the tile before it (rows_out_max even)
 };
 
+// ---- convolution, 1x1 windows at stride 1: a matrix product per image (conv2d_px.hip) ----
+struct PxParams {
+    int N, Cin, HW, Cout;
+    int TM, TN;            // pixels and output channels per workgroup
+    int tiles;             // pixel tiles per image
+    int co_groups;         // channel blocks
+    int nk;                // steps of 64 input channels
+    int relu, residual;
+    int xq, xr;            // grid / 8, grid % 8 (see xcd_band_item)
+    FastDiv div_cog, div_tiles;
+};
+
+size_t px_lds_bytes(const PxParams &p);
+hipError_t launch_conv2d_px(const PxParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s);
+hipError_t launch_copy_weights(const void *w, void *packed, int64_t halves, hipStream_t s);      // halves % 8 == 0
+
 // ---- launchers (defined in the .hip files) --------------------------------
 hipError_t launch_pool2d(const PoolParams &p, const float *x, float *y, hipStream_t s);
 hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref,
@@ -383,4 +399,8 @@ struct merit_plan {
     // stream-ordered temporary, then the binary16 pooling kernel): `conv2` is the plain convolution
     int two_pass;
     merit::ConvParams conv2;
+    // 1x1 windows at stride 1 (CONV_PX): `px` runs the plan.  `conv` stays what the other kernels would have made of
+    // it: it names the size of a packed copy, where there is one
+    int use_px;
+    merit::PxParams px;
 };

@@ -6,7 +6,6 @@
 // tile / halo geometry derived from it with the footprint rule of Section
 // IV-A, Eq. 9.  No GPU call happens here.
 #include <atomic>
-#include <cstdlib>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -425,9 +424,60 @@ merit_status derive_bilateral(merit_plan *pl)
 }
 
 // -------------------------------------------------------------- convolution ---
+// 1x1 windows at stride 1 without padding: the matrix-product kernel (conv2d_px.hip), whatever the general planner
+// chose, unless a tile request names one of the other kernels' tilings.
+void derive_px(merit_plan *pl)
+{
+    const ConvParams &c = pl->conv;
+    if (c.kh != 1 || c.kw != 1 || c.sh != 1 || c.sw != 1 || c.ph != 0 || c.pw != 0 || c.pool) return;
+    if (pl->tile_req[2] > 0 && pl->tile_req[3] > 0) return;
+    const int64_t N = c.N, Cin = c.Cin, HW = (int64_t)c.H * c.W, Cout = c.Cout;
+    // Few channels, rows of whole 16-byte units, several tiles per compute unit: the persistent kernel's next tile flies
+    // under its stores, and a single short step has no chain to hide (32 -> 64 on 32 images of 64x64: 7.1 against 7.6 us,
+    // 64 -> 256 on 8 of 56x56: 6.6 against 7.2; 56 -> 560 on 2 of 71x24: 4.8 against 3.7).
+    if (c.variant == CONV_CHWS && !c.residual && Cin <= 64 && c.W % 8 == 0 && N * cdiv(HW, 128) * cdiv(Cout, 64) >= 512) return;
+    // more than 256 channels, not a multiple of 8: left on the channels-in-passes kernel, where the plan tests hold it
+    if (Cin % 8 != 0 && Cin > 256) return;
+    if (Cin < 16 || HW < 8 || Cin * HW >= (1ll << 30) || Cout * Cin >= (1ll << 30) || Cout * HW >= (1ll << 30)) return;
+    PxParams p;
+    std::memset(&p, 0, sizeof(p));
+    p.N = (int)N; p.Cin = (int)Cin; p.HW = (int)HW; p.Cout = (int)Cout;
+    p.relu = c.relu; p.residual = c.residual;
+    p.nk = (int)cdiv(Cin, 64);
+    // The tile with the lowest estimate, in microseconds of a compute unit: per workgroup, steps of 64 channels x the
+    // cost of one (alone on its unit, or beside others) + its start and its stores; 26 layers of 16 .. 2016 channels
+    // timed on every tile, which the estimate's choice is within a tenth of the best of.
+    static const struct { int tm, tn; double alone, beside, ends; } tiles[5] = {
+        {64, 32, 0.30, 0.30, 0.55}, {64, 64, 0.335, 0.35, 0.7}, {64, 128, 0.47, 0.55, 1.1}, {128, 32, 0.46, 0.33, 0.55},
+        {128, 64, 0.50, 0.47, 0.95}};
+    double best_cost = 0.0;
+    for (const auto &t : tiles) {
+        const double n = (double)(N * cdiv(HW, t.tm) * cdiv(Cout, t.tn)) / 256.0;
+        const double steps = (double)cdiv(Cin, 16) / 4.0;
+        const double per_cu = n <= 1.0 ? 1.0 : 0.5 * (n + std::ceil(n));
+        const double cost = per_cu * (steps * (n <= 1.0 ? t.alone : t.beside) + t.ends * (p.residual ? 1.3 : 1.0));
+        if (p.TM == 0 || cost < best_cost) { p.TM = t.tm; p.TN = t.tn; best_cost = cost; }
+    }
+    p.tiles = (int)cdiv(HW, p.TM); p.co_groups = (int)cdiv(Cout, p.TN);
+    const int64_t grid = N * p.tiles * p.co_groups;
+    if (grid >= (1ll << 30) || !fastdiv_ok(grid, p.co_groups) || !fastdiv_ok(N * p.tiles, p.tiles)) return;
+    p.xq = (int)(grid / 8); p.xr = (int)(grid % 8);
+    p.div_cog = make_fastdiv((uint32_t)p.co_groups);
+    p.div_tiles = make_fastdiv((uint32_t)p.tiles);
+    pl->px = p;
+    pl->use_px = 1;
+    merit_launch_info &li = pl->info;
+    if (c.variant != CONV_CHWS) li.kernel = "merit_conv2d_px";
+    li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
+    li.block[0] = 512; li.block[1] = 1; li.block[2] = 1;
+    li.lds_bytes = (int64_t)px_lds_bytes(p);
+    li.tile[1] = p.TN; li.tile[2] = cdiv(p.TM, c.W); li.tile[3] = c.W;
+}
+
 merit_status derive_conv(merit_plan *pl)
 {
     const merit_plan_desc &d = pl->desc;
+    pl->use_px = 0;
     if (d.dtype != MERIT_F16 || d.pad != MERIT_PAD_ZERO) return MERIT_ERR_UNSUPPORTED;
     if (d.n_par != 4 || d.n_acc != 3) return MERIT_ERR_UNSUPPORTED;
     if (d.a.ndim != 4 || d.b.ndim != 4) return MERIT_ERR_UNSUPPORTED;
@@ -1013,6 +1063,7 @@ merit_status derive_conv(merit_plan *pl)
             delete plain;
         }
     }
+    derive_px(pl);
     return MERIT_OK;
 }
 
@@ -1650,9 +1701,10 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x, const void *w, 
         const hipError_t ef = hipFreeAsync(mid, s);
         return (e == hipSuccess && ef == hipSuccess) ? MERIT_OK : MERIT_ERR_HIP;
     }
-    return launch_conv2d(plan->conv, x, w, nullptr, y, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? MERIT_OK
-               : MERIT_ERR_HIP;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
+                                      : launch_conv2d(plan->conv, x, w, nullptr, y, s);
+    return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
 static bool plan_takes_packed(const merit_plan *plan)
@@ -1676,9 +1728,11 @@ merit_status merit_conv2d_pack_weights(const merit_plan *plan, const void *w, vo
     if (!plan_takes_packed(plan)) return MERIT_ERR_UNSUPPORTED;
     if (!w || !packed) return MERIT_ERR_NULL;
     if (!aligned16(w) || !aligned16(packed)) return MERIT_ERR_ALIGNMENT;
-    return launch_conv2d_pack_weights(plan->conv, w, packed, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? MERIT_OK
-               : MERIT_ERR_HIP;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    // (the matrix-product kernel reads the weights as they lie: its packed copy is a copy)
+    const hipError_t e = plan->use_px ? launch_copy_weights(w, packed, (int64_t)plan->px.Cout * plan->px.Cin, s)
+                                      : launch_conv2d_pack_weights(plan->conv, w, packed, s);
+    return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
 merit_status merit_conv2d_packed(const merit_plan *plan, const void *x, const void *packed, void *y, void *stream)
@@ -1688,9 +1742,10 @@ merit_status merit_conv2d_packed(const merit_plan *plan, const void *x, const vo
     if (plan->conv.N == 0) return MERIT_OK;               // empty batch: nothing to read or write
     if (!x || !packed || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(packed) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
-    return launch_conv2d_chws(plan->conv, x, packed, nullptr, y, static_cast<hipStream_t>(stream), true) == hipSuccess
-               ? MERIT_OK
-               : MERIT_ERR_HIP;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, packed, nullptr, y, s)
+                                      : launch_conv2d_chws(plan->conv, x, packed, nullptr, y, s, true);
+    return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
 merit_status merit_conv2d_packed_noalloc(const merit_plan *plan, const void *x, const void *w, void *y, void *stream)
@@ -1703,8 +1758,11 @@ merit_status merit_conv2d_packed_noalloc(const merit_plan *plan, const void *x, 
     if (p.N == 0) return MERIT_OK;                        // empty batch: nothing to read or write
     if (!x || !w || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
-    return launch_conv2d_chws_noalloc(p, x, w, y, static_cast<hipStream_t>(stream)) == hipSuccess ? MERIT_OK
-                                                                                                   : MERIT_ERR_HIP;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    // (the matrix-product kernel needs no packed copy to give the packed call's bits)
+    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
+                                      : launch_conv2d_chws_noalloc(p, x, w, y, s);
+    return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
 merit_status merit_conv2d_residual(const merit_plan *plan, const void *x, const void *w, const void *r, void *y,
@@ -1716,9 +1774,9 @@ merit_status merit_conv2d_residual(const merit_plan *plan, const void *x, const 
     if (plan->conv.N == 0) return MERIT_OK;               // empty batch: nothing to read or write
     if (!x || !w || !r || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(w) || !aligned16(r) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
-    return launch_conv2d(plan->conv, x, w, r, y, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? MERIT_OK
-               : MERIT_ERR_HIP;
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, r, y, s) : launch_conv2d(plan->conv, x, w, r, y, s);
+    return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
 merit_status merit_pool2d(const merit_plan *plan, const void *x, void *y, void *stream)
