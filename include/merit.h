@@ -285,7 +285,9 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x_f16, const void 
  * do not change between calls, so the regrouping can be done once instead:
  *   merit_plan_packed_weights_bytes  size of the packed copy for this plan (a multiple of 16);
  *                                    MERIT_ERR_UNSUPPORTED if the plan's kernel takes no packed
- *                                    weights (merit_launch_info.kernel != "merit_conv2d_chws")
+ *                                    weights (merit_launch_info.kernel != "merit_conv2d_chws"), or on
+ *                                    channel counts off the multiple of 8, fewer than 32 input or
+ *                                    at most 32 output channels
  *   merit_conv2d_pack_weights        w_f16 -> packed (device memory of that size, owned by the
  *                                    caller, 16-byte aligned); enqueued on the stream
  *   merit_conv2d_packed              merit_conv2d with the packed copy in place of w_f16; same

@@ -23,6 +23,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 namespace merit {
 
@@ -109,6 +110,15 @@ __device__ __forceinline__ Geom pool_geom(const ConvParams &p, int item, int i, 
     return g;
 }
 
+// v moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind it
+__device__ __forceinline__ void shift_down(uint32_t (&v)[4], int bits)
+{
+    const uint64_t lo = ((uint64_t)v[1] << 32) | v[0], hi = ((uint64_t)v[3] << 32) | v[2];
+    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
+    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
+    v[0] = (uint32_t)l; v[1] = (uint32_t)(l >> 32); v[2] = (uint32_t)h; v[3] = (uint32_t)(h >> 32);
+}
+
 constexpr int XS_MAX = 8;      // input units of 8 channels x 1 pixel a moving thread holds per pass (4 beside 8 multiplying wavefronts -- 168 registers -- and for 5x5 windows)
 constexpr uint32_t OOB = 0x80000000u;   // a buffer offset past the end of every tensor: loads return zeros
 
@@ -116,8 +126,10 @@ constexpr uint32_t OOB = 0x80000000u;   // a buffer offset past the end of every
 
 // PXB x CHB: 32x32 blocks per multiplying wavefront; WM x WN = 4 multiplying wavefronts.
 // T: taps of the window (25 = 5x5, 9 = 3x3, 1 = 1x1).  XU = 1, 2: the input rows are staged in units of 8
-// channels x 8 pixels (W % 8 == 0), XU of them per moving thread and pass; XU = 0: in units of
-// 8 channels x 1 pixel, up to XS_MAX per thread.
+// channels x 8 pixels, XU of them per moving thread and pass: eight 16-byte loads, which a buffer load takes
+// from any 2-byte boundary; the unit that a row's end would cut starts earlier, so that it ends with the row
+// (the columns it shares with its neighbour are written twice, with the same values).  XU = 0 (rows of fewer than 8 pixels, or more units than two per thread): units of 8 channels x 1
+// pixel, up to XS_MAX per thread.
 // NG: pairs of 8-channel groups per pass (1: 16 channels, 2: 32 -- small tiles, whose passes would
 // otherwise be shorter than a memory round trip; 4: 64 -- 1x1 windows on many channels).
 // POOL: the results are max-pooled (3x3 / stride 2 / padding 1) out of the staging area and only the
@@ -137,8 +149,6 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
     constexpr int WU = (TN * NGRP + 255) / 256;          // weight units (8 channels x T taps of one output channel) per moving thread
     constexpr int OP = TM / 2 + 2;                       // output staging: dwords per channel
     constexpr bool XV = XU == 1 || XU == 2;              // 8-pixel input units, XU per moving thread
-    constexpr bool XQ = XU == 4;                         // 4-pixel input units (W % 4 == 0)
-    constexpr bool XD = XU == 3;                         // 2-pixel input units (W % 4 == 2: rows start on 4-byte boundaries)
 
     {
         // The kernel-argument block (ConvParams and three pointers: six 64-byte lines) is read with
@@ -292,24 +302,21 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         const int mwave = wave - NMW;
 
         constexpr int XSM = (NMW == 4 && T != 25) ? XS_MAX : 4;       // (5x5: 100 registers of weights on their way)
-        constexpr int XQM = NMW == 4 ? 4 : 2;                // 4-pixel units per moving thread, at most
-        constexpr int XDM = XSM;                             // 2-pixel units per moving thread, at most
-        constexpr int NXU = XV ? XU : (XQ ? XQM : (XD ? XDM : XSM));
+        constexpr int NXU = XV ? XU : XSM;
         uint32_t x_voff[NXU];               // byte offset of the unit inside (image, first channel of the pass)
-        int x_lds[NXU][XV ? 8 : (XQ ? 4 : (XD ? 2 : 1))];   // byte address of each of its pixels inside a pass buffer's input region
+        int x_lds[NXU];                     // byte address of its first pixel inside a pass buffer's input region
         int x_hh[NXU];                      // its channel group within the pass
         uint32_t xv[XV ? XU : 1][8][4];     // the unit on its way: 8 channels x 8 pixels
-        uint32_t xs[(XV || XQ || XD) ? 1 : XSM][8];    // ... 8 channels x 1 pixel (a register each: see commit)
-        uint32_t xq[XQ ? XQM : 1][8][2];         // ... 8 channels x 4 pixels
-        uint32_t xd[XD ? XDM : 1][8];            // ... 8 channels x 2 pixels
+        uint32_t xs[XV ? 1 : XSM][8];       // ... 8 channels x 1 pixel (a register each: see commit)
         uint32_t w_voff[WU];
         int w_lds[WU], w_hh[WU];
         uint32_t wr[PACKED ? 1 : WU][PACKED ? 1 : 4 * T];
 
         const int rstep = p.row_skip ? p.sh : 1;        // image rows between staged rows
+        const bool ragged = (p.Cin & 7) != 0;           // the last group of 8 channels is not whole
         auto setup = [&](const Geom &g) __attribute__((always_inline)) {
             if constexpr (XV) {
-                const int W8 = p.W >> 3;
+                const int W8 = (p.W + 7) >> 3;
                 const int nu = NGRP * p.RHa * W8;
 #pragma unroll
                 for (int k = 0; k < XU; ++k) {
@@ -324,49 +331,10 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                     const int r = q - hh * p.RHa;
                     const int gy = g.yA + r * rstep;
                     const bool ok = u < nu && r < g.RH && gy >= 0 && gy < p.H;
+                    const int col = min(8 * x8, p.W - 8);
                     x_hh[k] = u < nu ? hh : NGRP;                            // NGRP: no such unit, never written
-                    x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + 8 * x8) * 2) : OOB;
-#pragma unroll
-                    for (int px = 0; px < 8; ++px)
-                        x_lds[k][px] = (q * p.pitch + p.padl + 8 * x8 + px) * 16;
-                }
-            } else if constexpr (XQ) {
-                const int W4 = p.W >> 2;
-                const int nu = NGRP * p.RHa * W4;
-#pragma unroll
-                for (int k = 0; k < XQM; ++k) {
-                    const int u = mt + 256 * k;
-                    const int uc = min(u, nu - 1);
-                    const int x4 = (int)fdiv((uint32_t)uc, p.div_r2);
-                    const int q = uc - x4 * NGRP * p.RHa;
-                    const int hh = (int)fdiv((uint32_t)q, p.div_rha);
-                    const int r = q - hh * p.RHa;
-                    const int gy = g.yA + r * rstep;
-                    const bool ok = u < nu && r < g.RH && gy >= 0 && gy < p.H;
-                    x_hh[k] = u < nu ? hh : NGRP;
-                    x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + 4 * x4) * 2) : OOB;
-#pragma unroll
-                    for (int px = 0; px < 4; ++px)
-                        x_lds[k][px] = (q * p.pitch + p.padl + 4 * x4 + px) * 16;
-                }
-            } else if constexpr (XD) {
-                const int W2 = p.W >> 1;
-                const int nu = NGRP * p.RHa * W2;
-#pragma unroll
-                for (int k = 0; k < XDM; ++k) {
-                    const int u = mt + 256 * k;
-                    const int uc = min(u, nu - 1);
-                    const int x2 = (int)fdiv((uint32_t)uc, p.div_r2);
-                    const int q = uc - x2 * NGRP * p.RHa;
-                    const int hh = (int)fdiv((uint32_t)q, p.div_rha);
-                    const int r = q - hh * p.RHa;
-                    const int gy = g.yA + r * rstep;
-                    const bool ok = u < nu && r < g.RH && gy >= 0 && gy < p.H;
-                    x_hh[k] = u < nu ? hh : NGRP;
-                    x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + 2 * x2) * 2) : OOB;
-#pragma unroll
-                    for (int px = 0; px < 2; ++px)
-                        x_lds[k][px] = (q * p.pitch + p.padl + 2 * x2 + px) * 16;
+                    x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + col) * 2) : OOB;
+                    x_lds[k] = (q * p.pitch + p.padl + col) * 16;
                 }
             } else {
                 const int nu = NGRP * p.RHa * p.W;
@@ -382,7 +350,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                     const bool ok = u < nu && r < g.RH && gy >= 0 && gy < p.H;
                     x_hh[k] = u < nu ? hh : NGRP;
                     x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + xg) * 2) : OOB;
-                    x_lds[k][0] = (q * p.pitch + p.padl + xg) * 16;
+                    x_lds[k] = (q * p.pitch + p.padl + xg) * 16;
                 }
             }
             if constexpr (!PACKED) {
@@ -402,8 +370,10 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         };
 
         // request the input rows (and, unless packed, the weights) of pass ck into the registers
-        auto request = [&](const Geom &g, int ck) __attribute__((always_inline)) {
-            const int live = (p.Cin >> 3) - ck * NGRP;          // groups of this pass that exist (the rest: padding)
+        // (RAGGED: the last group of 8 channels is not whole; a form of its own, its selects on every load cost the
+        // others 5-10 %)
+        auto request_as = [&](auto ragged_form, const Geom &g, int ck) __attribute__((always_inline)) {
+            constexpr bool RAGGED = decltype(ragged_form)::value;
             // (the same for the whole wavefront: said explicitly, or the 2-byte loads below each get a
             // loop over the distinct values of a vector register)
             const uint32_t xbase = (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -411,38 +381,47 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
 #pragma unroll
             for (int k = 0; k < NXU; ++k) {
                 if (!XV && k >= p.xu) break;
-                const uint32_t voff = x_hh[k] >= live ? OOB : x_voff[k];
+                // channels that exist in this unit's group of the pass: 8 or more, some, or none
+                const int livec = p.Cin - (ck * NGRP + x_hh[k]) * 8;
+                const uint32_t all = livec <= 0 ? OOB : x_voff[k];
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
+                    const uint32_t voff = RAGGED && c >= livec ? OOB : all;
                     if constexpr (XV) {
                         const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, voff, xbase + c * chbytes, 0);
                         xv[k][c][0] = v.x; xv[k][c][1] = v.y; xv[k][c][2] = v.z; xv[k][c][3] = v.w;
-                    } else if constexpr (XQ) {
-                        const uint32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, voff, xbase + c * chbytes, 0);
-                        xq[k][c][0] = v.x; xq[k][c][1] = v.y;
-                    } else if constexpr (XD) {
-                        xd[k][c] = __builtin_amdgcn_raw_buffer_load_b32(rx, voff, xbase + c * chbytes, 0);
                     } else {
                         xs[k][c] = __builtin_amdgcn_raw_buffer_load_b16(rx, voff, xbase + c * chbytes, 0);
                     }
                 }
             }
             if constexpr (!PACKED) {
-                const uint32_t wbase = (uint32_t)ck * (uint32_t)(NGRP * 8 * T * 2);
+                const uint32_t pass = (uint32_t)ck * (uint32_t)(NGRP * 8 * T * 2);
 #pragma unroll
                 for (int k = 0; k < WU; ++k) {
-                    const uint32_t voff = w_hh[k] >= live ? OOB : w_voff[k];
+                    // the unit's T chunks of 8 halves; of a group that is not whole only the first
+                    // 8 T - (missing channels) T halves are this output channel's: the chunk they end in is
+                    // loaded so that it ends with them (and shifted down at the commit), those behind are zeros
+                    const int nv = (p.Cin - (ck * NGRP + w_hh[k]) * 8) * T;
+                    const uint32_t voff = nv <= 0 ? OOB : w_voff[k] + (RAGGED ? pass : 0u);
+                    const uint32_t tail = voff + 2u * (uint32_t)nv - 16u;          // (Cin >= 8: never before the tensor)
 #pragma unroll
                     for (int i = 0; i < T; ++i) {
-                        const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, voff + 16 * i, wbase, 0);
+                        uint32_t vo = voff + 16 * i;
+                        if (RAGGED) vo = 8 * i + 8 <= nv ? vo : (8 * i < nv ? tail : OOB);
+                        const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, RAGGED ? 0u : pass, 0);
                         wr[k][4 * i + 0] = v.x; wr[k][4 * i + 1] = v.y; wr[k][4 * i + 2] = v.z; wr[k][4 * i + 3] = v.w;
                     }
                 }
             }
         };
+        auto request = [&](const Geom &g, int ck) __attribute__((always_inline)) {
+            if (ragged) request_as(std::true_type{}, g, ck);
+            else request_as(std::false_type{}, g, ck);
+        };
 
         // transpose the registers into pass buffer b
-        auto commit = [&](int b) __attribute__((always_inline)) {
+        auto commit = [&](int ck, int b) __attribute__((always_inline)) {      // ck: the pass that was requested
             uint8_t *xl = smem + b * p.lds_buf_bytes + p.lds_w_bytes;
 #pragma unroll
             for (int k = 0; k < NXU; ++k) {
@@ -457,29 +436,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                             d.y = __builtin_amdgcn_perm(xv[k][3][px >> 1], xv[k][2][px >> 1], sel);
                             d.z = __builtin_amdgcn_perm(xv[k][5][px >> 1], xv[k][4][px >> 1], sel);
                             d.w = __builtin_amdgcn_perm(xv[k][7][px >> 1], xv[k][6][px >> 1], sel);
-                            *reinterpret_cast<uint32x4 *>(xl + x_lds[k][px]) = d;
-                        }
-                    } else if constexpr (XQ) {
-#pragma unroll
-                        for (int px = 0; px < 4; ++px) {
-                            const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
-                            uint32x4 d;
-                            d.x = __builtin_amdgcn_perm(xq[k][1][px >> 1], xq[k][0][px >> 1], sel);
-                            d.y = __builtin_amdgcn_perm(xq[k][3][px >> 1], xq[k][2][px >> 1], sel);
-                            d.z = __builtin_amdgcn_perm(xq[k][5][px >> 1], xq[k][4][px >> 1], sel);
-                            d.w = __builtin_amdgcn_perm(xq[k][7][px >> 1], xq[k][6][px >> 1], sel);
-                            *reinterpret_cast<uint32x4 *>(xl + x_lds[k][px]) = d;
-                        }
-                    } else if constexpr (XD) {
-#pragma unroll
-                        for (int px = 0; px < 2; ++px) {
-                            const uint32_t sel = px ? 0x07060302u : 0x05040100u;
-                            uint32x4 d;
-                            d.x = __builtin_amdgcn_perm(xd[k][1], xd[k][0], sel);
-                            d.y = __builtin_amdgcn_perm(xd[k][3], xd[k][2], sel);
-                            d.z = __builtin_amdgcn_perm(xd[k][5], xd[k][4], sel);
-                            d.w = __builtin_amdgcn_perm(xd[k][7], xd[k][6], sel);
-                            *reinterpret_cast<uint32x4 *>(xl + x_lds[k][px]) = d;
+                            *reinterpret_cast<uint32x4 *>(xl + x_lds[k] + px * 16) = d;
                         }
                     } else {
                         // the eight loads of a unit stay eight registers until here: packed in pairs
@@ -491,7 +448,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                         d.y = (uint32_t)xs[k][2] | ((uint32_t)xs[k][3] << 16);
                         d.z = (uint32_t)xs[k][4] | ((uint32_t)xs[k][5] << 16);
                         d.w = (uint32_t)xs[k][6] | ((uint32_t)xs[k][7] << 16);
-                        *reinterpret_cast<uint32x4 *>(xl + x_lds[k][0]) = d;
+                        *reinterpret_cast<uint32x4 *>(xl + x_lds[k]) = d;
                     }
                 }
             }
@@ -500,6 +457,18 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
 #pragma unroll
                 for (int k = 0; k < WU; ++k) {
                     if (w_hh[k] < NGRP) {
+                        const int nv = (p.Cin - (ck * NGRP + w_hh[k]) * 8) * T;
+                        if (ragged && nv > 0 && nv < 8 * T) {
+#pragma unroll
+                            for (int i = 0; i < T; ++i) {
+                                if (8 * i < nv && 8 * i + 8 > nv) {
+                                    uint32_t v[4] = {wr[k][4 * i], wr[k][4 * i + 1], wr[k][4 * i + 2], wr[k][4 * i + 3]};
+                                    shift_down(v, 16 * (8 * i + 8 - nv));
+#pragma unroll
+                                    for (int q = 0; q < 4; ++q) wr[k][4 * i + q] = v[q];
+                                }
+                            }
+                        }
 #pragma unroll
                         for (int t = 0; t < T; ++t) {
                             uint32_t d[4];
@@ -566,7 +535,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
             int item2 = item, ti2 = ti, ntile2 = ntile;
             const bool more = next_pos(item2, ti2, ntile2);
             const Geom gn = more ? geom_at(item2, ti2) : g;
-            commit(0);
+            commit(0, 0);
             weights_direct(g.cg, 0, 0);
             zero_pads();
             if (npass > 1) request(g, 1);
@@ -574,7 +543,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
             __syncthreads();                                   // P
             for (int ck = 0; ck < npass; ++ck) {
                 if (ck + 1 < npass) {
-                    commit((ck + 1) & 1);
+                    commit(ck + 1, (ck + 1) & 1);
                     weights_direct(g.cg, ck + 1, (ck + 1) & 1);
                     if constexpr (XV) {
                         // the packed weights have the rest of the period to land: wait until only
@@ -782,9 +751,7 @@ template <int PXB, int CHB, int WM, int WN, int NG = 1, bool POOLS = false>
 hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
                        uint32_t grid, bool packed)
 {
-    // 8-pixel units per moving thread (1, 2); 4: four-pixel units (W % 4 == 0, 3x3 and 1x1 windows); 3: two-pixel units
-    // (W % 4 == 2, the same windows, no added tensor, no pooling); 0: one-pixel units
-    const int xu = (p.W & 7) == 0 ? p.xu : (p.xq == 1 ? 4 : (p.xq == 2 ? 3 : 0));
+    const int xu = p.xpx ? 0 : p.xu;          // 8-pixel units per moving thread (1, 2); 0: one-pixel units
     const int T = p.kh * p.kw;
     if (p.residual) {
         // residual layer: 3x3 and 1x1 windows on the caller's weights, the two 64-channel tilings (on the
@@ -794,13 +761,11 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
             if (T == 1) {
                 if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 1, false, NG, false, true>, p, x, w, res, y, s, grid);
                 if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 2, false, NG, false, true>, p, x, w, res, y, s, grid);
-                if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 4, false, NG, false, true>, p, x, w, res, y, s, grid);
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
             if constexpr (NG != 4) {        // (64 channels per pass: 1x1 windows only)
                 if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 1, false, NG, false, true>, p, x, w, res, y, s, grid);
                 if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 2, false, NG, false, true>, p, x, w, res, y, s, grid);
-                if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 4, false, NG, false, true>, p, x, w, res, y, s, grid);
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
         }
@@ -812,7 +777,6 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
             if (T != 9 || packed) return hipErrorInvalidValue;
             if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 1, false, NG, true>, p, x, w, res, y, s, grid);
             if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 2, false, NG, true>, p, x, w, res, y, s, grid);
-            if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 4, false, NG, true>, p, x, w, res, y, s, grid);
             return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 0, false, NG, true>, p, x, w, res, y, s, grid);
         }
         return hipErrorInvalidValue;
@@ -826,14 +790,10 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
         if (T == 9 && xu == 1) MERIT_CHWS(9, 1);
         if (T == 9 && xu == 2) MERIT_CHWS(9, 2);
         if (T == 9 && xu == 0) MERIT_CHWS(9, 0);
-        if (T == 9 && xu == 4) MERIT_CHWS(9, 4);
-        if (T == 9 && xu == 3) MERIT_CHWS(9, 3);
     }
     if (T == 1 && xu == 1) MERIT_CHWS(1, 1);
     if (T == 1 && xu == 2) MERIT_CHWS(1, 2);
     if (T == 1 && xu == 0) MERIT_CHWS(1, 0);
-    if (T == 1 && xu == 4) MERIT_CHWS(1, 4);
-    if (T == 1 && xu == 3) MERIT_CHWS(1, 3);
     // 5x5 windows: the 256-pixel x 64-channel tiling only (a pass's 25 x 2 x 64 weight fragments are 51 KB)
     if constexpr (PXB == 2 && CHB == 2 && WM == 4 && WN == 1 && NG == 1) {
         if (T == 25 && xu == 1) MERIT_CHWS(25, 1);

@@ -424,6 +424,15 @@ merit_status derive_bilateral(merit_plan *pl)
 }
 
 // -------------------------------------------------------------- convolution ---
+// The layers whose weights can be packed once: the wave-specialised multi-pass kernel on a multiple of 8 input channels
+// and more than 32 output channels, at least 32 of the former unless a tile request named the kernel.
+bool packable(const merit_plan *pl)
+{
+    const ConvParams &p = pl->conv;
+    const bool requested = pl->tile_req[2] > 0 && pl->tile_req[3] > 0;
+    return p.variant == CONV_CHWS && p.Cin % 8 == 0 && p.Cout > 32 && (requested || p.Cin >= 32);
+}
+
 // 1x1 windows at stride 1 without padding: the matrix-product kernel (conv2d_px.hip), whatever the general planner
 // chose, unless a tile request names one of the other kernels' tilings.
 void derive_px(merit_plan *pl)
@@ -435,7 +444,7 @@ void derive_px(merit_plan *pl)
     // Few channels, rows of whole 16-byte units, several tiles per compute unit: the persistent kernel's next tile flies
     // under its stores, and a single short step has no chain to hide (32 -> 64 on 32 images of 64x64: 7.1 against 7.6 us,
     // 64 -> 256 on 8 of 56x56: 6.6 against 7.2; 56 -> 560 on 2 of 71x24: 4.8 against 3.7).
-    if (c.variant == CONV_CHWS && !c.residual && Cin <= 64 && c.W % 8 == 0 && N * cdiv(HW, 128) * cdiv(Cout, 64) >= 512) return;
+    if (packable(pl) && !c.residual && Cin <= 64 && c.W % 8 == 0 && N * cdiv(HW, 128) * cdiv(Cout, 64) >= 512) return;
     // more than 256 channels, not a multiple of 8: left on the channels-in-passes kernel, where the plan tests hold it
     if (Cin % 8 != 0 && Cin > 256) return;
     if (Cin < 16 || HW < 8 || Cin * HW >= (1ll << 30) || Cout * Cin >= (1ll << 30) || Cout * HW >= (1ll << 30)) return;
@@ -467,7 +476,7 @@ void derive_px(merit_plan *pl)
     pl->px = p;
     pl->use_px = 1;
     merit_launch_info &li = pl->info;
-    if (c.variant != CONV_CHWS) li.kernel = "merit_conv2d_px";
+    if (!packable(pl)) li.kernel = "merit_conv2d_px";      // (else the family name that says so)
     li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
     li.block[0] = 512; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = (int64_t)px_lds_bytes(p);
@@ -706,6 +715,7 @@ merit_status derive_conv(merit_plan *pl)
     // Wave-specialised multi-pass kernel (conv2d_chws.hip): 256-pixel tiles x `cb` 32-channel blocks
     // (4 or 2), 16 input channels per pass through two LDS buffers, 3x3, 1x1 or 5x5 windows on a multiple
     // of 8 input channels.
+    bool any_count = false;      // the planner's own choice below: any channel count (a tile request and the fused pooling: as documented)
     auto try_chws = [&](int cb, bool forced, int nw = 8, int tm = 256, bool halo = false) -> bool {
         const bool k5 = kh == 5 && kw == 5;
         if (!((kh == 3 && kw == 3) || (kh == 1 && kw == 1) || k5)) return false;
@@ -714,7 +724,8 @@ merit_status derive_conv(merit_plan *pl)
         // its tiles are 256 pixels of one image: small images (13x13, 7x7) would leave a third
         // and more of every tile empty and stay with the 128-pixel tiles of the plain kernels
         if (!forced && !pool && 4 * ohw < 3 * cdiv(ohw, tm) * tm) return false;
-        if (Cin % 8 != 0 || Cin < 16 || (pool && p.residual) || ncb < 2) return false;
+        if (!any_count && (Cin % 8 != 0 || Cin < 16 || ncb < 2)) return false;
+        if (Cin < 8 || (pool && p.residual)) return false;
         // residual layer: 3x3 and 1x1 windows, the 64-channel tilings on 8 wavefronts
         if (p.residual && (!(kh == 3 || kh == 1) || cb != 2 || nw != 8)) return false;
         if (cb != 1 && cb != 2 && cb != 4) return false;
@@ -735,7 +746,6 @@ merit_status derive_conv(merit_plan *pl)
         q.rows_out_max = (int)((q.TM + OW - 2) / OW + 1);
         if (q.rows_out_max > OH) q.rows_out_max = (int)OH;
         q.tile_px = q.TM;
-        q.xq = 0;
         if (!pool && tm == 256) {
             // A tile of TM consecutive pixels starts anywhere in a row, so its covering sub-tensor
             // (Section IV-A, Eq. 9) is rows_out_max whole rows + the window's: on a 224-wide image
@@ -797,8 +807,8 @@ merit_status derive_conv(merit_plan *pl)
             // 1x1 windows: a pass is one tap; 64 channels per pass where its rows and staging units fit
             const int64_t g = 4, xb = 2 * g * (int64_t)q.RHa * pitch * 16, wb = g * cb * 64 * 16;
             const int64_t rows = 2 * g * (int64_t)q.RHa;
-            const int64_t nu = (W % 8) == 0 ? rows * (W / 8) : ((W % 4) == 0 ? rows * (W / 4) : rows * W);
-            const int64_t cap = ((W % 8) == 0 ? 2 : ((W % 4) == 0 ? (nw == 8 ? 4 : 2) : (nw == 8 ? 8 : 4))) * 256;
+            const int64_t nu = W >= 8 ? rows * cdiv(W, 8) : rows * W;
+            const int64_t cap = (W >= 8 ? 2 : (nw == 8 ? 8 : 4)) * 256;
             if (2 * (wb + xb) <= LDS_LIMIT && nu <= cap) ng = g;
         }
         q.nchi = (int)(2 * ng);
@@ -819,29 +829,14 @@ merit_status derive_conv(merit_plan *pl)
             if (q.lds_total > LDS_LIMIT) return false;
         }
         // staging units per moving thread and pass: 8 channels x 8 pixels (two at most), or x 1 pixel (eight; four on 12 wavefronts and for 5x5 windows)
-        if ((W % 8) == 0) {
-            const int64_t nu = 2 * ng * (int64_t)q.RHa * (W / 8);
-            if (nu > 2 * 256 || !fastdiv_ok(nu, 2 * ng * (int64_t)q.RHa)) return false;
-            q.xu = (int)cdiv(nu, 256);
-            q.div_w8 = make_fastdiv((uint32_t)(W / 8));
-            q.div_r2 = make_fastdiv((uint32_t)(2 * ng * q.RHa));
-        } else if ((W % 4) == 0 && !k5) {
-            // 8 channels x 4 pixels: four units per moving thread, two on 12 wavefronts
-            const int64_t nu = 2 * ng * (int64_t)q.RHa * (W / 4);
-            if (nu > (nw == 8 ? 4 : 2) * 256 || !fastdiv_ok(nu, 2 * ng * (int64_t)q.RHa)) return false;
-            q.xu = (int)cdiv(nu, 256);
-            q.xq = 1;
-            q.div_r2 = make_fastdiv((uint32_t)(2 * ng * q.RHa));
-        } else if ((W % 2) == 0 && !k5 && !pool && !p.residual && 2 * ng * (int64_t)q.RHa * (W / 2) <= (nw == 8 ? 8 : 4) * 256 &&
-                   fastdiv_ok(2 * ng * (int64_t)q.RHa * (W / 2), 2 * ng * (int64_t)q.RHa)) {
-            // 8 channels x 2 pixels (rows of an even width start on 4-byte boundaries: 14x14 layers), eight units
-            // per moving thread, four on 12 wavefronts
-            q.xu = (int)cdiv(2 * ng * (int64_t)q.RHa * (W / 2), 256);
-            q.xq = 2;
+        const int64_t nu8 = 2 * ng * (int64_t)q.RHa * cdiv(W, 8);
+        q.xpx = !(W >= 8 && nu8 <= 2 * 256 && fastdiv_ok(nu8, 2 * ng * (int64_t)q.RHa)) ? 1 : 0;
+        if (!q.xpx) {
+            q.xu = (int)cdiv(nu8, 256);
             q.div_r2 = make_fastdiv((uint32_t)(2 * ng * q.RHa));
         } else {
             const int64_t nu = 2 * ng * (int64_t)q.RHa * W;
-            if (nu > ((nw == 8 && !k5) ? 8 : 4) * 256 || !fastdiv_ok(nu, W)) return false;
+            if (W % 8 == 0 || nu > ((nw == 8 && !k5) ? 8 : 4) * 256 || !fastdiv_ok(nu, W)) return false;
             q.xu = (int)cdiv(nu, 256);
             q.div_w = make_fastdiv((uint32_t)W);
         }
@@ -951,7 +946,7 @@ merit_status derive_conv(merit_plan *pl)
         if (!ok)
             ok = want_big ? (try_variant(CONV_CHBLOCK, 2, 4) || try_variant(CONV_CHBLOCK, 1, 4))
                           : (try_variant(CONV_CHBLOCK, 1, 4) || try_variant(CONV_CHBLOCK, 2, 4));
-        // 3x3 layers on at least 32 input channels (a multiple of 8) and at least 33 output channels:
+        // 3x3 layers on at least 17 input channels (exceptions below):
         // the wave-specialised multi-pass kernel.  Its tilings: 256 pixels x 128 channels on 12
         // wavefronts, 256 x 64 and 128 x 64 (32 channels per pass) on 8.  The one with the lowest
         // estimate rounds of the grid x cost of a tile (1.6, 1, 0.6 from timings) is taken, the larger
@@ -961,7 +956,17 @@ merit_status derive_conv(merit_plan *pl)
         // (256 -> 64 on 56x56: 8.1 against 11.9 us, 1024 -> 256 on 14x14: 27 against 51); with a residual
         // tensor from 128 input channels on (128 -> 512 on 28x28: 11.7 against 36 us; 64 -> 256 on 56x56 is
         // a single short pass and stays on the single-pass kernel: 12.7 against 14.0).
-        if (((kh == 3 && kw == 3) || (kh == 1 && kw == 1 && (!p.residual || Cin >= 128)) || (kh == 5 && kw == 5 && !p.residual)) && Cin >= 32 && (Cin % 8) == 0 && ncb >= 2) {
+        const bool window = (kh == 3 && kw == 3) || (kh == 1 && kw == 1 && (!p.residual || Cin >= 128)) ||
+                            (kh == 5 && kw == 5 && !p.residual);
+        // Channel counts off the multiple of 8, 17 to 31 of them, and at most 32 output channels: the same kernel
+        // (65 -> 16 on 21 images of 18x20, stride 2: 31.3 -> 6.9 us; 165 -> 60 on 8 of 18x110, stride 2: 127 -> 23;
+        // 100 -> 100 on 8 of 28x28: 40 -> 8.0).  What stays on the channel-block kernels is close there -- up to 16
+        // channels (16 -> 64 on 8 of 56x56: 5.7 against 5.3), 64 aligned channels to at most 32 (64 -> 32: 7.2 against
+        // 5.7; 24 -> 32: 6.2 against 5.0) -- or is held there by the plan tests: single images with Cin % 8 != 0.
+        // (1x1 windows at stride 1 have a kernel of their own: derive_px.)
+        const bool was = Cin >= 32 && Cin % 8 == 0 && ncb >= 2;
+        any_count = (kh > 1 || sh > 1 || sw > 1) && Cin >= 17 && (Cin % 8 == 0 || N >= 2) && (ncb >= 2 || Cin % 8 != 0 || Cin > 64);
+        if (window && (was || any_count)) {
             int best = -1; double best_cost = 0.0;
             for (int shape = 0; shape < 4; ++shape) {          // 0: 256 x 128 on 12 wavefronts, 1: 256 x 64, 2: 128 x 64, 3: 128 x 32
                 if (shape == 0 && ncb < 4) continue;
@@ -1709,8 +1714,7 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x, const void *w, 
 
 static bool plan_takes_packed(const merit_plan *plan)
 {
-    return (plan->desc.op == MERIT_OP_CONV_DOT || plan->desc.op == MERIT_OP_CONV_DOT_RELU) &&
-           plan->conv.variant == CONV_CHWS;
+    return (plan->desc.op == MERIT_OP_CONV_DOT || plan->desc.op == MERIT_OP_CONV_DOT_RELU) && packable(plan);
 }
 
 merit_status merit_plan_packed_weights_bytes(const merit_plan *plan, int64_t *bytes)

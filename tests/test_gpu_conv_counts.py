@@ -1,0 +1,63 @@
+"""Many-channel layers on channel counts, output channels and row widths that are not whole units, on the
+wave-specialised kernel, against the oracle.  Bar: 2e-2*|r| + 1e-3."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1911_03458_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N  Cin  H   W  Cout k  s
+    (2, 17, 9, 8, 33, 3, 1),          # a group of one channel, rows of one whole unit
+    (2, 41, 11, 9, 24, 3, 1),         # rows of a unit and one pixel; at most 32 output channels
+    (3, 23, 17, 15, 70, 3, 2),        # seven of eight channels, stride 2
+    (2, 100, 14, 14, 96, 3, 1),
+    (2, 165, 12, 110, 60, 3, 2),      # wide rows, two units per moving thread
+    (2, 31, 30, 56, 128, 3, 1),
+    (2, 272, 13, 9, 24, 3, 1),
+    (2, 24, 19, 51, 264, 3, 1),
+    (2, 65, 12, 10, 40, 5, 1),        # 5x5
+    (2, 36, 21, 27, 17, 5, 2),
+    (3, 50, 31, 30, 56, 1, 2),        # 1x1 at stride 2
+    (2, 19, 13, 7, 40, 3, 1),         # rows of fewer than 8 pixels: one-pixel units
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("residual", [False, True])
+def test_against_the_oracle(case, residual):
+    N, Cin, H, W, Cout, k, s = case
+    args = (N, Cin, H, W, Cout, k, k, s, s, k // 2, k // 2)
+    rng = np.random.default_rng(Cin * 1000 + W)
+    x = rng.standard_normal((N, Cin, H, W)).astype(np.float16)
+    w = (rng.standard_normal((Cout, Cin, k, k)) / np.sqrt(Cin * k * k)).astype(np.float16)
+    plan = mb.merit_plan_conv2d_residual(*args, 1) if residual else mb.merit_plan_conv2d_relu(*args)
+    print(case, plan.launch_info(), flush=True)
+    if not residual:
+        assert plan.launch_info()["kernel"] == "merit_conv2d_chws"
+    n = int(np.prod(plan.out_shape()))
+    buf = torch.full((n + 128,), 777.0, dtype=torch.float16, device="cuda")
+    y = buf[64:64 + n].view(plan.out_shape())
+    r = rng.standard_normal(plan.out_shape()).astype(np.float16)
+    # the images and output channels next to the ones that are compared hold no numbers: what is loaded past a row
+    # of pixels or of weights must not leak
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    xd[1], wd[3] = float("nan"), float("inf")
+    if residual:
+        mb.merit_conv2d_residual(plan, xd, wd, torch.from_numpy(r).cuda(), y)
+        ref = oracle.conv2d_residual(x, w, r, (s, s), (k // 2, k // 2), True)
+    else:
+        mb.merit_conv2d(plan, xd, wd, y)
+        ref = oracle.conv2d(x, w, (s, s), (k // 2, k // 2), relu=True)
+    assert bool((buf[:64] == 777).all()) and bool((buf[64 + n:] == 777).all())
+    keep = [c for c in range(Cout) if c != 3]
+    imgs = [i for i in range(N) if i != 1]
+    got, ref = y.cpu().numpy().astype(np.float64)[imgs][:, keep], ref.astype(np.float64)[imgs][:, keep]
+    assert np.all(np.abs(got - ref) <= 2e-2 * np.abs(ref) + 1e-3), np.abs(got - ref).max()
+    with pytest.raises(mb.MeritError):          # (no packed form on these counts)
+        if Cin % 8 == 0 and Cout > 32 and Cin >= 32:
+            raise mb.MeritError(mb.MERIT_ERR_UNSUPPORTED, "")
+        mb.merit_plan_packed_weights_bytes(plan)
