@@ -148,9 +148,113 @@ __global__ __launch_bounds__(256) void merit_dwconv_rows_k3s1p1(DwParams p, cons
     }
 }
 
+// ---------------------------------------------------------------------------
+// K x K windows (3 or 5) at stride S (1 or 2), any padding, any width with OW >= 8 / S: no LDS, no barrier.
+//
+// A thread makes QW = 8 / S adjacent outputs of TR rows.  Bound by memory and by the launch on all but the largest of
+// these layers, so what counts is few, wide, early loads: the input columns an output row needs are one 16-byte load
+// and one of 4 or 8 bytes per input row, on any 2-byte boundary, all rows requested before the first is used; what lies
+// outside the plane is masked to zero.  The last unit of a row starts earlier where it would be cut (the outputs it
+// shares with its neighbour are stored twice, with the same values), so every store is whole.
+// us a launch, merit_dwconv_tile -> this: 12x144x94x24 5x5 26.8 -> 7.8, 1x24x96x80 5x5 / 2 17.2 -> 5.0, 8x96x112x112
+// 3x3 / 2 29.6 -> 8.3 (4.0 at the copy rate), 16x64x111x111 3x3 46.4 -> 12.9 (8.4), 32x512x14x14 3x3 20.5 -> 6.8.  On
+// rows of whole 16-byte chunks merit_dwconv_rows_k3s1p1 keeps the 3x3 layer (32x32x64x64: 5.5 against 6.3).
+// TR = 4: the rows that two strips share are read twice, but from L2.
+// ---------------------------------------------------------------------------
+template <int K, int S, int TR>
+__global__ __launch_bounds__(256) void merit_dwconv_lanes(DwParams p, const uint16_t *__restrict__ x,
+                                                         const uint16_t *__restrict__ w, uint16_t *__restrict__ y)
+{
+    constexpr int QW = 8 / S;                              // outputs of a row
+    constexpr int L = (QW - 1) * S + K;                    // input columns they need: 10, 12, 9, 11
+    constexpr int D = (L + 1) / 2;                         // dwords loaded per row: 5, 6, 5, 6
+    constexpr int RH = (TR - 1) * S + K;                   // input rows
+
+    const uint32_t item = xcd_band_item(blockIdx.x, p.xq, p.xr) * 256u + threadIdx.x;
+    if (item >= (uint32_t)p.items) return;
+    const uint32_t q = fdiv(item, p.div_units);            // (plane, strip)
+    const int u = (int)(item - q * (uint32_t)p.units);
+    const uint32_t nc = fdiv(q, p.div_tiles_y);
+    const int oy0 = (int)(q - nc * (uint32_t)p.tiles_y) * TR;
+    const int ox0 = min(u * QW, p.OW - QW);
+    const int c = (int)(nc - fdiv(nc, p.div_c) * (uint32_t)p.C);
+    const int gx0 = ox0 * S - p.pw, gy0 = oy0 * S - p.ph;
+
+    // which of the 2 D halves are inside the row
+    uint32_t mask[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const int a = gx0 + 2 * d, b = a + 1;
+        mask[d] = (a >= 0 && a < p.W ? 0x0000ffffu : 0u) | (b >= 0 && b < p.W ? 0xffff0000u : 0u);
+    }
+    const int total = p.NC * p.H * p.W;                    // (below 2^31: the planner)
+    const int plane = (int)nc * p.H * p.W;
+    uint32_t v[RH][D];
+    int moved[RH];                                         // halves by which a load was moved to stay inside the tensor
+#pragma unroll
+    for (int r = 0; r < RH; ++r) {
+        const int e = plane + min(max(gy0 + r, 0), p.H - 1) * p.W + gx0;
+        const int at = min(max(e, 0), total - 2 * D);
+        moved[r] = e - at;
+        __builtin_memcpy(v[r], x + at, 4 * D);
+    }
+    uint16_t wh[K * K];
+    __builtin_memcpy(wh, w + c * K * K, 2 * K * K);
+    float wk[K * K];
+#pragma unroll
+    for (int i = 0; i < K * K; ++i) wk[i] = h2f(wh[i]);
+    // the tensor's first and last units: back to where they belong, a half at a time (what comes in is masked)
+#pragma unroll
+    for (int r = 0; r < RH; ++r) {
+        for (int m = moved[r]; m > 0; --m) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) v[r][d] = (v[r][d] >> 16) | (d + 1 < D ? v[r][d + 1] << 16 : 0u);
+        }
+        for (int m = moved[r]; m < 0; ++m) {
+#pragma unroll
+            for (int d = D - 1; d >= 0; --d) v[r][d] = (v[r][d] << 16) | (d > 0 ? v[r][d - 1] >> 16 : 0u);
+        }
+    }
+
+    float acc[TR][QW];
+#pragma unroll
+    for (int t = 0; t < TR; ++t)
+#pragma unroll
+        for (int k = 0; k < QW; ++k) acc[t][k] = 0.0f;
+#pragma unroll
+    for (int r = 0; r < RH; ++r) {
+        const bool in = gy0 + r >= 0 && gy0 + r < p.H;
+        float f[2 * D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const uint32_t m = in ? v[r][d] & mask[d] : 0u;
+            f[2 * d] = h2f((uint16_t)m);
+            f[2 * d + 1] = h2f((uint16_t)(m >> 16));
+        }
+#pragma unroll
+        for (int t = 0; t < TR; ++t) {
+            const int ky = r - t * S;                      // an output's rows arrive in window scan order
+            if (ky < 0 || ky >= K) continue;
+#pragma unroll
+            for (int k = 0; k < QW; ++k)
+#pragma unroll
+                for (int kx = 0; kx < K; ++kx) acc[t][k] = fmaf(f[k * S + kx], wk[ky * K + kx], acc[t][k]);
+        }
+    }
+    uint16_t *yp = y + (size_t)nc * p.OH * p.OW + ox0;
+#pragma unroll
+    for (int t = 0; t < TR; ++t) {
+        if (oy0 + t >= p.OH) break;
+        uint32_t o[QW / 2];
+#pragma unroll
+        for (int k = 0; k < QW / 2; ++k) o[k] = (uint32_t)f2h(acc[t][2 * k]) | ((uint32_t)f2h(acc[t][2 * k + 1]) << 16);
+        __builtin_memcpy(yp + (size_t)(oy0 + t) * p.OW, o, 2 * QW);
+    }
+}
+
 hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *y, hipStream_t s)
 {
-    const int64_t grid = (int64_t)p.NC * p.tiles_y;
+    const int64_t grid = p.variant == DW_LANES ? ((int64_t)p.items + 255) / 256 : (int64_t)p.NC * p.tiles_y;
     if (grid == 0) return hipSuccess;
     const uint16_t *xs = reinterpret_cast<const uint16_t *>(x);
     const uint16_t *ws = reinterpret_cast<const uint16_t *>(w);
@@ -164,6 +268,17 @@ hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *
             e != hipSuccess)
             return e;
     }
+    if (p.variant == DW_LANES) {
+        const dim3 g((uint32_t)grid), b(256);
+        switch (p.kw * 10 + p.sw) {
+        case 31: hipLaunchKernelGGL((merit_dwconv_lanes<3, 1, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
+        case 32: hipLaunchKernelGGL((merit_dwconv_lanes<3, 2, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
+        case 51: hipLaunchKernelGGL((merit_dwconv_lanes<5, 1, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
+        case 52: hipLaunchKernelGGL((merit_dwconv_lanes<5, 2, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     if (p.variant == DW_ROWS_K3S1P1)
         hipLaunchKernelGGL(merit_dwconv_rows_k3s1p1, dim3((uint32_t)grid), dim3(256), (size_t)p.lds_bytes, s, p, xs, ws, ys);
     else
@@ -173,6 +288,7 @@ hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *
 
 const char *dwconv_kernel_name(const DwParams &p)
 {
+    if (p.variant == DW_LANES) return "merit_dwconv_lanes";
     return p.variant == DW_ROWS_K3S1P1 ? "merit_dwconv_rows_k3s1p1" : "merit_dwconv_tile";
 }
 

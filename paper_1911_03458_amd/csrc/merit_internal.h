@@ -299,7 +299,8 @@ struct CorrParams {
 };
 
 // ---- depthwise convolution -----------------------------------------------------
-enum DwVariant { DW_TILE_GENERIC = 0, DW_ROWS_K3S1P1 = 1 };
+enum DwVariant { DW_TILE_GENERIC = 0, DW_ROWS_K3S1P1 = 1, DW_LANES = 2 };
+constexpr int DW_LANES_ROWS = 4;       // output rows per thread there
 
 struct DwParams {
     int NC, C, H, W, OH, OW;
@@ -311,6 +312,10 @@ struct DwParams {
     int lds_bytes;
     FastDiv div_tiles_y, div_c, div_pitch;
     FastDiv div_ow;        // generic: OW; rows variant: W/8
+    // lanes variant: 8 / stride outputs of DW_LANES_ROWS rows per thread
+    int units, items;      // threads per output row, in all
+    int xq, xr;            // grid / 8, grid % 8 (see xcd_band_item)
+    FastDiv div_units;
 };
 
 hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *y, hipStream_t s);

@@ -1104,8 +1104,24 @@ merit_status derive_dw(merit_plan *pl)
     DwParams &p = pl->dw;
     p.NC = (int)(N * C); p.C = (int)C; p.H = (int)H; p.W = (int)W; p.OH = (int)OH; p.OW = (int)OW;
     p.kh = (int)kh; p.kw = (int)kw; p.sh = (int)sh; p.sw = (int)sw; p.ph = (int)ph; p.pw = (int)pw;
-    if (kh == 3 && kw == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && (W % 8) == 0 && W <= 4096 &&
-        pl->tile_req[2] <= 0) {
+    // 3x3 and 5x5 windows at stride 1 and 2 whose rows hold a thread's outputs: the kernel without LDS (not where a
+    // tile request names the rows of a workgroup)
+    const int64_t qw = 8 / (sw > 0 ? sw : 1), units = cdiv(OW, qw), strips = cdiv(OH, DW_LANES_ROWS);
+    const bool rows = kh == 3 && kw == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && W % 8 == 0 && W <= 4096 && pl->tile_req[2] <= 0;
+    const bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && OW >= qw && pl->tile_req[2] <= 0 &&
+                       N * C * H * W >= 16 && N * C * H * W < (1ll << 31) - 64 && N * C * strips * units < (1ll << 30) &&
+                       fastdiv_ok(N * C * strips * units + 256, units) && fastdiv_ok(N * C * strips, strips);
+    if (lanes) {
+        p.variant = DW_LANES;
+        p.TH = DW_LANES_ROWS;
+        p.pitch = 1;
+        p.lds_w_offset = 0; p.lds_bytes = 0;
+        p.units = (int)units;
+        p.items = (int)(N * C * strips * units);
+        p.div_units = make_fastdiv((uint32_t)units);
+        const int64_t wgs = cdiv(p.items, 256);
+        p.xq = (int)(wgs / 8); p.xr = (int)(wgs % 8);
+    } else if (rows) {
         p.variant = DW_ROWS_K3S1P1;
         int64_t TH = 4096 / W;                       // about two 8-pixel units per thread
         if (TH < 1) TH = 1;
@@ -1142,7 +1158,7 @@ merit_status derive_dw(merit_plan *pl)
     pl->out_shape[0] = N; pl->out_shape[1] = C; pl->out_shape[2] = OH; pl->out_shape[3] = OW;
     merit_launch_info &li = pl->info;
     li.kernel = dwconv_kernel_name(p);
-    li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
+    li.grid[0] = p.variant == DW_LANES ? cdiv(p.items, 256) : grid; li.grid[1] = 1; li.grid[2] = 1;
     li.block[0] = 256; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = p.lds_bytes;
     li.tile[0] = 1; li.tile[1] = 1; li.tile[2] = p.TH; li.tile[3] = OW; li.tile[4] = kh; li.tile[5] = kw;
