@@ -8,7 +8,10 @@
 // A workgroup owns 16 x 64 output pixels (the listing's 16-row tiles, a wavefront wide); the
 // covering sub-tensor (Section IV-A, Eq. 9) is staged in LDS with the clamping resolved
 // there, from column x0 - c4 (k/2 rounded up to 4), so that for W % 4 == 0 the staging is
-// aligned 16-byte loads without a branch.  A thread makes four outputs of one column, four
+// aligned 16-byte loads without a branch.  Any other W >= 4 the same: fp32 rows start on 4-byte
+// boundaries, which is all a 16-byte load or store needs, and the group that the row's end cuts
+// is loaded so that it ends with the row (element by element before: k = 13 on
+// 386x1202 19.0 us -> 17.8, k = 5 on 1000x1501 11.0 -> 10.2, k = 7 on 583x255 6.0 -> 5.3).  A thread makes four outputs of one column, four
 // rows apart: lanes run along the row (conflict-free 4-byte LDS reads) and the four
 // independent chains hide the latency of the exponential.  Five vector instructions per tap:
 // with s = sqrt(|norm| log2 e), the scaled difference d' = center*s - v*s is one fused
@@ -21,13 +24,14 @@ namespace merit {
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Staging of the covering sub-tensor: every element is a real (clamped) pixel.
+// Staging of the covering sub-tensor: every element is a real (clamped) pixel.  RAGGED = W % 4 != 0.
+template <bool RAGGED>
 __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float *__restrict__ img, float *in, int x0,
                                               int y0, int RH, int tid)
 {
-    if ((p.W & 3) == 0) {
+    if (!RAGGED || p.W >= 4) {
         constexpr int SB = 4;
-        const int P4 = p.PI >> 2, W4 = p.W >> 2;
+        const int P4 = p.PI >> 2, W4 = p.W >> 2, cut = p.W & 3;
         const int g0 = (x0 - p.c4) >> 2;                  // first staged 4-column group (may be < 0)
         const int total = RH * P4;
         for (int e0 = tid; e0 < total; e0 += 256 * SB) {
@@ -39,7 +43,10 @@ __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float 
                 const int r = (int)fdiv((uint32_t)e, p.div_p4);
                 g4[b] = g0 + (e - r * P4);
                 const int gyy = min(max(y0 - p.c + r, 0), p.H - 1);
-                v[b] = *reinterpret_cast<const float4v *>(img + (size_t)gyy * p.W + 4 * min(max(g4[b], 0), W4 - 1));
+                if (RAGGED)
+                    __builtin_memcpy(&v[b], img + (size_t)gyy * p.W + min(max(4 * g4[b], 0), p.W - 4), 16);
+                else
+                    v[b] = *reinterpret_cast<const float4v *>(img + (size_t)gyy * p.W + 4 * min(max(g4[b], 0), W4 - 1));
             }
 #pragma unroll
             for (int b = 0; b < SB; ++b) {
@@ -48,6 +55,10 @@ __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float 
                 float4v o;
                 o.x = inside ? v[b].x : edge; o.y = inside ? v[b].y : edge;
                 o.z = inside ? v[b].z : edge; o.w = inside ? v[b].w : edge;
+                if (RAGGED && g4[b] == W4) {                      // `cut` pixels, behind those shared with its neighbour
+                    o.x = cut == 1 ? v[b].w : (cut == 2 ? v[b].z : v[b].y);
+                    o.y = cut == 3 ? v[b].z : v[b].w;
+                }
                 if (e0 + 256 * b < total) reinterpret_cast<float4v *>(in)[e0 + 256 * b] = o;
             }
         }
@@ -64,7 +75,7 @@ __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float 
 }
 
 // NEG: the range constant is <= 0 (the usual decaying range term)
-template <bool NEG>
+template <bool NEG, bool RAGGED>
 __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const float *__restrict__ x,
                                                            const float *__restrict__ gx,
                                                            const float *__restrict__ gy, float *__restrict__ y)
@@ -93,7 +104,7 @@ __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const
         wxl[tid] = __builtin_amdgcn_logf(gx[tid]);        // log2
         wyl[tid] = gy[tid];
     }
-    stage_clamped(p, img, in, x0, y0, RH, tid);
+    stage_clamped<RAGGED>(p, img, in, x0, y0, RH, tid);
     __syncthreads();
 
     // outputs (row0 + 4j, col), j < 4; staged column of tap a2 for output column col:
@@ -147,7 +158,7 @@ __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const
 // aligned 16-byte read (staged column of output column j is j + c4 - c + a2; at a2 = c that
 // is j + c4).  Lanes 0-15 of a wavefront take the 16 column groups of one row.
 // ---------------------------------------------------------------------------
-template <int K, bool NEG>
+template <int K, bool NEG, bool RAGGED>
 __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const float *__restrict__ x,
                                                            const float *__restrict__ gx,
                                                            const float *__restrict__ gy, float *__restrict__ y)
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
         wxl[tid] = __builtin_amdgcn_logf(gx[tid]);        // log2
         wyl[tid] = gy[tid];
     }
-    stage_clamped(p, img, in, x0, y0, RH, tid);
+    stage_clamped<RAGGED>(p, img, in, x0, y0, RH, tid);
     __syncthreads();
 
     const int q = tid & 15, row = tid >> 4;               // column group, output row
@@ -230,10 +241,13 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
     const int gyo = y0 + row, gxo = x0 + 4 * q;
     if (gyo < p.H) {
         float *dst = y + (size_t)n * p.H * p.W + (size_t)gyo * p.W + gxo;
-        if ((p.W & 3) == 0) {
+        if (!RAGGED) {
             if (gxo < p.W)
                 *reinterpret_cast<float4v *>(dst) = (float4v){wxsum[0] / wsum[0], wxsum[1] / wsum[1],
                                                                wxsum[2] / wsum[2], wxsum[3] / wsum[3]};
+        } else if (gxo + 3 < p.W) {
+            const float4v o = {wxsum[0] / wsum[0], wxsum[1] / wsum[1], wxsum[2] / wsum[2], wxsum[3] / wsum[3]};
+            __builtin_memcpy(dst, &o, 16);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -242,16 +256,30 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
     }
 }
 
-template <int K>
+template <int K, bool RAGGED>
 static hipError_t launch_bil_rows(const BilatParams &p, const float *x, const float *gx, const float *gy, float *y,
                                   hipStream_t s, uint32_t grid)
 {
-    if (p.neg)
-        hipLaunchKernelGGL((merit_bilateral_rows<K, true>), dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, gx, gy,
-                           y);
-    else
-        hipLaunchKernelGGL((merit_bilateral_rows<K, false>), dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, gx,
-                           gy, y);
+    const auto k = p.neg ? merit_bilateral_rows<K, true, RAGGED> : merit_bilateral_rows<K, false, RAGGED>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, gx, gy, y);
+    return hipGetLastError();
+}
+
+template <bool RAGGED>
+static hipError_t launch_bil(const BilatParams &p, const float *x, const float *gx, const float *gy, float *y,
+                             hipStream_t s, uint32_t g)
+{
+    switch (p.k <= 16 ? p.k : 0) {
+#define MERIT_BIL_CASE(Kv) case Kv: return launch_bil_rows<Kv, RAGGED>(p, x, gx, gy, y, s, g)
+        MERIT_BIL_CASE(1); MERIT_BIL_CASE(2); MERIT_BIL_CASE(3); MERIT_BIL_CASE(4);
+        MERIT_BIL_CASE(5); MERIT_BIL_CASE(6); MERIT_BIL_CASE(7); MERIT_BIL_CASE(8);
+        MERIT_BIL_CASE(9); MERIT_BIL_CASE(10); MERIT_BIL_CASE(11); MERIT_BIL_CASE(12);
+        MERIT_BIL_CASE(13); MERIT_BIL_CASE(14); MERIT_BIL_CASE(15); MERIT_BIL_CASE(16);
+#undef MERIT_BIL_CASE
+    default: break;
+    }
+    const auto k = p.neg ? merit_bilateral_tile<true, RAGGED> : merit_bilateral_tile<false, RAGGED>;
+    hipLaunchKernelGGL(k, dim3(g), dim3(256), (size_t)p.lds_bytes, s, p, x, gx, gy, y);
     return hipGetLastError();
 }
 
@@ -260,23 +288,8 @@ hipError_t launch_bilateral(const BilatParams &p, const float *x, const float *g
 {
     const int64_t grid = (int64_t)p.N * p.tiles_y * p.tiles_x;
     if (grid == 0) return hipSuccess;
-    const uint32_t g = (uint32_t)grid;
-    switch (p.k <= 16 ? p.k : 0) {
-#define MERIT_BIL_CASE(Kv) case Kv: return launch_bil_rows<Kv>(p, x, gx, gy, y, s, g)
-        MERIT_BIL_CASE(1); MERIT_BIL_CASE(2); MERIT_BIL_CASE(3); MERIT_BIL_CASE(4);
-        MERIT_BIL_CASE(5); MERIT_BIL_CASE(6); MERIT_BIL_CASE(7); MERIT_BIL_CASE(8);
-        MERIT_BIL_CASE(9); MERIT_BIL_CASE(10); MERIT_BIL_CASE(11); MERIT_BIL_CASE(12);
-        MERIT_BIL_CASE(13); MERIT_BIL_CASE(14); MERIT_BIL_CASE(15); MERIT_BIL_CASE(16);
-#undef MERIT_BIL_CASE
-    default: break;
-    }
-    if (p.neg)
-        hipLaunchKernelGGL(merit_bilateral_tile<true>, dim3((uint32_t)grid), dim3(256), (size_t)p.lds_bytes, s, p, x,
-                           gx, gy, y);
-    else
-        hipLaunchKernelGGL(merit_bilateral_tile<false>, dim3((uint32_t)grid), dim3(256), (size_t)p.lds_bytes, s, p,
-                           x, gx, gy, y);
-    return hipGetLastError();
+    return (p.W & 3) != 0 ? launch_bil<true>(p, x, gx, gy, y, s, (uint32_t)grid)
+                          : launch_bil<false>(p, x, gx, gy, y, s, (uint32_t)grid);
 }
 
 }  // namespace merit

@@ -17,7 +17,11 @@
 // The staged columns start at x0 - c4, c4 = k/2 rounded up to 4, so that (for W % 4 == 0) every
 // group of four staged columns is one aligned 16-byte run of the image, entirely inside it or
 // entirely outside (then it is four copies of the edge pixel): the staging is 16-byte loads
-// without a branch, and the row pass reads its window c4 - k/2 columns further right.
+// without a branch, and the row pass reads its window c4 - k/2 columns further right.  Any other
+// W >= 4 the same: fp32 rows start on 4-byte boundaries, which is all a 16-byte load or store
+// needs, and the group that the row's end cuts is loaded so that it ends with the row, its pixels
+// picked out of the four.  (Such widths were staged element by element: k = 13 on 2x678x1861
+// 23.0 us -> 9.3, k = 6 on 2x806x869 12.0 -> 6.6, k = 17 on 1080x1919 20.3 -> 10.5.)
 #include "merit_internal.h"
 
 namespace merit {
@@ -25,8 +29,9 @@ namespace merit {
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 // K = window length (compile time: every tap index is an immediate, the sliding windows live
-// in renamed registers and no zero tap is multiplied)
-template <int K>
+// in renamed registers and no zero tap is multiplied).  RAGGED = W % 4 != 0 (an instance of its
+// own: as a run-time condition it cost the aligned rows 1.5 %)
+template <int K, bool RAGGED>
 __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(SepParams p, const float *__restrict__ x,
                                                            const float *__restrict__ kx,
                                                            const float *__restrict__ ky, float *__restrict__ y)
@@ -69,7 +74,7 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
     // issued before the first LDS write (one memory round trip per batch).
     constexpr int SB = K <= 16 ? 8 : 12;                  // 8 rows per step: 64 or 96 staged rows at most
     const int P4 = p.PI >> 2, W4 = p.W >> 2;              // P4 <= 32 for every K <= 32
-    const bool vec = (p.W & 3) == 0;
+    const bool vec = !RAGGED || p.W >= 4;
     constexpr int lg = 5;                                 // lanes per staged row
     const int cg = tid & ((1 << lg) - 1);
     const bool live = cg < P4;
@@ -83,11 +88,13 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
         const int g4 = ((T.x0 - C4) >> 2) + cg;           // image 4-column group (may be outside)
         // uniform image base + 32-bit element offsets (the plan keeps H*W below 2^31)
         const float *img = x + (size_t)T.n * p.H * p.W;
-        const uint32_t col = 4u * (uint32_t)min(max(g4, 0), W4 - 1);
+        const uint32_t col = RAGGED ? (uint32_t)min(max(4 * g4, 0), p.W - 4) : 4u * (uint32_t)min(max(g4, 0), W4 - 1);
 #pragma unroll
         for (int b = 0; b < SB; ++b) {
             const int gy = min(max(T.y0 - C + r0 + rstep * b, 0), p.H - 1);
-            pre[b] = *reinterpret_cast<const float4v *>(img + (col + (uint32_t)gy * (uint32_t)p.W));
+            const float *src = img + (col + (uint32_t)gy * (uint32_t)p.W);
+            if (RAGGED) __builtin_memcpy(&pre[b], src, 16);
+            else pre[b] = *reinterpret_cast<const float4v *>(src);
         }
     };
     auto commit = [&](const Tile &T, int r0) {
@@ -102,6 +109,20 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
             o.x = inside ? pre[b].x : edge; o.y = inside ? pre[b].y : edge;
             o.z = inside ? pre[b].z : edge; o.w = inside ? pre[b].w : edge;
             if (live && r < RH) reinterpret_cast<float4v *>(in)[r * P4 + cg] = o;
+        }
+        // the group that the row's end cuts: its first pixels lie behind those it shares with its neighbour (written once
+        // more, so that the common form above stays as short as it is)
+        if (RAGGED && g4 == W4) {
+            const int cut = p.W & 3;                      // pixels of the group that exist
+#pragma unroll
+            for (int b = 0; b < SB; ++b) {
+                const int r = r0 + rstep * b;
+                float4v o = pre[b];
+                o.x = cut == 1 ? pre[b].w : (cut == 2 ? pre[b].z : pre[b].y);
+                o.y = cut == 3 ? pre[b].z : pre[b].w;
+                o.z = pre[b].w;
+                if (live && r < RH) reinterpret_cast<float4v *>(in)[r * P4 + cg] = o;
+            }
         }
     };
 
@@ -243,13 +264,14 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
                 const int gy = y0 + PR * rg + i;
                 if (gy >= p.H) continue;
                 float *dst = out + (size_t)gy * p.W + gx;
-                if (vec) {
+                if (!RAGGED) {
                     if (gx < p.W) *reinterpret_cast<float4v *>(dst) = o[i];
+                } else if (gx + 3 < p.W) {
+                    __builtin_memcpy(dst, &o[i], 16);
                 } else {
                     if (gx < p.W) dst[0] = o[i].x;
                     if (gx + 1 < p.W) dst[1] = o[i].y;
                     if (gx + 2 < p.W) dst[2] = o[i].z;
-                    if (gx + 3 < p.W) dst[3] = o[i].w;
                 }
             }
         }
@@ -257,12 +279,12 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
     }
 }
 
-template <int K>
-static hipError_t launch_sep(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
+template <int K, bool RAGGED>
+static hipError_t launch_sep_rows(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
                              hipStream_t s, int64_t ntiles, int cus)
 {
     static std::atomic<int> raised{0};
-    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_sepfilter_tile<K>), raised);
+    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_sepfilter_tile<K, RAGGED>), raised);
         e != hipSuccess)
         return e;
     // Persistent workgroups.  The plan's count per CU is what LDS allows.  Long windows need so
@@ -280,7 +302,7 @@ static hipError_t launch_sep(const SepParams &p, const float *x, const float *kx
         int answer = (int)(seen & 0xffffffffu);
         if ((seen >> 32) != (uint64_t)(uint32_t)p.lds_bytes || answer <= 0) {
             int r = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, merit_sepfilter_tile<K>, 256,
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, merit_sepfilter_tile<K, RAGGED>, 256,
                                                              (size_t)p.lds_bytes) != hipSuccess || r <= 0)
                 r = 1;
             answer = r;
@@ -290,8 +312,16 @@ static hipError_t launch_sep(const SepParams &p, const float *x, const float *kx
     }
     const int64_t slots = (int64_t)cus * per_cu;
     const uint32_t grid = (uint32_t)(ntiles < slots ? ntiles : slots);
-    hipLaunchKernelGGL(merit_sepfilter_tile<K>, dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, kx, ky, y);
+    hipLaunchKernelGGL((merit_sepfilter_tile<K, RAGGED>), dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, kx, ky, y);
     return hipGetLastError();
+}
+
+template <int K>
+static hipError_t launch_sep(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
+                             hipStream_t s, int64_t ntiles, int cus)
+{
+    return (p.W & 3) != 0 ? launch_sep_rows<K, true>(p, x, kx, ky, y, s, ntiles, cus)
+                          : launch_sep_rows<K, false>(p, x, kx, ky, y, s, ntiles, cus);
 }
 
 hipError_t launch_sepfilter(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
