@@ -23,7 +23,6 @@
 
 #include <atomic>
 #include <mutex>
-#include <type_traits>
 
 namespace merit {
 
@@ -135,7 +134,9 @@ constexpr uint32_t OOB = 0x80000000u;   // a buffer offset past the end of every
 // POOL: the results are max-pooled (3x3 / stride 2 / padding 1) out of the staging area and only the
 // pooled tensor is written; work items are bands of pooled rows (pool_geom above).
 // RES: a tensor of the output's shape is added to the fp32 sums before the clip and the rounding.
-template <int PXB, int CHB, int WM, int WN, int T, int XU, bool PACKED, int NG = 1, bool POOL = false, bool RES = false>
+// RAGGED: Cin % 8 != 0, the last group of 8 channels is not whole (an instance of its own: the selects on every load
+// cost the others 3-10 %; 8-pixel units and the caller's weights only).
+template <int PXB, int CHB, int WM, int WN, int T, int XU, bool PACKED, int NG = 1, bool POOL = false, bool RES = false, bool RAGGED = false>
 __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvParams p, const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ w,
                                                             const uint16_t *res, uint16_t *y)
@@ -147,6 +148,14 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
     constexpr int WITEMS = NG * T * NCB * 64;            // 16-byte weight fragments per pass
     constexpr int NGRP = 2 * NG;                         // 8-channel groups per pass
     constexpr int WU = (TN * NGRP + 255) / 256;          // weight units (8 channels x T taps of one output channel) per moving thread
+    // Packed weights on the 128-pixel tiles go through registers, requested two passes ahead like the input rows: their
+    // passes are shorter than the memory round trip that a copy straight into LDS, started when its buffer is free, takes
+    // inside one of them (256 -> 256 on 8x14x14: 11.7 us on the direct copy, 10.3; 512 -> 512 20.2, 18.5).
+    constexpr bool WREG = PACKED && TM == 128;
+    constexpr int WP = (WITEMS + 255) / 256;             // fragments per moving thread there
+    // Passes on their way in registers: two with those (and 8-pixel units), else one (on the caller's weights a second
+    // one gained nothing: there a pass waits for its load instructions, not for memory).
+    constexpr int SETS = WREG && XU == 1 ? 2 : 1;
     constexpr int OP = TM / 2 + 2;                       // output staging: dwords per channel
     constexpr bool XV = XU == 1 || XU == 2;              // 8-pixel input units, XU per moving thread
 
@@ -306,14 +315,14 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         uint32_t x_voff[NXU];               // byte offset of the unit inside (image, first channel of the pass)
         int x_lds[NXU];                     // byte address of its first pixel inside a pass buffer's input region
         int x_hh[NXU];                      // its channel group within the pass
-        uint32_t xv[XV ? XU : 1][8][4];     // the unit on its way: 8 channels x 8 pixels
+        uint32_t xv[SETS][XV ? XU : 1][8][4];     // the unit on its way: 8 channels x 8 pixels
         uint32_t xs[XV ? 1 : XSM][8];       // ... 8 channels x 1 pixel (a register each: see commit)
         uint32_t w_voff[WU];
         int w_lds[WU], w_hh[WU];
-        uint32_t wr[PACKED ? 1 : WU][PACKED ? 1 : 4 * T];
+        uint32_t wr[SETS][PACKED ? 1 : WU][PACKED ? 1 : 4 * T];
+        uint32_t wp[SETS][WREG ? WP : 1][4];      // packed fragments on their way (WREG)
 
         const int rstep = p.row_skip ? p.sh : 1;        // image rows between staged rows
-        const bool ragged = (p.Cin & 7) != 0;           // the last group of 8 channels is not whole
         auto setup = [&](const Geom &g) __attribute__((always_inline)) {
             if constexpr (XV) {
                 const int W8 = (p.W + 7) >> 3;
@@ -370,10 +379,16 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         };
 
         // request the input rows (and, unless packed, the weights) of pass ck into the registers
-        // (RAGGED: the last group of 8 channels is not whole; a form of its own, its selects on every load cost the
-        // others 5-10 %)
-        auto request_as = [&](auto ragged_form, const Geom &g, int ck) __attribute__((always_inline)) {
-            constexpr bool RAGGED = decltype(ragged_form)::value;
+        auto request = [&](const Geom &g, int ck, int set) __attribute__((always_inline)) {
+            if constexpr (WREG) {
+                const uint32_t soff = (uint32_t)((g.cg * npass + ck) * WITEMS) * 16u;
+#pragma unroll
+                for (int k = 0; k < WP; ++k) {
+                    const int i = mt + 256 * k;
+                    const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, i < WITEMS ? (uint32_t)i * 16u : OOB, soff, 0);
+                    wp[set][k][0] = v.x; wp[set][k][1] = v.y; wp[set][k][2] = v.z; wp[set][k][3] = v.w;
+                }
+            }
             // (the same for the whole wavefront: said explicitly, or the 2-byte loads below each get a
             // loop over the distinct values of a vector register)
             const uint32_t xbase = (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -389,7 +404,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                     const uint32_t voff = RAGGED && c >= livec ? OOB : all;
                     if constexpr (XV) {
                         const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, voff, xbase + c * chbytes, 0);
-                        xv[k][c][0] = v.x; xv[k][c][1] = v.y; xv[k][c][2] = v.z; xv[k][c][3] = v.w;
+                        xv[set][k][c][0] = v.x; xv[set][k][c][1] = v.y; xv[set][k][c][2] = v.z; xv[set][k][c][3] = v.w;
                     } else {
                         xs[k][c] = __builtin_amdgcn_raw_buffer_load_b16(rx, voff, xbase + c * chbytes, 0);
                     }
@@ -410,18 +425,13 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                         uint32_t vo = voff + 16 * i;
                         if (RAGGED) vo = 8 * i + 8 <= nv ? vo : (8 * i < nv ? tail : OOB);
                         const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, RAGGED ? 0u : pass, 0);
-                        wr[k][4 * i + 0] = v.x; wr[k][4 * i + 1] = v.y; wr[k][4 * i + 2] = v.z; wr[k][4 * i + 3] = v.w;
+                        wr[set][k][4 * i + 0] = v.x; wr[set][k][4 * i + 1] = v.y; wr[set][k][4 * i + 2] = v.z; wr[set][k][4 * i + 3] = v.w;
                     }
                 }
             }
         };
-        auto request = [&](const Geom &g, int ck) __attribute__((always_inline)) {
-            if (ragged) request_as(std::true_type{}, g, ck);
-            else request_as(std::false_type{}, g, ck);
-        };
-
         // transpose the registers into pass buffer b
-        auto commit = [&](int ck, int b) __attribute__((always_inline)) {      // ck: the pass that was requested
+        auto commit = [&](int ck, int b, int set) __attribute__((always_inline)) {      // ck: the pass that was requested
             uint8_t *xl = smem + b * p.lds_buf_bytes + p.lds_w_bytes;
 #pragma unroll
             for (int k = 0; k < NXU; ++k) {
@@ -432,10 +442,10 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                         for (int px = 0; px < 8; ++px) {
                             const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
                             uint32x4 d;
-                            d.x = __builtin_amdgcn_perm(xv[k][1][px >> 1], xv[k][0][px >> 1], sel);
-                            d.y = __builtin_amdgcn_perm(xv[k][3][px >> 1], xv[k][2][px >> 1], sel);
-                            d.z = __builtin_amdgcn_perm(xv[k][5][px >> 1], xv[k][4][px >> 1], sel);
-                            d.w = __builtin_amdgcn_perm(xv[k][7][px >> 1], xv[k][6][px >> 1], sel);
+                            d.x = __builtin_amdgcn_perm(xv[set][k][1][px >> 1], xv[set][k][0][px >> 1], sel);
+                            d.y = __builtin_amdgcn_perm(xv[set][k][3][px >> 1], xv[set][k][2][px >> 1], sel);
+                            d.z = __builtin_amdgcn_perm(xv[set][k][5][px >> 1], xv[set][k][4][px >> 1], sel);
+                            d.w = __builtin_amdgcn_perm(xv[set][k][7][px >> 1], xv[set][k][6][px >> 1], sel);
                             *reinterpret_cast<uint32x4 *>(xl + x_lds[k] + px * 16) = d;
                         }
                     } else {
@@ -452,20 +462,30 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                     }
                 }
             }
+            if constexpr (WREG) {
+                uint8_t *wl = smem + b * p.lds_buf_bytes;
+#pragma unroll
+                for (int k = 0; k < WP; ++k) {
+                    const int i = mt + 256 * k;
+                    uint32x4 v;
+                    v.x = wp[set][k][0]; v.y = wp[set][k][1]; v.z = wp[set][k][2]; v.w = wp[set][k][3];
+                    if (WITEMS % 256 == 0 || i < WITEMS) *reinterpret_cast<uint32x4 *>(wl + i * 16) = v;
+                }
+            }
             if constexpr (!PACKED) {
                 uint8_t *wl = smem + b * p.lds_buf_bytes;
 #pragma unroll
                 for (int k = 0; k < WU; ++k) {
                     if (w_hh[k] < NGRP) {
                         const int nv = (p.Cin - (ck * NGRP + w_hh[k]) * 8) * T;
-                        if (ragged && nv > 0 && nv < 8 * T) {
+                        if (RAGGED && nv > 0 && nv < 8 * T) {
 #pragma unroll
                             for (int i = 0; i < T; ++i) {
                                 if (8 * i < nv && 8 * i + 8 > nv) {
-                                    uint32_t v[4] = {wr[k][4 * i], wr[k][4 * i + 1], wr[k][4 * i + 2], wr[k][4 * i + 3]};
+                                    uint32_t v[4] = {wr[set][k][4 * i], wr[set][k][4 * i + 1], wr[set][k][4 * i + 2], wr[set][k][4 * i + 3]};
                                     shift_down(v, 16 * (8 * i + 8 - nv));
 #pragma unroll
-                                    for (int q = 0; q < 4; ++q) wr[k][4 * i + q] = v[q];
+                                    for (int q = 0; q < 4; ++q) wr[set][k][4 * i + q] = v[q];
                                 }
                             }
                         }
@@ -478,7 +498,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                                 const int e0 = (2 * q) * T + t, e1 = (2 * q + 1) * T + t;
                                 const uint32_t sel =
                                     ((e0 & 1) ? 0x00000302u : 0x00000100u) | ((e1 & 1) ? 0x07060000u : 0x05040000u);
-                                d[q] = __builtin_amdgcn_perm(wr[k][e1 >> 1], wr[k][e0 >> 1], sel);
+                                d[q] = __builtin_amdgcn_perm(wr[set][k][e1 >> 1], wr[set][k][e0 >> 1], sel);
                             }
                             uint32x4 dv;
                             dv.x = d[0]; dv.y = d[1]; dv.z = d[2]; dv.w = d[3];
@@ -492,7 +512,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         // packed weights of pass ck of channel block cg: global memory -> pass buffer b directly
         // (no registers; each wavefront instruction moves 64 consecutive fragments)
         auto weights_direct = [&](int cg, int ck, int b) __attribute__((always_inline)) {
-            if constexpr (PACKED) {
+            if constexpr (PACKED && !WREG) {
                 const uint32_t soff = (uint32_t)((cg * npass + ck) * WITEMS) * 16u;
                 constexpr int ROUNDS = (WITEMS / 64 + 3) / 4;
 #pragma unroll
@@ -507,7 +527,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         };
         // ... and the wait for them: everything this wavefront has requested has arrived
         auto weights_landed = [&]() __attribute__((always_inline)) {
-            if constexpr (PACKED) __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xF << 8));    // vmcnt(0)
+            if constexpr (PACKED && !WREG) __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xF << 8));    // vmcnt(0)
         };
 
         // the padding columns of the staged rows, both buffers (the output staging overwrites them)
@@ -530,39 +550,65 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         // after the commit, so one pass is in flight at a time, for a whole period.
         Geom g = geom_at(item, 0);
         setup(g);
-        request(g, 0);
+        request(g, 0, 0);
+        if (SETS == 2 && npass > 1) request(g, 1, SETS - 1);
         for (;;) {
             int item2 = item, ti2 = ti, ntile2 = ntile;
             const bool more = next_pos(item2, ti2, ntile2);
             const Geom gn = more ? geom_at(item2, ti2) : g;
-            commit(0, 0);
+            commit(0, 0, 0);
             weights_direct(g.cg, 0, 0);
             zero_pads();
-            if (npass > 1) request(g, 1);
+            if (npass > SETS) request(g, SETS, 0);
             weights_landed();                                  // (waits for the request too: once per item)
             __syncthreads();                                   // P
-            for (int ck = 0; ck < npass; ++ck) {
+            if constexpr (SETS == 2) {
+                // pass ck + 1 to its buffer, pass ck + 3 into the registers this frees: in pairs of periods without a
+                // branch round the requests (the compiler's waits then count what is in flight), then up to four more
+                int ck = 0;
+                for (; ck + 4 < npass; ck += 2) {
+                    commit(ck + 1, 1, 1);
+                    request(g, ck + 3, 1);
+                    __syncthreads();                // B_ck
+                    commit(ck + 2, 0, 0);
+                    request(g, ck + 4, 0);
+                    __syncthreads();                // B_ck+1
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (ck + i < npass) {
+                        if (ck + i + 1 < npass) commit(ck + i + 1, (i + 1) & 1, (i + 1) & 1);
+                        if (ck + i + 3 < npass) request(g, ck + i + 3, (i + 1) & 1);
+                        __syncthreads();
+                    }
+                }
+            }
+            for (int ck = 0; SETS == 1 && ck < npass; ++ck) {
                 if (ck + 1 < npass) {
-                    commit(ck + 1, (ck + 1) & 1);
+                    commit(ck + 1, (ck + 1) & 1, 0);
                     weights_direct(g.cg, ck + 1, (ck + 1) & 1);
                     if constexpr (XV) {
                         // the packed weights have the rest of the period to land: wait until only
                         // the request that follows them is still in flight
                         if (ck + 2 < npass) {
-                            request(g, ck + 2);
-                            if constexpr (PACKED) __builtin_amdgcn_s_waitcnt((8 * XU) | (0x7 << 4) | (0xF << 8));
+                            request(g, ck + 2, 0);
+                            if constexpr (PACKED && !WREG) __builtin_amdgcn_s_waitcnt((8 * XU) | (0x7 << 4) | (0xF << 8));
                         } else {
                             weights_landed();
                         }
                     } else {
                         weights_landed();
-                        if (ck + 2 < npass) request(g, ck + 2);
+                        if (ck + 2 < npass) request(g, ck + 2, 0);
                     }
                 }
                 __syncthreads();                    // B_ck
             }
             // the next item's first pass flies under the result stores
-            if (more) { setup(gn); request(gn, 0); }
+            if (more) {
+                setup(gn);
+                request(gn, 0, 0);
+                if (SETS == 2 && npass > 1) request(gn, 1, SETS - 1);
+            }
             __syncthreads();                                   // E1
             if constexpr (POOL) pool_out(g);
             else store_out(g);
@@ -747,25 +793,33 @@ hipError_t launch_one(K kernel, const ConvParams &p, const void *x, const void *
     return hipGetLastError();
 }
 
+template <int PXB, int CHB, int WM, int WN, int T, int XU, int NG>
+hipError_t launch_res(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s, uint32_t grid)
+{
+    if ((p.Cin & 7) != 0) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, T, XU, false, NG, false, true, true>, p, x, w, res, y, s, grid);
+    return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, T, XU, false, NG, false, true>, p, x, w, res, y, s, grid);
+}
+
 template <int PXB, int CHB, int WM, int WN, int NG = 1, bool POOLS = false>
 hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
                        uint32_t grid, bool packed)
 {
     const int xu = p.xpx ? 0 : p.xu;          // 8-pixel units per moving thread (1, 2); 0: one-pixel units
     const int T = p.kh * p.kw;
+    if ((p.Cin & 7) != 0 && (xu == 0 || packed || p.pool)) return hipErrorInvalidValue;
     if (p.residual) {
         // residual layer: 3x3 and 1x1 windows on the caller's weights, the two 64-channel tilings (on the
         // others the 32 registers of the added tensor would spill)
         if constexpr (POOLS && WN == 1) {
             if ((T != 9 && T != 1) || packed || p.pool) return hipErrorInvalidValue;
             if (T == 1) {
-                if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 1, false, NG, false, true>, p, x, w, res, y, s, grid);
-                if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 2, false, NG, false, true>, p, x, w, res, y, s, grid);
+                if (xu == 1) return launch_res<PXB, CHB, WM, WN, 1, 1, NG>(p, x, w, res, y, s, grid);
+                if (xu == 2) return launch_res<PXB, CHB, WM, WN, 1, 2, NG>(p, x, w, res, y, s, grid);
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
             if constexpr (NG != 4) {        // (64 channels per pass: 1x1 windows only)
-                if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 1, false, NG, false, true>, p, x, w, res, y, s, grid);
-                if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 2, false, NG, false, true>, p, x, w, res, y, s, grid);
+                if (xu == 1) return launch_res<PXB, CHB, WM, WN, 9, 1, NG>(p, x, w, res, y, s, grid);
+                if (xu == 2) return launch_res<PXB, CHB, WM, WN, 9, 2, NG>(p, x, w, res, y, s, grid);
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
         }
@@ -783,19 +837,24 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
     }
 #define MERIT_CHWS(Tv, XUv)                                                                             \
     do {                                                                                                \
+        if (XUv != 0 && !packed && (p.Cin & 7) != 0)                                                     \
+            return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG, false, false, XUv != 0>, p, x, w, res, y, s, grid); \
         if (packed) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, true, NG>, p, x, w, res, y, s, grid);  \
         return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG>, p, x, w, res, y, s, grid);    \
     } while (0)
-    if constexpr (NG != 4) {
+    constexpr bool ONLY5 = PXB == 1 && NG == 1;          // 128-pixel tiles with 16 channels per pass: 5x5 windows only
+    if constexpr (NG != 4 && !ONLY5) {
         if (T == 9 && xu == 1) MERIT_CHWS(9, 1);
         if (T == 9 && xu == 2) MERIT_CHWS(9, 2);
         if (T == 9 && xu == 0) MERIT_CHWS(9, 0);
     }
-    if (T == 1 && xu == 1) MERIT_CHWS(1, 1);
-    if (T == 1 && xu == 2) MERIT_CHWS(1, 2);
-    if (T == 1 && xu == 0) MERIT_CHWS(1, 0);
-    // 5x5 windows: the 256-pixel x 64-channel tiling only (a pass's 25 x 2 x 64 weight fragments are 51 KB)
-    if constexpr (PXB == 2 && CHB == 2 && WM == 4 && WN == 1 && NG == 1) {
+    if constexpr (!ONLY5) {
+        if (T == 1 && xu == 1) MERIT_CHWS(1, 1);
+        if (T == 1 && xu == 2) MERIT_CHWS(1, 2);
+        if (T == 1 && xu == 0) MERIT_CHWS(1, 0);
+    }
+    // 5x5 windows: the 64- and 32-channel tilings, 16 channels per pass (25 x 2 x 64 weight fragments are 51 KB)
+    if constexpr (WM == 4 && WN == 1 && NG == 1) {
         if (T == 25 && xu == 1) MERIT_CHWS(25, 1);
         if (T == 25 && xu == 2) MERIT_CHWS(25, 2);
         if (T == 25 && xu == 0) MERIT_CHWS(25, 0);
@@ -822,6 +881,10 @@ hipError_t launch_conv2d_chws(const ConvParams &p, const void *x, const void *w,
         if (p.TM == 128 && p.CB == 1) return launch_tile<1, 1, 4, 1, 4, false>(p, x, w, res, y, s, grid, packed);
         if (p.TM == 128) return launch_tile<1, 2, 4, 1, 4, true>(p, x, w, res, y, s, grid, packed);
         return launch_tile<2, 2, 4, 1, 4, true>(p, x, w, res, y, s, grid, packed);
+    }
+    if (p.kh == 5 && p.TM == 128) {
+        if (p.CB == 1) return launch_tile<1, 1, 4, 1, 1, false>(p, x, w, res, y, s, grid, packed);
+        return launch_tile<1, 2, 4, 1, 1, false>(p, x, w, res, y, s, grid, packed);
     }
     if (p.CB == 4 && p.NW == 12) return launch_tile<2, 2, 4, 2, 1, true>(p, x, w, res, y, s, grid, packed);   // 256 x 128, 8 x (64 x 64)
     if (p.CB == 4) return launch_tile<4, 2, 2, 2>(p, x, w, res, y, s, grid, packed);     // 256 pixels x 128 channels, 4 x (128 x 64)

@@ -719,8 +719,9 @@ merit_status derive_conv(merit_plan *pl)
     auto try_chws = [&](int cb, bool forced, int nw = 8, int tm = 256, bool halo = false) -> bool {
         const bool k5 = kh == 5 && kw == 5;
         if (!((kh == 3 && kw == 3) || (kh == 1 && kw == 1) || k5)) return false;
-        // 5x5 windows: the 256 x 64 tiling on 8 wavefronts, no added tensor, no pooling
-        if (k5 && (cb != 2 || nw != 8 || tm != 256 || pool || p.residual)) return false;
+        // 5x5 windows: the 64- and 32-channel tilings on 8 wavefronts (a tile request: 256 x 64), no added tensor, no pooling
+        if (k5 && (cb > 2 || nw != 8 || pool || p.residual)) return false;
+        if (k5 && tm != 256 && pl->tile_req[2] > 0 && pl->tile_req[3] > 0) return false;
         // its tiles are 256 pixels of one image: small images (13x13, 7x7) would leave a third
         // and more of every tile empty and stay with the 128-pixel tiles of the plain kernels
         if (!forced && !pool && 4 * ohw < 3 * cdiv(ohw, tm) * tm) return false;
@@ -731,7 +732,7 @@ merit_status derive_conv(merit_plan *pl)
         if (cb != 1 && cb != 2 && cb != 4) return false;
         // 32-channel tiles: 128 pixels on 8 wavefronts, 3x3 and 1x1 windows, no added tensor, no pooling (for launches
         // that would otherwise leave half the chip idle)
-        if (cb == 1 && (nw != 8 || tm != 128 || pool || p.residual || k5)) return false;
+        if (cb == 1 && (nw != 8 || tm != 128 || pool || p.residual)) return false;
         // fused pooling: 3x3 windows, the 64-channel tilings and the 128-channel one on 12 wavefronts; a tile is whole rows
         if (pool && (kh != 3 || !((cb == 2 && nw == 8) || (cb == 4 && nw == 12)) || (halo ? 3 : 2) * OW > tm)) return false;
         ConvParams q = p;
@@ -802,7 +803,7 @@ merit_status derive_conv(merit_plan *pl)
         q.pitch = (int)pitch;
         // 16 input channels per pass; 32 with the small tile, whose passes would otherwise be
         // shorter than the memory round trip that brings the next one
-        int64_t ng = tm == 128 ? 2 : 1;
+        int64_t ng = tm == 128 && !k5 ? 2 : 1;
         if (kh == 1 && kw == 1 && Cin >= 128 && !pool) {
             // 1x1 windows: a pass is one tap; 64 channels per pass where its rows and staging units fit
             const int64_t g = 4, xb = 2 * g * (int64_t)q.RHa * pitch * 16, wb = g * cb * 64 * 16;
@@ -836,7 +837,7 @@ merit_status derive_conv(merit_plan *pl)
             q.div_r2 = make_fastdiv((uint32_t)(2 * ng * q.RHa));
         } else {
             const int64_t nu = 2 * ng * (int64_t)q.RHa * W;
-            if (W % 8 == 0 || nu > ((nw == 8 && !k5) ? 8 : 4) * 256 || !fastdiv_ok(nu, W)) return false;
+            if (W % 8 == 0 || Cin % 8 != 0 || nu > ((nw == 8 && !k5) ? 8 : 4) * 256 || !fastdiv_ok(nu, W)) return false;
             q.xu = (int)cdiv(nu, 256);
             q.div_w = make_fastdiv((uint32_t)W);
         }

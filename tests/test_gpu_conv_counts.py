@@ -22,7 +22,9 @@ CASES = [
     (2, 65, 12, 10, 40, 5, 1),        # 5x5
     (2, 36, 21, 27, 17, 5, 2),
     (3, 50, 31, 30, 56, 1, 2),        # 1x1 at stride 2
-    (2, 19, 13, 7, 40, 3, 1),         # rows of fewer than 8 pixels: one-pixel units
+    (2, 40, 13, 7, 40, 3, 1),         # rows of fewer than 8 pixels: one-pixel units
+    (2, 52, 24, 28, 64, 5, 1),        # 5x5 on 128-pixel tiles, 64 and 32 channels
+    (2, 128, 14, 15, 96, 5, 2),
 ]
 
 
