@@ -278,10 +278,10 @@ merit_status derive_sad(merit_plan *pl)
         }
     }
 
-    // two blocks per wavefront, eight per workgroup: 8x8 blocks with R = 8 or 16, 16x16 blocks
-    // with R = 16 (a tile request of four blocks per workgroup keeps the one-block-per-wavefront
+    // two blocks per wavefront, eight per workgroup: 8x8 and 16x16 blocks
+    // with R = 8 or 16 (a tile request of four blocks per workgroup keeps the one-block-per-wavefront
     // kernel there)
-    if (rowscan_ok && ((B == 8 && (R == 8 || R == 16)) || (B == 16 && R == 16)) && pl->tile_req[1] != 1 &&
+    if (rowscan_ok && ((B == 8 || B == 16) && (R == 8 || R == 16)) && pl->tile_req[1] != 1 &&
         pl->tile_req[1] != 4) {
         const int64_t c4 = cdiv(8 * B + 2 * R, 4);
         if (fastdiv_ok((B + 2 * R) * c4, c4)) {

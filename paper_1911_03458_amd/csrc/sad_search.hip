@@ -368,7 +368,8 @@ __global__ __launch_bounds__(256) void merit_sad_rowscan16(SadParams p, const ui
 // covers eight horizontally adjacent blocks.  The walk over the window rows is the one
 // described above with B block rows and B rotating accumulators; the current block lives
 // in vector registers (it differs between the halves).  Columns beyond the 32nd are run
-// one candidate per lane.  B = 8 or 16.
+// one candidate per lane.  B = 8 or 16.  (16x16 blocks with R = 8: 17 of 32 lanes have a column, and it is still
+// 14.7 us against 40.2 of the kernel that takes any shape, on 1080x1920; 7.7 against 13.1 on 326x552.)
 // ---------------------------------------------------------------------------
 template <int B4>
 __device__ __forceinline__ void load_aligned_row(const uint32_t *rowp, uint32_t sh, uint32_t (&r)[B4])
@@ -589,6 +590,8 @@ hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref
             hipLaunchKernelGGL((merit_sad_rowscan_pair<8, 8>), dim3(grid), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
         else if (p.B == 16 && p.R == 16)
             hipLaunchKernelGGL((merit_sad_rowscan_pair<16, 16>), dim3(grid), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
+        else if (p.B == 16 && p.R == 8)
+            hipLaunchKernelGGL((merit_sad_rowscan_pair<16, 8>), dim3(grid), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
         else
             return hipErrorInvalidValue;
         return hipGetLastError();
@@ -602,7 +605,7 @@ const char *sad_kernel_name(const SadParams &p)
 {
     if (p.variant == SAD_ROWSCAN_B16) return p.R == 32 ? "merit_sad_rowscan16<32>" : "merit_sad_rowscan16<16>";
     if (p.variant == SAD_ROWSCAN_PAIR)
-        return p.B == 16 ? "merit_sad_rowscan_pair<16,16>" : (p.R == 16 ? "merit_sad_rowscan_pair<8,16>" : "merit_sad_rowscan_pair<8,8>");
+        return p.B == 16 ? (p.R == 16 ? "merit_sad_rowscan_pair<16,16>" : "merit_sad_rowscan_pair<16,8>") : (p.R == 16 ? "merit_sad_rowscan_pair<8,16>" : "merit_sad_rowscan_pair<8,8>");
     return "merit_sad_generic";
 }
 
