@@ -262,8 +262,10 @@ merit_status derive_sad(merit_plan *pl)
     int64_t grid = (int64_t)p.nby * p.nbx;
     int64_t lds = ((int64_t)p.win * (p.pitch / 4) + 1 + B * (B / 4) + 4) * 4;
     int64_t tile_bx = 1;
-    // (the row-scan kernels fetch the current block in aligned dwords: W % 4 == 0; any H)
-    const bool rowscan_ok = W % 4 == 0;
+    // The row-scan kernels, any H.  Rows that are not whole dwords: from 64 blocks on (500x702, R = 32: 90.7 us on the
+    // kernel for any shape, 25.0 on the row scan); on the smallest frames that kernel's workgroup per block fills more of
+    // the chip, and both are done in the time of a launch.
+    const bool rowscan_ok = W % 4 == 0 || (W >= 4 && (int64_t)p.nby * p.nbx >= 64);
     if (rowscan_ok && B == 16 && (R == 16 || R == 32) && pl->tile_req[1] != 1) {
         const int64_t c4 = cdiv(4 * 16 + 2 * R, 4);
         if (fastdiv_ok((16 + 2 * R) * c4, c4)) {
