@@ -234,7 +234,7 @@ merit_status merit_plan_conv2d_depthwise(int N, int C, int H, int W, int kh, int
                                          int ph, int pw, merit_plan **out);
 /* Correlation layer (Section III-C, Eq. 8): y[n,p1,p2,p3,p4] = sum_c x1[n,c,p1,p2] *
  * x2[n,c,p1+(p3-R)*sd,p2+(p4-R)*sd], p3,p4 in [0, 2R]; 0 outside the image; no
- * normalisation by the channel count.  W must be a multiple of 8, R <= 15, sd <= 8. */
+ * normalisation by the channel count.  Every range; W >= 8, R <= 15 and sd <= 8 on the MFMA kernel. */
 merit_status merit_plan_correlation(int N, int C, int H, int W, int R, int sd, merit_plan **out);
 
 /* Copy of the descriptor the plan was created from. */
