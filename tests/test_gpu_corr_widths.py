@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # N  C   H   W   R  sd
-    (1, 16, 5, 9, 2, 1),         # one whole unit and one pixel
+    (1, 16, 40, 9, 2, 1),        # one whole unit and one pixel
     (2, 20, 4, 15, 3, 2),        # one pixel short of two units, channels not a multiple of 8
     (1, 64, 6, 65, 5, 2),        # a second chunk of one pixel
     (1, 130, 3, 71, 3, 3),       # two channel passes, a second chunk of seven pixels
