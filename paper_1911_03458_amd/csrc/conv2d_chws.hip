@@ -119,7 +119,9 @@ __device__ __forceinline__ void shift_down(uint32_t (&v)[4], int bits)
 }
 
 constexpr int XS_MAX = 8;      // input units of 8 channels x 1 pixel a moving thread holds per pass (4 beside 8 multiplying wavefronts -- 168 registers -- and for 5x5 windows)
-constexpr uint32_t OOB = 0x80000000u;   // a buffer offset past the end of every tensor: loads return zeros
+// A buffer offset past the end of every tensor: loads return zeros.  (The planner and the launcher keep a launch's input
+// and the weights below it, whatever the batch; the added tensor may be larger: what is loaded there is never stored.)
+constexpr uint32_t OOB = 0x80000000u;
 
 }  // namespace
 
@@ -865,10 +867,9 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
 
 }  // namespace
 
-hipError_t launch_conv2d_chws(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
-                              bool packed)
+static hipError_t launch_images(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
+                                bool packed)
 {
-    if ((p.residual != 0) != (res != nullptr)) return hipErrorInvalidValue;
     const int64_t nitems = p.pool ? (int64_t)p.N * p.NB * p.co_groups : (int64_t)p.N * p.tiles_per_image * p.co_groups;
     if (nitems == 0) return hipSuccess;
     const int64_t slots = device_cu_count();            // one 512-thread workgroup per compute unit
@@ -891,6 +892,27 @@ hipError_t launch_conv2d_chws(const ConvParams &p, const void *x, const void *w,
     if (p.TM == 128 && p.CB == 1) return launch_tile<1, 1, 4, 1, 2, false>(p, x, w, res, y, s, grid, packed);   // 128 pixels x 32 channels, 4 x (32 x 32)
     if (p.TM == 128) return launch_tile<1, 2, 4, 1, 2, true>(p, x, w, res, y, s, grid, packed);   // 128 pixels x 64 channels, 4 x (32 x 64), 32 channels per pass
     return launch_tile<2, 2, 4, 1, 1, true>(p, x, w, res, y, s, grid, packed);           // 256 pixels x 64 channels, 4 x (64 x 64)
+}
+
+hipError_t launch_conv2d_chws(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
+                              bool packed)
+{
+    if ((p.residual != 0) != (res != nullptr)) return hipErrorInvalidValue;
+    const int64_t each = chws_images_per_launch(p);
+    if (p.N <= each) return launch_images(p, x, w, res, y, s, packed);
+    if (each == 0) return hipErrorInvalidValue;           // (the planner makes no such plan)
+    const size_t image = (size_t)p.Cin * p.H * p.W;
+    const size_t out = (size_t)p.Cout * (p.pool ? (size_t)p.PH * p.PW : (size_t)p.OH * p.OW);
+    for (int64_t n = 0; n < p.N; n += each) {
+        ConvParams q = p;
+        q.N = (int)(p.N - n < each ? p.N - n : each);
+        const uint16_t *r = static_cast<const uint16_t *>(res);
+        if (hipError_t e = launch_images(q, static_cast<const uint16_t *>(x) + n * image, w, r ? r + n * out : nullptr,
+                                         static_cast<uint16_t *>(y) + n * out, s, packed);
+            e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_conv2d_pack_weights(const ConvParams &p, const void *w, void *packed, hipStream_t s)

@@ -264,6 +264,22 @@ hipError_t launch_conv2d(const ConvParams &p, const void *x, const void *w, cons
 const char *pool_kernel_name(const PoolParams &p);
 const char *sad_kernel_name(const SadParams &p);
 const char *conv_kernel_name(const ConvParams &p);
+// Images of one launch of the wave-specialised multi-pass kernel: its byte offsets into the input, the padding channels
+// of the last pass counted, stay below 2 GiB, where its offset for "outside the tensor" begins.  A larger batch is
+// several launches, each on 16-byte boundaries of the input and the output (0: no such split).
+inline int64_t chws_images_per_launch(const ConvParams &p)
+{
+    const int64_t plane = (int64_t)p.H * p.W, image = p.Cin * plane;
+    const int64_t out = (int64_t)p.Cout * (p.pool ? (int64_t)p.PH * p.PW : (int64_t)p.OH * p.OW);
+    const int64_t pad = ((int64_t)p.nchunks * p.nchi * 8 - p.Cin) * plane;
+    const int64_t most = ((1ll << 30) - 1 - pad) / image;                // halves
+    if (p.N <= most) return p.N;
+    if (most <= 0) return 0;
+    int64_t step = 1;
+    while ((step * image) % 8 != 0 || (step * out) % 8 != 0) step *= 2;  // (8 images at most)
+    return most / step * step;
+}
+
 // wave-specialised multi-pass kernel: w is the [Cout][Cin][kh][kw] tensor, or (packed) what
 // launch_conv2d_pack_weights wrote
 hipError_t launch_conv2d_chws(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,

@@ -848,6 +848,10 @@ merit_status derive_conv(merit_plan *pl)
             !fastdiv_ok(ohw, OW) || !fastdiv_ok(N * q.tiles_per_image, q.tiles_per_image))
             return false;
         if (N * Cin * H * W >= (1ll << 31) || N * Cout * ohw >= (1ll << 31)) return false;
+        // byte offsets into the input and into the weights, as they lie or packed
+        if ((N > 0 && chws_images_per_launch(q) == 0) || Cout * Cin * kh * kw * 2 >= (1ll << 31) - 64 ||
+            q.co_groups * q.nchunks * w_bytes >= (1ll << 31))
+            return false;
         q.div_cog = make_fastdiv((uint32_t)q.co_groups);
         q.div_rha = make_fastdiv((uint32_t)q.RHa);
         q.div_ow = make_fastdiv((uint32_t)OW);
