@@ -126,11 +126,12 @@ constexpr uint32_t OOB = 0x80000000u;
 }  // namespace
 
 // PXB x CHB: 32x32 blocks per multiplying wavefront; WM x WN = 4 multiplying wavefronts.
-// T: taps of the window (25 = 5x5, 9 = 3x3, 1 = 1x1).  XU = 1, 2: the input rows are staged in units of 8
-// channels x 8 pixels, XU of them per moving thread and pass: eight 16-byte loads, which a buffer load takes
-// from any 2-byte boundary; the unit that a row's end would cut starts earlier, so that it ends with the row
-// (the columns it shares with its neighbour are written twice, with the same values).  XU = 0 (rows of fewer than 8 pixels, or more units than two per thread): units of 8 channels x 1
-// pixel, up to XS_MAX per thread.
+// T: taps of the window (25 = 5x5, 9 = 3x3, 1 = 1x1).  XU: how the input rows are staged.  1, 2: in units of 8 channels
+// x 8 pixels, one or two of them per moving thread and pass: eight 16-byte loads, which a buffer load takes from any
+// 2-byte boundary; the unit that a row's end would cut starts earlier, so that it ends with the row (the columns it
+// shares with its neighbour are written twice, with the same values).  Where that is more than two units (tall windows'
+// worth of narrow rows: 3x3 / 3 on 138x10) or the rows have fewer than 8 pixels: 4: units x 4 pixels (W % 4 == 0),
+// 3: x 2 pixels (W even), 0: x 1 pixel, up to XS_MAX per thread.
 // NG: pairs of 8-channel groups per pass (1: 16 channels, 2: 32 -- small tiles, whose passes would
 // otherwise be shorter than a memory round trip; 4: 64 -- 1x1 windows on many channels).
 // POOL: the results are max-pooled (3x3 / stride 2 / padding 1) out of the staging area and only the
@@ -160,6 +161,7 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
     constexpr int SETS = WREG && XU == 1 ? 2 : 1;
     constexpr int OP = TM / 2 + 2;                       // output staging: dwords per channel
     constexpr bool XV = XU == 1 || XU == 2;              // 8-pixel input units, XU per moving thread
+    constexpr int UP = XV ? 8 : (XU == 4 ? 4 : (XU == 3 ? 2 : 1));       // pixels of a unit
 
     {
         // The kernel-argument block (ConvParams and three pointers: six 64-byte lines) is read with
@@ -313,12 +315,12 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
         const int mwave = wave - NMW;
 
         constexpr int XSM = (NMW == 4 && T != 25) ? XS_MAX : 4;       // (5x5: 100 registers of weights on their way)
-        constexpr int NXU = XV ? XU : XSM;
+        constexpr int NXU = XV ? XU : (XU == 4 ? (NMW == 4 ? 4 : 2) : XSM);      // units per moving thread, at most
         uint32_t x_voff[NXU];               // byte offset of the unit inside (image, first channel of the pass)
         int x_lds[NXU];                     // byte address of its first pixel inside a pass buffer's input region
         int x_hh[NXU];                      // its channel group within the pass
-        uint32_t xv[SETS][XV ? XU : 1][8][4];     // the unit on its way: 8 channels x 8 pixels
-        uint32_t xs[XV ? 1 : XSM][8];       // ... 8 channels x 1 pixel (a register each: see commit)
+        uint32_t xv[SETS][UP > 1 ? NXU : 1][8][UP > 1 ? UP / 2 : 1];     // the unit on its way: 8 channels x UP pixels
+        uint32_t xs[UP > 1 ? 1 : XSM][8];       // ... 8 channels x 1 pixel (a register each: see commit)
         uint32_t w_voff[WU];
         int w_lds[WU], w_hh[WU];
         uint32_t wr[SETS][PACKED ? 1 : WU][PACKED ? 1 : 4 * T];
@@ -326,23 +328,22 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
 
         const int rstep = p.row_skip ? p.sh : 1;        // image rows between staged rows
         auto setup = [&](const Geom &g) __attribute__((always_inline)) {
-            if constexpr (XV) {
-                const int W8 = (p.W + 7) >> 3;
-                const int nu = NGRP * p.RHa * W8;
+            if constexpr (UP > 1) {
+                const int nu = NGRP * p.RHa * ((p.W + UP - 1) / UP);
 #pragma unroll
-                for (int k = 0; k < XU; ++k) {
+                for (int k = 0; k < NXU; ++k) {
                     // consecutive threads take consecutive staged rows (q = group * RHa + row) of one
-                    // 8-pixel column chunk: their LDS writes are q * pitch items apart, and the pitch
+                    // column chunk: their LDS writes are q * pitch items apart, and the pitch
                     // is odd, so 16 of them fall into 16 different bank groups
                     const int u = mt + 256 * k;
                     const int uc = min(u, nu - 1);
-                    const int x8 = (int)fdiv((uint32_t)uc, p.div_r2);
-                    const int q = uc - x8 * NGRP * p.RHa;
+                    const int xc = (int)fdiv((uint32_t)uc, p.div_r2);
+                    const int q = uc - xc * NGRP * p.RHa;
                     const int hh = (int)fdiv((uint32_t)q, p.div_rha);
                     const int r = q - hh * p.RHa;
                     const int gy = g.yA + r * rstep;
                     const bool ok = u < nu && r < g.RH && gy >= 0 && gy < p.H;
-                    const int col = min(8 * x8, p.W - 8);
+                    const int col = min(UP * xc, p.W - UP);
                     x_hh[k] = u < nu ? hh : NGRP;                            // NGRP: no such unit, never written
                     x_voff[k] = ok ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + col) * 2) : OOB;
                     x_lds[k] = (q * p.pitch + p.padl + col) * 16;
@@ -407,6 +408,11 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
                     if constexpr (XV) {
                         const uint32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, voff, xbase + c * chbytes, 0);
                         xv[set][k][c][0] = v.x; xv[set][k][c][1] = v.y; xv[set][k][c][2] = v.z; xv[set][k][c][3] = v.w;
+                    } else if constexpr (UP == 4) {
+                        const uint32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rx, voff, xbase + c * chbytes, 0);
+                        xv[set][k][c][0] = v.x; xv[set][k][c][1] = v.y;
+                    } else if constexpr (UP == 2) {
+                        xv[set][k][c][0] = __builtin_amdgcn_raw_buffer_load_b32(rx, voff, xbase + c * chbytes, 0);
                     } else {
                         xs[k][c] = __builtin_amdgcn_raw_buffer_load_b16(rx, voff, xbase + c * chbytes, 0);
                     }
@@ -439,9 +445,9 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
             for (int k = 0; k < NXU; ++k) {
                 if (!XV && k >= p.xu) break;
                 if (x_hh[k] < NGRP) {
-                    if constexpr (XV) {
+                    if constexpr (UP > 1) {
 #pragma unroll
-                        for (int px = 0; px < 8; ++px) {
+                        for (int px = 0; px < UP; ++px) {
                             const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
                             uint32x4 d;
                             d.x = __builtin_amdgcn_perm(xv[set][k][1][px >> 1], xv[set][k][0][px >> 1], sel);
@@ -806,9 +812,9 @@ template <int PXB, int CHB, int WM, int WN, int NG = 1, bool POOLS = false>
 hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s,
                        uint32_t grid, bool packed)
 {
-    const int xu = p.xpx ? 0 : p.xu;          // 8-pixel units per moving thread (1, 2); 0: one-pixel units
+    const int xu = p.xpx == 8 ? p.xu : (p.xpx == 4 ? 4 : (p.xpx == 2 ? 3 : 0));      // the template's XU
     const int T = p.kh * p.kw;
-    if ((p.Cin & 7) != 0 && (xu == 0 || packed || p.pool)) return hipErrorInvalidValue;
+    if ((p.Cin & 7) != 0 && (p.xpx != 8 || packed || p.pool)) return hipErrorInvalidValue;
     if (p.residual) {
         // residual layer: 3x3 and 1x1 windows on the caller's weights, the two 64-channel tilings (on the
         // others the 32 registers of the added tensor would spill)
@@ -817,11 +823,15 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
             if (T == 1) {
                 if (xu == 1) return launch_res<PXB, CHB, WM, WN, 1, 1, NG>(p, x, w, res, y, s, grid);
                 if (xu == 2) return launch_res<PXB, CHB, WM, WN, 1, 2, NG>(p, x, w, res, y, s, grid);
+                if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 4, false, NG, false, true>, p, x, w, res, y, s, grid);
+                if (xu == 3) return hipErrorInvalidValue;
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 1, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
             if constexpr (NG != 4) {        // (64 channels per pass: 1x1 windows only)
                 if (xu == 1) return launch_res<PXB, CHB, WM, WN, 9, 1, NG>(p, x, w, res, y, s, grid);
                 if (xu == 2) return launch_res<PXB, CHB, WM, WN, 9, 2, NG>(p, x, w, res, y, s, grid);
+                if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 4, false, NG, false, true>, p, x, w, res, y, s, grid);
+                if (xu == 3) return hipErrorInvalidValue;
                 return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 0, false, NG, false, true>, p, x, w, res, y, s, grid);
             }
         }
@@ -833,14 +843,17 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
             if (T != 9 || packed) return hipErrorInvalidValue;
             if (xu == 1) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 1, false, NG, true>, p, x, w, res, y, s, grid);
             if (xu == 2) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 2, false, NG, true>, p, x, w, res, y, s, grid);
+            if (xu == 4) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 4, false, NG, true>, p, x, w, res, y, s, grid);
+            if (xu == 3) return hipErrorInvalidValue;
             return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 0, false, NG, true>, p, x, w, res, y, s, grid);
         }
         return hipErrorInvalidValue;
     }
 #define MERIT_CHWS(Tv, XUv)                                                                             \
     do {                                                                                                \
-        if (XUv != 0 && !packed && (p.Cin & 7) != 0)                                                     \
-            return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG, false, false, XUv != 0>, p, x, w, res, y, s, grid); \
+        constexpr bool R8 = XUv == 1 || XUv == 2;                                                       \
+        if (R8 && !packed && (p.Cin & 7) != 0)                                                          \
+            return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG, false, false, R8>, p, x, w, res, y, s, grid); \
         if (packed) return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, true, NG>, p, x, w, res, y, s, grid);  \
         return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG>, p, x, w, res, y, s, grid);    \
     } while (0)
@@ -849,11 +862,15 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
         if (T == 9 && xu == 1) MERIT_CHWS(9, 1);
         if (T == 9 && xu == 2) MERIT_CHWS(9, 2);
         if (T == 9 && xu == 0) MERIT_CHWS(9, 0);
+        if (T == 9 && xu == 4) MERIT_CHWS(9, 4);
+        if (T == 9 && xu == 3) MERIT_CHWS(9, 3);
     }
     if constexpr (!ONLY5) {
         if (T == 1 && xu == 1) MERIT_CHWS(1, 1);
         if (T == 1 && xu == 2) MERIT_CHWS(1, 2);
         if (T == 1 && xu == 0) MERIT_CHWS(1, 0);
+        if (T == 1 && xu == 4) MERIT_CHWS(1, 4);
+        if (T == 1 && xu == 3) MERIT_CHWS(1, 3);
     }
     // 5x5 windows: the 64- and 32-channel tilings, 16 channels per pass (25 x 2 x 64 weight fragments are 51 KB)
     if constexpr (WM == 4 && WN == 1 && NG == 1) {

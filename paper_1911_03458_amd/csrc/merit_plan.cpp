@@ -810,8 +810,8 @@ merit_status derive_conv(merit_plan *pl)
             // 1x1 windows: a pass is one tap; 64 channels per pass where its rows and staging units fit
             const int64_t g = 4, xb = 2 * g * (int64_t)q.RHa * pitch * 16, wb = g * cb * 64 * 16;
             const int64_t rows = 2 * g * (int64_t)q.RHa;
-            const int64_t nu = W >= 8 ? rows * cdiv(W, 8) : rows * W;
-            const int64_t cap = (W >= 8 ? 2 : (nw == 8 ? 8 : 4)) * 256;
+            const int64_t nu = W >= 8 ? rows * cdiv(W, 8) : (W == 4 ? rows : rows * W);
+            const int64_t cap = (W >= 8 ? 2 : (W == 4 ? (nw == 8 ? 4 : 2) : (nw == 8 ? 8 : 4))) * 256;
             if (2 * (wb + xb) <= LDS_LIMIT && nu <= cap) ng = g;
         }
         q.nchi = (int)(2 * ng);
@@ -831,18 +831,26 @@ merit_status derive_conv(merit_plan *pl)
             q.lds_total = (int)(q.lds_o_offset + carry);
             if (q.lds_total > LDS_LIMIT) return false;
         }
-        // staging units per moving thread and pass: 8 channels x 8 pixels (two at most), or x 1 pixel (eight; four on 12 wavefronts and for 5x5 windows)
-        const int64_t nu8 = 2 * ng * (int64_t)q.RHa * cdiv(W, 8);
-        q.xpx = !(W >= 8 && nu8 <= 2 * 256 && fastdiv_ok(nu8, 2 * ng * (int64_t)q.RHa)) ? 1 : 0;
-        if (!q.xpx) {
-            q.xu = (int)cdiv(nu8, 256);
-            q.div_r2 = make_fastdiv((uint32_t)(2 * ng * q.RHa));
-        } else {
-            const int64_t nu = 2 * ng * (int64_t)q.RHa * W;
-            if (W % 8 == 0 || Cin % 8 != 0 || nu > ((nw == 8 && !k5) ? 8 : 4) * 256 || !fastdiv_ok(nu, W)) return false;
+        // staging units per moving thread and pass: 8 channels x 8 pixels, two at most.  Where more would be needed (the
+        // many rows of a tile on narrow images with a row stride), or rows are shorter: x 4 pixels (W % 4 == 0; four,
+        // two on 12 wavefronts) and x 2 (W even; no added tensor, no pooling) or 1, eight of them (four on 12 wavefronts
+        // and for 5x5 windows).  3x3 / 3, 400 -> 221 on 3 of 138x10: 65 us, on the channels-in-passes kernel 262;
+        // 3x3 / 4, 888 -> 60 on 9 of 174x4: 45 us, with one-pixel units 82.
+        const int64_t rows = 2 * ng * (int64_t)q.RHa;
+        auto units_of = [&](int64_t px, int64_t most) -> bool {
+            const int64_t nu = rows * cdiv(W, px);
+            if (W < px || nu > most * 256 || !fastdiv_ok(nu, px == 1 ? W : rows)) return false;
+            q.xpx = (int)px;
             q.xu = (int)cdiv(nu, 256);
-            q.div_w = make_fastdiv((uint32_t)W);
-        }
+            if (px == 1) q.div_w = make_fastdiv((uint32_t)W);
+            else q.div_r2 = make_fastdiv((uint32_t)rows);
+            return true;
+        };
+        const bool short_units = Cin % 8 == 0 && W % 8 != 0;
+        if (!units_of(8, 2) && !(short_units && !k5 && W % 4 == 0 && units_of(4, nw == 8 ? 4 : 2)) &&
+            !(short_units && !k5 && W % 2 == 0 && !pool && !p.residual && units_of(2, nw == 8 ? 8 : 4)) &&
+            !(short_units && units_of(1, nw == 8 && !k5 ? 8 : 4)))
+            return false;
         const int64_t nitems = pool ? N * q.NB * q.co_groups : N * q.tiles_per_image * q.co_groups;
         if (nitems >= (1ll << 30) || !fastdiv_ok(nitems + 256, q.co_groups) || !fastdiv_ok(2 * ng * (int64_t)q.RHa, q.RHa) ||
             !fastdiv_ok(ohw, OW) || !fastdiv_ok(N * q.tiles_per_image, q.tiles_per_image))

@@ -24,3 +24,24 @@ def test_byte_offsets_of_the_multi_pass_kernel(shape):
 def test_a_batch_may_be_larger_than_one_image():
     for shape in ((64, 100, 421, 421, 40, 3, 3, 1, 1, 1, 1), (64, 128, 400, 400, 72, 3, 3, 1, 1, 1, 1)):
         assert _conv(*shape).launch_info()["kernel"] == "merit_conv2d_chws"
+
+
+@pytest.mark.parametrize("shape,tile", [
+    ((3, 40, 138, 10, 72, 3, 3, 3, 3, 2, 1), None),
+    ((2, 72, 129, 12, 40, 3, 3, 2, 4, 0, 0), None),
+    ((2, 48, 91, 18, 74, 3, 3, 4, 4, 2, 1), None),
+    ((1, 128, 199, 6, 70, 3, 3, 2, 2, 0, 0), None),
+    ((2, 64, 150, 4, 256, 3, 3, 2, 2, 1, 1), (0, 0, 12, 64)),
+    ((2, 64, 160, 6, 256, 3, 3, 2, 2, 1, 1), (0, 0, 12, 64)),
+])
+def test_narrow_layers_keep_the_multi_pass_kernel(shape, tile):
+    """Many staged rows a tile: the kernel, its packed weights and its tile requests, whatever the width of its units."""
+    plan = _conv(*shape)
+    if tile:
+        plan.set_tile(tile)
+    assert plan.launch_info()["kernel"] == "merit_conv2d_chws"
+    assert mb.merit_plan_packed_weights_bytes(plan) > 0
+
+
+def test_narrow_layers_keep_the_fused_pooling():
+    assert mb.merit_plan_conv2d_pool(2, 24, 126, 12, 72, 3, 3, 6, 4, 2, 2).launch_info()["kernel"] == "merit_conv2d_chws_pool"
