@@ -45,3 +45,9 @@ def test_narrow_layers_keep_the_multi_pass_kernel(shape, tile):
 
 def test_narrow_layers_keep_the_fused_pooling():
     assert mb.merit_plan_conv2d_pool(2, 24, 126, 12, 72, 3, 3, 6, 4, 2, 2).launch_info()["kernel"] == "merit_conv2d_chws_pool"
+
+
+def test_tiles_of_5x5_layers():
+    """Two rounds of 256-pixel tiles (125 us) rather than three of 128-pixel tiles (156)."""
+    li = _conv(9, 384, 63, 6, 734, 5, 5, 1, 1, 3, 3).launch_info()
+    assert li["kernel"] == "merit_conv2d_chws" and li["tile"][1] == 64 and li["tile"][2] == 33      # rows of 8 pixels
