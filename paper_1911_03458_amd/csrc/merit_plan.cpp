@@ -847,7 +847,17 @@ merit_status derive_conv(merit_plan *pl)
             return true;
         };
         const bool short_units = Cin % 8 == 0 && W % 8 != 0;
-        if (!units_of(8, 2) && !(short_units && !k5 && W % 4 == 0 && units_of(4, nw == 8 ? 4 : 2)) &&
+        // Rows of an odd width start on 2-byte boundaries, where a 16-byte load takes twice the time, so that on many
+        // channels, where passes count, the eight coalesced 2-byte loads of a one-pixel unit can be the faster ones.
+        // 3x3 windows on rows of 63 pixels and more, from 128 channels on (448 -> 48 on 11 of 11x65: 24 us against 33;
+        // 64 channels: equal at best, 32 -> 336 on 12 of 13x75: 16.2 against 11.4) or with a row stride (96 -> 841 on 10
+        // of 30x111 / 2: 43 against 50); from 256 channels on also rows of a
+        // power of two and one (512 -> 64 on 6 of 9x9: 10 % faster; 64 channels: 8 % slower) and where 8-pixel units
+        // would be two per thread (512 -> 64 on 6 of 21x21 / 2: 14 %).  Elsewhere the 8-pixel units gain 5-25 %.
+        const bool one_px = short_units && kh == 3 && W % 2 == 1 &&
+                            ((W >= 63 && (Cin >= 128 || sh > 1)) ||
+                             (Cin >= 256 && (((W - 1) & (W - 2)) == 0 || rows * cdiv(W, 8) > 256)));
+        if (!(one_px && units_of(1, nw == 8 ? 8 : 4)) && !units_of(8, 2) && !(short_units && !k5 && W % 4 == 0 && units_of(4, nw == 8 ? 4 : 2)) &&
             !(short_units && !k5 && W % 2 == 0 && !pool && !p.residual && units_of(2, nw == 8 ? 8 : 4)) &&
             !(short_units && units_of(1, nw == 8 && !k5 ? 8 : 4)))
             return false;
@@ -991,9 +1001,12 @@ merit_status derive_conv(merit_plan *pl)
                 const bool fits = try_chws(cbs, true, shape == 0 ? 12 : 8, (int)tm);
                 const int64_t items = N * (int64_t)p.tiles_per_image * p.co_groups;     // (of the trial, if it fits)
                 // cost of a tile, from timings.  5x5 windows (16 channels per pass on every tiling: the weights of a pass
-                // are moved as often as on the large tile): 0.87 and 0.67 over 30 and 380 layers
+                // are moved as often as on the large tile): 0.87 and 0.67 over 30 and 380 layers; 8-pixel staging units
+                // on wide rows of an odd width (see try_chws): with a row stride they are most of a tile's time (80 -> 352 on
+                // 12 of 6x123 / 2: 13.9 us in one round of large tiles with one-pixel units, 21.8 in two of small ones)
                 static const double tile_cost[2][4] = {{1.6, 1.0, 0.6, 0.42}, {0.0, 1.0, 0.87, 0.67}};
-                const double cost = (double)cdiv(items, 256) * tile_cost[kh == 5][shape];
+                const double units = fits && W % 2 == 1 && W >= 63 && (Cin >= 128 || sh > 1) && p.xpx == 8 ? (sh > 1 ? 2.0 : 1.3) : 1.0;
+                const double cost = (double)cdiv(items, 256) * tile_cost[kh == 5][shape] * units;
                 p = saved;
                 if (fits && (best < 0 || cost < best_cost)) { best = shape; best_cost = cost; }
             }

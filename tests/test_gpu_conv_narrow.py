@@ -1,5 +1,6 @@
-"""Many-channel layers on tall, narrow images, whose tiles have more staged rows than two 8-pixel units per moving thread
-hold: units of 4 and 2 pixels on the wave-specialised kernel, against the oracle.  Bar: 2e-2*|r| + 1e-3."""
+"""Many-channel layers on the wave-specialised kernel whose input rows are not staged in 8-pixel units, against the oracle:
+tall, narrow images (more staged rows than two such units per moving thread hold: units of 4 and 2 pixels) and rows of an
+odd width where one-pixel units are faster.  Bar: 2e-2*|r| + 1e-3."""
 import numpy as np
 import pytest
 import torch
@@ -19,6 +20,10 @@ CASES = [
     ("conv",     (2, 136, 141, 4, 70, 1, 1, 1, 4, 0, 1), None),            # 1x1, 64 channels per pass
     ("conv",     (2, 64, 160, 6, 256, 3, 3, 2, 2, 1, 1), (0, 0, 12, 64)),  # 12 wavefronts
     ("conv",     (2, 64, 150, 4, 256, 3, 3, 2, 2, 1, 1), (0, 0, 12, 64)),
+    ("conv",     (2, 136, 5, 65, 40, 3, 3, 1, 1, 1, 1), None),             # odd widths, one-pixel units
+    ("conv",     (2, 264, 9, 17, 72, 3, 3, 1, 1, 1, 1), None),
+    ("conv",     (2, 256, 23, 21, 64, 3, 3, 2, 2, 1, 1), None),
+    ("conv",     (2, 72, 7, 105, 100, 3, 3, 2, 2, 1, 1), None),
     ("residual", (2, 40, 151, 12, 77, 3, 3, 4, 4, 0, 1), None),
     ("pool",     (2, 24, 126, 12, 72, 3, 3, 6, 4, 2, 2), None),
 ]
