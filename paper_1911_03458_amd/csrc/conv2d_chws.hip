@@ -10,9 +10,9 @@
 //     fragments from LDS for PXB * CHB MFMAs (6 reads per 8 MFMAs instead of 3 per 2), and the
 //     reads of step s+1 are issued before the MFMAs of step s.
 //   * Wavefronts 4-7 only move data.  The input channels go through LDS in passes of 16 (two
-//     groups of 8, one per half of a wavefront); pass q+1 is transposed into the other LDS
-//     buffer while pass q is multiplied, and the global loads of passes q+2 and q+3 are in
-//     flight meanwhile (two register sets).  One barrier per pass.
+//     groups of 8, one per half of a wavefront) to 64; pass q+1 is transposed into the other LDS
+//     buffer while pass q is multiplied, and the global loads of pass q+2 are in flight meanwhile
+//     (of q+3 as well where a second register set pays: see SETS).  One barrier per pass.
 //   * The covering sub-tensor of a tile (Section IV-A, Eq. 9) is TM consecutive output pixels
 //     of one image (whole rows: only a vertical halo) x 16 channels per pass.
 //
@@ -151,17 +151,19 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
     constexpr int WITEMS = NG * T * NCB * 64;            // 16-byte weight fragments per pass
     constexpr int NGRP = 2 * NG;                         // 8-channel groups per pass
     constexpr int WU = (TN * NGRP + 255) / 256;          // weight units (8 channels x T taps of one output channel) per moving thread
-    // Packed weights on the 128-pixel tiles go through registers, requested two passes ahead like the input rows: their
-    // passes are shorter than the memory round trip that a copy straight into LDS, started when its buffer is free, takes
-    // inside one of them (256 -> 256 on 8x14x14: 11.7 us on the direct copy, 10.3; 512 -> 512 20.2, 18.5).
-    constexpr bool WREG = PACKED && TM == 128;
-    constexpr int WP = (WITEMS + 255) / 256;             // fragments per moving thread there
-    // Passes on their way in registers: two with those (and 8-pixel units), else one (on the caller's weights a second
-    // one gained nothing: there a pass waits for its load instructions, not for memory).
-    constexpr int SETS = WREG && XU == 1 ? 2 : 1;
-    constexpr int OP = TM / 2 + 2;                       // output staging: dwords per channel
     constexpr bool XV = XU == 1 || XU == 2;              // 8-pixel input units, XU per moving thread
     constexpr int UP = XV ? 8 : (XU == 4 ? 4 : (XU == 3 ? 2 : 1));       // pixels of a unit
+    // Packed weights on the 128-pixel tiles go through registers like the input rows, and with one 8-pixel unit per thread
+    // both are requested two passes ahead: the passes are shorter than the memory round trip that a copy straight into
+    // LDS, started when its buffer is free, takes inside one of them (256 -> 256 on 8x14x14: 11.7 us on the direct copy,
+    // 9.7; 512 -> 512 20.2, 16.8).  Shorter units keep the direct copy: they leave no registers for a second pass, and
+    // one pass ahead the detour costs 2-8 % (512 channels on 17x17).
+    constexpr bool WREG = PACKED && TM == 128 && XV;
+    constexpr int WP = (WITEMS + 255) / 256;             // fragments per moving thread there
+    // Passes on their way in registers: two with those and one unit per thread, else one (on the caller's weights a
+    // second one gained nothing: there a pass waits for its load instructions, not for memory).
+    constexpr int SETS = WREG && XU == 1 ? 2 : 1;
+    constexpr int OP = TM / 2 + 2;                       // output staging: dwords per channel
 
     {
         // The kernel-argument block (ConvParams and three pointers: six 64-byte lines) is read with
