@@ -305,9 +305,10 @@ merit_status merit_conv2d_packed(const merit_plan *plan, const void *x_f16, cons
  * merit_conv2d_packed in one call, with the packed copy in a fixed device buffer that lives
  * inside the library instead of one the caller brings.  The buffer is
  * MERIT_NOALLOC_SCRATCH_BYTES per GPU, part of the loaded library on every GPU it runs on
- * until the process ends; a plan whose packed weights are larger is refused with
- * MERIT_ERR_SCRATCH_LIMIT (nothing launched), a plan whose kernel takes no packed weights with
- * MERIT_ERR_UNSUPPORTED.  Neither this call nor anything it runs allocates or frees memory.
+ * until the process ends; a plan whose packed weights are larger, on every tiling that the layer
+ * fits, is refused with MERIT_ERR_SCRATCH_LIMIT (nothing launched), a plan whose kernel takes no
+ * packed weights with MERIT_ERR_UNSUPPORTED.  Neither this call nor anything it runs allocates or
+ * frees memory.
  * Every call on a GPU uses that GPU's one buffer and overwrites all of the part it needs:
  * two calls that overlap in time on one GPU (different streams, different threads) race and
  * give undefined results; calls on one stream are ordered and safe.  Same result, bit for

@@ -420,7 +420,11 @@ struct merit_plan {
     // stream-ordered temporary, then the binary16 pooling kernel): `conv2` is the plain convolution
     int two_pass;
     merit::ConvParams conv2;
-    // 1x1 windows at stride 1 (CONV_PX): `px` runs the plan.  `conv` stays what the other kernels would have made of
+    // a layer whose packed weights exceed the library's fixed buffer on the tiling that runs it, but not on another one:
+    // that one, for the calls that use the buffer (the same sums in the same order)
+    int use_na;
+    merit::ConvParams conv_na;
+    // 1x1 windows at stride 1 (conv2d_px.hip): `px` runs the plan.  `conv` stays what the other kernels would have made of
     // it: it names the size of a packed copy, where there is one
     int use_px;
     merit::PxParams px;

@@ -426,6 +426,9 @@ merit_status derive_bilateral(merit_plan *pl)
 }
 
 // -------------------------------------------------------------- convolution ---
+// The size of the packed copy of a wave-specialised multi-pass tiling.
+int64_t packed_bytes(const ConvParams &p) { return (int64_t)p.co_groups * p.nchunks * p.lds_w_bytes; }
+
 // The layers whose weights can be packed once: the wave-specialised multi-pass kernel on a multiple of 8 input channels
 // and more than 32 output channels, at least 32 of the former unless a tile request named the kernel.
 bool packable(const merit_plan *pl)
@@ -488,7 +491,7 @@ void derive_px(merit_plan *pl)
 merit_status derive_conv(merit_plan *pl)
 {
     const merit_plan_desc &d = pl->desc;
-    pl->use_px = 0;
+    pl->use_px = pl->use_na = 0;
     if (d.dtype != MERIT_F16 || d.pad != MERIT_PAD_ZERO) return MERIT_ERR_UNSUPPORTED;
     if (d.n_par != 4 || d.n_acc != 3) return MERIT_ERR_UNSUPPORTED;
     if (d.a.ndim != 4 || d.b.ndim != 4) return MERIT_ERR_UNSUPPORTED;
@@ -717,6 +720,7 @@ merit_status derive_conv(merit_plan *pl)
     // Wave-specialised multi-pass kernel (conv2d_chws.hip): 256-pixel tiles x `cb` 32-channel blocks
     // (4 or 2), 16 input channels per pass through two LDS buffers, 3x3, 1x1 or 5x5 windows on a multiple
     // of 8 input channels.
+    bool short_pass = false;     // 1x1 windows: no 64-channel passes
     bool any_count = false;      // the planner's own choice below: any channel count (a tile request and the fused pooling: as documented)
     auto try_chws = [&](int cb, bool forced, int nw = 8, int tm = 256, bool halo = false) -> bool {
         const bool k5 = kh == 5 && kw == 5;
@@ -806,7 +810,7 @@ merit_status derive_conv(merit_plan *pl)
         // 16 input channels per pass; 32 with the small tile, whose passes would otherwise be
         // shorter than the memory round trip that brings the next one
         int64_t ng = tm == 128 && !k5 ? 2 : 1;
-        if (kh == 1 && kw == 1 && Cin >= 128 && !pool) {
+        if (kh == 1 && kw == 1 && Cin >= 128 && !pool && !short_pass) {
             // 1x1 windows: a pass is one tap; 64 channels per pass where its rows and staging units fit
             const int64_t g = 4, xb = 2 * g * (int64_t)q.RHa * pitch * 16, wb = g * cb * 64 * 16;
             const int64_t rows = 2 * g * (int64_t)q.RHa;
@@ -992,27 +996,46 @@ merit_status derive_conv(merit_plan *pl)
         const bool was = Cin >= 32 && Cin % 8 == 0 && ncb >= 2;
         any_count = (kh > 1 || sh > 1 || sw > 1) && Cin >= 17 && (Cin % 8 == 0 || N >= 2) && (ncb >= 2 || Cin % 8 != 0 || Cin > 64);
         if (window && (was || any_count)) {
-            int best = -1; double best_cost = 0.0;
-            for (int shape = 0; shape < 4; ++shape) {          // 0: 256 x 128 on 12 wavefronts, 1: 256 x 64, 2: 128 x 64, 3: 128 x 32
-                if (shape == 0 && ncb < 4) continue;
-                const int64_t tm = shape >= 2 ? 128 : 256;
-                const int cbs = shape == 0 ? 4 : (shape == 3 ? 1 : 2);
-                const ConvParams saved = p;
-                const bool fits = try_chws(cbs, true, shape == 0 ? 12 : 8, (int)tm);
-                const int64_t items = N * (int64_t)p.tiles_per_image * p.co_groups;     // (of the trial, if it fits)
-                // cost of a tile, from timings.  5x5 windows (16 channels per pass on every tiling: the weights of a pass
-                // are moved as often as on the large tile): 0.87 and 0.67 over 30 and 380 layers; 8-pixel staging units
-                // on wide rows of an odd width (see try_chws): with a row stride they are most of a tile's time (80 -> 352 on
-                // 12 of 6x123 / 2: 13.9 us in one round of large tiles with one-pixel units, 21.8 in two of small ones)
-                static const double tile_cost[2][4] = {{1.6, 1.0, 0.6, 0.42}, {0.0, 1.0, 0.87, 0.67}};
-                const double units = fits && W % 2 == 1 && W >= 63 && (Cin >= 128 || sh > 1) && p.xpx == 8 ? (sh > 1 ? 2.0 : 1.3) : 1.0;
-                const double cost = (double)cdiv(items, 256) * tile_cost[kh == 5][shape] * units;
-                p = saved;
-                if (fits && (best < 0 || cost < best_cost)) { best = shape; best_cost = cost; }
-            }
-            if (best >= 0 && try_chws(best == 0 ? 4 : (best == 3 ? 1 : 2), true, best == 0 ? 12 : 8, best >= 2 ? 128 : 256)) {
+            // the tiling with the lowest estimate among those whose packed weights are at most so many bytes
+            auto choose = [&](int64_t most_bytes, double *best_cost) -> bool {
+                bool found = false;
+                ConvParams best = p;
+                for (int shape = 0; shape < 4; ++shape) {          // 0: 256 x 128 on 12 wavefronts, 1: 256 x 64, 2: 128 x 64, 3: 128 x 32
+                    if (shape == 0 && ncb < 4) continue;
+                    const int64_t tm = shape >= 2 ? 128 : 256;
+                    const int cbs = shape == 0 ? 4 : (shape == 3 ? 1 : 2);
+                    const ConvParams saved = p;
+                    const bool fits = try_chws(cbs, true, shape == 0 ? 12 : 8, (int)tm);
+                    const int64_t items = N * (int64_t)p.tiles_per_image * p.co_groups;     // (of the trial, if it fits)
+                    // cost of a tile, from timings.  5x5 windows (16 channels per pass on every tiling: the weights of a pass
+                    // are moved as often as on the large tile): 0.87 and 0.67 over 30 and 380 layers; 8-pixel staging units
+                    // on wide rows of an odd width (see try_chws): with a row stride they are most of a tile's time (80 -> 352 on
+                    // 12 of 6x123 / 2: 13.9 us in one round of large tiles with one-pixel units, 21.8 in two of small ones)
+                    static const double tile_cost[2][4] = {{1.6, 1.0, 0.6, 0.42}, {0.0, 1.0, 0.87, 0.67}};
+                    const double units = fits && W % 2 == 1 && W >= 63 && (Cin >= 128 || sh > 1) && p.xpx == 8 ? (sh > 1 ? 2.0 : 1.3) : 1.0;
+                    const double cost = (double)cdiv(items, 256) * tile_cost[kh == 5][shape] * units;
+                    const int64_t bytes = packed_bytes(p);
+                    const ConvParams trial = p;
+                    p = saved;
+                    if (fits && bytes <= most_bytes && (!found || cost < *best_cost)) { found = true; best = trial; *best_cost = cost; }
+                }
+                if (found) p = best;
+                return found;
+            };
+            double cost = 0.0;
+            if (choose(INT64_MAX, &cost)) {
                 ok = true;
-                pl->est_units = best_cost;
+                pl->est_units = cost;
+                if (packed_bytes(p) > MERIT_NOALLOC_SCRATCH_BYTES) {
+                    // (channel blocks and passes are padded by different amounts on different tilings)
+                    const ConvParams run = p;
+                    for (int i = 0; i < 2 && !pl->use_na; ++i) {
+                        short_pass = i == 1;
+                        if (choose(MERIT_NOALLOC_SCRATCH_BYTES, &cost)) { pl->conv_na = p; pl->use_na = 1; }
+                        p = run;
+                    }
+                    short_pass = false;
+                }
             }
         }
     }
@@ -1769,7 +1792,7 @@ merit_status merit_plan_packed_weights_bytes(const merit_plan *plan, int64_t *by
     if (!plan || !bytes) return MERIT_ERR_NULL;
     if (!plan_takes_packed(plan)) return MERIT_ERR_UNSUPPORTED;
     const ConvParams &p = plan->conv;
-    *bytes = (int64_t)p.co_groups * p.nchunks * p.lds_w_bytes;
+    *bytes = packed_bytes(p);
     return MERIT_OK;
 }
 
@@ -1803,14 +1826,14 @@ merit_status merit_conv2d_packed_noalloc(const merit_plan *plan, const void *x, 
 {
     if (!plan) return MERIT_ERR_NULL;
     if (!plan_takes_packed(plan)) return MERIT_ERR_UNSUPPORTED;
-    const ConvParams &p = plan->conv;
-    if ((int64_t)p.co_groups * p.nchunks * p.lds_w_bytes > (int64_t)MERIT_NOALLOC_SCRATCH_BYTES)
-        return MERIT_ERR_SCRATCH_LIMIT;
+    const ConvParams &p = plan->use_na ? plan->conv_na : plan->conv;
+    // (the matrix-product kernel reads the weights as they lie: no copy, but the same limit)
+    const int64_t bytes = plan->use_px ? (int64_t)plan->px.Cout * plan->px.Cin * 2 : packed_bytes(p);
+    if (bytes > (int64_t)MERIT_NOALLOC_SCRATCH_BYTES) return MERIT_ERR_SCRATCH_LIMIT;
     if (p.N == 0) return MERIT_OK;                        // empty batch: nothing to read or write
     if (!x || !w || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    // (the matrix-product kernel needs no packed copy to give the packed call's bits)
     const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
                                       : launch_conv2d_chws_noalloc(p, x, w, y, s);
     return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;

@@ -57,3 +57,19 @@ def test_tiles_of_wide_odd_rows_with_a_stride():
     """One round of 64-channel tiles (13.9 us) rather than two of 32-channel ones (21.8)."""
     li = _conv(12, 80, 6, 123, 352, 3, 3, 2, 2, 1, 1).launch_info()
     assert li["kernel"] == "merit_conv2d_chws" and li["tile"][1] == 64
+
+
+@pytest.mark.parametrize("shape", [
+    (6, 1192, 83, 13, 381, 3, 3, 2, 2, 1, 1),       # 64-channel tiles 7.9 MiB, 32-channel ones 8.02
+    (8, 336, 17, 102, 1344, 3, 3, 2, 2, 1, 1),      # ... 128-channel ones 8.12
+    (5, 2824, 123, 63, 1431, 1, 1, 3, 3, 0, 0),     # passes of 16 channels 7.95 MiB, of 64 channels 8.3
+    (4, 3632, 36, 110, 1079, 1, 1, 1, 1, 0, 0),     # weights of 7.5 MiB, read as they lie
+])
+def test_the_fixed_buffer_takes_the_smallest_packed_copy(shape):
+    """A layer is not refused because the tiling that runs it pads its weights past the buffer."""
+    plan = _conv(*shape)
+    assert mb.merit_plan_packed_weights_bytes(plan) > mb.MERIT_NOALLOC_SCRATCH_BYTES
+    accepted = mb.lib().merit_conv2d_packed_noalloc(plan.handle, None, None, None, None)       # (nothing is launched)
+    assert accepted == mb.MERIT_ERR_NULL
+    too_large = _conv(1, 1024, 16, 16, 1024, 3, 3, 1, 1, 1, 1)
+    assert mb.lib().merit_conv2d_packed_noalloc(too_large.handle, None, None, None, None) == mb.MERIT_ERR_SCRATCH_LIMIT
