@@ -1675,6 +1675,10 @@ merit_status merit_plan_set_tile(merit_plan *plan, const int64_t tile[MERIT_MAX_
             if (tile[j] > 0) return MERIT_ERR_UNSUPPORTED;
         return MERIT_OK;
     }
+    if (plan->desc.op == MERIT_OP_CORR_DOT && plan->desc.a.shape[3] % 8 != 0) {      // one tiling, and no request names it
+        for (int j = 0; j < MERIT_MAX_INDEX; ++j)
+            if (tile[j] > 0) return MERIT_ERR_UNSUPPORTED;
+    }
     merit_plan trial = *plan;
     for (int j = 0; j < MERIT_MAX_INDEX; ++j) trial.tile_req[j] = tile[j];
     merit_status st;

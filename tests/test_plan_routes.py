@@ -73,3 +73,16 @@ def test_the_fixed_buffer_takes_the_smallest_packed_copy(shape):
     assert accepted == mb.MERIT_ERR_NULL
     too_large = _conv(1, 1024, 16, 16, 1024, 3, 3, 1, 1, 1, 1)
     assert mb.lib().merit_conv2d_packed_noalloc(too_large.handle, None, None, None, None) == mb.MERIT_ERR_SCRATCH_LIMIT
+
+
+@pytest.mark.parametrize("shape", [(1, 184, 60, 36, 3, 1), (1, 32, 17, 41, 4, 1), (1, 8, 16, 20, 2, 1)])
+def test_correlation_off_the_multiple_of_8_refuses_tile_requests(shape):
+    """Whichever kernel runs it: there is nothing to choose, and no request is accepted without effect."""
+    plan = mb.merit_plan_correlation(*shape)
+    before = plan.launch_info()
+    for tile in ((0, 4), (1, 1, 1, 1), (0, 0, 4, 32)):
+        with pytest.raises(mb.MeritError) as e:
+            plan.set_tile(tile)
+        assert e.value.status == mb.MERIT_ERR_UNSUPPORTED
+    plan.set_tile((0,))                                     # no request: accepted
+    assert plan.launch_info() == before
