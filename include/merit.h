@@ -284,10 +284,11 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x_f16, const void 
  * [Cout,Cin,kh,kw] tensor that is a register transposition on every pass of every tile; weights
  * do not change between calls, so the regrouping can be done once instead:
  *   merit_plan_packed_weights_bytes  size of the packed copy for this plan (a multiple of 16);
- *                                    MERIT_ERR_UNSUPPORTED if the plan's kernel takes no packed
- *                                    weights (merit_launch_info.kernel != "merit_conv2d_chws"), or on
- *                                    channel counts off the multiple of 8, fewer than 32 input or
- *                                    at most 32 output channels
+ *                                    MERIT_ERR_UNSUPPORTED if the plan takes no packed weights.
+ *                                    Those that do: 1x1, 3x3 and 5x5 layers on a multiple of 8
+ *                                    and at least 32 input and more than 32 output channels that
+ *                                    run on merit_conv2d_chws or merit_conv2d_px, without an added
+ *                                    tensor or pooling (ask this call, not the kernel's name)
  *   merit_conv2d_pack_weights        w_f16 -> packed (device memory of that size, owned by the
  *                                    caller, 16-byte aligned); enqueued on the stream
  *   merit_conv2d_packed              merit_conv2d with the packed copy in place of w_f16; same

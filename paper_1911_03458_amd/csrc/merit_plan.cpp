@@ -481,7 +481,7 @@ void derive_px(merit_plan *pl)
     pl->px = p;
     pl->use_px = 1;
     merit_launch_info &li = pl->info;
-    if (!packable(pl)) li.kernel = "merit_conv2d_px";      // (else the family name that says so)
+    li.kernel = "merit_conv2d_px";
     li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
     li.block[0] = 512; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = (int64_t)px_lds_bytes(p);

@@ -81,7 +81,7 @@ CHWS_CASES = [
     # two-pixel input units (W % 4 == 2: rows start on 4-byte boundaries)
     ((2, 128, 14, 14, 40, 3, 3, 1, 1, 1, 1), (1, 1), 0, None),              # the 14x14 layers' shape class, ragged channel block
     ((1, 200, 13, 14, 64, 3, 3, 1, 1, 1, 1), (1, 1), 1, None),              # last pass half empty, odd height
-    ((3, 64, 14, 14, 96, 1, 1, 1, 1, 0, 0), (1, 1), 0, None),               # 1x1
+    ((3, 64, 14, 14, 96, 1, 1, 1, 1, 0, 0), (1, 1), 0, (0, 0, 8, 32)),      # 1x1
     ((2, 96, 30, 30, 64, 3, 3, 2, 2, 1, 1), (1, 1), 0, None),               # stride 2 from 30 to 15 columns
     ((2, 64, 20, 42, 128, 3, 3, 1, 1, 2, 2), (2, 2), 1, (0, 0, 8, 64)),     # 256-pixel tiles, dilated
     ((1, 48, 12, 22, 256, 3, 3, 1, 1, 1, 1), (1, 1), 0, (0, 0, 12, 64)),    # 8 multiplying wavefronts: four units per moving thread
@@ -231,22 +231,31 @@ def test_chws_whole_row_tiles_with_an_added_tensor(mb):
     assert np.all(np.abs(got - ref) <= 2e-2 * np.abs(ref) + 1e-3)
 
 
-@pytest.mark.parametrize("shape", [(2, 128, 28, 28, 512), (1, 256, 14, 14, 1000), (3, 136, 9, 20, 70)])
-def test_chws_1x1_layer_with_an_added_tensor(mb, shape):
-    """1x1 windows with an added tensor and clipping (the closing layer of a bottleneck block) on the
-    residual instance: the planner's own choice from 128 input channels on."""
+@pytest.mark.parametrize("shape,stride,kernel", [
+    ((2, 128, 28, 28, 512), 1, "merit_conv2d_px"),
+    ((1, 256, 14, 14, 1000), 1, "merit_conv2d_px"),
+    ((3, 136, 9, 20, 70), 1, "merit_conv2d_px"),
+    ((2, 128, 28, 28, 512), 2, "merit_conv2d_chws"),
+    ((1, 256, 31, 56, 200), 2, "merit_conv2d_chws"),
+    ((3, 136, 19, 20, 70), 3, "merit_conv2d_chws"),
+    ((2, 131, 18, 22, 72), 2, "merit_conv2d_chws"),            # a last group of three channels
+    ((2, 203, 33, 57, 40), 2, "merit_conv2d_chws"),
+])
+def test_chws_1x1_layer_with_an_added_tensor(mb, shape, stride, kernel):
+    """1x1 windows with an added tensor and clipping (the closing layer of a bottleneck block): the matrix-product
+    kernel, and with a stride the residual instances, the planner's own choice from 128 input channels on."""
     N, Cin, H, W, Cout = shape
     rng = np.random.default_rng(Cin + Cout)
+    plan = mb.merit_plan_conv2d_residual(N, Cin, H, W, Cout, 1, 1, stride, stride, 0, 0, 1)
+    assert plan.launch_info()["kernel"] == kernel, plan.launch_info()
     x = rng.standard_normal((N, Cin, H, W)).astype(np.float16)
     w = (rng.standard_normal((Cout, Cin, 1, 1)) / np.sqrt(Cin)).astype(np.float16)
-    r = rng.standard_normal((N, Cout, H, W)).astype(np.float16)
-    plan = mb.merit_plan_conv2d_residual(N, Cin, H, W, Cout, 1, 1, 1, 1, 0, 0, 1)
-    assert plan.launch_info()["kernel"] == "merit_conv2d_chws", plan.launch_info()
+    r = rng.standard_normal(plan.out_shape()).astype(np.float16)
     buf, y, pad = guarded(plan.out_shape())
     mb.merit_conv2d_residual(plan, dev(x), dev(w), dev(r), y)
     torch.cuda.synchronize()
     assert canary_ok(buf, pad)
-    ref = oracle.conv2d_residual(x, w, r, (1, 1), (0, 0), True).astype(np.float64)
+    ref = oracle.conv2d_residual(x, w, r, (stride, stride), (0, 0), True).astype(np.float64)
     got = y.cpu().numpy().astype(np.float64)
     assert np.all(np.abs(got - ref) <= 2e-2 * np.abs(ref) + 1e-3)
 

@@ -1,5 +1,5 @@
-"""1x1 layers on the matrix-product kernel (csrc/conv2d_px.hip) against the oracle: every tile, planes and channel
-counts that are not whole 16-byte units, the added tensor, packed weights.  Bar: 2e-2*|r| + 1e-3 (fp16 products, fp32
+"""1x1 layers on the matrix-product kernel (csrc/conv2d_px.hip) against the oracle: every tile with and without the added
+tensor, planes and channel counts that are not whole 16-byte units, packed weights.  Bar: 2e-2*|r| + 1e-3 (fp16 products, fp32
 accumulation, one rounding, against a double sum)."""
 import gc
 
@@ -20,7 +20,7 @@ def no_garbage_left():
     gc.collect()
 
 CASES = [
-    # N   Cin  H   W   Cout  residual  tile the planner takes (channels)
+    # N   Cin  H   W   Cout  residual
     (1, 16, 2, 4, 1, False),          # a single unit, a single step a quarter full
     (2, 24, 3, 3, 40, False),         # nine pixels: a unit and one cut
     (1, 17, 5, 7, 33, True),          # odd channels: rows of the weights on any 2-byte boundary
@@ -33,6 +33,22 @@ CASES = [
     (24, 72, 60, 20, 24, False),      # at most 32 output channels
     (5, 255, 57, 19, 64, False),      # rows of 255 channels
     (1, 248, 40, 41, 1000, False),
+]
+
+# One of each tile with a plane and channels that are not whole units, and one whose steps reach the loop that has the
+# next ones in flight and leave a remainder (four steps ahead on the first two tiles, two or one on the others).
+TILES = [
+    # N   Cin  H   W   Cout  tile
+    (3, 212, 12, 5, 1, (64, 32)),
+    (2, 808, 3, 19, 1, (64, 32)),
+    (17, 173, 2, 5, 585, (64, 64)),
+    (11, 680, 3, 5, 827, (64, 64)),
+    (17, 211, 3, 3, 981, (64, 128)),
+    (21, 520, 6, 3, 1079, (64, 128)),
+    (10, 129, 31, 52, 1, (128, 32)),
+    (6, 520, 53, 26, 69, (128, 32)),
+    (23, 130, 6, 23, 222, (128, 64)),
+    (24, 544, 2, 33, 703, (128, 64)),
 ]
 
 
@@ -50,7 +66,7 @@ def _run(case, relu):
         ref = oracle.conv2d(x, w, (1, 1), (0, 0), relu=bool(relu))
     li = plan.launch_info()
     print(case, li, flush=True)
-    assert li["block"][0] == 512 and li["kernel"] in ("merit_conv2d_px", "merit_conv2d_chws")
+    assert li["block"][0] == 512 and li["kernel"] == "merit_conv2d_px"
     n = int(np.prod(plan.out_shape()))
     buf = torch.full((n + 128,), 777.0, dtype=torch.float16, device="cuda")
     y = buf[64:64 + n].view(plan.out_shape())
@@ -72,13 +88,22 @@ def test_against_the_oracle(case, relu):
     if case[5]:                       # the added tensor may be the output itself
         z = dr.clone()
         assert torch.equal(mb.merit_conv2d_residual(plan, dx, dw, z, z), y)
-    elif plan.launch_info()["kernel"] == "merit_conv2d_chws":
+    elif case[1] % 8 == 0 and case[1] >= 32 and case[4] > 32:
         assert torch.equal(mb.merit_conv2d_packed(plan, dx, mb.merit_conv2d_pack_weights(plan, dw)), y)
         z = torch.empty_like(y)
         assert torch.equal(mb.merit_conv2d_packed_noalloc(plan, dx, dw, z), y)
     else:
         with pytest.raises(mb.MeritError):
             mb.merit_plan_packed_weights_bytes(plan)
+
+
+@pytest.mark.parametrize("case", TILES)
+@pytest.mark.parametrize("residual", [False, True])
+def test_every_tile(case, residual):
+    plan, dx, dw, dr, y = _run(case[:5] + (residual,), 0)
+    (tm, tn), W = case[5], case[3]
+    tile = plan.launch_info()["tile"]
+    assert tile[1] == tn and tile[2] == -(-tm // W), tile
 
 
 @pytest.mark.parametrize("Cin,H,W", [(33, 3, 5), (70, 9, 9), (100, 13, 9)])

@@ -86,3 +86,14 @@ def test_correlation_off_the_multiple_of_8_refuses_tile_requests(shape):
         assert e.value.status == mb.MERIT_ERR_UNSUPPORTED
     plan.set_tile((0,))                                     # no request: accepted
     assert plan.launch_info() == before
+
+
+def test_launch_info_names_the_kernel_that_runs():
+    """1x1 layers at stride 1, with and without a packed form; a tile request names the other kernel."""
+    for make in (mb.merit_plan_conv2d, mb.merit_plan_conv2d_relu):
+        plan = make(8, 256, 14, 14, 1024, 1, 1, 1, 1, 0, 0)
+        assert plan.launch_info()["kernel"] == "merit_conv2d_px" and mb.merit_plan_packed_weights_bytes(plan) > 0
+        plan.set_tile((0, 0, 8, 64))
+        assert plan.launch_info()["kernel"] == "merit_conv2d_chws" and mb.merit_plan_packed_weights_bytes(plan) > 0
+    assert mb.merit_plan_conv2d_residual(8, 256, 14, 14, 1024, 1, 1, 1, 1, 0, 0).launch_info()["kernel"] == "merit_conv2d_px"
+    assert _conv(8, 256, 14, 14, 1024, 1, 1, 2, 2, 0, 0).launch_info()["kernel"] == "merit_conv2d_chws"
