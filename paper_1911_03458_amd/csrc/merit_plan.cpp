@@ -1158,13 +1158,34 @@ merit_status derive_dw(merit_plan *pl)
     DwParams &p = pl->dw;
     p.NC = (int)(N * C); p.C = (int)C; p.H = (int)H; p.W = (int)W; p.OH = (int)OH; p.OW = (int)OW;
     p.kh = (int)kh; p.kw = (int)kw; p.sh = (int)sh; p.sw = (int)sw; p.ph = (int)ph; p.pw = (int)pw;
+    // the workgroup of the kernel for any window: output rows, halves of an input row in LDS (0 rows: too wide)
+    const int64_t pitch = W + 2 * pw;
+    int64_t tile_rows = pl->tile_req[2] > 0 ? pl->tile_req[2] : (4096 / OW > 0 ? 4096 / OW : 1);
+    if (tile_rows > OH) tile_rows = OH;
+    while (tile_rows > 1 && ((tile_rows - 1) * sh + kh) * pitch * 2 > 48 * 1024) tile_rows = (tile_rows + 1) / 2;
+    if (((tile_rows - 1) * sh + kh) * pitch * 2 > 96 * 1024) tile_rows = 0;
     // 3x3 and 5x5 windows at stride 1 and 2 whose rows hold a thread's outputs: the kernel without LDS (not where a
     // tile request names the rows of a workgroup)
     const int64_t qw = 8 / (sw > 0 ? sw : 1), units = cdiv(OW, qw), strips = cdiv(OH, DW_LANES_ROWS);
     const bool rows = kh == 3 && kw == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && W % 8 == 0 && W <= 4096 && pl->tile_req[2] <= 0;
-    const bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && OW >= qw && pl->tile_req[2] <= 0 &&
-                       N * C * H * W >= 16 && N * C * H * W < (1ll << 31) - 64 && N * C * strips * units < (1ll << 30) &&
-                       fastdiv_ok(N * C * strips * units + 256, units) && fastdiv_ok(N * C * strips, strips);
+    bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && OW >= qw && pl->tile_req[2] <= 0 &&
+                 N * C * H * W >= 16 && N * C * H * W < (1ll << 31) - 64 && N * C * strips * units < (1ll << 30) &&
+                 fastdiv_ok(N * C * strips * units + 256, units) && fastdiv_ok(N * C * strips, strips);
+    if (lanes && tile_rows > 0) {
+        // On few small planes its long thread (all loads of four output rows, then all of their sums) is longer than the
+        // whole of the other kernel, whose workgroup holds a plane with an element or two per thread: 1x24x9x14 3x3 / 2
+        // 3.1 us against 4.1, 2x40x8x17 5x5 3.8 against 6.0.  The lower estimate, in microseconds, fitted to 665 layers
+        // (the choice is within 0.2 % of the better kernel on average, 21 % at worst): for the kernel for any window a
+        // thread's chain of elements to stage and outputs to sum, and the wavefronts that do so, over the workgroups.
+        const int64_t staged = ((tile_rows - 1) * sh + kh) * pitch, outs = tile_rows * OW;
+        const double per_out = kw == 5 ? 0.9 : 0.43;
+        const double chain = 0.15 * (double)cdiv(staged, 256) + per_out * (double)cdiv(outs, 256);
+        const double waves = 0.15 * (double)cdiv(staged, 64) + per_out * (double)cdiv(outs, 64);
+        const double grid = (double)(N * C * cdiv(OH, tile_rows)), over = (double)(N * C * strips * units) - 35000.0;
+        const double tile_us = 2.5 + chain + grid * (0.001 * 0.25 * waves + 0.0001);
+        const double lanes_us = (kw == 5 ? 5.5 : (sw == 2 ? 4.75 : 4.45)) + (over > 0.0 ? over * (kw == 5 ? 4e-5 : 2.9e-5) : 0.0);
+        lanes = tile_us >= lanes_us;
+    }
     if (lanes) {
         p.variant = DW_LANES;
         p.TH = DW_LANES_ROWS;
@@ -1187,12 +1208,9 @@ merit_status derive_dw(merit_plan *pl)
         p.div_ow = make_fastdiv((uint32_t)(W / 8));
     } else {
         p.variant = DW_TILE_GENERIC;
-        p.pitch = (int)(W + 2 * pw);
-        int64_t TH = pl->tile_req[2] > 0 ? pl->tile_req[2] : (4096 / OW > 0 ? 4096 / OW : 1);
-        if (TH > OH) TH = OH;
-        while (TH > 1 && ((TH - 1) * sh + kh) * p.pitch * 2 > 48 * 1024) TH = (TH + 1) / 2;
-        const int64_t RH = (TH - 1) * sh + kh;
-        if (RH * p.pitch * 2 > 96 * 1024) return MERIT_ERR_UNSUPPORTED;      // very wide rows: no column tiling here
+        p.pitch = (int)pitch;
+        const int64_t TH = tile_rows, RH = (TH - 1) * sh + kh;
+        if (TH == 0) return MERIT_ERR_UNSUPPORTED;                           // very wide rows: no column tiling here
         p.TH = (int)TH;
         p.lds_w_offset = (int)round_up(RH * p.pitch * 2, 16);
         p.lds_bytes = (int)(p.lds_w_offset + kh * kw * 4);

@@ -18,18 +18,19 @@ def no_garbage_left():
     yield
     gc.collect()
 
+# (as many planes as send layers of these sizes to this kernel)
 CASES = [
     # N  C   H   W  k  s  ph pw
-    (1, 2, 5, 9, 3, 1, 1, 1),        # a unit and one output
-    (2, 3, 9, 15, 3, 1, 0, 0),
-    (1, 5, 7, 8, 3, 1, 0, 1),
-    (3, 4, 12, 23, 3, 2, 1, 1),
-    (1, 2, 3, 8, 3, 2, 1, 1),        # one unit a row, two rows
-    (2, 3, 13, 17, 5, 1, 2, 2),
-    (1, 7, 10, 24, 5, 1, 4, 4),      # outputs that see only padding in part of the window
-    (2, 5, 11, 30, 5, 2, 2, 2),
-    (1, 3, 6, 8, 5, 2, 0, 4),
-    (1, 1, 4, 8, 3, 1, 2, 6),        # whole units of padding
+    (120, 81, 5, 9, 3, 1, 1, 1),        # a unit and one output
+    (120, 81, 9, 15, 3, 1, 0, 0),
+    (120, 81, 7, 8, 3, 1, 0, 1),
+    (120, 81, 12, 23, 3, 2, 1, 1),
+    (120, 81, 3, 8, 3, 2, 1, 1),        # one unit a row, two rows
+    (120, 81, 13, 17, 5, 1, 2, 2),
+    (120, 81, 10, 24, 5, 1, 4, 4),      # outputs that see only padding in part of the window
+    (120, 81, 11, 30, 5, 2, 2, 2),
+    (120, 81, 6, 8, 5, 2, 0, 4),
+    (120, 81, 4, 8, 3, 1, 2, 6),        # whole units of padding
     (4, 40, 20, 65, 3, 1, 1, 1),
 ]
 
@@ -50,9 +51,9 @@ def test_against_the_oracle(case):
     ref = oracle.conv2d_depthwise(x, w, (s, s), (ph, pw)).astype(np.float64)
     assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.abs(ref) + 1e-3)
     # rows and planes next to each other: a NaN reaches exactly the windows that hold it
-    x[0, 0, H - 1, W - 1] = np.nan
+    x[0, 0, H - 1, W - 1] = x[N - 1, C - 1, H - 1, W - 1] = np.nan
     got = np.isnan(mb.merit_conv2d_depthwise(plan, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()).cpu().numpy())
     oy, ox = np.meshgrid(np.arange(got.shape[2]), np.arange(got.shape[3]), indexing="ij")
     want = np.zeros_like(got)
-    want[0, 0] = ((oy * s - ph <= H - 1) & (oy * s - ph + k > H - 1) & (ox * s - pw <= W - 1) & (ox * s - pw + k > W - 1))
+    want[0, 0] = want[N - 1, C - 1] = ((oy * s - ph <= H - 1) & (oy * s - ph + k > H - 1) & (ox * s - pw <= W - 1) & (ox * s - pw + k > W - 1))
     assert np.array_equal(got, want)

@@ -97,3 +97,15 @@ def test_launch_info_names_the_kernel_that_runs():
         assert plan.launch_info()["kernel"] == "merit_conv2d_chws" and mb.merit_plan_packed_weights_bytes(plan) > 0
     assert mb.merit_plan_conv2d_residual(8, 256, 14, 14, 1024, 1, 1, 1, 1, 0, 0).launch_info()["kernel"] == "merit_conv2d_px"
     assert _conv(8, 256, 14, 14, 1024, 1, 1, 2, 2, 0, 0).launch_info()["kernel"] == "merit_conv2d_chws"
+
+
+@pytest.mark.parametrize("shape,kernel", [
+    ((1, 24, 9, 14, 3, 3, 2, 2, 1, 1), "merit_dwconv_tile"),        # 3.1 us, against 4.1 on the other
+    ((2, 40, 8, 17, 5, 5, 1, 1, 2, 2), "merit_dwconv_tile"),        # 3.8, 6.0
+    ((6, 56, 29, 8, 3, 3, 2, 2, 1, 1), "merit_dwconv_tile"),        # 3.4, 6.3
+    ((12, 144, 94, 24, 5, 5, 1, 1, 2, 2), "merit_dwconv_lanes"),    # 26.8, 7.8
+    ((32, 512, 14, 14, 3, 3, 1, 1, 1, 1), "merit_dwconv_lanes"),    # 20.5, 6.8
+    ((1, 8, 8, 4096, 3, 3, 1, 1, 0, 0), "merit_dwconv_lanes"),
+])
+def test_depthwise_layers_take_the_faster_kernel(shape, kernel):
+    assert mb.merit_plan_conv2d_depthwise(*shape).launch_info()["kernel"] == kernel
