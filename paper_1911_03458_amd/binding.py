@@ -1,14 +1,20 @@
-"""ctypes binding of libmerit.so -- argument marshalling only.
+"""Python binding of libmerit.so -- argument marshalling only.
 
 Function names mirror include/merit.h.  Tensors are torch CUDA (ROCm) tensors:
 PyTorch provides device memory and the current HIP stream, nothing else; every
 step of the computation runs in the library's kernels.  There is no fallback:
 if the library is missing or a call fails, an exception is raised.
+
+Two ways into the library: ctypes, for everything, and for the ordinary form of
+an operation (plain contiguous tensors, a new output, the current stream) the
+module built from csrc/torch_calls.cpp, which costs the host less.  A call that
+the module does not take goes the first way.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 from . import build as _build
 
@@ -277,31 +283,41 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
-# The operations of csrc/torch_calls.cpp, in its order.
-(_CONV2D, _CONV2D_PACKED, _RESIDUAL, _POOL2D, _SAD, _DEPTHWISE, _SEPFILTER, _BILATERAL, _CORRELATION) = range(9)
-_calls = None
+_calls = None            # the module built from csrc/torch_calls.cpp
+_ops = {}                # its number for each entry point it takes
+_calls_lock = threading.Lock()
+
+
+def _load_calls():
+    """The module (built here only if there is none)."""
+    import importlib.util
+
+    import torch  # noqa: F401  (its libraries, before the module that uses them)
+    lib()
+    if not os.path.exists(_build.CALLS_PATH):
+        _build.build_torch_calls()
+    spec = importlib.util.spec_from_file_location(__package__ + "._torch_calls", _build.CALLS_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
 
 
 def _native():
-    """The module built from csrc/torch_calls.cpp (built here only if there is none)."""
-    global _calls
+    """The module, loaded once."""
+    global _calls, _ops
     if _calls is None:
-        import importlib.util
-
-        import torch  # noqa: F401  (its libraries, before the module that uses them)
-        lib()
-        if not os.path.exists(_build.CALLS_PATH):
-            _build.build_torch_calls()
-        spec = importlib.util.spec_from_file_location(__package__ + "._torch_calls", _build.CALLS_PATH)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
-        _calls = module
+        with _calls_lock:
+            if _calls is None:
+                module = _load_calls()
+                _ops, _calls = module.OPS, module
     return _calls
 
 
-def _ordinary(where, op, plan, *args):
+def _ordinary(where, plan, *args):
     """The call natively if it is of the ordinary form (see csrc/torch_calls.cpp), else None."""
-    spec = plan._spec or plan._new_spec()
+    spec, op = plan._spec or plan._new_spec(), _ops.get(where)
+    if op is None:
+        return None
     r = _calls.call(op, spec, *args)
     if r.__class__ is int:
         raise MeritError(r, where)
@@ -310,7 +326,7 @@ def _ordinary(where, op, plan, *args):
 
 def merit_conv2d(plan: Plan, x, w, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_conv2d", _CONV2D, plan, x, w)
+        r = _ordinary("merit_conv2d", plan, x, w)
         if r is not None:
             return r
     import torch
@@ -349,7 +365,7 @@ def merit_conv2d_pack_weights(plan: Plan, w, packed=None, stream=None):
 
 def merit_conv2d_packed(plan: Plan, x, packed, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_conv2d_packed", _CONV2D_PACKED, plan, x, packed)
+        r = _ordinary("merit_conv2d_packed", plan, x, packed)
         if r is not None:
             return r
     import torch
@@ -380,7 +396,7 @@ def merit_conv2d_packed_noalloc(plan: Plan, x, w, y, stream=None):
 
 def merit_conv2d_residual(plan: Plan, x, w, r, y=None, stream=None):
     if y is None and stream is None:
-        out = _ordinary("merit_conv2d_residual", _RESIDUAL, plan, x, w, r)
+        out = _ordinary("merit_conv2d_residual", plan, x, w, r)
         if out is not None:
             return out
     import torch
@@ -399,7 +415,7 @@ def merit_conv2d_residual(plan: Plan, x, w, r, y=None, stream=None):
 
 def merit_pool2d(plan: Plan, x, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_pool2d", _POOL2D, plan, x)
+        r = _ordinary("merit_pool2d", plan, x)
         if r is not None:
             return r
     import torch
@@ -417,7 +433,7 @@ def merit_pool2d(plan: Plan, x, y=None, stream=None):
 
 def merit_sad_search(plan: Plan, cur, ref, sad=None, mv=None, stream=None):
     if sad is None and mv is None and stream is None:
-        r = _ordinary("merit_sad_search", _SAD, plan, cur, ref)
+        r = _ordinary("merit_sad_search", plan, cur, ref)
         if r is not None:
             return r
     import torch
@@ -445,7 +461,7 @@ def merit_plan_conv2d_depthwise(N, C, H, W, kh, kw, sh, sw, ph, pw) -> Plan:
 
 def merit_conv2d_depthwise(plan: Plan, x, w, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_conv2d_depthwise", _DEPTHWISE, plan, x, w)
+        r = _ordinary("merit_conv2d_depthwise", plan, x, w)
         if r is not None:
             return r
     import torch
@@ -477,7 +493,7 @@ def _sep_args(plan, x, kx, ky, y, stream):
 
 def merit_sepfilter(plan: Plan, x, kx, ky, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_sepfilter", _SEPFILTER, plan, x, kx, ky)
+        r = _ordinary("merit_sepfilter", plan, x, kx, ky)
         if r is not None:
             return r
     import torch
@@ -511,7 +527,7 @@ def _bilateral_args(plan, x, gx, gy, norm, y, stream):
 
 def merit_bilateral(plan: Plan, x, gx, gy, norm, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_bilateral", _BILATERAL, plan, x, gx, gy, norm)
+        r = _ordinary("merit_bilateral", plan, x, gx, gy, norm)
         if r is not None:
             return r
     import torch
@@ -554,7 +570,7 @@ def merit_plan_correlation(N, C, H, W, R, sd=1) -> Plan:
 
 def merit_correlation(plan: Plan, x1, x2, y=None, stream=None):
     if y is None and stream is None:
-        r = _ordinary("merit_correlation", _CORRELATION, plan, x1, x2)
+        r = _ordinary("merit_correlation", plan, x1, x2)
         if r is not None:
             return r
     import torch

@@ -1,4 +1,5 @@
-"""Build libmerit.so (HIP kernels + C ABI) in-tree with hipcc for gfx950, and _torch_calls.so beside it."""
+"""Build libmerit.so (HIP kernels + C ABI; needs hipcc only) in-tree for gfx950, and _torch_calls.so beside it (a Python
+module over the library; needs g++ and PyTorch's headers)."""
 from __future__ import annotations
 
 import os
@@ -16,6 +17,7 @@ CALLS_PATH = os.path.join(_HERE, "_torch_calls.so")      # a Python module over 
 SOURCES = ["merit_plan.cpp", "pool2d.hip", "sad_search.hip", "conv2d.hip", "conv2d_chws.hip", "conv2d_px.hip", "maxpool_f16.hip", "generic.hip", "corr.hip", "dwconv.hip", "sepfilter.hip", "bilateral.hip", "probe.hip"]
 HEADERS = [os.path.join(CSRC, "merit_internal.h"), os.path.join(ROOT, "include", "merit.h"),
            os.path.join(ROOT, "include", "merit_probe.h")]
+CALLS_DEPS = [CALLS_SRC, os.path.join(ROOT, "include", "merit.h")]
 
 
 def hipcc_path() -> str:
@@ -58,13 +60,19 @@ def build_library(force: bool = True, extra_flags=()) -> str:
     proc = subprocess.run(common + ["-shared", "-o", LIB_PATH] + objs, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc (link) failed:\n" + proc.stdout + proc.stderr)
-    build_torch_calls(force=True)
     return LIB_PATH
+
+
+def calls_are_stale() -> bool:
+    if not os.path.exists(CALLS_PATH):
+        return True
+    t = os.path.getmtime(CALLS_PATH)
+    return any(os.path.getmtime(d) > t for d in CALLS_DEPS)
 
 
 def build_torch_calls(force: bool = True) -> str:
     """Compile csrc/torch_calls.cpp (host code, no kernels) against PyTorch and the built library."""
-    if not force and os.path.exists(CALLS_PATH) and os.path.getmtime(CALLS_PATH) >= os.path.getmtime(CALLS_SRC):
+    if not force and not calls_are_stale():
         return CALLS_PATH
     import sysconfig
 
@@ -75,7 +83,8 @@ def build_torch_calls(force: bool = True) -> str:
     libs = ext.library_paths()
     tmp = CALLS_PATH + ".%d.tmp" % os.getpid()      # (never a half-written module in the way of another process)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), CALLS_SRC, "-o", tmp,
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DMERIT_TORCH="%s"' % torch.__version__, CALLS_SRC, "-o", tmp,
            "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
     cmd += ["-isystem" + d for d in ext.include_paths() + [os.path.join(rocm, "include")]]
     cmd += ["-L" + _HERE, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"] + ["-L" + d for d in libs]
@@ -85,6 +94,12 @@ def build_torch_calls(force: bool = True) -> str:
         raise RuntimeError("g++ (torch_calls) failed:\n" + proc.stdout + proc.stderr)
     os.replace(tmp, CALLS_PATH)
     return CALLS_PATH
+
+
+def build_all(force: bool = True) -> None:
+    """The library and the Python module over it."""
+    build_library(force=force)
+    build_torch_calls(force=force)
 
 
 def build_host_check(sanitizer: str = "address,undefined") -> str:
@@ -135,4 +150,5 @@ def build_host_check(sanitizer: str = "address,undefined") -> str:
 
 
 if __name__ == "__main__":
-    print(build_library())
+    build_all()
+    print(LIB_PATH, CALLS_PATH)

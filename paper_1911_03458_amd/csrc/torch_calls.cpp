@@ -20,8 +20,14 @@
 
 namespace {
 
-// (binding.py numbers them in the same order)
+// (binding.py takes their numbers from the module: OPS)
 enum Op { CONV2D, CONV2D_PACKED, RESIDUAL, POOL2D, SAD, DEPTHWISE, SEPFILTER, BILATERAL, CORRELATION };
+constexpr struct {
+  const char *name;
+  Op op;
+} kOps[] = {{"merit_conv2d", CONV2D},       {"merit_conv2d_packed", CONV2D_PACKED},  {"merit_conv2d_residual", RESIDUAL},
+            {"merit_pool2d", POOL2D},       {"merit_sad_search", SAD},               {"merit_conv2d_depthwise", DEPTHWISE},
+            {"merit_sepfilter", SEPFILTER}, {"merit_bilateral", BILATERAL},          {"merit_correlation", CORRELATION}};
 
 struct Shape {
   int64_t d[MERIT_MAX_DIMS];
@@ -163,4 +169,16 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_torch_calls", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__torch_calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__torch_calls() {
+  PyObject *m = PyModule_Create(&module), *ops = m ? PyDict_New() : nullptr;
+  bool ok = ops != nullptr;
+  for (const auto &o : kOps) {
+    PyObject *v = ok ? PyLong_FromLong(o.op) : nullptr;
+    ok = v && PyDict_SetItemString(ops, o.name, v) == 0;
+    Py_XDECREF(v);
+  }
+  ok = ok && PyObject_SetAttrString(m, "OPS", ops) == 0 && PyModule_AddStringConstant(m, "TORCH", MERIT_TORCH) == 0;
+  Py_XDECREF(ops);
+  if (!ok) Py_CLEAR(m);
+  return m;
+}
