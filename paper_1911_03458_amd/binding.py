@@ -8,13 +8,14 @@ if the library is missing or a call fails, an exception is raised.
 Two ways into the library: ctypes, for everything, and for the ordinary form of
 an operation (plain contiguous tensors, a new output, the current stream) the
 module built from csrc/torch_calls.cpp, which costs the host less.  A call that
-the module does not take goes the first way.
+the module does not take, or a process that cannot load it, goes the first way.
 """
 from __future__ import annotations
 
 import ctypes
 import os
 import threading
+import warnings
 
 from . import build as _build
 
@@ -153,8 +154,8 @@ class Plan:
         return self._shapes
 
     def _new_spec(self):
-        """What the native calls take in place of this object (handle and shapes)."""
-        self._spec = _native().spec(self.handle.value, *self.shapes())
+        """What the native calls take in place of this object (handle and shapes); None without the module."""
+        self._spec = _calls.spec(self.handle.value, *self.shapes()) if _native() else None
         return self._spec
 
     @property
@@ -283,7 +284,7 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
-_calls = None            # the module built from csrc/torch_calls.cpp
+_calls = None            # the module built from csrc/torch_calls.cpp; False: it cannot be used here
 _ops = {}                # its number for each entry point it takes
 _calls_lock = threading.Lock()
 
@@ -292,31 +293,41 @@ def _load_calls():
     """The module (built here only if there is none)."""
     import importlib.util
 
-    import torch  # noqa: F401  (its libraries, before the module that uses them)
+    import torch  # (its libraries, before the module that uses them)
     lib()
     if not os.path.exists(_build.CALLS_PATH):
         _build.build_torch_calls()
     spec = importlib.util.spec_from_file_location(__package__ + "._torch_calls", _build.CALLS_PATH)
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
+    if module.TORCH != torch.__version__:
+        raise ImportError(f"built for PyTorch {module.TORCH}, this is {torch.__version__}")
     return module
 
 
 def _native():
-    """The module, loaded once."""
+    """Whether the native calls can be used; says so once if not (the calls then go through ctypes)."""
     global _calls, _ops
     if _calls is None:
         with _calls_lock:
             if _calls is None:
-                module = _load_calls()
-                _ops, _calls = module.OPS, module
-    return _calls
+                try:
+                    module = _load_calls()
+                    _ops, _calls = module.OPS, module
+                except (ImportError, OSError, RuntimeError, AttributeError) as e:
+                    if _lib is None:
+                        raise              # (the library itself)
+                    warnings.warn(f"{_build.CALLS_PATH} cannot be used ({e}): calls go through ctypes, at about twice the "
+                                  "host time; build it anew with python -m paper_1911_03458_amd.build", RuntimeWarning,
+                                  stacklevel=5)
+                    _calls = False
+    return _calls is not False
 
 
 def _ordinary(where, plan, *args):
     """The call natively if it is of the ordinary form (see csrc/torch_calls.cpp), else None."""
     spec, op = plan._spec or plan._new_spec(), _ops.get(where)
-    if op is None:
+    if spec is None or op is None:
         return None
     r = _calls.call(op, spec, *args)
     if r.__class__ is int:

@@ -90,6 +90,19 @@ def test_what_the_general_path_refuses_stays_refused(name):
         op(plan, *args)
 
 
+@pytest.mark.parametrize("name", list(CALLS))
+def test_without_the_module(name, monkeypatch):
+    """A process that cannot load it: every call through ctypes, with the same results."""
+    make, op, inputs = CALLS[name]
+    args = inputs()
+    want = op(make(), *args)
+    monkeypatch.setattr(mb, "_calls", False)
+    monkeypatch.setattr(mb, "_ops", {})
+    got = op(make(), *args)
+    for a, b in zip(got if isinstance(got, tuple) else (got,), want if isinstance(want, tuple) else (want,)):
+        assert torch.equal(a, b)
+
+
 def test_packed_weights_and_a_changed_tiling():
     plan = mb.merit_plan_conv2d(2, 64, 16, 16, 64, 3, 3, 1, 1, 1, 1)
     x, w = _h(2, 64, 16, 16), _h(64, 64, 3, 3)

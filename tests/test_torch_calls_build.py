@@ -1,5 +1,6 @@
-"""The Python module over the library: when it is built anew, and what it is asked for."""
+"""The Python module over the library: when it is built anew, what it is asked for, and a process that cannot load it."""
 import os
+import warnings
 
 import pytest
 import torch
@@ -56,3 +57,31 @@ def test_the_library_needs_no_pytorch(tmp_path, monkeypatch):
     monkeypatch.setattr(build, "build_torch_calls", lambda force=True: pytest.fail("built the module"))
     build.build_library(force=True)
     assert len(ran) == len(build.SOURCES) + 1 and set(ran) == {build.hipcc_path()}
+
+
+def test_a_module_that_does_not_load_costs_a_warning_and_no_call(tmp_path, monkeypatch):
+    broken = tmp_path / "_torch_calls.so"
+    broken.write_text("not a module")
+    monkeypatch.setattr(build, "CALLS_PATH", str(broken))
+    monkeypatch.setattr(mb, "_calls", None)
+    monkeypatch.setattr(mb, "_ops", {})
+    plan = mb.merit_plan_pool2d(1, 3, 8, 8, 3, 3, 2, 2, 1, 1, 0)
+    x = torch.zeros((1, 3, 8, 8))
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert mb._ordinary("merit_pool2d", plan, x) is None
+    with warnings.catch_warnings():                     # said once
+        warnings.simplefilter("error")
+        with pytest.raises(TypeError, match="device tensor"):       # the general path judges the call
+            mb.merit_pool2d(plan, x)
+    plan.destroy()
+    with pytest.raises(ValueError):
+        mb.merit_pool2d(plan, x)
+
+
+def test_a_module_of_another_pytorch_is_not_used(monkeypatch):
+    monkeypatch.setattr(mb, "_calls", None)
+    monkeypatch.setattr(mb, "_ops", {})
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    plan = mb.merit_plan_pool2d(1, 3, 8, 8, 3, 3, 2, 2, 1, 1, 0)
+    with pytest.warns(RuntimeWarning, match="built for PyTorch"):
+        assert mb._ordinary("merit_pool2d", plan, torch.zeros(1)) is None
