@@ -1,7 +1,5 @@
 """Bilateral filter on rows that are not whole 16-byte groups, against the oracle (tolerance of the parity tests: weight
 error plus the fp32 sums, over each window's own range)."""
-import gc
-
 import numpy as np
 import pytest
 import torch
@@ -10,13 +8,6 @@ import oracle
 from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 
 @pytest.mark.parametrize("W", [3, 4, 5, 6, 7, 63, 65, 66, 67, 131])

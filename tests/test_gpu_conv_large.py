@@ -1,20 +1,11 @@
 """Many-channel layers on batches of more than 2 GiB: every image as in a small batch, the first ones' padding rows
 above all (byte offsets past the end of a descriptor are how the kernel gets its zeros)."""
-import gc
-
 import pytest
 import torch
 
 from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    yield
-    gc.collect()
-    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("N,Cin,H,W,Cout,form", [

@@ -1,8 +1,6 @@
 """1x1 layers on the matrix-product kernel (csrc/conv2d_px.hip) against the oracle: every tile with and without the added
 tensor, planes and channel counts that are not whole 16-byte units, packed weights.  Bar: 2e-2*|r| + 1e-3 (fp16 products, fp32
 accumulation, one rounding, against a double sum)."""
-import gc
-
 import numpy as np
 import pytest
 import torch
@@ -12,12 +10,6 @@ from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
 
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 CASES = [
     # N   Cin  H   W   Cout  residual

@@ -1,6 +1,4 @@
 """Correlation layers whose rows are not whole 8-pixel units, on the MFMA kernel, against the oracle."""
-import gc
-
 import numpy as np
 import pytest
 import torch
@@ -10,12 +8,6 @@ from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
 
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 CASES = [
     # N  C   H   W   R  sd

@@ -1,7 +1,5 @@
 """Depthwise layers on the kernel without LDS, against the oracle: rows that are not whole units, strips cut by the
 image's end, paddings beyond the window, the tensor's first and last units."""
-import gc
-
 import numpy as np
 import pytest
 import torch
@@ -11,12 +9,6 @@ from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
 
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 # (as many planes as send layers of these sizes to this kernel)
 CASES = [

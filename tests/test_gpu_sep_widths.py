@@ -1,7 +1,5 @@
 """Separable filter on rows that are not whole 16-byte groups, against the oracle; the border is replicated from the
 row's true last pixel whatever the last group holds.  Tolerance: 2k fp32 multiply-adds of at most |kx| |ky| max|x|."""
-import gc
-
 import numpy as np
 import pytest
 import torch
@@ -10,13 +8,6 @@ import oracle
 from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 
 @pytest.mark.parametrize("W", [3, 4, 5, 6, 7, 63, 65, 66, 67, 127, 190])

@@ -1,6 +1,6 @@
 """The native form of the ordinary calls against the general path (an output tensor given): same results, same
 refusals, the current stream, and nothing taken that the general path would not take."""
-import gc
+import threading
 
 import pytest
 import torch
@@ -8,13 +8,6 @@ import torch
 from paper_1911_03458_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(autouse=True, scope="module")
-def no_garbage_left():
-    """Tensors in reference cycles (a caught error's frames) go here, not under a later test that counts memory."""
-    yield
-    gc.collect()
 
 
 def _h(*shape):
@@ -104,14 +97,73 @@ def test_without_the_module(name, monkeypatch):
 
 
 def test_packed_weights_and_a_changed_tiling():
-    plan = mb.merit_plan_conv2d(2, 64, 16, 16, 64, 3, 3, 1, 1, 1, 1)
-    x, w = _h(2, 64, 16, 16), _h(64, 64, 3, 3)
-    packed = mb.merit_conv2d_pack_weights(plan, w)
-    assert torch.equal(mb.merit_conv2d_packed(plan, x, packed), mb.merit_conv2d(plan, x, w))
+    plan = mb.merit_plan_conv2d(2, 40, 16, 16, 72, 3, 3, 1, 1, 1, 1)
+    x, w = _h(2, 40, 16, 16), _h(72, 40, 3, 3)
+    packed, want = mb.merit_conv2d_pack_weights(plan, w), mb.merit_conv2d(plan, x, w)
+    assert torch.equal(mb.merit_conv2d_packed(plan, x, packed), want)
     with pytest.raises(ValueError):
         mb.merit_conv2d_packed(plan, x, packed[:-8])
-    with pytest.raises(ValueError):                 # every result is checked against the plan it came from
+    with pytest.raises(ValueError):
         mb.merit_conv2d_packed(plan, x[:1], packed)
+    before = mb.merit_plan_packed_weights_bytes(plan)
+    plan.set_tile((0, 0, 8, 32))                    # the same plan, another size of packed copy
+    assert mb.merit_plan_packed_weights_bytes(plan) != before
+    with pytest.raises(ValueError):
+        mb.merit_conv2d_packed(plan, x, packed)
+    assert torch.equal(mb.merit_conv2d_packed(plan, x, mb.merit_conv2d_pack_weights(plan, w)), want)
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_under_graph_capture(name):
+    """The output comes from the graph's pool, the launch is in the graph: every replay sees the inputs of its time."""
+    make, op, inputs = CALLS[name]
+    plan, args = make(), inputs()
+    op(plan, *args)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = op(plan, *args)
+    got = got if isinstance(got, tuple) else (got,)
+    for _ in range(4):
+        for a, b in zip(args, inputs()):
+            if isinstance(a, torch.Tensor):
+                a.copy_(b)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = op(plan, *args)
+        for a, b in zip(got, want if isinstance(want, tuple) else (want,)):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_threads_share_a_plan(name):
+    """Four threads, a stream each, one plan."""
+    make, op, inputs = CALLS[name]
+    plan = make()
+    sets = [inputs() for _ in range(4)]
+    wants = [op(plan, *args) for args in sets]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(args, want):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(20):
+                    got = op(plan, *args)
+                    stream.synchronize()
+                    for a, b in zip(got if isinstance(got, tuple) else (got,), want if isinstance(want, tuple) else (want,)):
+                        if not torch.equal(a, b):
+                            wrong.append("differs")
+        except Exception as e:          # (an assertion in a thread is lost)
+            wrong.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=z) for z in zip(sets, wants)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
 
 
 def test_tensor_subclass_takes_the_general_path():
