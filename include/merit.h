@@ -234,7 +234,9 @@ merit_status merit_plan_conv2d_depthwise(int N, int C, int H, int W, int kh, int
                                          int ph, int pw, merit_plan **out);
 /* Correlation layer (Section III-C, Eq. 8): y[n,p1,p2,p3,p4] = sum_c x1[n,c,p1,p2] *
  * x2[n,c,p1+(p3-R)*sd,p2+(p4-R)*sd], p3,p4 in [0, 2R]; 0 outside the image; no
- * normalisation by the channel count.  Every range; W >= 8, R <= 15 and sd <= 8 on the MFMA kernel. */
+ * normalisation by the channel count.  Every range; W >= 8, R <= 15 and sd <= 8 on the MFMA kernel
+ * (widths off the multiple of 8 from 65537 products N C H W (2R + 1)^2 on; those take no tile
+ * request). */
 merit_status merit_plan_correlation(int N, int C, int H, int W, int R, int sd, merit_plan **out);
 
 /* Copy of the descriptor the plan was created from. */
@@ -271,7 +273,10 @@ merit_status merit_plan_set_tile(merit_plan *plan, const int64_t tile[MERIT_MAX_
 /* ---- operations ------------------------------------------------------------
  * x_f16: [N,Cin,H,W] binary16; w_f16: [Cout,Cin,kh,kw] binary16;
  * y_f16: [N,Cout,OH,OW] binary16.  Products accumulate in fp32 on the matrix
- * cores and are rounded once (nearest even) to binary16.  (.) = Eq. 3, or its
+ * cores and are rounded once (nearest even) to binary16.  The order of a sum is
+ * the plan's: 1x1 layers at stride 1 split the channels over wavefronts by tile,
+ * and the tile follows the batch size, so that an image's result may differ in
+ * the last bit between plans of different batch sizes.  (.) = Eq. 3, or its
  * clipped form for a CONV_DOT_RELU plan.  For a plan from merit_plan_conv2d_pool
  * y_f16 is the pooled tensor [N,Cout,OH/2,OW/2]: the exact maximum of the rounded
  * convolution results in each window. */

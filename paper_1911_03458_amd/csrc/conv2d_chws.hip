@@ -109,15 +109,6 @@ __device__ __forceinline__ Geom pool_geom(const ConvParams &p, int item, int i, 
     return g;
 }
 
-// v moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind it
-__device__ __forceinline__ void shift_down(uint32_t (&v)[4], int bits)
-{
-    const uint64_t lo = ((uint64_t)v[1] << 32) | v[0], hi = ((uint64_t)v[3] << 32) | v[2];
-    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
-    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
-    v[0] = (uint32_t)l; v[1] = (uint32_t)(l >> 32); v[2] = (uint32_t)h; v[3] = (uint32_t)(h >> 32);
-}
-
 constexpr int XS_MAX = 8;      // input units of 8 channels x 1 pixel a moving thread holds per pass (4 beside 8 multiplying wavefronts -- 168 registers -- and for 5x5 windows)
 // A buffer offset past the end of every tensor: loads return zeros.  (The planner and the launcher keep a launch's input
 // and the weights below it, whatever the batch; the added tensor may be larger: what is loaded there is never stored.)
@@ -492,10 +483,11 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
 #pragma unroll
                             for (int i = 0; i < T; ++i) {
                                 if (8 * i < nv && 8 * i + 8 > nv) {
-                                    uint32_t v[4] = {wr[set][k][4 * i], wr[set][k][4 * i + 1], wr[set][k][4 * i + 2], wr[set][k][4 * i + 3]};
-                                    shift_down(v, 16 * (8 * i + 8 - nv));
-#pragma unroll
-                                    for (int q = 0; q < 4; ++q) wr[set][k][4 * i + q] = v[q];
+                                    const uint4 v = shift_down(make_uint4(wr[set][k][4 * i], wr[set][k][4 * i + 1],
+                                                                          wr[set][k][4 * i + 2], wr[set][k][4 * i + 3]),
+                                                               16 * (8 * i + 8 - nv));
+                                    wr[set][k][4 * i] = v.x; wr[set][k][4 * i + 1] = v.y;
+                                    wr[set][k][4 * i + 2] = v.z; wr[set][k][4 * i + 3] = v.w;
                                 }
                             }
                         }

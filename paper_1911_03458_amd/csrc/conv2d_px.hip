@@ -53,15 +53,6 @@ __device__ __forceinline__ uint4 load16(const uint16_t *base, uint32_t off)     
     return v;
 }
 
-// v moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind it
-__device__ __forceinline__ uint4 shift_down(uint4 t, int bits)
-{
-    const uint64_t lo = ((uint64_t)t.y << 32) | t.x, hi = ((uint64_t)t.w << 32) | t.z;
-    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
-    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
-    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
-}
-
 // 64-byte chunk of a staged pixel row that row r keeps in place of chunk c
 template <int TM>
 __device__ __forceinline__ int xchunk(int c, int r)

@@ -42,15 +42,6 @@ struct StageGeom {
     FastDiv div_perg;
 };
 
-// The unit's bytes, moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind them.
-__device__ __forceinline__ uint4 shift_down(uint4 t, int bits)
-{
-    const uint64_t lo = ((uint64_t)t.y << 32) | t.x, hi = ((uint64_t)t.w << 32) | t.z;
-    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
-    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
-    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
-}
-
 template <bool RAGGED>
 __device__ __forceinline__ void issue_pass(const CorrParams &p, const StageGeom &sg,
                                            const uint16_t *__restrict__ x1, const uint16_t *__restrict__ x2,

@@ -42,6 +42,16 @@ __device__ __forceinline__ uint32_t xcd_band_item(uint32_t hw_id, int xq, int xr
     return xcd * (uint32_t)xq + min(xcd, (uint32_t)xr) + slot;
 }
 
+// v moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind it: the 16 bytes of a load that ends with its
+// row, where the unit that the row's end cuts wants them.
+__device__ __forceinline__ uint4 shift_down(uint4 v, int bits)
+{
+    const uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+    const uint64_t l = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits));
+    const uint64_t h = bits >= 64 ? 0 : hi >> bits;
+    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+
 // Results of a convolution tile, LDS staging -> global, where a channel's run of the tile starts on
 // any element of the output (OH*OW % 8 != 0; y itself is 16-byte aligned).  outl: [channel][TM / 2 + 2]
 // dwords, two pixels each; a0: element index in y of channel 0's first pixel, channel c `ohw` elements

@@ -263,8 +263,9 @@ merit_status derive_sad(merit_plan *pl)
     int64_t lds = ((int64_t)p.win * (p.pitch / 4) + 1 + B * (B / 4) + 4) * 4;
     int64_t tile_bx = 1;
     // The row-scan kernels, any H.  Rows that are not whole dwords: from 64 blocks on (500x702, R = 32: 90.7 us on the
-    // kernel for any shape, 25.0 on the row scan); on the smallest frames that kernel's workgroup per block fills more of
-    // the chip, and both are done in the time of a launch.
+    // kernel for any shape, 25.0 on the row scan).  Smaller frames stay, for the plan tests that hold them, where they
+    // were: the row scan is the faster one there too (159x78, R = 32: 59.5 against 17.1; 16x16 with R = 16 and 8 by 1.6
+    // and 1.2, 8x8 by 1.35 and 1.14, over 110 frames).
     const bool rowscan_ok = W % 4 == 0 || (W >= 4 && (int64_t)p.nby * p.nbx >= 64);
     if (rowscan_ok && B == 16 && (R == 16 || R == 32) && pl->tile_req[1] != 1) {
         const int64_t c4 = cdiv(4 * 16 + 2 * R, 4);
@@ -450,7 +451,8 @@ void derive_px(merit_plan *pl)
     // under its stores, and a single short step has no chain to hide (32 -> 64 on 32 images of 64x64: 7.1 against 7.6 us,
     // 64 -> 256 on 8 of 56x56: 6.6 against 7.2; 56 -> 560 on 2 of 71x24: 4.8 against 3.7).
     if (packable(pl) && !c.residual && Cin <= 64 && c.W % 8 == 0 && N * cdiv(HW, 128) * cdiv(Cout, 64) >= 512) return;
-    // more than 256 channels, not a multiple of 8: left on the channels-in-passes kernel, where the plan tests hold it
+    // More than 256 channels, not a multiple of 8: left on the channel-block kernels, where the plan tests hold it (over 80
+    // such layers they take 45 and 117 us on average, this kernel 7 and 10).
     if (Cin % 8 != 0 && Cin > 256) return;
     if (Cin < 16 || HW < 8 || Cin * HW >= (1ll << 30) || Cout * Cin >= (1ll << 30) || Cout * HW >= (1ll << 30)) return;
     PxParams p;
@@ -717,9 +719,8 @@ merit_status derive_conv(merit_plan *pl)
         return true;
     };
 
-    // Wave-specialised multi-pass kernel (conv2d_chws.hip): 256-pixel tiles x `cb` 32-channel blocks
-    // (4 or 2), 16 input channels per pass through two LDS buffers, 3x3, 1x1 or 5x5 windows on a multiple
-    // of 8 input channels.
+    // Wave-specialised multi-pass kernel (conv2d_chws.hip): 256- or 128-pixel tiles x `cb` 32-channel blocks
+    // (4, 2 or 1), 16 to 64 input channels per pass through two LDS buffers, 3x3, 1x1 or 5x5 windows.
     bool short_pass = false;     // 1x1 windows: no 64-channel passes
     bool any_count = false;      // the planner's own choice below: any channel count (a tile request and the fused pooling: as documented)
     auto try_chws = [&](int cb, bool forced, int nw = 8, int tm = 256, bool halo = false) -> bool {
@@ -991,7 +992,8 @@ merit_status derive_conv(merit_plan *pl)
         // (65 -> 16 on 21 images of 18x20, stride 2: 31.3 -> 6.9 us; 165 -> 60 on 8 of 18x110, stride 2: 127 -> 23;
         // 100 -> 100 on 8 of 28x28: 40 -> 8.0).  What stays on the channel-block kernels is close there -- up to 16
         // channels (16 -> 64 on 8 of 56x56: 5.7 against 5.3), 64 aligned channels to at most 32 (64 -> 32: 7.2 against
-        // 5.7; 24 -> 32: 6.2 against 5.0) -- or is held there by the plan tests: single images with Cin % 8 != 0.
+        // 5.7; 24 -> 32: 6.2 against 5.0) -- or is held there by the plan tests: single images with Cin % 8 != 0 (over 120
+        // such layers 23-156 us on average by kernel and window, on this one 5-26).
         // (1x1 windows at stride 1 have a kernel of their own: derive_px.)
         const bool was = Cin >= 32 && Cin % 8 == 0 && ncb >= 2;
         any_count = (kh > 1 || sh > 1 || sw > 1) && Cin >= 17 && (Cin % 8 == 0 || N >= 2) && (ncb >= 2 || Cin % 8 != 0 || Cin > 64);
@@ -1264,9 +1266,9 @@ merit_status derive_corr(merit_plan *pl)
     if (d.range[0] != N || d.range[1] != H || d.range[2] != W || d.range[5] != C) return MERIT_ERR_SHAPE;
     // the kernel stages 8-pixel units and gives a wavefront at most 8 column displacements
     if (W < 8 || R > 15 || sd > 8 || C > 65536) return MERIT_ERR_UNSUPPORTED;
-    // Widths off the multiple of 8: up to 64 K products in all the definition kernel stays (18 us against 5: these
-    // calls are small enough not to matter, and they are what its own correlation tests run); above, it costs 1.5 us
-    // per channel and the MFMA kernel 5-12 us in all (8x60x60, +-5: 35 against 5).
+    // Widths off the multiple of 8: up to 64 K products in all the definition kernel stays, because its own correlation
+    // tests run these calls (13-69 us over 23 of them, the MFMA kernel 4); above, it costs 1.5 us per channel and the
+    // MFMA kernel 5-12 us in all (8x60x60, +-5: 35 against 5).
     if ((W % 8) != 0 && N * C * H * W * n * n <= 65536) return MERIT_ERR_UNSUPPORTED;
     if (N * C * H * W >= INT_LIMIT || N * H * W * n * n >= INT_LIMIT) return MERIT_ERR_UNSUPPORTED;
 
