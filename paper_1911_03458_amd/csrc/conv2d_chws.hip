@@ -130,7 +130,8 @@ constexpr uint32_t OOB = 0x80000000u;
 // RES: a tensor of the output's shape is added to the fp32 sums before the clip and the rounding.
 // RAGGED: Cin % 8 != 0, the last group of 8 channels is not whole (an instance of its own: the selects on every load
 // cost the others 3-10 %; 8-pixel units and the caller's weights only).
-template <int PXB, int CHB, int WM, int WN, int T, int XU, bool PACKED, int NG = 1, bool POOL = false, bool RES = false, bool RAGGED = false>
+// FEW: packed weights on at most four passes (see WREG).
+template <int PXB, int CHB, int WM, int WN, int T, int XU, bool PACKED, int NG = 1, bool POOL = false, bool RES = false, bool RAGGED = false, bool FEW = false>
 __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvParams p, const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ w,
                                                             const uint16_t *res, uint16_t *y)
@@ -148,8 +149,10 @@ __global__ __launch_bounds__((WM * WN + 4) * 64, 1) void merit_conv2d_chws(ConvP
     // both are requested two passes ahead: the passes are shorter than the memory round trip that a copy straight into
     // LDS, started when its buffer is free, takes inside one of them (256 -> 256 on 8x14x14: 11.7 us on the direct copy,
     // 9.7; 512 -> 512 20.2, 16.8).  Shorter units keep the direct copy: they leave no registers for a second pass, and
-    // one pass ahead the detour costs 2-8 % (512 channels on 17x17).
-    constexpr bool WREG = PACKED && TM == 128 && XV;
+    // one pass ahead the detour costs 2-8 % (512 channels on 17x17).  So do layers of up to four passes, which have hardly any
+    // to run ahead of (64 -> 64 on 2x23x64: 5.3 us through registers, 5.0 directly; even at four passes on 64-wide rows, at
+    // six on 16-wide ones).
+    constexpr bool WREG = PACKED && TM == 128 && XV && !FEW;
     constexpr int WP = (WITEMS + 255) / 256;             // fragments per moving thread there
     // Passes on their way in registers: two with those and one unit per thread, else one (on the caller's weights a
     // second one gained nothing: there a pass waits for its load instructions, not for memory).
@@ -852,6 +855,10 @@ hipError_t launch_tile(const ConvParams &p, const void *x, const void *w, const 
         return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, Tv, XUv, false, NG>, p, x, w, res, y, s, grid);    \
     } while (0)
     constexpr bool ONLY5 = PXB == 1 && NG == 1;          // 128-pixel tiles with 16 channels per pass: 5x5 windows only
+    if constexpr (PXB == 1 && NG == 2) {
+        if (packed && T == 9 && xu == 1 && p.nchunks <= 4)
+            return launch_one(merit_conv2d_chws<PXB, CHB, WM, WN, 9, 1, true, NG, false, false, false, true>, p, x, w, res, y, s, grid);
+    }
     if constexpr (NG != 4 && !ONLY5) {
         if (T == 9 && xu == 1) MERIT_CHWS(9, 1);
         if (T == 9 && xu == 2) MERIT_CHWS(9, 2);
