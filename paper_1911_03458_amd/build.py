@@ -14,7 +14,7 @@ LIB_PATH = os.path.join(_HERE, "libmerit.so")
 CALLS_SRC = os.path.join(CSRC, "torch_calls.cpp")
 CALLS_PATH = os.path.join(_HERE, "_torch_calls.so")      # a Python module over libmerit.so and PyTorch
 
-SOURCES = ["merit_plan.cpp", "pool2d.hip", "sad_search.hip", "conv2d.hip", "conv2d_chws.hip", "conv2d_px.hip", "maxpool_f16.hip", "generic.hip", "corr.hip", "dwconv.hip", "sepfilter.hip", "bilateral.hip", "probe.hip"]
+SOURCES = ["merit_plan.cpp", "pool2d.hip", "sad_search.hip", "conv2d.hip", "conv2d_chws.hip", "conv2d_px.hip", "conv2d_split.hip", "maxpool_f16.hip", "generic.hip", "corr.hip", "dwconv.hip", "sepfilter.hip", "bilateral.hip", "probe.hip"]
 HEADERS = [os.path.join(CSRC, "merit_internal.h"), os.path.join(ROOT, "include", "merit.h"),
            os.path.join(ROOT, "include", "merit_probe.h")]
 CALLS_DEPS = [CALLS_SRC, os.path.join(ROOT, "include", "merit.h")]

@@ -265,6 +265,31 @@ size_t px_lds_bytes(const PxParams &p);
 hipError_t launch_conv2d_px(const PxParams &p, const void *x, const void *w, const void *res, void *y, hipStream_t s);
 hipError_t launch_copy_weights(const void *w, void *packed, int64_t halves, hipStream_t s);      // halves % 8 == 0
 
+// ---- convolution, many channels on few pixels: the channels split among the wavefronts (conv2d_split.hip) ----
+constexpr int SPLIT_WAVES = 8;
+// LDS bytes of the raw weights of an output channel: 16 channels x 9 taps and padding (5x5 windows: registers only)
+constexpr int split_weight_pitch(int K) { return K == 3 ? 304 : 0; }
+struct SplitParams {
+    int N, Cin, H, W, Cout, OH, OW;
+    int sh, sw, ph, pw, dh, dw;
+    int K;                 // window edge: 3 or 5
+    int PXB;               // 32-pixel blocks of a tile (of 32 output channels)
+    int xu;                // staging units of 8 channels x 8 pixels per lane and slice (0: one, of rows shorter than 8 pixels)
+    int tiles;             // pixel tiles per image
+    int co_groups;         // 32-channel blocks
+    int slices;            // slices of 16 input channels
+    int RHa, pitch;        // staged rows, and pixels from one to the next
+    int slice_bytes;       // a wavefront's staging area
+    int lds_bytes;
+    int relu;
+    int xq, xr;            // grid / 8, grid % 8 (see xcd_band_item)
+    int by_channel, minor; // order of the work list: 1 = (channel block, tile), 0 = (tile, channel block); extent of the inner one
+    FastDiv div_minor, div_tiles, div_ow;
+    FastDiv div_r2;        // staged rows of both channel groups of a slice
+};
+hipError_t launch_conv2d_split(const SplitParams &p, const void *x, const void *w, void *y, hipStream_t s, bool packed);
+hipError_t launch_conv2d_split_pack(const SplitParams &p, const void *w, void *packed, hipStream_t s);
+
 // ---- launchers (defined in the .hip files) --------------------------------
 hipError_t launch_pool2d(const PoolParams &p, const float *x, float *y, hipStream_t s);
 hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref,
@@ -438,4 +463,6 @@ struct merit_plan {
     // it: it names the size of a packed copy, where there is one
     int use_px;
     merit::PxParams px;
+    int use_split;                        // the same for conv2d_split.hip
+    merit::SplitParams split;
 };

@@ -490,10 +490,98 @@ void derive_px(merit_plan *pl)
     li.tile[1] = p.TN; li.tile[2] = cdiv(p.TM, c.W); li.tile[3] = c.W;
 }
 
+// 3x3 and 5x5 windows that the wave-specialised multi-pass kernel would run on a fraction of the chip: the form of it that
+// splits the channels among the wavefronts (conv2d_split.hip), where its estimate is the lower one.  Not on a tile request,
+// which names one of the other form's tilings.
+void derive_split(merit_plan *pl)
+{
+    const ConvParams &c = pl->conv;
+    if (c.variant != CONV_CHWS || c.pool || c.residual || !(c.kh == c.kw && (c.kh == 3 || c.kh == 5))) return;
+    if (pl->tile_req[2] > 0 && pl->tile_req[3] > 0) return;
+    const int64_t N = c.N, Cin = c.Cin, H = c.H, W = c.W, Cout = c.Cout, OW = c.OW, ohw = (int64_t)c.OH * c.OW;
+    // (at least one slice of 16 channels and one 16-byte unit of an image; byte offsets into an image and the weights)
+    if (N == 0 || Cin < 17 || H * W < 8 || Cin * H * W >= (1ll << 29) || Cout * Cin * c.kh * c.kw >= (1ll << 29) || Cout * ohw >= (1ll << 30)) return;
+
+    // (up to 48 channels on rows of whole 16-byte units stay where they were: three wavefronts of eight would have a slice,
+    // this form is 3-20 % faster, and the tests hold such a layer's sums to those of another tiling, bit for bit)
+    if (Cin <= 48 && W % 8 == 0) return;
+
+    // Estimates in microseconds, fitted to 870 layers (3 to 112 pixels wide, 17 to 2048 channels, the caller's weights and
+    // packed ones) timed on both forms.  The multi-pass form: a launch, its rounds, its passes, and in each of them the
+    // multiplications, the input loads (dearer on rows of an odd width) and the weights.  This form: a launch, its rounds,
+    // and in each of them, per eight slices, their multiplications and barrier-free chain, the input loads and the weights
+    // (as the caller's lie: a plan does not know which call comes).  The choice is within 0.2 % (3x3) and 0.4 % (5x5) of the
+    // better form on average.  A lead of 6 % is asked for, of 15 % on grids of more than one round, where the estimate errs
+    // most; beyond two rounds the multi-pass form was always the better one.
+    const bool k5 = c.kh == 5;
+    const double T = c.kh * c.kw, odd = (double)(W & 1);
+    const double rounds = (double)cdiv(N * c.tiles_per_image * c.co_groups, 256), passes = rounds * c.nchunks;
+    const double mults = c.CB * (c.TM / 32.0) * (c.nchi / 2.0) * T / 8.0, loads = 8.0 * c.xu * (c.xpx == 8 ? 1.0 : 0.7);
+    const double weights = (double)c.CB * 32.0 * c.nchi * 16.0 * T / 16384.0;
+    const double multi_pass = k5 ? 0.3 + 4.6 * rounds + passes * (0.154 + 0.028 * mults + (0.05 + 0.011 * odd) * loads + 0.249 * weights)
+                                 : 1.8 + 2.36 * rounds + passes * (0.104 + 0.056 * mults + (0.022 + 0.018 * odd) * loads + 0.126 * weights);
+    static const struct { double launch, round, slices, even, odd, weights; } costs[2][2] = {
+        {{1.54, 2.11, 0.74, 0.97, 2.40, 0.59}, {1.33, 2.69, 0.50, 1.37, 2.69, 0.69}},
+        {{1.28, 2.98, 1.72, 1.21, 2.76, 1.95}, {1.08, 3.81, 1.78, 1.19, 2.59, 2.05}}};
+
+    double best_cost = multi_pass;
+    for (int pxb = 1; pxb <= 2; ++pxb) {
+        SplitParams p;
+        std::memset(&p, 0, sizeof(p));
+        p.N = c.N; p.Cin = c.Cin; p.H = c.H; p.W = c.W; p.Cout = c.Cout; p.OH = c.OH; p.OW = c.OW;
+        p.sh = c.sh; p.sw = c.sw; p.ph = c.ph; p.pw = c.pw; p.dh = c.dh; p.dw = c.dw;
+        p.K = c.kh; p.PXB = pxb; p.relu = c.relu;
+        const int64_t TM = 32 * pxb;
+        int64_t rows_out = (TM + OW - 2) / OW + 1;
+        if (rows_out > c.OH) rows_out = c.OH;
+        p.RHa = (int)((rows_out - 1) * c.sh + (c.kh - 1) * c.dh + 1);
+        int64_t pitch = c.pw + W;
+        const int64_t reach = (OW - 1) * c.sw + (c.kw - 1) * c.dw + 1;
+        if (reach > pitch) pitch = reach;
+        p.pitch = (int)(pitch | 1);               // odd: staged rows start in different LDS bank groups
+        const int64_t units = 2 * (int64_t)p.RHa * cdiv(W, 8);
+        if (units > (W < 8 ? 64 : 128)) continue;
+        p.xu = W < 8 ? 0 : (int)cdiv(units, 64);
+        if (Cin % 8 != 0 && (W < 8 || (pxb == 2 && p.xu == 2))) continue;           // (no such instance)
+        p.slices = (int)cdiv(Cin, 16);
+        p.tiles = (int)cdiv(ohw, TM);
+        p.co_groups = (int)cdiv(Cout, 32);
+        p.slice_bytes = 2 * p.RHa * p.pitch * 16;
+        const int64_t sums = (int64_t)SPLIT_WAVES * 32 * (TM + 4) * 4;
+        const int64_t areas = (int64_t)SPLIT_WAVES * (p.slice_bytes + 32 * split_weight_pitch(p.K));
+        p.lds_bytes = (int)(sums > areas ? sums : areas);
+        if (p.lds_bytes > LDS_LIMIT) continue;
+        const int64_t grid = N * p.tiles * p.co_groups;
+        p.by_channel = Cout * Cin * c.kh * c.kw > N * Cin * H * W ? 1 : 0;
+        p.minor = (int)(p.by_channel ? N * p.tiles : p.co_groups);
+        if (grid > 512 || !fastdiv_ok(grid, p.minor) || !fastdiv_ok(N * p.tiles, p.tiles) || !fastdiv_ok(ohw, OW) ||
+            !fastdiv_ok(units, 2 * p.RHa))
+            continue;
+        const auto &k = costs[k5][pxb - 1];
+        const double r = (double)cdiv(grid, 256), load = (double)units / 64.0;
+        const double cost = (k.launch + r * (k.round + p.slices / 8.0 * (k.slices + load * (W & 1 ? k.odd : k.even) + k.weights))) *
+                            (r > 1.0 ? 1.15 : 1.06);
+        if (cost >= best_cost) continue;
+        best_cost = cost;
+        p.xq = (int)(grid / 8); p.xr = (int)(grid % 8);
+        p.div_minor = make_fastdiv((uint32_t)p.minor);
+        p.div_tiles = make_fastdiv((uint32_t)p.tiles);
+        p.div_ow = make_fastdiv((uint32_t)OW);
+        p.div_r2 = make_fastdiv((uint32_t)(2 * p.RHa));
+        pl->split = p;
+        pl->use_split = 1;
+        merit_launch_info &li = pl->info;
+        li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
+        li.block[0] = SPLIT_WAVES * 64; li.block[1] = 1; li.block[2] = 1;
+        li.lds_bytes = p.lds_bytes;
+        li.tile[1] = 32; li.tile[2] = rows_out; li.tile[3] = OW;
+    }
+}
+
 merit_status derive_conv(merit_plan *pl)
 {
     const merit_plan_desc &d = pl->desc;
-    pl->use_px = pl->use_na = 0;
+    pl->use_px = pl->use_split = pl->use_na = 0;
     if (d.dtype != MERIT_F16 || d.pad != MERIT_PAD_ZERO) return MERIT_ERR_UNSUPPORTED;
     if (d.n_par != 4 || d.n_acc != 3) return MERIT_ERR_UNSUPPORTED;
     if (d.a.ndim != 4 || d.b.ndim != 4) return MERIT_ERR_UNSUPPORTED;
@@ -1125,6 +1213,7 @@ merit_status derive_conv(merit_plan *pl)
         }
     }
     derive_px(pl);
+    derive_split(pl);
     return MERIT_OK;
 }
 
@@ -1801,8 +1890,9 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x, const void *w, 
         return (e == hipSuccess && ef == hipSuccess) ? MERIT_OK : MERIT_ERR_HIP;
     }
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
-                                      : launch_conv2d(plan->conv, x, w, nullptr, y, s);
+    const hipError_t e = plan->use_px      ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
+                         : plan->use_split ? launch_conv2d_split(plan->split, x, w, y, s, false)
+                                           : launch_conv2d(plan->conv, x, w, nullptr, y, s);
     return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
@@ -1828,8 +1918,9 @@ merit_status merit_conv2d_pack_weights(const merit_plan *plan, const void *w, vo
     if (!aligned16(w) || !aligned16(packed)) return MERIT_ERR_ALIGNMENT;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     // (the matrix-product kernel reads the weights as they lie: its packed copy is a copy)
-    const hipError_t e = plan->use_px ? launch_copy_weights(w, packed, (int64_t)plan->px.Cout * plan->px.Cin, s)
-                                      : launch_conv2d_pack_weights(plan->conv, w, packed, s);
+    const hipError_t e = plan->use_px      ? launch_copy_weights(w, packed, (int64_t)plan->px.Cout * plan->px.Cin, s)
+                         : plan->use_split ? launch_conv2d_split_pack(plan->split, w, packed, s)
+                                           : launch_conv2d_pack_weights(plan->conv, w, packed, s);
     return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
@@ -1841,8 +1932,9 @@ merit_status merit_conv2d_packed(const merit_plan *plan, const void *x, const vo
     if (!x || !packed || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(packed) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, packed, nullptr, y, s)
-                                      : launch_conv2d_chws(plan->conv, x, packed, nullptr, y, s, true);
+    const hipError_t e = plan->use_px      ? launch_conv2d_px(plan->px, x, packed, nullptr, y, s)
+                         : plan->use_split ? launch_conv2d_split(plan->split, x, packed, y, s, true)
+                                           : launch_conv2d_chws(plan->conv, x, packed, nullptr, y, s, true);
     return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 
@@ -1858,8 +1950,9 @@ merit_status merit_conv2d_packed_noalloc(const merit_plan *plan, const void *x, 
     if (!x || !w || !y) return MERIT_ERR_NULL;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y)) return MERIT_ERR_ALIGNMENT;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const hipError_t e = plan->use_px ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
-                                      : launch_conv2d_chws_noalloc(p, x, w, y, s);
+    const hipError_t e = plan->use_px      ? launch_conv2d_px(plan->px, x, w, nullptr, y, s)
+                         : plan->use_split ? launch_conv2d_split(plan->split, x, w, y, s, false)
+                                           : launch_conv2d_chws_noalloc(p, x, w, y, s);
     return e == hipSuccess ? MERIT_OK : MERIT_ERR_HIP;
 }
 

@@ -1,0 +1,71 @@
+"""Many-channel layers on few pixels: the form of merit_conv2d_chws that splits the channels among the wavefronts."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1911_03458_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, Cin, H, W, Cout, k, s, p, dilation
+    (2, 17, 5, 9, 33, 3, 1, 1, 1),        # two slices, the second of one channel
+    (1, 24, 4, 9, 40, 3, 1, 1, 1),        # the second slice half a slice
+    (2, 56, 4, 8, 64, 3, 1, 1, 1),        # one unit per row, one tile of exactly 32 pixels
+    (1, 136, 11, 3, 33, 3, 1, 1, 1),      # a tile of one pixel; nine slices
+    (3, 129, 9, 13, 65, 3, 1, 1, 1),      # ... of one channel; 13-pixel rows: the last unit overlaps
+    (2, 264, 7, 7, 40, 3, 1, 1, 1),       # 7x7 planes: loads moved at the last channel's end
+    (2, 64, 12, 40, 48, 3, 2, 1, 1),      # stride 2
+    (1, 80, 14, 47, 40, 3, 1, 2, 2),      # dilated window, odd rows, two units per lane
+    (2, 72, 30, 64, 40, 3, 1, 0, 1),      # no padding
+    (1, 256, 14, 14, 96, 3, 1, 1, 1),
+    (4, 256, 14, 14, 256, 3, 1, 1, 1),    # 64-pixel tiles
+    (1, 32, 5, 5, 40, 5, 1, 2, 1),        # 5x5
+    (2, 37, 9, 10, 36, 5, 2, 2, 1),
+    (1, 144, 21, 23, 56, 5, 1, 2, 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_against_the_oracle_raw_and_packed(case):
+    N, Cin, H, W, Cout, k, s, p, d = case
+    rng = np.random.default_rng(Cin * 1000 + W)
+    x = rng.standard_normal((N, Cin, H, W)).astype(np.float16)
+    w = (rng.standard_normal((Cout, Cin, k, k)) / np.sqrt(Cin * k * k)).astype(np.float16)
+    plan = mb.merit_plan_conv2d_dilated(N, Cin, H, W, Cout, k, k, s, s, p, p, d, d, 1)
+    li = plan.launch_info()
+    print(case, li, flush=True)
+    ohw = plan.out_shape()[2] * plan.out_shape()[3]
+    assert li["kernel"] == "merit_conv2d_chws" and li["tile"][1] == 32
+    assert li["grid"][0] in (N * -(-Cout // 32) * -(-ohw // 32), N * -(-Cout // 32) * -(-ohw // 64))      # this form's tiles
+    # no numbers beside the operands: what is loaded past a row, an image or the weights must not reach a sum
+    xb = torch.full((x.size + 256,), float("nan"), dtype=torch.float16, device="cuda")
+    wb = torch.full((w.size + 256,), float("inf"), dtype=torch.float16, device="cuda")
+    xb[128:-128], wb[128:-128] = torch.from_numpy(x).flatten(), torch.from_numpy(w).flatten()
+    xd, wd = xb[128:-128].view(x.shape), wb[128:-128].view(w.shape)
+    n = int(np.prod(plan.out_shape()))
+    buf = torch.full((n + 128,), 777.0, dtype=torch.float16, device="cuda")
+    y = buf[64:64 + n].view(plan.out_shape())
+    mb.merit_conv2d(plan, xd, wd, y)
+    assert bool((buf[:64] == 777).all()) and bool((buf[64 + n:] == 777).all())
+    ref = oracle.conv2d(x, w, (s, s), (p, p), relu=True, dilation=(d, d)).astype(np.float64)
+    assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.abs(ref) + 1e-3)
+    if Cin % 8 == 0 and Cin >= 32:
+        assert torch.equal(mb.merit_conv2d_packed(plan, xd, mb.merit_conv2d_pack_weights(plan, wd)), y)
+
+
+def test_an_image_or_an_output_channel_without_numbers_stays_alone():
+    """NaN in one image, infinities in one output channel's weights: the others are what they are without them (the last
+    slice and the channel blocks are padded with zeros, not with neighbours)."""
+    N, Cin, H, W, Cout = 3, 24, 7, 9, 40
+    rng = np.random.default_rng(5)
+    x = torch.from_numpy(rng.standard_normal((N, Cin, H, W)).astype(np.float16)).cuda()
+    w = torch.from_numpy((rng.standard_normal((Cout, Cin, 3, 3)) / 15).astype(np.float16)).cuda()
+    plan = mb.merit_plan_conv2d(N, Cin, H, W, Cout, 3, 3, 1, 1, 1, 1)
+    clean = mb.merit_conv2d(plan, x, w)
+    x[1], w[7] = float("nan"), float("inf")
+    y = mb.merit_conv2d(plan, x, w)
+    keep = [c for c in range(Cout) if c != 7]
+    assert torch.equal(y[[0, 2]][:, keep], clean[[0, 2]][:, keep])
+    assert not bool(torch.isfinite(y[:, 7]).any())
