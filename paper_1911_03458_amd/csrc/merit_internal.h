@@ -180,6 +180,19 @@ struct SadParams {
     FastDiv div_nbx;
 };
 
+// dwords of a staged row there: whole 16-byte units, and one dword past the last pixel
+constexpr int sad_rowscan16_pitch4(int R, int bpw) { return (16 * bpw + 2 * R) / 4 + 4; }
+constexpr int SAD_LIST = 96;          // candidates a wavefront evaluates one by one at most
+// halves of a row of its 4x4 sums (even)
+constexpr int sad_rowscan16_cols(int R, int bpw) { return (16 * (bpw - 1) + 2 * R + 1 + 12 + 1) / 2 * 2; }
+// LDS of the elimination kernel: the window's bytes, its 4x4 sums, the wavefronts' results
+inline size_t sad_rowscan16_lds(const SadParams &p)
+{
+    const size_t rows = 16 + 2 * (size_t)p.R, cols = (size_t)sad_rowscan16_cols(p.R, p.bpw);
+    const size_t waves = p.bpw == 4 ? 8 : 4;
+    return (rows * (size_t)(p.pitch / 4) + (rows - 3) * cols / 2 + 3 * waves + (size_t)p.bpw * 65) * 4 + waves * SAD_LIST * 2;
+}
+
 // ---- convolution -----------------------------------------------------------
 enum ConvVariant { CONV_PLANAR_SMALLC = 0, CONV_CHBLOCK = 1, CONV_DIRECT = 2, CONV_CHWS = 3 };
 

@@ -81,6 +81,48 @@ __device__ __forceinline__ void stage_window(const SadParams &p, const uint8_t *
     }
 }
 
+// The same for frames of 16 and more columns, 16 pixels a load and all of a thread's loads in flight before the first is
+// written (one by one they were ten trips to memory in a row).  A load that crosses an edge of its row is moved inside it,
+// its pixels moved back and the edge's pixel repeated beside them.  PITCH4: dwords of a staged row (a multiple of 4).
+template <int ROWS, int COLS16, int PITCH4, int NTHREADS>
+__device__ __forceinline__ void stage_window16(const SadParams &p, const uint8_t *__restrict__ ref, uint32_t *win32, int gy0,
+                                               int gx0, int tid)
+{
+    constexpr int U = ROWS * COLS16, NU = (U + NTHREADS - 1) / NTHREADS;
+    static_assert(PITCH4 % 4 == 0 && PITCH4 >= 4 * COLS16, "16-byte rows");
+    uint4 v[NU];
+    int moved[NU];                                                 // pixels by which the load was moved right
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        const int u = min(tid + NTHREADS * k, U - 1);
+        const int wy = u / COLS16, gx = gx0 + 16 * (u - wy * COLS16);
+        const int at = min(max(gx, 0), p.W - 16);
+        moved[k] = at - gx;
+        __builtin_memcpy(&v[k], ref + (size_t)min(max(gy0 + wy, 0), p.H - 1) * p.W + at, 16);
+    }
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        if (moved[k] != 0) {
+            const int n = min(abs(moved[k]), 16);
+            uint64_t lo = ((uint64_t)v[k].y << 32) | v[k].x, hi = ((uint64_t)v[k].w << 32) | v[k].z;
+            if (moved[k] > 0) {                                    // past the left edge: up by n, the first pixel below
+                const uint64_t e = (lo & 0xff) * 0x0101010101010101ull;
+                const uint64_t l = n >= 8 ? e : (lo << (8 * n)) | (e >> (64 - 8 * n));
+                const uint64_t h = n >= 16 ? e : n > 8 ? (lo << (8 * n - 64)) | (e >> (128 - 8 * n)) : n == 8 ? lo : (hi << (8 * n)) | (lo >> (64 - 8 * n));
+                lo = l; hi = h;
+            } else {                                               // past the right edge: down by n, the last pixel above
+                const uint64_t e = (hi >> 56) * 0x0101010101010101ull;
+                const uint64_t h = n >= 8 ? e : (hi >> (8 * n)) | (e << (64 - 8 * n));
+                const uint64_t l = n >= 16 ? e : n > 8 ? (hi >> (8 * n - 64)) | (e << (128 - 8 * n)) : n == 8 ? hi : (lo >> (8 * n)) | (hi << (64 - 8 * n));
+                lo = l; hi = h;
+            }
+            v[k] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+        }
+        const int u = tid + NTHREADS * k;
+        if (U % NTHREADS == 0 || u < U) *reinterpret_cast<uint4 *>(win32 + u / COLS16 * PITCH4 + 4 * (u % COLS16)) = v[k];
+    }
+}
+
 // Pixels x .. x + 3 of a row of W >= 4, those past its end repeating the last one, from one load on any byte boundary.
 __device__ __forceinline__ uint32_t row_dword(const uint8_t *__restrict__ row, int x, int W)
 {
@@ -167,23 +209,35 @@ __global__ __launch_bounds__(256) void merit_sad_generic(SadParams p, const uint
 }
 
 // ---------------------------------------------------------------------------
-// Row-scan kernel for 16x16 blocks and a compile-time search range R >= 8.
+// Row-scan kernel for 16x16 blocks, R = 32 or 16: candidates are eliminated by a lower bound first.
 //
-// A workgroup stages the joint search window of four horizontally adjacent
-// blocks ((16+2R) rows x (64+2R) bytes); each of its four wavefronts owns one
-// block.  Lane l of a wavefront owns the column of candidates dx = l - R (all
-// dy).  The current block sits in 64 wave-uniform registers.  The wavefront
-// walks the window rows top to bottom; for window row r a lane byte-aligns its
-// 16 reference pixels once (4 x v_alignbyte) and adds them into the partial
-// SADs of the (up to) sixteen candidates dy = r - i that use this row as block
-// row i (4 x v_sad_u8 each), so a reference row is fetched and aligned once
-// for sixteen uses.  Sixteen accumulators rotate: candidate dy completes at row
-// dy + 15 and its slot restarts for dy + 16.  A lane keeps its best (sad, dy)
-// as one packed key; at the end keys are widened to (sad, raster index) and
-// reduced across the wavefront with DPP.
-// The 2R+1 columns do not fill whole wavefronts: what is left after the full
-// 64-column chunks is either run as one more (partly idle) chunk or, when it is
-// narrow, one candidate per lane.
+// Bound by the vector ALU: the full scan is 64 v_sad_u8 a candidate, 56 us of them on a full-HD frame.  Most candidates
+// need not be scanned: the sixteen 4x4 sums of a block and of its candidate differ by no more than the pixels do (the
+// triangle inequality; multilevel successive elimination, Gao, Duanmu and Zou 2000), and compare in eight v_sad_u16.
+//   1. A workgroup (four adjacent blocks, two wavefronts each) stages the joint search window in LDS, and from it the 4x4
+//      sums at every position.
+//   2. Lane l owns the candidates dx = l - R.  It walks the rows of sums; a row is fetched once for the four candidates
+//      whose block rows it holds.  All bounds of the column stay in registers.
+//   3. The candidate with the lowest bound is evaluated, a dword per lane; then every candidate whose bound is not above
+//      the best sum so far (three of 4225, at the median, on a moving scene with sensor noise).  The key (sum, raster
+//      index) decides ties as the full scan does: the result is the same for any input.
+//   4. Blocks that this cannot help are scanned in full: those whose pixels differ from their 4x4 means by more than
+//      the means do from the block's (flat or noisy ones, recognised before anything is built), and those with more
+//      candidates left than a tenth of the scan's time.
+// The full scan: the wavefront walks the window rows top to bottom; for window row r a lane byte-aligns its 16 reference
+// pixels once (4 x v_alignbyte) and adds them into the partial sums of the (up to) sixteen candidates dy = r - i that
+// use this row as block row i (4 x v_sad_u8 each).  Sixteen accumulators rotate: candidate dy completes at row dy + 15
+// and its slot restarts for dy + 16.
+// The 65th column at R = 32: its bounds one candidate per lane, its sums sixteen lanes to a candidate.
+// BPW: blocks per workgroup: four, the rows of a block's candidates split between two wavefronts, or one, split among four.
+// Workgroups go round-robin to the XCDs, not in bands of block rows: a band of sky or water would be the whole work of
+// one of them (1080x1920: 77 us in bands, 53).
+//
+// us a launch, R = 32, full scan (one wavefront a block, in a kernel of its own) -> this: moving scenes with sensor noise,
+// 1080x1920 75.5 -> 52.5, 720x1280 41.5 -> 28.3, 480x640 24.4 -> 15.0, 120x160 16.9 -> 8.9; two unrelated scenes of that
+// kind 76.8 -> 68.5; a still picture 76 -> 47; white noise, where every block is scanned, 75.9 -> 79.4 (480x640: 24.8 ->
+// 17.5).  With every block decided by its bounds a full-HD frame takes 27 us; the rest is the scans of a sixth of the
+// blocks, which come in clusters and are dealt to the compute units by position.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void load_aligned16(const uint32_t *rowp, uint32_t sh, uint32_t (&r)[4])
 {
@@ -194,195 +248,312 @@ __device__ __forceinline__ void load_aligned16(const uint32_t *rowp, uint32_t sh
     r[3] = __builtin_amdgcn_alignbyte(d4, d3, sh);
 }
 
-// ANY: rows of any width; without it W % 4 == 0, which saves the condition (1080x1920, R = 32: 75.1 us against 75.5).
-template <int R, bool ANY>
-__global__ __launch_bounds__(256) void merit_sad_rowscan16(SadParams p, const uint8_t *__restrict__ cur,
-                                                          const uint8_t *__restrict__ ref,
-                                                          int32_t *__restrict__ sad, int32_t *__restrict__ mv)
+// the sum over a wavefront's lanes, the same for all
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {
-    static_assert(R >= 8 && R <= 63, "steady state needs 2R >= 15");
+    v = group_sum_u32<16>(v);                                                                     // lane 15 of every row
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);               // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);               // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+
+// Row (lane % 16) of the block of which every lane holds a dword (row lane / 4).
+__device__ __forceinline__ void rows_of_lanes(uint32_t cl, int lane, uint32_t (&crow)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) crow[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((4 * (lane & 15) + j) * 4, (int)cl);
+}
+
+// The full scan of ND candidate rows from d0 on of block wb, whose pixels are `cl` (four per lane): the lowest key, the
+// same for all lanes.
+template <int R, int ND, int PITCH4>
+__device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl, int wb, int d0, int lane)
+{
+    constexpr int N = 2 * R + 1, NCOL = N < 64 ? N : 64, NLEFT = N - NCOL;
+    // (a value to the compiler: with offsets that it knows it fetches the rows of all steps first, into registers that are
+    // not there)
+    int pitch = PITCH4;
+    asm("" : "+s"(pitch));
+    uint32_t c[16][4];                                             // the current block, wave-uniform
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[i][j] = (uint32_t)__builtin_amdgcn_readlane((int)cl, 4 * i + j);
+    const int o = 16 * wb + min(lane, NCOL - 1);                   // idle lanes repeat the last column
+    const uint32_t sh = (uint32_t)(o & 3);
+    const uint32_t *base = lds32 + d0 * pitch + (o >> 2);
+    uint32_t acc[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc[k] = 0;
+    uint32_t lbest = 0xffffffffu;                                  // (sum << 7) | row
+
+    // one window row: block rows i in [ilo, ihi] accumulate into slot (rot - i) & 15;
+    // then candidate `fin` (if >= 0), which sits in slot (rot + 1) & 15, is complete
+    auto step = [&](const uint32_t *rowp, int ilo, int ihi, int rot, int fin) __attribute__((always_inline)) {
+        uint32_t r4[4];
+        load_aligned16(rowp, sh, r4);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (i < ilo || i > ihi) continue;
+            const int slot = (rot - i) & 15;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[slot] = __builtin_amdgcn_sad_u8(c[i][j], r4[j], acc[slot]);
+        }
+        if (fin >= 0) {
+            const int slot = (rot + 1) & 15;
+            const uint32_t key = (acc[slot] << 7) | (uint32_t)fin;
+            lbest = key < lbest ? key : lbest;
+            acc[slot] = 0;
+        }
+    };
+    if constexpr (ND < 32) {
+#pragma unroll
+        for (int r = 0; r < ND + 15; ++r) step(base + r * pitch, max(0, r - ND + 1), min(15, r), r & 15, r - 15);
+    } else {
+        constexpr int NS = ND - 15, NSB = NS / 16, NSR = NS % 16;  // rows 15 .. ND - 1 use all 16 block rows
+#pragma unroll
+        for (int r = 0; r < 15; ++r) step(base + r * pitch, 0, r, r, -1);
+#pragma unroll 1
+        for (int k = 0; k < NSB; ++k) {
+            const uint32_t *rp = base + (15 + 16 * k) * pitch;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) step(rp + j * pitch, 0, 15, (15 + j) & 15, 16 * k + j);
+        }
+#pragma unroll
+        for (int j = 0; j < NSR; ++j)
+            step(base + (15 + 16 * NSB + j) * pitch, 0, 15, (15 + j) & 15, 16 * NSB + j);
+#pragma unroll
+        for (int e = 1; e <= 15; ++e)
+            step(base + (ND - 1 + e) * pitch, e, 15, (ND - 1 + e) & 15, ND - 1 + e - 15);
+    }
+    uint32_t key = lane < NCOL ? ((lbest >> 7) << KEY_SHIFT) | ((uint32_t)(d0 + (int)(lbest & 127u)) * N + (uint32_t)lane) : 0xffffffffu;
+    if (NLEFT > 0 && pitch != 0) {                                 // the last column: sixteen lanes to a candidate, a row each
+        uint32_t crow[4];
+        rows_of_lanes(cl, lane, crow);
+        const int ol = 16 * wb + NCOL;
+#pragma unroll 1
+        for (int i = 0; i < ND; i += 4) {
+            const int dy = d0 + min(i + (lane >> 4), ND - 1);
+            uint32_t r4[4], a = 0;
+            load_aligned16(lds32 + (dy + (lane & 15)) * pitch + (ol >> 2), (uint32_t)(ol & 3), r4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(crow[j], r4[j], a);
+            a = (group_sum_u32<16>(a) << KEY_SHIFT) | (uint32_t)(dy * N + NCOL);
+            if ((lane & 15) == 15) key = a < key ? a : key;        // (whole in the last lane of the sixteen)
+        }
+    }
+    return wave_min_u32(key);
+}
+
+template <int R, int BPW>
+__global__ __launch_bounds__(BPW == 4 ? 512 : 256, R == 32 ? 8 : 4) void merit_sad_rowscan16(SadParams p, const uint8_t *__restrict__ cur,
+                                                                             const uint8_t *__restrict__ ref,
+                                                                             int32_t *__restrict__ sad, int32_t *__restrict__ mv)
+{
+    static_assert(BPW == 1 || BPW == 4, "blocks per workgroup");
     constexpr int N = 2 * R + 1, ROWS = 16 + 2 * R;
-    constexpr int NLEFT0 = N % 64;
-    constexpr bool LEFT_AS_CHUNK = NLEFT0 * N > 640;
-    constexpr int NCHUNK = N / 64 + ((LEFT_AS_CHUNK && NLEFT0) ? 1 : 0);
-    constexpr int NLEFT = LEFT_AS_CHUNK ? 0 : NLEFT0;
-    constexpr int NS = 2 * R - 14, NSB = NS / 16, NSR = NS % 16;   // rows 15..2R use all 16 block rows
+    constexpr int WPB = BPW == 1 ? 4 : 2, NW = BPW * WPB, NT = 64 * NW;           // wavefronts per block, per workgroup
+    constexpr int ND = (N + WPB - 1) / WPB;                        // candidate rows per wavefront
+    constexpr int NCOL = N < 64 ? N : 64, NLEFT = N - NCOL;        // candidate columns that are lanes; the rest
+    static_assert(N >= 16 && NLEFT <= 1 && ND <= 64, "R = 8 .. 32");
+    constexpr int SROWS = ROWS - 3, SCOLS = sad_rowscan16_cols(R, BPW);            // 4x4 sums: rows, halves of a row
+    constexpr int NSEG = NT / SCOLS, SEG = (SROWS + NSEG - 1) / NSEG;             // rows per thread when they are built
+    constexpr int MOST = SAD_LIST;                                 // candidates worth evaluating one by one
+    constexpr int pitch4 = sad_rowscan16_pitch4(R, BPW);
 
     extern __shared__ __align__(16) uint32_t lds32[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int pitch4 = p.pitch >> 2;
-    const uint32_t g = xcd_band_item(blockIdx.x, p.xq, p.xr);     // a band of block rows per XCD
-    const int by = (int)(g / (uint32_t)p.groups_x);
-    const int bx0 = (int)(g - (uint32_t)by * p.groups_x) * 4;
+    const int wb = wv / WPB, part = wv % WPB;                      // block inside the workgroup, share of its candidates
+    uint16_t *sums = reinterpret_cast<uint16_t *>(lds32 + ROWS * pitch4);         // [SROWS][SCOLS]
+    uint32_t *red = lds32 + ROWS * pitch4 + SROWS * SCOLS / 2;     // [2][NW]
+    uint32_t *result = red + 2 * NW;                               // [BPW] keys
+    uint16_t *list = reinterpret_cast<uint16_t *>(result + BPW) + wv * MOST;      // this wavefront's [MOST]
+    const int by = (int)(blockIdx.x / (uint32_t)p.groups_x);
+    const int bx0 = (int)(blockIdx.x - (uint32_t)by * p.groups_x) * BPW;
+    const int bx = min(bx0 + wb, p.nbx - 1);                       // (ragged last group: the last block again, not stored)
 
-    stage_window(p, ref, lds32, by * 16 - R, bx0 * 16 - R, ROWS, pitch4 - 1, p.div_win4, pitch4, tid, 256);
+    // the current block, four pixels per lane: row lane / 4, columns 4 (lane % 4) .. + 3; pixels past the frame's edge
+    // repeat the edge
+    const uint32_t cl = row_dword(cur + (size_t)min(by * 16 + (lane >> 2), p.H - 1) * p.W, bx * 16 + 4 * (lane & 3), p.W);
+    if (p.W >= 16) stage_window16<ROWS, (16 * BPW + 2 * R) / 16, pitch4, NT>(p, ref, lds32, by * 16 - R, bx0 * 16 - R, tid);
+    else stage_window(p, ref, lds32, by * 16 - R, bx0 * 16 - R, ROWS, (16 * BPW + 2 * R) / 4, p.div_win4, pitch4, tid, NT);
+
+    // its 4x4 sums: the rows of a 4x4 are lanes 4 apart
+    uint32_t s4 = __builtin_amdgcn_sad_u8(cl, 0, 0);
+    s4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s4, 0x124, 0xf, 0xf, true);          // row_ror:4
+    s4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s4, 0x128, 0xf, 0xf, true);          // row_ror:8
+    // (means rounded down; four lanes hold each 4x4 sum)
+    const uint32_t mean = wave_sum_u32(s4) >> 6;                   // of the 4x4 sums
+    const uint32_t coarse = wave_sum_u32(s4 > mean ? s4 - mean : mean - s4) >> 2;
+    const uint32_t fine = wave_sum_u32(__builtin_amdgcn_sad_u8(cl, (s4 >> 4) * 0x01010101u, 0));
+    const bool bounds = coarse >= fine;
+    if (lane == 0) red[wv] = bounds ? 1u : 0u;
+    if (tid < BPW) result[tid] = 0xffffffffu;
     __syncthreads();
-    const int bx = bx0 + wv;
-    if (bx >= p.nbx) return;                       // ragged last group (no barrier follows)
 
-    // current block: wave-uniform loads
-    uint32_t c[16][4];
-    {
-        // rows past the last one (H % 16 != 0) repeat it; dwords past the end of a row
-        // (W % 16 != 0, W % 4 == 0) are four copies of its last pixel
-        const uint32_t *cp = reinterpret_cast<const uint32_t *>(cur);
-        const int W4 = p.W >> 2;
-        if ((p.W & 15) == 0) {                       // whole blocks per row: the plain loads
+    const int d0 = min(part * ND, N - ND);                         // first candidate row (the last share overlaps)
+    uint32_t best = 0xffffffffu;                                   // wave-uniform (sum << 14) | raster index
+    bool scan = !bounds;
+    uint32_t any_bounds = 0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int row = min(by * 16 + i, p.H - 1);
+    for (int i = 0; i < NW; i += WPB) any_bounds |= red[i];
+    if (any_bounds != 0) {
+        const int seg = tid / SCOLS, x = tid - seg * SCOLS;
+        if (seg < NSEG) {
+            const uint32_t sh = (uint32_t)(x & 3);
+            const int y0 = min(seg * SEG, SROWS - SEG);            // (the last segment overlaps the one before: the same values)
+            const uint32_t *src = lds32 + y0 * pitch4 + (x >> 2);
+            uint16_t *dst = sums + y0 * SCOLS + x;
+            auto row4 = [&](const uint32_t *r) __attribute__((always_inline)) {
+                return __builtin_amdgcn_sad_u8(__builtin_amdgcn_alignbyte(r[1], r[0], sh), 0, 0);
+            };
+            uint32_t h[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) c[i][j] = cp[row * W4 + bx * 4 + j];
+            for (int i = 0; i < 3; ++i) h[i] = row4(src + i * pitch4);
+            uint32_t s = h[0] + h[1] + h[2];
+#pragma unroll
+            for (int y = 0; y < SEG; ++y) {
+                h[3] = row4(src + (y + 3) * pitch4);
+                s += h[3];
+                dst[y * SCOLS] = (uint16_t)s;
+                s -= h[0];
+                h[0] = h[1]; h[1] = h[2]; h[2] = h[3];
             }
-        } else if (ANY && (p.W & 3) != 0) {          // rows on any byte boundary: a dword per lane, then wave-uniform
-            const int row = min(by * 16 + (lane >> 2), p.H - 1);
-            const uint32_t v = row_dword(cur + (size_t)row * p.W, bx * 16 + 4 * (lane & 3), p.W);
+        }
+        __syncthreads();
+
+        uint32_t lb[ND], lb_left = 0xffffffffu, low = 0xffffffffu;
+        if (bounds) {
+            uint32_t sp[4][2];                                     // the block's sums, in the same pairs, wave-uniform
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
+            for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) c[i][j] = (uint32_t)__builtin_amdgcn_readlane((int)v, 4 * i + j);
-        } else {
+                for (int j = 0; j < 2; ++j)
+                    sp[a][j] = (uint32_t)__builtin_amdgcn_readlane((int)s4, 16 * a + 2 * j) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)s4, 16 * a + 2 * j + 1) << 16;
+            auto pair = [](const uint16_t *at) __attribute__((always_inline)) {       // the sums at x and x + 4
+                ushort2v v;
+                v.x = at[0]; v.y = at[4];
+                return __builtin_bit_cast(uint32_t, v);
+            };
+            const uint16_t *src = sums + d0 * SCOLS + 16 * wb + min(lane, NCOL - 1);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int row = min(by * 16 + i, p.H - 1);
+            for (int y = 0; y < ND + 12; ++y) {
+                const uint32_t v0 = pair(src + y * SCOLS), v1 = pair(src + y * SCOLS + 8);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int d = bx * 4 + j;
-                    const uint32_t v = cp[row * W4 + min(d, W4 - 1)];
-                    c[i][j] = d < W4 ? v : (v >> 24) * 0x01010101u;
+                for (int a = 0; a < 4; ++a) {
+                    const int dy = y - 4 * a;
+                    if (dy < 0 || dy >= ND) continue;
+                    lb[dy] = __builtin_amdgcn_sad_u16(sp[a][0], v0, a == 0 ? 0u : lb[dy]);
+                    lb[dy] = __builtin_amdgcn_sad_u16(sp[a][1], v1, lb[dy]);
+                }
+            }
+#pragma unroll
+            for (int dy = 0; dy < ND; ++dy) {
+                const uint32_t k = (lb[dy] << 7) | (uint32_t)dy;
+                low = k < low ? k : low;
+            }
+            low = lane < NCOL ? ((low >> 7) << KEY_SHIFT) | ((uint32_t)(d0 + (int)(low & 127u)) * N + (uint32_t)lane) : 0xffffffffu;
+            if constexpr (NLEFT > 0) {                             // the last column: candidate row d0 + lane
+                uint32_t v = 0;
+                const uint16_t *end = sums + (d0 + min(lane, ND - 1)) * SCOLS + 16 * wb + NCOL;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    v = __builtin_amdgcn_sad_u16(sp[a][0], pair(end + 4 * a * SCOLS), v);
+                    v = __builtin_amdgcn_sad_u16(sp[a][1], pair(end + 4 * a * SCOLS + 8), v);
+                }
+                if (lane < ND) {
+                    lb_left = v;
+                    const uint32_t k = (v << KEY_SHIFT) | ((uint32_t)(d0 + lane) * N + NCOL);
+                    low = k < low ? k : low;
+                }
+            }
+            low = wave_min_u32(low);
+        }
+        if (lane == 0) red[NW + wv] = low;
+        __syncthreads();
+        if (bounds) {
+            // the block's candidate with the lowest bound, a dword per lane
+            uint32_t first = red[NW + wb * WPB];
+#pragma unroll
+            for (int i = 1; i < WPB; ++i) first = min(first, red[NW + wb * WPB + i]);
+            first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(first & KEY_MASK));
+            {
+                const int dy = (int)(first / (uint32_t)N), o = 16 * wb + (int)first - dy * N;
+                const uint32_t *r = lds32 + (dy + (lane >> 2)) * pitch4 + (o >> 2) + (lane & 3);
+                best = (wave_sum_u32(__builtin_amdgcn_sad_u8(cl, __builtin_amdgcn_alignbyte(r[1], r[0], (uint32_t)(o & 3)), 0)) << KEY_SHIFT) | first;
+            }
+            const uint32_t most = best >> KEY_SHIFT;
+            // the candidates that are left, if any: a bit for each row of a lane's column
+            if ((low >> KEY_SHIFT) <= most) {
+                constexpr int NM = (ND + 31) / 32;
+                uint32_t m[NM], left = 0;
+#pragma unroll
+                for (int i = 0; i < NM; ++i) {
+                    m[i] = 0;
+#pragma unroll
+                    for (int dy = min(32 * i + 31, ND - 1); dy >= 32 * i; --dy) m[i] = m[i] + m[i] + (lb[dy] <= most ? 1u : 0u);
+                    if (lane >= NCOL) m[i] = 0;
+                    left += (uint32_t)__popc(m[i]);
+                }
+                const bool last = NLEFT > 0 && lb_left <= most;
+                left += last ? 1u : 0u;
+                // their places in the list: the sum over the lanes up to this one
+                uint32_t upto = group_sum_u32<16>(left);
+                upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x142, 0xa, 0xf, false);
+                upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x143, 0xc, 0xf, false);
+                const int count = __builtin_amdgcn_readlane((int)upto, 63);
+                if (count > MOST) {
+                    scan = true;
+                } else if (count > 0) {
+                    int at = (int)(upto - left);
+                    if (last) list[at++] = (uint16_t)(lane << 7 | NCOL);
+#pragma unroll
+                    for (int i = 0; i < NM; ++i)
+                        while (m[i] != 0) {
+                            list[at++] = (uint16_t)((32 * i + __builtin_ctz(m[i])) << 7 | lane);
+                            m[i] &= m[i] - 1;
+                        }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // (this wavefront's own: no barrier)
+                    // sixteen lanes to a candidate, a block row each
+                    uint32_t crow[4];
+                    rows_of_lanes(cl, lane, crow);
+                    uint32_t key = 0xffffffffu;
+#pragma unroll 1
+                    for (int i = 0; i < count; i += 8) {
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            const int e = list[min(i + 4 * k + (lane >> 4), count - 1)];
+                            const int dy = d0 + (e >> 7), dx = e & 127, o = 16 * wb + dx;
+                            uint32_t r4[4], a = 0;
+                            load_aligned16(lds32 + (dy + (lane & 15)) * pitch4 + (o >> 2), (uint32_t)(o & 3), r4);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(crow[j], r4[j], a);
+                            a = (group_sum_u32<16>(a) << KEY_SHIFT) | (uint32_t)(dy * N + dx);
+                            key = a < key ? a : key;                   // (whole in lane 15 of the sixteen)
+                        }
+                    }
+                    key = wave_min_u32((lane & 15) == 15 ? key : 0xffffffffu);
+                    best = key < best ? key : best;
                 }
             }
         }
     }
-
-    // row (lane & 15) of the current block in vector registers, for the split tail below
-    // (requested here, used after the row scan)
-    uint32_t crow[4];
-    {
-        const uint32_t *cp = reinterpret_cast<const uint32_t *>(cur);
-        const int W4 = p.W >> 2;
-        const int row = min(by * 16 + (lane & 15), p.H - 1);
-        if (ANY && (p.W & 3) != 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) crow[j] = row_dword(cur + (size_t)row * p.W, bx * 16 + 4 * j, p.W);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int d = bx * 4 + j;
-                const uint32_t v = cp[row * W4 + min(d, W4 - 1)];
-                crow[j] = d < W4 ? v : (v >> 24) * 0x01010101u;
-            }
-        }
-    }
-
-    uint32_t best = 0xffffffffu;                   // (sad << 14) | raster index
-#pragma unroll 1
-    for (int ch = 0; ch < NCHUNK; ++ch) {
-        const int dxi = ch * 64 + lane;
-        const int o = 16 * wv + min(dxi, N - 1);   // idle lanes repeat the last column
-        const uint32_t sh = (uint32_t)(o & 3);
-        const uint32_t *base = lds32 + (o >> 2);
-        uint32_t acc[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] = 0;
-        uint32_t lbest = 0xffffffffu;              // (sad << 7) | (dy + R)
-
-        // one window row: block rows i in [ilo, ihi] accumulate into slot (rot - i) & 15;
-        // then candidate `fin` (if >= 0), which sits in slot (rot + 1) & 15, is complete
-        auto step = [&](const uint32_t *rowp, int ilo, int ihi, int rot, int fin) __attribute__((always_inline)) {
-            uint32_t r4[4];
-            load_aligned16(rowp, sh, r4);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (i < ilo || i > ihi) continue;
-                const int slot = (rot - i) & 15;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[slot] = __builtin_amdgcn_sad_u8(c[i][j], r4[j], acc[slot]);
-            }
-            if (fin >= 0) {
-                const int slot = (rot + 1) & 15;
-                const uint32_t key = (acc[slot] << 7) | (uint32_t)fin;
-                lbest = key < lbest ? key : lbest;
-                acc[slot] = 0;
-            }
-        };
-
-#pragma unroll
-        for (int r = 0; r < 15; ++r) step(base + r * pitch4, 0, r, r, -1);
-#pragma unroll 1
-        for (int k = 0; k < NSB; ++k) {
-            const uint32_t *rp = base + (15 + 16 * k) * pitch4;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) step(rp + j * pitch4, 0, 15, (15 + j) & 15, 16 * k + j);
-        }
-#pragma unroll
-        for (int j = 0; j < NSR; ++j)
-            step(base + (15 + 16 * NSB + j) * pitch4, 0, 15, (15 + j) & 15, 16 * NSB + j);
-#pragma unroll
-        for (int e = 1; e <= 15; ++e)
-            step(base + (2 * R + e) * pitch4, e, 15, (2 * R + e) & 15, 2 * R + e - 15);
-
-        if (dxi < N) {
-            const uint32_t dyi = lbest & 127u;
-            const uint32_t key = ((lbest >> 7) << KEY_SHIFT) | (dyi * (uint32_t)N + (uint32_t)dxi);
-            best = key < best ? key : best;
-        }
-    }
-
-    if (NLEFT > 0) {
-        // the last NLEFT columns, one candidate per lane; what does not fill a pass of 64
-        // (one candidate at R = 32) is split sixteen lanes per candidate, a block row each
-        constexpr int NCAND = NLEFT * N;
-        constexpr int REM = NCAND % 64;
-        constexpr bool SPLIT = REM > 0 && REM <= 4;
-        constexpr int NFULL = SPLIT ? NCAND - REM : NCAND;
-#pragma unroll 1
-        for (int c0 = 0; c0 < NFULL; c0 += 64) {
-            const int cand = min(c0 + lane, NCAND - 1);
-            const int dyi = cand / NLEFT;
-            const int dxi = (N / 64) * 64 + (cand - dyi * NLEFT);
-            const int o = 16 * wv + dxi;
-            const uint32_t sh = (uint32_t)(o & 3);
-            const uint32_t *base = lds32 + dyi * pitch4 + (o >> 2);
-            uint32_t a = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                uint32_t r4[4];
-                load_aligned16(base + i * pitch4, sh, r4);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(c[i][j], r4[j], a);
-            }
-            const uint32_t key = (a << KEY_SHIFT) | (uint32_t)(dyi * N + dxi);
-            best = key < best ? key : best;        // idle lanes recompute the last candidate
-        }
-        if (SPLIT) {
-            const int i = lane & 15;
-            const int cand = min(NFULL + (lane >> 4), NCAND - 1);
-            const int dyi = cand / NLEFT;
-            const int dxi = (N / 64) * 64 + (cand - dyi * NLEFT);
-            const int o = 16 * wv + dxi;
-            uint32_t r4[4];
-            load_aligned16(lds32 + (dyi + i) * pitch4 + (o >> 2), (uint32_t)(o & 3), r4);
-            uint32_t a = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(crow[j], r4[j], a);
-            a = group_sum_u32<16>(a);
-            const uint32_t key = (a << KEY_SHIFT) | (uint32_t)(dyi * N + dxi);
-            if (i == 15 && NFULL + (lane >> 4) < NCAND) best = key < best ? key : best;
-        }
-    }
-
-    best = wave_min_u32(best);
-    if (lane == 0) {
-        const uint32_t blk = (uint32_t)by * p.nbx + bx;
-        const uint32_t cidx = best & KEY_MASK;
-        const int dyi = (int)(cidx / (uint32_t)N);
-        sad[blk] = (int32_t)(best >> KEY_SHIFT);
-        mv[2 * blk + 0] = dyi - R;
-        mv[2 * blk + 1] = (int)cidx - dyi * N - R;
-    }
+    if (scan) best = min(best, scan_rows<R, ND, pitch4>(lds32, cl, wb, d0, lane));
+    if (lane == 0) atomicMin(&result[wb], best);
+    __syncthreads();
+    if (tid >= BPW || bx0 + tid >= p.nbx) return;
+    best = result[tid];
+    const uint32_t blk = (uint32_t)by * p.nbx + bx0 + tid;
+    const uint32_t cidx = best & KEY_MASK;
+    const int dyi = (int)(cidx / (uint32_t)N);
+    sad[blk] = (int32_t)(best >> KEY_SHIFT);
+    mv[2 * blk + 0] = dyi - R;
+    mv[2 * blk + 1] = (int)cidx - dyi * N - R;
 }
 
 // ---------------------------------------------------------------------------
@@ -609,11 +780,9 @@ hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref
     const int pitch4 = p.pitch >> 2;
     if (p.variant == SAD_ROWSCAN_B16) {
         const uint32_t grid = (uint32_t)(p.nby * p.groups_x);
-        const size_t lds_bytes = (size_t)((16 + 2 * p.R) * pitch4 + 1) * 4;
-        const bool any = (p.W & 3) != 0;
-        const auto k = p.R == 32 ? (any ? merit_sad_rowscan16<32, true> : merit_sad_rowscan16<32, false>)
-                                 : (any ? merit_sad_rowscan16<16, true> : merit_sad_rowscan16<16, false>);
-        hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
+        const auto k = p.R == 32 ? (p.bpw == 1 ? merit_sad_rowscan16<32, 1> : merit_sad_rowscan16<32, 4>)
+                                 : merit_sad_rowscan16<16, 4>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(p.bpw == 1 ? 256 : 512), sad_rowscan16_lds(p), s, p, cur, ref, sad, mv);
         return hipGetLastError();
     }
     if (p.variant == SAD_ROWSCAN_PAIR) {
