@@ -20,6 +20,14 @@
 //   40 -> 40 on 2 of 31x18                  5.8 -> 4.2
 //   432 -> 196 on 23x26, stride 2, packed   24.8 -> 10.5
 //   5x5 680 -> 22 on 3 of 47x11, stride 2   83 -> 36
+// Tiles are adjacent pixels of the plane, for which whole input rows are staged, or rectangles 8, 16 or 32 pixels wide, for
+// which the columns they need are: long rows and row strides did not fit otherwise, and left such layers to a few dozen
+// tiles of the other form.  Rectangles, us a launch, before -> with them (41 of 400 layers of 7 to 112 pixels a side take
+// them, 1.37x in the geometric mean):
+//   536 -> 32 on 14x109                      50.2 -> 14.8
+//   414 -> 32 on 3 of 32x92, stride 2        28.0 -> 9.8
+//   5x5 72 -> 56 on 6 of 16x105, stride 2    16.1 -> 7.9
+//   264 -> 264 on 34x41                      11.9 -> 10.3
 // and on larger launches the other form keeps (64 -> 64 on 8 of 56x56 6.8 against 19, 256 -> 256 on 56x56 12.0 against 20):
 // its wavefronts share what they stage.
 #include "merit_internal.h"
@@ -71,9 +79,18 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
     const int major = (int)fdiv((uint32_t)item, p.div_minor), minor = item - major * p.minor;
     const int tile = p.by_channel ? minor : major, cg = p.by_channel ? major : minor;
     const int n = (int)fdiv((uint32_t)tile, p.div_tiles);
-    const int m0 = (tile - n * p.tiles) * TM;
     const int ohw = p.OH * p.OW;
-    const int oyA = (int)fdiv((uint32_t)m0, p.div_ow);
+    // a run of TM adjacent pixels from m0 on, or a rectangle at (oyA, oxA); image column of staged column 0
+    const int at = tile - n * p.tiles;
+    int m0 = at * TM, oyA, oxA = 0, colA = -p.pw;
+    if (p.lg_tw == 0) {
+        oyA = (int)fdiv((uint32_t)m0, p.div_ow);
+    } else {
+        const int ty = (int)fdiv((uint32_t)at, p.div_tiles_x);
+        oyA = ty * (TM >> p.lg_tw);
+        oxA = (at - ty * p.tiles_x) << p.lg_tw;
+        colA = min(oxA * p.sw - p.pw, p.W - 8) & ~1;         // (units are whole: the last one of a row ends with it)
+    }
     const int yA = oyA * p.sh - p.ph;
     const int chbytes = p.H * p.W * 2;
 
@@ -88,7 +105,7 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
     uint32_t x_voff[NXU];
     int x_lds[NXU], x_hh[NXU];
     {
-        const int nu = 2 * p.RHa * ((p.W + 7) >> 3);
+        const int nu = 2 * p.RHa * p.units_x;
 #pragma unroll
         for (int k = 0; k < NXU; ++k) {
             // consecutive lanes: consecutive staged rows (the pitch is odd: their LDS writes start in different banks)
@@ -97,10 +114,10 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
             const int q = uc - xc * 2 * p.RHa;
             const int hh = q >= p.RHa ? 1 : 0;
             const int gy = yA + q - hh * p.RHa;
-            const int col = XU == 0 ? 0 : min(8 * xc, p.W - 8);       // (a row's last unit ends with the row)
+            const int col = XU == 0 ? 0 : min(max(colA, 0) + 8 * xc, p.W - 8);       // (a row's last unit ends with the row)
             x_hh[k] = u < nu ? hh : 2;
             x_voff[k] = u < nu && gy >= 0 && gy < p.H ? (uint32_t)(((hh * 8 * p.H + gy) * p.W + col) * 2) : OOB;
-            x_lds[k] = (q * p.pitch + p.pw + col) * 16;
+            x_lds[k] = (q * p.pitch + col - colA) * 16;
         }
     }
 
@@ -205,10 +222,17 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
     int xa[PXB];
 #pragma unroll
     for (int pb = 0; pb < PXB; ++pb) {
-        const int m = min(m0 + pb * 32 + c32, ohw - 1);
-        const int oy = (int)fdiv((uint32_t)m, p.div_ow);
-        const int ox = m - oy * p.OW;
-        xa[pb] = ((h * p.RHa + (oy - oyA) * p.sh) * p.pitch + ox * p.sw) * 16;
+        int oy, ox;
+        if (p.lg_tw == 0) {
+            const int m = min(m0 + pb * 32 + c32, ohw - 1);
+            oy = (int)fdiv((uint32_t)m, p.div_ow);
+            ox = m - oy * p.OW;
+        } else {
+            const int m = pb * 32 + c32;
+            oy = min(oyA + (m >> p.lg_tw), p.OH - 1);
+            ox = min(oxA + (m & ((1 << p.lg_tw) - 1)), p.OW - 1);
+        }
+        xa[pb] = ((h * p.RHa + (oy - oyA) * p.sh) * p.pitch + ox * p.sw - p.pw - colA) * 16;
     }
     floatx16 acc[PXB];
 #pragma unroll
@@ -312,8 +336,14 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
     const half2v z = {(_Float16)0.0f, (_Float16)0.0f};
     const int live = min(WAVES, p.slices);                 // wavefronts that had a slice
     for (int u = tid; u < 32 * (TM / 8); u += NT) {
-        const int c = u / (TM / 8), px = m0 + 8 * (u % (TM / 8)), oc = cg * 32 + c;
-        if (px >= ohw || oc >= p.Cout) continue;
+        const int c = u / (TM / 8), oc = cg * 32 + c;
+        int px = m0 + 8 * (u % (TM / 8)), left = ohw - px;          // pixels that there are
+        if (p.lg_tw != 0) {
+            const int m = 8 * (u % (TM / 8)), oy = oyA + (m >> p.lg_tw), ox = oxA + (m & ((1 << p.lg_tw) - 1));
+            px = oy * p.OW + ox;
+            left = oy < p.OH ? p.OW - ox : 0;
+        }
+        if (left <= 0 || oc >= p.Cout) continue;
         float f[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) f[k] = 0.0f;
@@ -332,13 +362,13 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
             o[k] = __builtin_bit_cast(uint32_t, e);
         }
         uint16_t *dst = y + ((size_t)n * p.Cout + oc) * ohw + px;
-        if (px + 8 <= ohw) {
+        if (left >= 8) {
             const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
             __builtin_memcpy(dst, &v, 16);
         } else {
 #pragma unroll
             for (int k = 0; k < 8; ++k)
-                if (px + k < ohw) dst[k] = (uint16_t)(o[k >> 1] >> (16 * (k & 1)));
+                if (k < left) dst[k] = (uint16_t)(o[k >> 1] >> (16 * (k & 1)));
         }
     }
 }

@@ -289,15 +289,18 @@ struct SplitParams {
     int PXB;               // 32-pixel blocks of a tile (of 32 output channels)
     int xu;                // staging units of 8 channels x 8 pixels per lane and slice (0: one, of rows shorter than 8 pixels)
     int tiles;             // pixel tiles per image
+    int lg_tw;             // log2 of a tile's columns; 0: a run of adjacent pixels, whole input rows staged
+    int tiles_x;           // tiles side by side (1: runs)
     int co_groups;         // 32-channel blocks
     int slices;            // slices of 16 input channels
     int RHa, pitch;        // staged rows, and pixels from one to the next
+    int units_x;           // units of 8 pixels of a staged row
     int slice_bytes;       // a wavefront's staging area
     int lds_bytes;
     int relu;
     int xq, xr;            // grid / 8, grid % 8 (see xcd_band_item)
     int by_channel, minor; // order of the work list: 1 = (channel block, tile), 0 = (tile, channel block); extent of the inner one
-    FastDiv div_minor, div_tiles, div_ow;
+    FastDiv div_minor, div_tiles, div_ow, div_tiles_x;
     FastDiv div_r2;        // staged rows of both channel groups of a slice
 };
 hipError_t launch_conv2d_split(const SplitParams &p, const void *x, const void *w, void *y, hipStream_t s, bool packed);

@@ -528,26 +528,36 @@ void derive_split(merit_plan *pl)
         {{1.28, 2.98, 1.72, 1.21, 2.76, 1.95}, {1.08, 3.81, 1.78, 1.19, 2.59, 2.05}}};
 
     double best_cost = multi_pass;
-    for (int pxb = 1; pxb <= 2; ++pxb) {
+    // tiles of 32 or 64 pixels: adjacent ones of the plane (whole input rows are staged), or rectangles 8, 16 or 32 wide
+    // (part of a row is staged: what long rows and row strides need to fit at all).  Where both fit, the rectangle has to
+    // lead by 12 %: its units start on even columns only, and within that lead it was up to 9 % slower, over 400 layers.
+    for (int form = 0; form < 8; ++form) {
+        const int pxb = 1 + (form & 1), lg_tw = form < 2 ? 0 : 2 + form / 2;
+        if (form == 2 && pl->use_split) best_cost *= 0.88;
         SplitParams p;
         std::memset(&p, 0, sizeof(p));
         p.N = c.N; p.Cin = c.Cin; p.H = c.H; p.W = c.W; p.Cout = c.Cout; p.OH = c.OH; p.OW = c.OW;
         p.sh = c.sh; p.sw = c.sw; p.ph = c.ph; p.pw = c.pw; p.dh = c.dh; p.dw = c.dw;
-        p.K = c.kh; p.PXB = pxb; p.relu = c.relu;
-        const int64_t TM = 32 * pxb;
-        int64_t rows_out = (TM + OW - 2) / OW + 1;
+        p.K = c.kh; p.PXB = pxb; p.relu = c.relu; p.lg_tw = lg_tw;
+        const int64_t TM = 32 * pxb, TW = lg_tw > 0 ? 1ll << lg_tw : OW;
+        if (lg_tw > 0 && (W < 8 || TW / 2 >= OW)) continue;
+        int64_t rows_out = lg_tw > 0 ? TM / TW : (TM + OW - 2) / OW + 1;
         if (rows_out > c.OH) rows_out = c.OH;
         p.RHa = (int)((rows_out - 1) * c.sh + (c.kh - 1) * c.dh + 1);
-        int64_t pitch = c.pw + W;
-        const int64_t reach = (OW - 1) * c.sw + (c.kw - 1) * c.dw + 1;
+        const int64_t span = (TW - 1) * c.sw + (c.kw - 1) * c.dw + 1;     // input columns of a tile
+        // (a rectangle's first staged column is an even one: loads on rows of an even width stay on 4-byte boundaries)
+        p.units_x = (int)cdiv(lg_tw > 0 ? std::min(span + 1, W) : W, 8);
+        int64_t pitch = lg_tw > 0 ? 8 * (int64_t)p.units_x + c.pw + 1 : c.pw + W;
+        const int64_t reach = lg_tw > 0 ? span + 9 : span;
         if (reach > pitch) pitch = reach;
         p.pitch = (int)(pitch | 1);               // odd: staged rows start in different LDS bank groups
-        const int64_t units = 2 * (int64_t)p.RHa * cdiv(W, 8);
+        const int64_t units = 2 * (int64_t)p.RHa * p.units_x;
         if (units > (W < 8 ? 64 : 128)) continue;
         p.xu = W < 8 ? 0 : (int)cdiv(units, 64);
         if (Cin % 8 != 0 && (W < 8 || (pxb == 2 && p.xu == 2))) continue;           // (no such instance)
         p.slices = (int)cdiv(Cin, 16);
-        p.tiles = (int)cdiv(ohw, TM);
+        p.tiles_x = lg_tw > 0 ? (int)cdiv(OW, TW) : 1;
+        p.tiles = lg_tw > 0 ? (int)(p.tiles_x * cdiv(c.OH, TM / TW)) : (int)cdiv(ohw, TM);
         p.co_groups = (int)cdiv(Cout, 32);
         p.slice_bytes = 2 * p.RHa * p.pitch * 16;
         const int64_t sums = (int64_t)SPLIT_WAVES * 32 * (TM + 4) * 4;
@@ -558,7 +568,7 @@ void derive_split(merit_plan *pl)
         p.by_channel = Cout * Cin * c.kh * c.kw > N * Cin * H * W ? 1 : 0;
         p.minor = (int)(p.by_channel ? N * p.tiles : p.co_groups);
         if (grid > 512 || !fastdiv_ok(grid, p.minor) || !fastdiv_ok(N * p.tiles, p.tiles) || !fastdiv_ok(ohw, OW) ||
-            !fastdiv_ok(units, 2 * p.RHa))
+            !fastdiv_ok(p.tiles, p.tiles_x) || !fastdiv_ok(units, 2 * p.RHa))
             continue;
         const auto &k = costs[k5][pxb - 1];
         const double r = (double)cdiv(grid, 256), load = (double)units / 64.0;
@@ -569,6 +579,7 @@ void derive_split(merit_plan *pl)
         p.xq = (int)(grid / 8); p.xr = (int)(grid % 8);
         p.div_minor = make_fastdiv((uint32_t)p.minor);
         p.div_tiles = make_fastdiv((uint32_t)p.tiles);
+        p.div_tiles_x = make_fastdiv((uint32_t)p.tiles_x);
         p.div_ow = make_fastdiv((uint32_t)OW);
         p.div_r2 = make_fastdiv((uint32_t)(2 * p.RHa));
         pl->split = p;
@@ -577,7 +588,7 @@ void derive_split(merit_plan *pl)
         li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
         li.block[0] = SPLIT_WAVES * 64; li.block[1] = 1; li.block[2] = 1;
         li.lds_bytes = p.lds_bytes;
-        li.tile[1] = 32; li.tile[2] = rows_out; li.tile[3] = OW;
+        li.tile[1] = 32; li.tile[2] = rows_out; li.tile[3] = TW;
     }
 }
 

@@ -24,6 +24,12 @@ CASES = [
     (1, 32, 5, 5, 40, 5, 1, 2, 1),        # 5x5
     (2, 37, 9, 10, 36, 5, 2, 2, 1),
     (1, 144, 21, 23, 56, 5, 1, 2, 1),
+    # rectangular tiles: rows too long to be staged whole
+    (1, 40, 9, 95, 40, 5, 2, 2, 1),       # 48 columns: a cut tile beside whole ones, the last unit moved back
+    (2, 72, 11, 111, 33, 3, 2, 1, 1),     # 56 columns, six rows
+    (1, 88, 5, 130, 40, 3, 1, 1, 1),      # two columns in the last tile
+    (2, 49, 7, 97, 24, 3, 2, 0, 1),       # channels off the multiple of 8, no padding
+    (1, 80, 12, 150, 40, 3, 1, 2, 2),     # dilated window
 ]
 
 
@@ -38,7 +44,10 @@ def test_against_the_oracle_raw_and_packed(case):
     print(case, li, flush=True)
     ohw = plan.out_shape()[2] * plan.out_shape()[3]
     assert li["kernel"] == "merit_conv2d_chws" and li["tile"][1] == 32
-    assert li["grid"][0] in (N * -(-Cout // 32) * -(-ohw // 32), N * -(-Cout // 32) * -(-ohw // 64))      # this form's tiles
+    oh, ow = plan.out_shape()[2:]
+    tiles = [-(-ohw // 32), -(-ohw // 64)] + [-(-oh // (m // t)) * -(-ow // t) for m in (32, 64) for t in (8, 16, 32)]
+    assert li["grid"][0] in [N * -(-Cout // 32) * t for t in tiles]      # this form's tiles
+    if W >= 95: assert li["tile"][3] in (8, 16, 32)
     # no numbers beside the operands: what is loaded past a row, an image or the weights must not reach a sum
     xb = torch.full((x.size + 256,), float("nan"), dtype=torch.float16, device="cuda")
     wb = torch.full((w.size + 256,), float("inf"), dtype=torch.float16, device="cuda")
