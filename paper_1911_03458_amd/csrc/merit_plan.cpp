@@ -1092,13 +1092,18 @@ merit_status derive_conv(merit_plan *pl)
                             (kh == 5 && kw == 5 && !p.residual);
         // Channel counts off the multiple of 8, 17 to 31 of them, and at most 32 output channels: the same kernel
         // (65 -> 16 on 21 images of 18x20, stride 2: 31.3 -> 6.9 us; 165 -> 60 on 8 of 18x110, stride 2: 127 -> 23;
-        // 100 -> 100 on 8 of 28x28: 40 -> 8.0).  What stays on the channel-block kernels is close there -- up to 16
-        // channels (16 -> 64 on 8 of 56x56: 5.7 against 5.3), 64 aligned channels to at most 32 (64 -> 32: 7.2 against
-        // 5.7; 24 -> 32: 6.2 against 5.0) -- or is held there by the plan tests: single images with Cin % 8 != 0 (over 120
-        // such layers 23-156 us on average by kernel and window, on this one 5-26).
+        // 100 -> 100 on 8 of 28x28: 40 -> 8.0).  On rows off the 8 pixels, which the channel-block kernels stage a pixel at
+        // a time, and with 5x5 windows, also 16 channels and 64 aligned ones to at most 32 (16 -> 184 on 33 of 16x13, 5x5:
+        // 34.3 -> 6.9 us; 48 -> 32 on 4 of 8x81, stride 2: 38 -> 5.5; 16 -> 24 on 52 of 106x86: 51.7 -> 38.4; over 120 such
+        // layers 2.3x, none slower).  What stays on the channel-block kernels is close there, on rows of whole units (16 ->
+        // 64 on 8 of 56x56: 5.7 against 5.3; 64 -> 32: 7.2 against 5.7; 24 -> 32: 6.2 against 5.0), or is held there by the
+        // plan tests: single images with Cin % 8 != 0 (over 120 such layers 23-156 us on average by kernel and window, on
+        // this one 5-26).
         // (1x1 windows at stride 1 have a kernel of their own: derive_px.)
         const bool was = Cin >= 32 && Cin % 8 == 0 && ncb >= 2;
-        any_count = (kh > 1 || sh > 1 || sw > 1) && Cin >= 17 && (Cin % 8 == 0 || N >= 2) && (ncb >= 2 || Cin % 8 != 0 || Cin > 64);
+        const bool off_units = W % 8 != 0 || kh == 5;
+        any_count = (kh > 1 || sh > 1 || sw > 1) && Cin >= (off_units ? 16 : 17) && (Cin % 8 == 0 || N >= 2) &&
+                    (ncb >= 2 || Cin % 8 != 0 || Cin > 64 || off_units);
         if (window && (was || any_count)) {
             // the tiling with the lowest estimate among those whose packed weights are at most so many bytes
             auto choose = [&](int64_t most_bytes, double *best_cost) -> bool {

@@ -26,6 +26,11 @@ CASES = [
     (2, 40, 13, 7, 40, 3, 1),         # rows of fewer than 8 pixels: one-pixel units
     (2, 52, 24, 28, 64, 5, 1),        # 5x5 on 128-pixel tiles, 64 and 32 channels
     (2, 128, 14, 15, 96, 5, 2),
+    (2, 16, 11, 13, 40, 3, 1),        # 16 channels on rows off the 8 pixels
+    (3, 16, 8, 16, 24, 5, 1),         # ... and with 5x5 windows on any row
+    (2, 32, 12, 15, 32, 3, 2),        # at most 32 output channels, likewise
+    (2, 64, 9, 10, 24, 3, 1),
+    (2, 24, 8, 32, 24, 5, 2),
 ]
 
 
