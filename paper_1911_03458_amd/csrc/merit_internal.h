@@ -164,7 +164,8 @@ struct PoolParams {
 };
 
 // ---- block matching --------------------------------------------------------
-enum SadVariant { SAD_GENERIC = 0, SAD_ROWSCAN_B16 = 1, SAD_ROWSCAN_PAIR = 2 };
+enum SadVariant { SAD_GENERIC = 0, SAD_ROWSCAN_B16 = 1, SAD_ROWSCAN_PAIR = 2, SAD_ROWSCAN_SEVEN = 3 };
+constexpr int SEVEN_ROWS = 40, SEVEN_PITCH4 = 20;      // seven-block row scan: staged window rows, dwords of a staged row
 
 struct SadParams {
     int H, W, B, R, n;     // n = 2R+1 candidates per axis

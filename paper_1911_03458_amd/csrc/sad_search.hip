@@ -772,6 +772,74 @@ __global__ __launch_bounds__(256) void merit_sad_rowscan_pair(SadParams p, const
 }
 
 // ---------------------------------------------------------------------------
+// Row-scan kernel, seven blocks per wavefront: 8x8 blocks with R = 4, whose nine candidate columns fill 63 of the 64 lanes.
+// The walk over the window rows is the one described above, eight accumulators rotating over the nine rows of candidates:
+// 144 v_sad_u8 for nine candidates of seven blocks, where the kernel for any shape spends a workgroup on 81 candidates and
+// as much again on its window.  A workgroup is four block rows of seven blocks, so that their windows share a staged area of
+// 40 x 64 pixels (1.4 times the blocks' own, 2.1 for a single row of 28 blocks); that and the current blocks are one 16-byte
+// load a thread each.  Bound by the launch and this one trip to memory.
+// us a launch in a graph, kernel for any shape -> this: 64x64 3.3 -> 2.8, 480x640 8.2 -> 3.0, 822x1002 17.8 -> 3.4, 1080x1920
+// 40.0 -> 4.6.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void merit_sad_rowscan_seven(SadParams p, const uint8_t *__restrict__ cur,
+                                                              const uint8_t *__restrict__ ref,
+                                                              int32_t *__restrict__ sad, int32_t *__restrict__ mv)
+{
+    constexpr int B = 8, R = 4, N = 2 * R + 1, BW = 7, PITCH4 = SEVEN_PITCH4;
+    __shared__ __align__(16) uint32_t win32[SEVEN_ROWS * PITCH4], cur32[4 * B * PITCH4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint32_t g = xcd_band_item(blockIdx.x, p.xq, p.xr);     // a band of block rows per XCD
+    const int gy = (int)(g / (uint32_t)p.groups_x);
+    const int bx0 = (int)(g - (uint32_t)gy * p.groups_x) * BW, by0 = gy * 4;
+
+    // (64 columns of both; the planner asks for rows of 16 pixels)
+    stage_window16<SEVEN_ROWS, 4, PITCH4, 256>(p, ref, win32, by0 * B - R, bx0 * B - R, tid);
+    stage_window16<4 * B, 4, PITCH4, 256>(p, cur, cur32, by0 * B, bx0 * B, tid);
+    __syncthreads();
+
+    const int bl = min(lane / N, BW - 1), dx = lane < N * BW ? lane - bl * N : 0;         // (the last lane repeats a column)
+    uint32_t c[B][2];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        const uint2 v = *reinterpret_cast<const uint2 *>(cur32 + (B * wv + i) * PITCH4 + 2 * bl);
+        c[i][0] = v.x; c[i][1] = v.y;
+    }
+    const int o = B * bl + dx;
+    const uint32_t sh = (uint32_t)(o & 3);
+    const uint32_t *base = win32 + B * wv * PITCH4 + (o >> 2);
+    uint32_t acc[N], best = 0xffffffffu;
+#pragma unroll
+    for (int r = 0; r < B + 2 * R; ++r) {
+        const uint32_t d0 = base[r * PITCH4], d1 = base[r * PITCH4 + 1], d2 = base[r * PITCH4 + 2];
+        const uint32_t r0 = __builtin_amdgcn_alignbyte(d1, d0, sh), r1 = __builtin_amdgcn_alignbyte(d2, d1, sh);
+#pragma unroll
+        for (int dy = 0; dy < N; ++dy) {
+            const int i = r - dy;
+            if (i < 0 || i >= B) continue;
+            acc[dy] = __builtin_amdgcn_sad_u8(c[i][0], r0, i == 0 ? 0u : acc[dy]);
+            acc[dy] = __builtin_amdgcn_sad_u8(c[i][1], r1, acc[dy]);
+        }
+        if (r >= B - 1) best = min(best, (acc[r - B + 1] << KEY_SHIFT) | (uint32_t)((r - B + 1) * N));
+    }
+    best += (uint32_t)dx;
+    // the lowest of a block's nine lanes, in its first one (what the others take from their neighbours is not used)
+    auto down = [&](uint32_t v, int by) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (lane + by), (int)v);
+    };
+    const uint32_t ninth = down(best, 8);
+#pragma unroll
+    for (int k = 4; k >= 1; k >>= 1) best = min(best, down(best, k));
+    best = min(best, ninth);
+    const int by = by0 + wv, bx = bx0 + bl;
+    if (dx != 0 || lane >= N * BW || by >= p.nby || bx >= p.nbx) return;
+    const uint32_t blk = (uint32_t)by * p.nbx + bx, cidx = best & KEY_MASK;
+    const int dyi = (int)(cidx / (uint32_t)N);
+    sad[blk] = (int32_t)(best >> KEY_SHIFT);
+    mv[2 * blk + 0] = dyi - R;
+    mv[2 * blk + 1] = (int)cidx - dyi * N - R;
+}
+
+// ---------------------------------------------------------------------------
 hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref, int32_t *sad,
                       int32_t *mv, hipStream_t s)
 {
@@ -799,6 +867,11 @@ hipError_t launch_sad(const SadParams &p, const uint8_t *cur, const uint8_t *ref
         hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
         return hipGetLastError();
     }
+    if (p.variant == SAD_ROWSCAN_SEVEN) {
+        const uint32_t grid = (uint32_t)((p.nby + 3) / 4 * p.groups_x);
+        hipLaunchKernelGGL(merit_sad_rowscan_seven, dim3(grid), dim3(256), 0, s, p, cur, ref, sad, mv);
+        return hipGetLastError();
+    }
     const size_t lds_bytes = (size_t)(p.win * pitch4 + 1 + p.B * (p.B >> 2) + 4) * 4;
     hipLaunchKernelGGL(merit_sad_generic, dim3(nblocks), dim3(256), lds_bytes, s, p, cur, ref, sad, mv);
     return hipGetLastError();
@@ -809,6 +882,7 @@ const char *sad_kernel_name(const SadParams &p)
     if (p.variant == SAD_ROWSCAN_B16) return p.R == 32 ? "merit_sad_rowscan16<32>" : "merit_sad_rowscan16<16>";
     if (p.variant == SAD_ROWSCAN_PAIR)
         return p.B == 16 ? (p.R == 16 ? "merit_sad_rowscan_pair<16,16>" : "merit_sad_rowscan_pair<16,8>") : (p.R == 16 ? "merit_sad_rowscan_pair<8,16>" : "merit_sad_rowscan_pair<8,8>");
+    if (p.variant == SAD_ROWSCAN_SEVEN) return "merit_sad_rowscan_seven";
     return "merit_sad_generic";
 }
 
