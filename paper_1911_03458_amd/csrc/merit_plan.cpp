@@ -660,8 +660,9 @@ merit_status derive_conv(merit_plan *pl)
     p.CB = ncb >= 2 ? 2 : 1;
     // A grid that would leave more than half of the 256 CUs idle gets 32-channel blocks, i.e. twice
     // the workgroups (channel-block kernels; 8x128x56x56 -> 128, 3x3 / s2: 112 -> 224 workgroups,
-    // 24.4 -> 14.5 us; with more workgroups than that the 64-channel blocks win: half the input staging).
-    if (ncb >= 2 && Cin >= 8 && !pool && N * cdiv(ohw, 128) * cdiv(ncb, 2) <= 128) p.CB = 1;
+    // 24.4 -> 14.5 us; with more workgroups than that the 64-channel blocks win: half the input staging), the few-channel
+    // kernel too (its weights are then staged in half the time: 11x11 3 -> 64 on 3 of 147x74 13.2 -> 11.5 us).
+    if (ncb >= 2 && !pool && N * cdiv(ohw, 128) * cdiv(ncb, 2) <= 128) p.CB = 1;
     p.co_groups = (int)cdiv(ncb, p.CB);
 
     // try both tile sizes for a variant; prefer 256 pixels when the grid stays large
@@ -821,6 +822,17 @@ merit_status derive_conv(merit_plan *pl)
                 q.tile_px = q.TM - 8;
                 q.tiles_per_image = (int)t_ov;
             }
+        }
+        // Room for the weights as they lie, out of which the few-channel kernel cuts its operands: where the tile's area is
+        // smaller (11x11 windows on narrow images) it would gather them from memory a tap at a time (4 -> 64 on 19 of 124x142:
+        // 29.8 -> 17.1 us, 3 -> 64 on 3 of 147x74: 23.1 -> 13.2).  Not where that costs a resident workgroup that the grid has
+        // a use for.
+        if (variant == CONV_PLANAR_SMALLC && !q.ws) {
+            const int64_t raw = round_up((int64_t)q.lds_w_bytes + 32 + std::min<int64_t>(Cout, q.CB * 32) * Cin * kh * kw * 2 + 64, 16);
+            const int64_t now = (int64_t)conv_lds_bytes(q), items = N * q.tiles_per_image * q.co_groups;
+            if (raw > now && raw <= LDS_LIMIT &&
+                (std::min<int64_t>(3, LDS_LIMIT / raw) == std::min<int64_t>(3, LDS_LIMIT / now) || items <= 256 * (LDS_LIMIT / raw)))
+                q.lds_total = (int)raw;
         }
         if ((int64_t)conv_lds_bytes(q) > LDS_LIMIT) return false;
         q.wg_per_cu = (int)(LDS_LIMIT / (int64_t)conv_lds_bytes(q));
