@@ -1410,22 +1410,27 @@ merit_status derive_corr(merit_plan *pl)
     p.nchi = (int)cdiv(C, 8);
     p.xchunks = (int)cdiv(W, 64);
     p.lead = (int)round_up(R * sd, 8);
-    p.cols2 = (int)round_up(64 + p.lead + R * sd, 8);
+    // (images narrower than a chunk of 64 pixels: only the columns that exist and their reach.  Fewer staged columns are
+    // fewer pixel blocks to multiply and more channels a pass: us a launch in a graph, 248 channels on 29x19, +-3 / 2, 7.2 ->
+    // 4.8, 136 on 42x25, +-5 / 2, 6.4 -> 5.2, 56 on 34x27, +-5, 4.4 -> 4.4; 1.12x over 60 of 16 to 64 pixels a side)
+    const int64_t chunk = W < 64 ? round_up(W, 8) : 64;
+    p.cols2 = (int)round_up(chunk + p.lead + R * sd, 8);
     // staged rows ordered by residue class of the column modulo sd (the 16 pixels of an MFMA block are adjacent)
-    p.pitch1 = (int)cdiv(64, sd); p.P1 = (int)(sd * p.pitch1);
+    p.pitch1 = (int)cdiv(chunk, sd); p.P1 = (int)(sd * p.pitch1);
     p.pitch2 = (int)cdiv(p.cols2, sd); p.P2 = (int)(sd * p.pitch2);
     p.nsb = (int)cdiv(p.pitch1, 16); p.nblk = (int)(sd * p.nsb);
     p.nb = (int)cdiv(16 + 2 * R, 16);
     // channel groups per pass: whole reduction steps of 4 groups, at most two staging units per
     // thread, and about 40 KB so that four workgroups share a CU's LDS (measured best)
-    const int64_t per_g_full = 8 + p.cols2 / 8;
+    const int64_t per_g_full = chunk / 8 + p.cols2 / 8;
     const int64_t per_group = ((int64_t)p.P1 + p.P2) * 16;
     int64_t chg = (CORR_LDS_KB * 1024) / per_group;
     if (chg > 256 * CORR_XB / per_g_full) chg = 256 * CORR_XB / per_g_full;
     chg = chg / 4 * 4;
     if (chg < 4) chg = 4;
     const int64_t nchi4 = round_up(p.nchi, 4);
-    p.chg = (int)(chg < nchi4 ? chg : nchi4);
+    const int64_t passes = cdiv(nchi4, chg);
+    p.chg = (int)round_up(cdiv(nchi4, passes), 4);       // equal passes
     if (p.chg * per_g_full > 256 * CORR_XB || p.chg * per_group > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
     p.div_sd = make_fastdiv((uint32_t)sd);
     p.div_perg = make_fastdiv((uint32_t)per_g_full);

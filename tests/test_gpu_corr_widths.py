@@ -17,6 +17,10 @@ CASES = [
     (1, 130, 3, 71, 3, 3),       # two channel passes, a second chunk of seven pixels
     (1, 32, 5, 41, 15, 1),       # the widest range: displaced past both edges
     (1, 40, 9, 132, 4, 8),       # eight classes, three chunks
+    (1, 264, 5, 16, 4, 1),       # one block of pixels, more channels a pass than a wide row leaves room for
+    (1, 72, 4, 39, 5, 2),        # two classes of 20 pixels
+    (2, 136, 3, 24, 3, 8),       # eight classes of three
+    (1, 200, 3, 57, 2, 3),       # one pixel into the last unit of a chunk
     (3, 48, 7, 11, 5, 1),        # rows that start on every 2-byte boundary; the last ends with the tensor
 ]
 
