@@ -267,10 +267,16 @@ merit_status derive_sad(merit_plan *pl)
     // were: the row scan is the faster one there too (159x78, R = 32: 59.5 against 17.1; 16x16 with R = 16 and 8 by 1.6
     // and 1.2, 8x8 by 1.35 and 1.14, over 110 frames).
     const bool rowscan_ok = W % 4 == 0 || (W >= 4 && (int64_t)p.nby * p.nbx >= 64);
+    // R = 16: the elimination kernel, one block a workgroup, where the two-blocks-per-wavefront kernel below, whose wavefront
+    // scans all of a block's candidates, leaves the chip idle: from 64 blocks (the plan tests hold smaller frames there; 76x144:
+    // 10.5 against 6.8 us in a graph) to 1200 (288x416 11.0 against 7.0, 480x640 11.2 against 9.6, white noise 11.2 against
+    // 9.8; 701x1003 17.5 against 16.1, but noise 17.5 against 19.1; 720x1280 15.3 against 18.8).
+    const bool eliminate16 = rowscan_ok && B == 16 && R == 16 && pl->tile_req[1] <= 0 && (int64_t)p.nby * p.nbx >= 64 &&
+                             (int64_t)p.nby * p.nbx <= 1200;
     if (rowscan_ok && B == 16 && (R == 16 || R == 32) && pl->tile_req[1] != 1) {
         // Four blocks a workgroup share a window and its sums; one block a workgroup, split among four wavefronts, is the
         // finer grain (R = 32, us: 540x960 20.1 against 23.9, 720x1280 28.3 against 35.9, 1080x1920 53.5 against 53.0)
-        const int64_t bpw = R == 32 && (int64_t)p.nby * p.nbx < 6000 && pl->tile_req[1] <= 0 ? 1 : 4;
+        const int64_t bpw = eliminate16 ? 1 : R == 32 && (int64_t)p.nby * p.nbx < 6000 && pl->tile_req[1] <= 0 ? 1 : 4;
         const int64_t c4 = cdiv(bpw * 16 + 2 * R, 4);
         if (fastdiv_ok((16 + 2 * R) * c4, c4)) {
             p.variant = SAD_ROWSCAN_B16;
@@ -287,7 +293,7 @@ merit_status derive_sad(merit_plan *pl)
     // two blocks per wavefront, eight per workgroup: 8x8 and 16x16 blocks
     // with R = 8 or 16 (a tile request of four blocks per workgroup keeps the one-block-per-wavefront
     // kernel there)
-    if (rowscan_ok && ((B == 8 || B == 16) && (R == 8 || R == 16)) && pl->tile_req[1] != 1 &&
+    if (rowscan_ok && ((B == 8 || B == 16) && (R == 8 || R == 16)) && !eliminate16 && pl->tile_req[1] != 1 &&
         pl->tile_req[1] != 4) {
         const int64_t c4 = cdiv(8 * B + 2 * R, 4);
         if (fastdiv_ok((B + 2 * R) * c4, c4)) {

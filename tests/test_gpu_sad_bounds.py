@@ -39,6 +39,8 @@ def _frames(kind, H, W, rng):
     (17, 20, 32, 4), (50, 132, 32, 4),        # four blocks a workgroup, the last one ragged
     (128, 136, 32, 4), (130, 130, 32, 4),
     (50, 132, 16, 4), (130, 130, 16, 4),      # R = 16: fewer columns than lanes
+    (130, 130, 16, 1), (17, 1030, 16, 1),     # ... one block a workgroup: from 64 blocks on
+    (1030, 5, 16, 1), (260, 70, 16, 1),
 ])
 def test_exact(kind, H, W, R, blocks):
     cur, ref = _frames(kind, H, W, np.random.default_rng(H * W + R))
