@@ -23,9 +23,10 @@
 namespace merit {
 
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float2v __attribute__((ext_vector_type(2)));
 
 // Staging of the covering sub-tensor: every element is a real (clamped) pixel.  RAGGED = W % 4 != 0.
-template <bool RAGGED>
+template <bool RAGGED, int NT>
 __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float *__restrict__ img, float *in, int x0,
                                               int y0, int RH, int tid)
 {
@@ -34,12 +35,12 @@ __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float 
         const int P4 = p.PI >> 2, W4 = p.W >> 2, cut = p.W & 3;
         const int g0 = (x0 - p.c4) >> 2;                  // first staged 4-column group (may be < 0)
         const int total = RH * P4;
-        for (int e0 = tid; e0 < total; e0 += 256 * SB) {
+        for (int e0 = tid; e0 < total; e0 += NT * SB) {
             float4v v[SB];
             int g4[SB];
 #pragma unroll
             for (int b = 0; b < SB; ++b) {
-                const int e = min(e0 + 256 * b, total - 1);
+                const int e = min(e0 + NT * b, total - 1);
                 const int r = (int)fdiv((uint32_t)e, p.div_p4);
                 g4[b] = g0 + (e - r * P4);
                 const int gyy = min(max(y0 - p.c + r, 0), p.H - 1);
@@ -59,12 +60,12 @@ __device__ __forceinline__ void stage_clamped(const BilatParams &p, const float 
                     o.x = cut == 1 ? v[b].w : (cut == 2 ? v[b].z : v[b].y);
                     o.y = cut == 3 ? v[b].z : v[b].w;
                 }
-                if (e0 + 256 * b < total) reinterpret_cast<float4v *>(in)[e0 + 256 * b] = o;
+                if (e0 + NT * b < total) reinterpret_cast<float4v *>(in)[e0 + NT * b] = o;
             }
         }
     } else {
         const int total = RH * p.PI;
-        for (int e = tid; e < total; e += 256) {
+        for (int e = tid; e < total; e += NT) {
             const int r = e / p.PI;
             const int cc = e - r * p.PI;
             const int gyy = min(max(y0 - p.c + r, 0), p.H - 1);
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const
         wxl[tid] = __builtin_amdgcn_logf(gx[tid]);        // log2
         wyl[tid] = gy[tid];
     }
-    stage_clamped<RAGGED>(p, img, in, x0, y0, RH, tid);
+    stage_clamped<RAGGED, 256>(p, img, in, x0, y0, RH, tid);
     __syncthreads();
 
     // outputs (row0 + 4j, col), j < 4; staged column of tap a2 for output column col:
@@ -151,21 +152,21 @@ __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const
 }
 
 // ---------------------------------------------------------------------------
-// Windows up to 16 taps wide: the same tile and staging, but a thread makes four adjacent
-// outputs of one row and the window length is a template parameter.  A window row is then
-// K + 3 consecutive staged pixels = a few aligned 16-byte LDS reads for 4 K taps (instead of
-// one 4-byte read per tap), every tap index is an immediate, and the centre pixels are one
-// aligned 16-byte read (staged column of output column j is j + c4 - c + a2; at a2 = c that
-// is j + c4).  Lanes 0-15 of a wavefront take the 16 column groups of one row.
+// Windows up to 16 taps wide: the same staging, but a thread makes J adjacent outputs of one row and the window length is
+// a template parameter: a window row is K + J - 1 staged pixels for J K taps and every tap index is an immediate.
+//   J = 2, 512 threads on 16 x 64 outputs: frames that fill the chip.  (Four outputs of 256 threads, as this was, save LDS
+//     reads, which do not bound it, and leave half the wavefronts to hide the exponentials' latency behind: k = 9 on 1080x1920
+//     32.0 -> 28.8 us a launch in a graph, k = 13 on 720x1280 30.0 -> 28.2.)
+//   J = 1, 256 threads on 4 x 64 outputs: smaller frames, where a thread's chain of J K^2 taps is the whole launch (k = 13 on
+//     120x160 10.6 -> 4.9, on 480x640 16.9 -> 10.9; k = 9 on 240x320 6.3 -> 4.2).
 // ---------------------------------------------------------------------------
-template <int K, bool NEG, bool RAGGED>
-__global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const float *__restrict__ x,
+template <int K, bool NEG, bool RAGGED, int J, int NT>
+__global__ __launch_bounds__(NT) void merit_bilateral_rows(BilatParams p, const float *__restrict__ x,
                                                            const float *__restrict__ gx,
                                                            const float *__restrict__ gy, float *__restrict__ y)
 {
-    constexpr int TH = 16, TW = 64;
+    constexpr int TW = 64, TPR = TW / J, TH = NT / TPR;         // threads per row of the tile, its rows
     constexpr int C = K / 2, C4 = (C + 3) / 4 * 4, D = C4 - C;
-    constexpr int NW = (D + K + 3 + 3) / 4;               // 16-byte groups of one window row
     constexpr int RH = TH + K - 1;
     extern __shared__ __align__(16) float smem[];
     float *in = smem;                                     // [RH][PI]
@@ -189,20 +190,18 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
         wxl[tid] = __builtin_amdgcn_logf(gx[tid]);        // log2
         wyl[tid] = gy[tid];
     }
-    stage_clamped<RAGGED>(p, img, in, x0, y0, RH, tid);
+    stage_clamped<RAGGED, NT>(p, img, in, x0, y0, RH, tid);
     __syncthreads();
 
-    const int q = tid & 15, row = tid >> 4;               // column group, output row
+    const int q = tid % TPR, row = tid / TPR;             // column group, output row
     // the scale in a vector register: a multiply-add with a scalar-register operand issues at
     // two thirds of the rate of one whose operands are all vector registers (measured)
     float sc = p.scale;
     asm("" : "+v"(sc));
-    const float *base = in + row * p.PI + 4 * q;
-    const float4v c4v = *reinterpret_cast<const float4v *>(base + C * p.PI + C4);
-    const float cenv[4] = {c4v.x, c4v.y, c4v.z, c4v.w};
-    float cen[4], wsum[4], wxsum[4];
+    const float *base = in + row * p.PI + J * q;
+    float cen[J], wsum[J], wxsum[J];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { cen[j] = cenv[j] * sc; wsum[j] = 0.0f; wxsum[j] = 0.0f; }
+    for (int j = 0; j < J; ++j) { cen[j] = base[C * p.PI + C4 + j] * sc; wsum[j] = 0.0f; wxsum[j] = 0.0f; }
     float lgx[K];
 #pragma unroll
     for (int a = 0; a < K; ++a) lgx[a] = wxl[a];
@@ -210,18 +209,15 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
     for (int a1 = 0; a1 < K; ++a1) {
         const float gyv = wyl[a1];
         const float *rowp = base + a1 * p.PI;
-        float w[4 * NW];
+        float w[K + J - 1];
 #pragma unroll
-        for (int g = 0; g < NW; ++g) {
-            const float4v h = *reinterpret_cast<const float4v *>(rowp + 4 * g);
-            w[4 * g] = h.x; w[4 * g + 1] = h.y; w[4 * g + 2] = h.z; w[4 * g + 3] = h.w;
-        }
-        float rs[4], rxs[4];
+        for (int i = 0; i < K + J - 1; ++i) w[i] = rowp[D + i];
+        float rs[J], rxs[J];
 #pragma unroll
         for (int a2 = 0; a2 < K; ++a2)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = w[j + D + a2];
+            for (int j = 0; j < J; ++j) {
+                const float v = w[j + a2];
                 const float d = fmaf(-v, sc, cen[j]);
                 const float e = __builtin_amdgcn_exp2f(NEG ? fmaf(-d, d, lgx[a2]) : fmaf(d, d, lgx[a2]));
                 if (a2 == 0) {                            // the row sums start at the first tap
@@ -233,24 +229,19 @@ __global__ __launch_bounds__(256) void merit_bilateral_rows(BilatParams p, const
                 }
             }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < J; ++j) {
             wsum[j] = fmaf(gyv, rs[j], wsum[j]);
             wxsum[j] = fmaf(gyv, rxs[j], wxsum[j]);
         }
     }
-    const int gyo = y0 + row, gxo = x0 + 4 * q;
+    const int gyo = y0 + row, gxo = x0 + J * q;
     if (gyo < p.H) {
         float *dst = y + (size_t)n * p.H * p.W + (size_t)gyo * p.W + gxo;
-        if (!RAGGED) {
-            if (gxo < p.W)
-                *reinterpret_cast<float4v *>(dst) = (float4v){wxsum[0] / wsum[0], wxsum[1] / wsum[1],
-                                                               wxsum[2] / wsum[2], wxsum[3] / wsum[3]};
-        } else if (gxo + 3 < p.W) {
-            const float4v o = {wxsum[0] / wsum[0], wxsum[1] / wsum[1], wxsum[2] / wsum[2], wxsum[3] / wsum[3]};
-            __builtin_memcpy(dst, &o, 16);
+        if (J == 2 && !RAGGED) {                          // (rows of whole pairs)
+            if (gxo < p.W) *reinterpret_cast<float2v *>(dst) = (float2v){wxsum[0] / wsum[0], wxsum[J - 1] / wsum[J - 1]};
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < J; ++j)
                 if (gxo + j < p.W) dst[j] = wxsum[j] / wsum[j];
         }
     }
@@ -260,8 +251,9 @@ template <int K, bool RAGGED>
 static hipError_t launch_bil_rows(const BilatParams &p, const float *x, const float *gx, const float *gy, float *y,
                                   hipStream_t s, uint32_t grid)
 {
-    const auto k = p.neg ? merit_bilateral_rows<K, true, RAGGED> : merit_bilateral_rows<K, false, RAGGED>;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, gx, gy, y);
+    const auto k = p.J == 1 ? (p.neg ? merit_bilateral_rows<K, true, RAGGED, 1, 256> : merit_bilateral_rows<K, false, RAGGED, 1, 256>)
+                            : (p.neg ? merit_bilateral_rows<K, true, RAGGED, 2, 512> : merit_bilateral_rows<K, false, RAGGED, 2, 512>);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(p.NT), (size_t)p.lds_bytes, s, p, x, gx, gy, y);
     return hipGetLastError();
 }
 

@@ -409,7 +409,8 @@ hipError_t launch_sepfilter(const SepParams &p, const float *x, const float *kx,
 struct BilatParams {
     int N, H, W, k;
     int c, c4;             // window offset k/2; the staged columns start at x0 - c4 (c rounded up to 4)
-    int tiles_y, tiles_x;  // 16 x 64 output tiles
+    int J, NT;             // outputs of a thread, threads of a workgroup
+    int tiles_y, tiles_x;  // output tiles of J NT / 64 x 64
     int PI;                // LDS row pitch in floats (a multiple of 4)
     int lds_bytes;
     float scale;           // sqrt(|norm| log2 e): exp(d*d*norm) = 2^(-+ (d*scale)^2); set per call

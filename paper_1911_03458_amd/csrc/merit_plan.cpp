@@ -423,10 +423,17 @@ merit_status derive_bilateral(merit_plan *pl)
     BilatParams &p = pl->bil;
     p.N = (int)N; p.H = (int)H; p.W = (int)W; p.k = (int)k; p.c = (int)c;
     p.c4 = (int)round_up(c, 4);
-    p.tiles_y = (int)cdiv(H, 16);
+    // Windows of up to 16 taps: one output a thread on frames of up to 400 16 x 64 tiles, and of up to 1200 from 9 taps on,
+    // else two (k = 9: 720x1280 14.2 us against 15.4, 1080x1920 29.6 against 28.8; k = 3: 333x1203 3.7 both, 720x1280 5.3
+    // against 4.6).  Longer windows: merit_bilateral_tile's 16 x 64 outputs on 256 threads.
+    const int64_t tiles16 = N * cdiv(H, 16) * cdiv(W, 64);
+    p.J = k > 16 ? 4 : (tiles16 <= 400 || (k >= 9 && tiles16 <= 1200) ? 1 : 2);
+    p.NT = k <= 16 && p.J == 2 ? 512 : 256;
+    const int64_t TH = p.J * p.NT / 64;
+    p.tiles_y = (int)cdiv(H, TH);
     p.tiles_x = (int)cdiv(W, 64);
     p.PI = (int)round_up(64 + p.c4 + (k - 1 - c), 4);
-    const int64_t RH = 16 + k - 1;
+    const int64_t RH = TH + k - 1;
     p.lds_bytes = (int)((RH * p.PI + 2 * k + 4) * 4);     // + one 16-byte group: whole-group reads of the last row
     p.scale = 0.0f; p.neg = 1;
     const int64_t grid = N * p.tiles_y * p.tiles_x;
@@ -442,9 +449,9 @@ merit_status derive_bilateral(merit_plan *pl)
     merit_launch_info &li = pl->info;
     li.kernel = k <= 16 ? "merit_bilateral_rows" : "merit_bilateral_tile";   // four outputs along a row / down a column
     li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
-    li.block[0] = 256; li.block[1] = 1; li.block[2] = 1;
+    li.block[0] = p.NT; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = p.lds_bytes;
-    li.tile[0] = 1; li.tile[1] = 16; li.tile[2] = 64; li.tile[3] = k; li.tile[4] = k;
+    li.tile[0] = 1; li.tile[1] = TH; li.tile[2] = 64; li.tile[3] = k; li.tile[4] = k;
     return MERIT_OK;
 }
 
