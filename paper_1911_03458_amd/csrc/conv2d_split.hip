@@ -140,9 +140,9 @@ __global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const 
                 const bool in = (RAGGED ? c : 0) + 8 * x_hh[k] >= early;
                 uint32_t voff = in ? x_voff[k] + (uint32_t)(c * chbytes) : OOB;
                 if constexpr (XU == 0) {
-                    const int over = (int)(base + voff) + 16 - p.Cin * chbytes;      // (OOB: far below zero)
-                    xmoved[c] = over > 0 ? 8u * (uint32_t)over : 0u;
-                    voff -= xmoved[c] >> 3;
+                    const uint32_t moved = moved_to_end(base + voff, (uint32_t)(p.Cin * chbytes));
+                    xmoved[c] = 8u * moved;
+                    voff -= moved;
                 }
                 xv[k][c] = __builtin_amdgcn_raw_buffer_load_b128(rx, voff, base, 0);
             }

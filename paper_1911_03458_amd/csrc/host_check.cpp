@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "merit.h"
+#include "merit_internal.h"
 
 namespace {
 
@@ -140,6 +141,18 @@ void refuse(merit_plan *plan)
     }
 }
 
+// the move of a load that would cross a tensor's end: ends with the tensor, leaves every other load where it was, and none for
+// the kernels' out-of-range offset, whatever is added to it
+void check_moves()
+{
+    for (const uint32_t bytes : {16u, 18u, 98u, 4096u, 1u << 20, (1u << 30) - 2u, 1u << 30}) {
+        for (uint32_t back = 2; back <= 64 && back <= bytes; back += 2)
+            CHECK(merit::moved_to_end(bytes - back, bytes) == (back < 16 ? 16 - back : 0));
+        CHECK(merit::moved_to_end(0, bytes) == 0);
+        for (const uint32_t more : {0u, 2u, bytes - 16u, bytes}) CHECK(merit::moved_to_end(0x80000000u + more, bytes) == 0);
+    }
+}
+
 void take(merit_status s, merit_plan *plan, int *made)
 {
     CHECK(s >= MERIT_OK && s <= MERIT_ERR_SCRATCH_LIMIT);
@@ -204,6 +217,7 @@ int main(int argc, char **argv)
 {
     const int nthreads = argc > 1 ? std::atoi(argv[1]) : 1;
     int made = 0;
+    check_moves();
     if (nthreads <= 1) {
         made = sweep(1911, 120);
     } else {

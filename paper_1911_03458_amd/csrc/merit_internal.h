@@ -25,6 +25,14 @@ inline FastDiv make_fastdiv(uint32_t d)
     f.magic = d == 1u ? 0u : (uint32_t)((0x100000000ull / d) + 1ull);   // d == 1 does not fit: see fdiv
     return f;
 }
+
+// Bytes by which the 16-byte load at byte `at` of a tensor of `bytes` (16 to 2^30) is moved down to end with it.  None for an
+// offset past the tensor, whose load comes back as zeros.
+__host__ __device__ inline uint32_t moved_to_end(uint32_t at, uint32_t bytes)
+{
+    return at < bytes && bytes - at < 16u ? 16u - (bytes - at) : 0u;
+}
+
 #ifdef __HIPCC__
 __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f)
 {
