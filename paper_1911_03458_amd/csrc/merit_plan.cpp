@@ -926,7 +926,7 @@ merit_status derive_conv(merit_plan *pl)
             q.rows_out_max = (int)R;
             q.pool_halo = halo ? 1 : 0;
             q.PH = (int)(OH / 2); q.PW = (int)(OW / 2);
-            int64_t nb = 256 / (N * q.co_groups);
+            int64_t nb = 256 / (N * q.co_groups > 0 ? N * q.co_groups : 1);
             if (nb < 1) nb = 1;
             int64_t pb = halo ? hp : round_up(cdiv(q.PH, nb), hp);
             q.PB = (int)pb;

@@ -109,3 +109,13 @@ def test_launch_info_names_the_kernel_that_runs():
 ])
 def test_depthwise_layers_take_the_faster_kernel(shape, kernel):
     assert mb.merit_plan_conv2d_depthwise(*shape).launch_info()["kernel"] == kernel
+
+
+@pytest.mark.parametrize("shape", [
+    (0, 64, 56, 56, 64, 3, 3, 1, 1, 1, 1), (0, 16, 12, 20, 64, 3, 3, 1, 1, 1, 1), (0, 256, 56, 56, 256, 3, 3, 1, 1, 1, 1),
+    (0, 3, 64, 64, 64, 7, 7, 2, 2, 3, 3),
+])
+def test_fused_pooling_of_an_empty_batch(shape):
+    plan = mb.merit_plan_conv2d_pool(*shape)
+    assert plan.out_shape()[0] == 0 and plan.launch_info()["grid"][0] == 0
+    assert mb.lib().merit_conv2d(plan.handle, None, None, None, None) == mb.MERIT_OK
