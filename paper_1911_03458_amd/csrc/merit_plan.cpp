@@ -618,7 +618,9 @@ void derive_split(merit_plan *pl)
     }
 }
 
-merit_status derive_conv(merit_plan *pl)
+// Every family but the two forms for few pixels and for 1x1 layers (derive_px, derive_split), which only an unpooled layer
+// takes: the convolution of a plan that pools in a launch of its own is planned here too, and sums in the fused form's order.
+merit_status derive_conv_families(merit_plan *pl)
 {
     const merit_plan_desc &d = pl->desc;
     pl->use_px = pl->use_split = pl->use_na = 0;
@@ -1250,7 +1252,7 @@ merit_status derive_conv(merit_plan *pl)
         merit_plan *plain = new (std::nothrow) merit_plan(*pl);
         if (plain) {
             plain->desc.op = p.relu ? MERIT_OP_CONV_DOT_RELU : MERIT_OP_CONV_DOT;
-            if (derive_conv(plain) == MERIT_OK && plain->conv.variant == CONV_CHWS && plain->est_units > 0.0) {
+            if (derive_conv_families(plain) == MERIT_OK && plain->conv.variant == CONV_CHWS && plain->est_units > 0.0) {
                 const double unit = 1.5 + 0.058 * (double)Cin * (double)(kh * kw) / 9.0;
                 const double conv_bytes = (double)N * (double)Cout * (double)ohw * 2.0;
                 const double t_fused = 4.0 + pl->est_units * unit;
@@ -1269,6 +1271,12 @@ merit_status derive_conv(merit_plan *pl)
             delete plain;
         }
     }
+    return MERIT_OK;
+}
+
+merit_status derive_conv(merit_plan *pl)
+{
+    if (const merit_status st = derive_conv_families(pl); st != MERIT_OK) return st;
     derive_px(pl);
     derive_split(pl);
     return MERIT_OK;

@@ -119,3 +119,24 @@ def test_fused_pooling_of_an_empty_batch(shape):
     plan = mb.merit_plan_conv2d_pool(*shape)
     assert plan.out_shape()[0] == 0 and plan.launch_info()["grid"][0] == 0
     assert mb.lib().merit_conv2d(plan.handle, None, None, None, None) == mb.MERIT_OK
+
+
+@pytest.mark.parametrize("shape,tile", [
+    ((2, 1024, 18, 18, 512, 3, 3, 1, 1, 1, 1), None),                 # the unfused layer splits the channels among the wavefronts
+    ((1, 552, 50, 92, 88, 3, 3, 1, 1, 1, 1), None),
+    ((1, 536, 96, 26, 416, 3, 3, 1, 1, 1, 1), (0, 0, 8, 32)),
+    ((4, 256, 40, 56, 256, 3, 3, 1, 1, 1, 1), (0, 0, 8, 64)),
+])
+def test_launch_info_of_pooling_in_two_launches_is_the_multi_pass_kernels(shape, tile):
+    """Its convolution sums in the order of the fused form, whatever the unfused layer's own plan takes; the figures are of
+    the launch that runs: 128 or 256 pixels x a multiple of 32 channels."""
+    N, Cin, H, W, Cout = shape[:5]
+    li = mb.merit_plan_conv2d_pool(*shape).launch_info()
+    assert li["kernel"] == "merit_conv2d_chws+merit_maxpool_f16"
+    unfused = _conv(*shape)
+    if tile:
+        unfused.set_tile(tile)
+        u = unfused.launch_info()
+        assert (li["grid"][0], li["lds_bytes"], li["tile"][1]) == (u["grid"][0], u["lds_bytes"], u["tile"][1])
+    blocks = -(-Cout // li["tile"][1])
+    assert li["grid"][0] in [min(256, N * -(-H * W // m) * blocks) for m in (128, 256)] and li["tile"][3] == W
