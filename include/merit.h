@@ -292,8 +292,9 @@ merit_status merit_conv2d(const merit_plan *plan, const void *x_f16, const void 
  *                                    MERIT_ERR_UNSUPPORTED if the plan takes no packed weights.
  *                                    Those that do: 1x1, 3x3 and 5x5 layers on a multiple of 8
  *                                    and at least 32 input and more than 32 output channels that
- *                                    run on merit_conv2d_chws or merit_conv2d_px, without an added
- *                                    tensor or pooling (ask this call, not the kernel's name)
+ *                                    run on merit_conv2d_chws, merit_conv2d_split or
+ *                                    merit_conv2d_px, without an added tensor or pooling (ask
+ *                                    this call, not the kernel's name)
  *   merit_conv2d_pack_weights        w_f16 -> packed (device memory of that size, owned by the
  *                                    caller, 16-byte aligned); enqueued on the stream
  *   merit_conv2d_packed              merit_conv2d with the packed copy in place of w_f16; same

@@ -52,7 +52,7 @@ constexpr int WAVES = SPLIT_WAVES, NT = WAVES * 64;
 // K: window edge (3 or 5).  PXB: 32-pixel blocks of the tile.  XU: staging units of 8 channels x 8 pixels per lane and
 // slice (0: one, of rows shorter than 8 pixels).  RAGGED: Cin % 8 != 0.
 template <int K, int PXB, int XU, bool PACKED, bool RAGGED>
-__global__ __launch_bounds__(NT, 2) void merit_conv2d_chws(SplitParams p, const uint16_t *__restrict__ x,
+__global__ __launch_bounds__(NT, 2) void merit_conv2d_split(SplitParams p, const uint16_t *__restrict__ x,
                                                            const uint16_t *__restrict__ w, uint16_t *__restrict__ y)
 {
     static_assert(!(PACKED && RAGGED), "packed weights: whole groups of 8 channels");
@@ -397,7 +397,7 @@ template <int K, int PXB, int XU, bool PACKED, bool RAGGED>
 hipError_t launch_one(const SplitParams &p, const void *x, const void *w, void *y, hipStream_t s)
 {
     static std::atomic<int> raised{0};
-    void (*k)(SplitParams, const uint16_t *, const uint16_t *, uint16_t *) = merit_conv2d_chws<K, PXB, XU, PACKED, RAGGED>;
+    void (*k)(SplitParams, const uint16_t *, const uint16_t *, uint16_t *) = merit_conv2d_split<K, PXB, XU, PACKED, RAGGED>;
     if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(k), raised); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3((uint32_t)(p.N * p.tiles * p.co_groups)), dim3(NT), (size_t)p.lds_bytes, s, p,
                        reinterpret_cast<const uint16_t *>(x), reinterpret_cast<const uint16_t *>(w),

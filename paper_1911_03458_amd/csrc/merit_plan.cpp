@@ -611,6 +611,7 @@ void derive_split(merit_plan *pl)
         pl->split = p;
         pl->use_split = 1;
         merit_launch_info &li = pl->info;
+        li.kernel = "merit_conv2d_split";
         li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
         li.block[0] = SPLIT_WAVES * 64; li.block[1] = 1; li.block[2] = 1;
         li.lds_bytes = p.lds_bytes;

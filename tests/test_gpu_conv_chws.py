@@ -95,24 +95,29 @@ def test_chws_against_the_oracle_raw_and_packed(mb, case, dil, relu, tile):
     rng = np.random.default_rng(abs(hash(case)) % 2 ** 31)
     x = rng.standard_normal((N, Cin, H, W)).astype(np.float16)
     w = (rng.standard_normal((Cout, Cin, kh, kw)) / np.sqrt(Cin * kh * kw)).astype(np.float16)
-    if dil != (1, 1):
-        plan = mb.merit_plan_conv2d_dilated(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, *dil, relu)
-    elif relu:
-        plan = mb.merit_plan_conv2d_relu(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw)
-    else:
-        plan = mb.merit_plan_conv2d(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw)
+    def make(images):
+        if dil != (1, 1):
+            return mb.merit_plan_conv2d_dilated(images, *case[1:], *dil, relu)
+        return (mb.merit_plan_conv2d_relu if relu else mb.merit_plan_conv2d)(images, *case[1:])
+
+    plan = make(N)
     if tile is not None:
         plan.set_tile(tile)
+    copies = 1                             # as many images as this kernel takes over at, the given ones repeated
+    while plan.launch_info()["kernel"] == "merit_conv2d_split":
+        copies *= 2
+        plan = make(copies * N)
     li = plan.launch_info()
     print("chws", case, dil, relu, li, flush=True)
     assert li["kernel"] == "merit_conv2d_chws" and li["block"][0] in (512, 768) and li["lds_bytes"] <= 160 * 1024
-    dx, dw_ = dev(x), dev(w)
+    dx, dw_ = dev(np.tile(x, (copies, 1, 1, 1))), dev(w)
     buf, y, pad = guarded(plan.out_shape())
     mb.merit_conv2d(plan, dx, dw_, y)
     torch.cuda.synchronize()
     assert canary_ok(buf, pad), "write outside the output"
     got = y.cpu().numpy()
     ref = oracle.conv2d(x, w, (sh, sw), (ph, pw), relu=bool(relu), dilation=dil).astype(np.float64)
+    ref = np.tile(ref, (copies, 1, 1, 1))
     err = np.abs(got.astype(np.float64) - ref)
     tol = 2e-2 * np.abs(ref) + 1e-3
     assert np.all(err <= tol), f"max excess {np.max(err - tol)} at {np.unravel_index(np.argmax(err - tol), err.shape)}"

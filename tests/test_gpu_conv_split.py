@@ -1,4 +1,4 @@
-"""Many-channel layers on few pixels: the form of merit_conv2d_chws that splits the channels among the wavefronts."""
+"""Many-channel layers on few pixels: the kernel that splits the channels among the wavefronts."""
 import numpy as np
 import pytest
 import torch
@@ -43,7 +43,7 @@ def test_against_the_oracle_raw_and_packed(case):
     li = plan.launch_info()
     print(case, li, flush=True)
     ohw = plan.out_shape()[2] * plan.out_shape()[3]
-    assert li["kernel"] == "merit_conv2d_chws" and li["tile"][1] == 32
+    assert li["kernel"] == "merit_conv2d_split" and li["tile"][1] == 32
     oh, ow = plan.out_shape()[2:]
     tiles = [-(-ohw // 32), -(-ohw // 64)] + [-(-oh // (m // t)) * -(-ow // t) for m in (32, 64) for t in (8, 16, 32)]
     assert li["grid"][0] in [N * -(-Cout // 32) * t for t in tiles]      # this form's tiles

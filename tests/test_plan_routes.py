@@ -28,7 +28,7 @@ def test_a_batch_may_be_larger_than_one_image():
 
 @pytest.mark.parametrize("shape,tile", [
     ((3, 40, 138, 10, 72, 3, 3, 3, 3, 2, 1), None),
-    ((2, 72, 129, 12, 40, 3, 3, 2, 4, 0, 0), None),
+    ((64, 72, 129, 12, 40, 3, 3, 2, 4, 0, 0), None),       # (two images: the channels split among the wavefronts)
     ((2, 48, 91, 18, 74, 3, 3, 4, 4, 2, 1), None),
     ((1, 128, 199, 6, 70, 3, 3, 2, 2, 0, 0), None),
     ((2, 64, 150, 4, 256, 3, 3, 2, 2, 1, 1), (0, 0, 12, 64)),

@@ -19,15 +19,15 @@ def mb():
     return binding
 
 
-def _one(mb, shape, seed):
+def _one(mb, shape, seed, kernel="merit_conv2d_chws", tile=None):
     N, Cin, H, W, Cout = shape
     g = torch.Generator(device="cpu").manual_seed(seed)
     x = torch.randn((N, Cin, H, W), generator=g).to(torch.float16).to("cuda:0")
     w = (torch.randn((Cout, Cin, 3, 3), generator=g) / (Cin * 9) ** 0.5).to(torch.float16).to("cuda:0")
     plan = mb.merit_plan_conv2d(N, Cin, H, W, Cout, 3, 3, 1, 1, 1, 1)
-    if plan.launch_info()["kernel"] != "merit_conv2d_chws":
-        plan.set_tile((0, 0, 8, 64))
-    assert plan.launch_info()["kernel"] == "merit_conv2d_chws"
+    if tile:
+        plan.set_tile(tile)
+    assert plan.launch_info()["kernel"] == kernel
     # the existing entry points: the caller brings the packed buffer
     packed = mb.merit_conv2d_pack_weights(plan, w)
     ref = mb.merit_conv2d_packed(plan, x, packed)
@@ -46,13 +46,14 @@ def _one(mb, shape, seed):
 
 def test_two_calls_in_a_row_the_second_smaller(mb):
     _one(mb, (2, 256, 28, 56, 256), 1)       # 1.18 MB of packed weights
-    _one(mb, (1, 64, 20, 24, 64), 2)         # 74 KB: the rest of the buffer still holds the first call's
+    _one(mb, (1, 64, 20, 24, 64), 2, tile=(0, 0, 8, 32))    # 74 KB: the rest of the buffer still holds the first call's
+    _one(mb, (1, 64, 20, 24, 64), 4, kernel="merit_conv2d_split")       # (reads the weights as they lie: no buffer)
     _one(mb, (2, 256, 28, 56, 256), 3)       # and back, with other weights
 
 
 def test_a_plan_beyond_the_scratch_limit_is_refused(mb):
     plan = mb.merit_plan_conv2d(1, 1024, 16, 16, 1024, 3, 3, 1, 1, 1, 1)     # 18.9 MB of packed weights
-    assert plan.launch_info()["kernel"] == "merit_conv2d_chws"
+    assert plan.launch_info()["kernel"] == "merit_conv2d_split"              # (refused too, though it reads them as they lie)
     assert mb.merit_plan_packed_weights_bytes(plan) > mb.MERIT_NOALLOC_SCRATCH_BYTES
     x = torch.zeros((1, 1024, 16, 16), dtype=torch.float16, device="cuda:0")
     w = torch.zeros((1024, 1024, 3, 3), dtype=torch.float16, device="cuda:0")
