@@ -263,8 +263,14 @@ merit_status merit_plan_launch_info(const merit_plan *plan, merit_launch_info *o
  * pixels x 64 channels, 32 input channels per pass) and 12 x 64 (8 multiplying +
  * 4 moving wavefronts, 256 pixels x 128 channels); a fused-pooling plan on many
  * channels takes 8 x 64, 8 x 32 and 12 x 64.  Block matching
- * tile[1] = blocks per workgroup (1, 4 or 8; a value the shape has no kernel for
- * keeps the library's choice); separable filter tile[1] = staged rows per workgroup
+ * tile[1]: 1 = merit_sad_generic, the kernel for any shape; 4 = merit_sad_rowscan16
+ * with four blocks per workgroup (16x16 blocks, range 16 or 32), and merit_sad_generic
+ * where the library would take merit_sad_rowscan_pair; any other value = the library's
+ * choice without merit_sad_rowscan16's form of one block per workgroup (range 16: then
+ * merit_sad_rowscan_pair).  The tile[1] that merit_plan_launch_info reports is the
+ * number of blocks side by side in a workgroup of the plan (1 also for that form; 7 in
+ * each of tile[0] = 4 block rows for merit_sad_rowscan_seven) and need not, as a
+ * request, give the same plan; separable filter tile[1] = staged rows per workgroup
  * at most (output rows = that minus k - 1, rounded down to a multiple of 4).  On error
  * the plan is unchanged.  Not safe to
  * call while another thread launches with the same plan. */
@@ -275,8 +281,13 @@ merit_status merit_plan_set_tile(merit_plan *plan, const int64_t tile[MERIT_MAX_
  * y_f16: [N,Cout,OH,OW] binary16.  Products accumulate in fp32 on the matrix
  * cores and are rounded once (nearest even) to binary16.  The order of a sum is
  * the plan's: 1x1 layers at stride 1 split the channels over wavefronts by tile,
- * and the tile follows the batch size, so that an image's result may differ in
- * the last bit between plans of different batch sizes.  (.) = Eq. 3, or its
+ * and the tile follows the batch size; 3x3 and 5x5 layers on 17 and more input
+ * channels split them over wavefronts on few pixels (merit_conv2d_split) and run
+ * through them in passes on many (merit_conv2d_chws), which follows the batch size
+ * too.  An image's result may so differ in the last bit between plans of different
+ * batch sizes, and between a plan and the pooled plan of the same layer, which never
+ * splits; a tile request (merit_plan_set_tile: 8 x 64, 8 x 32, 12 x 64) keeps the
+ * passes whatever the batch.  (.) = Eq. 3, or its
  * clipped form for a CONV_DOT_RELU plan.  For a plan from merit_plan_conv2d_pool
  * y_f16 is the pooled tensor [N,Cout,OH/2,OW/2]: the exact maximum of the rounded
  * convolution results in each window. */

@@ -140,3 +140,22 @@ def test_launch_info_of_pooling_in_two_launches_is_the_multi_pass_kernels(shape,
         assert (li["grid"][0], li["lds_bytes"], li["tile"][1]) == (u["grid"][0], u["lds_bytes"], u["tile"][1])
     blocks = -(-Cout // li["tile"][1])
     assert li["grid"][0] in [min(256, N * -(-H * W // m) * blocks) for m in (128, 256)] and li["tile"][3] == W
+
+
+def test_tile_requests_of_block_matching():
+    """What the header says of each request, and of the reported tile beside it."""
+    def kernels(block, search, shape=(480, 640)):
+        out = []
+        for request in (None, 1, 4, 8, 2):
+            plan = mb.merit_plan_sad(*shape, block, search)
+            if request:
+                plan.set_tile((0, request))
+            li = plan.launch_info()
+            out.append((li["kernel"].replace("merit_sad_", ""), li["tile"][1]))
+        return out
+    assert kernels(16, 32) == [("rowscan16<32>", 1), ("generic", 1)] + 3 * [("rowscan16<32>", 4)]
+    assert kernels(16, 16) == [("rowscan16<16>", 1), ("generic", 1), ("rowscan16<16>", 4)] + 2 * [("rowscan_pair<16,16>", 8)]
+    assert kernels(16, 8) == [("rowscan_pair<16,8>", 8), ("generic", 1), ("generic", 1)] + 2 * [("rowscan_pair<16,8>", 8)]
+    assert kernels(8, 16) == [("rowscan_pair<8,16>", 8), ("generic", 1), ("generic", 1)] + 2 * [("rowscan_pair<8,16>", 8)]
+    assert kernels(8, 4) == [("rowscan_seven", 7), ("generic", 1)] + 3 * [("rowscan_seven", 7)]
+    assert kernels(16, 32, (2160, 3840))[0] == ("rowscan16<32>", 4) and kernels(12, 5)[0] == ("generic", 1)
