@@ -159,6 +159,8 @@ __global__ __launch_bounds__(256) void merit_bilateral_tile(BilatParams p, const
 //     32.0 -> 28.8 us a launch in a graph, k = 13 on 720x1280 30.0 -> 28.2.)
 //   J = 1, 256 threads on 4 x 64 outputs: smaller frames, where a thread's chain of J K^2 taps is the whole launch (k = 13 on
 //     120x160 10.6 -> 4.9, on 480x640 16.9 -> 10.9; k = 9 on 240x320 6.3 -> 4.2).
+//   J = 4, 256 threads on 16 x 64 outputs: one or two taps on larger frames, which memory bounds: 16-byte reads and stores
+//     (two outputs a thread there: k = 2 on 2 of 1017x496 4.4 us against 3.9, k = 1 on 4 of 477x825 5.1 against 4.7).
 // ---------------------------------------------------------------------------
 template <int K, bool NEG, bool RAGGED, int J, int NT>
 __global__ __launch_bounds__(NT) void merit_bilateral_rows(BilatParams p, const float *__restrict__ x,
@@ -210,8 +212,18 @@ __global__ __launch_bounds__(NT) void merit_bilateral_rows(BilatParams p, const 
         const float gyv = wyl[a1];
         const float *rowp = base + a1 * p.PI;
         float w[K + J - 1];
+        if constexpr (J == 4) {
 #pragma unroll
-        for (int i = 0; i < K + J - 1; ++i) w[i] = rowp[D + i];
+            for (int i = 0; i < D + K + J - 1; i += 4) {
+                const float4v h = *reinterpret_cast<const float4v *>(rowp + i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e >= D && i + e < D + K + J - 1) w[i + e - D] = h[e];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < K + J - 1; ++i) w[i] = rowp[D + i];
+        }
         float rs[J], rxs[J];
 #pragma unroll
         for (int a2 = 0; a2 < K; ++a2)
@@ -237,7 +249,19 @@ __global__ __launch_bounds__(NT) void merit_bilateral_rows(BilatParams p, const 
     const int gyo = y0 + row, gxo = x0 + J * q;
     if (gyo < p.H) {
         float *dst = y + (size_t)n * p.H * p.W + (size_t)gyo * p.W + gxo;
-        if (J == 2 && !RAGGED) {                          // (rows of whole pairs)
+        if (J == 4 && !RAGGED) {                          // (rows of whole fours)
+            if (gxo < p.W) {
+                float4v o;
+#pragma unroll
+                for (int j = 0; j < J; ++j) o[j] = wxsum[j] / wsum[j];
+                *reinterpret_cast<float4v *>(dst) = o;
+            }
+        } else if (J == 4 && gxo + J <= p.W) {            // (rows on any 4-byte boundary: one store all the same)
+            float4v o;
+#pragma unroll
+            for (int j = 0; j < J; ++j) o[j] = wxsum[j] / wsum[j];
+            __builtin_memcpy(dst, &o, 16);
+        } else if (J == 2 && !RAGGED) {                   // (rows of whole pairs)
             if (gxo < p.W) *reinterpret_cast<float2v *>(dst) = (float2v){wxsum[0] / wsum[0], wxsum[J - 1] / wsum[J - 1]};
         } else {
 #pragma unroll
@@ -251,8 +275,9 @@ template <int K, bool RAGGED>
 static hipError_t launch_bil_rows(const BilatParams &p, const float *x, const float *gx, const float *gy, float *y,
                                   hipStream_t s, uint32_t grid)
 {
+    constexpr int J = K <= 2 ? 4 : 2, NT = K <= 2 ? 256 : 512;
     const auto k = p.J == 1 ? (p.neg ? merit_bilateral_rows<K, true, RAGGED, 1, 256> : merit_bilateral_rows<K, false, RAGGED, 1, 256>)
-                            : (p.neg ? merit_bilateral_rows<K, true, RAGGED, 2, 512> : merit_bilateral_rows<K, false, RAGGED, 2, 512>);
+                            : (p.neg ? merit_bilateral_rows<K, true, RAGGED, J, NT> : merit_bilateral_rows<K, false, RAGGED, J, NT>);
     hipLaunchKernelGGL(k, dim3(grid), dim3(p.NT), (size_t)p.lds_bytes, s, p, x, gx, gy, y);
     return hipGetLastError();
 }

@@ -425,10 +425,12 @@ merit_status derive_bilateral(merit_plan *pl)
     p.c4 = (int)round_up(c, 4);
     // Windows of up to 16 taps: one output a thread on frames of up to 400 16 x 64 tiles, and of up to 1200 from 9 taps on,
     // else two (k = 9: 720x1280 14.2 us against 15.4, 1080x1920 29.6 against 28.8; k = 3: 333x1203 3.7 both, 720x1280 5.3
-    // against 4.6).  Longer windows: merit_bilateral_tile's 16 x 64 outputs on 256 threads.
+    // against 4.6).  With one or two taps, which memory bounds, four from 200 tiles on (k = 2 on 2 of 1017x496, 1024 tiles:
+    // 3.9 against 4.4 with two; on 2 of 463x322, 348: 3.3 against 3.6 with one; k = 1 on 4 of 313x130, 240: 2.6 against 2.7).
+    // Longer windows: merit_bilateral_tile's 16 x 64 outputs on 256 threads, four a thread down a column.
     const int64_t tiles16 = N * cdiv(H, 16) * cdiv(W, 64);
-    p.J = k > 16 ? 4 : (tiles16 <= 400 || (k >= 9 && tiles16 <= 1200) ? 1 : 2);
-    p.NT = k <= 16 && p.J == 2 ? 512 : 256;
+    p.J = k > 16 ? 4 : k <= 2 ? (tiles16 <= 200 ? 1 : 4) : (tiles16 <= 400 || (k >= 9 && tiles16 <= 1200) ? 1 : 2);
+    p.NT = p.J == 2 ? 512 : 256;
     const int64_t TH = p.J * p.NT / 64;
     p.tiles_y = (int)cdiv(H, TH);
     p.tiles_x = (int)cdiv(W, 64);
@@ -447,7 +449,7 @@ merit_status derive_bilateral(merit_plan *pl)
     pl->out_ndim = 3;
     pl->out_shape[0] = N; pl->out_shape[1] = H; pl->out_shape[2] = W;
     merit_launch_info &li = pl->info;
-    li.kernel = k <= 16 ? "merit_bilateral_rows" : "merit_bilateral_tile";   // four outputs along a row / down a column
+    li.kernel = k <= 16 ? "merit_bilateral_rows" : "merit_bilateral_tile";
     li.grid[0] = grid; li.grid[1] = 1; li.grid[2] = 1;
     li.block[0] = p.NT; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = p.lds_bytes;
