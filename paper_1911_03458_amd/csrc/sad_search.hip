@@ -228,17 +228,22 @@ __global__ __launch_bounds__(256) void merit_sad_generic(SadParams p, const uint
 // pixels once (4 x v_alignbyte) and adds them into the partial sums of the (up to) sixteen candidates dy = r - i that
 // use this row as block row i (4 x v_sad_u8 each).  Sixteen accumulators rotate: candidate dy completes at row dy + 15
 // and its slot restarts for dy + 16.
-// The 65th column at R = 32: its bounds one candidate per lane, its sums sixteen lanes to a candidate.
+// Four blocks a workgroup, a block inside a frame of whole dwords: its pixels come from memory once more, as scalar loads
+// (64 v_readlane less a wavefront; the loads' latency shows on smaller frames, which have the other form).
+// The 65th column at R = 32: its bounds one candidate per lane, its sums too where a wavefront has half of the rows, else
+// sixteen lanes to a candidate.
 // BPW: blocks per workgroup: four, the rows of a block's candidates split between two wavefronts, or one, split among four
 // (R = 16 as well, on frames of 64 to 1200 blocks: 288x416 11.0 us on the kernel below -> 7.0, 480x640 11.2 -> 9.6).
 // Workgroups go round-robin to the XCDs, not in bands of block rows: a band of sky or water would be the whole work of
 // one of them (1080x1920: 77 us in bands, 53).
 //
 // us a launch, R = 32, full scan (one wavefront a block, in a kernel of its own) -> this: moving scenes with sensor noise,
-// 1080x1920 75.5 -> 52.5, 720x1280 41.5 -> 28.3, 480x640 24.4 -> 15.0, 120x160 16.9 -> 8.9; two unrelated scenes of that
-// kind 76.8 -> 68.5; a still picture 76 -> 47; white noise, where every block is scanned, 75.9 -> 79.4 (480x640: 24.8 ->
-// 17.5).  With every block decided by its bounds a full-HD frame takes 27 us; the rest is the scans of a sixth of the
-// blocks, which come in clusters and are dealt to the compute units by position.
+// 1080x1920 75.0 -> 51.7, 720x1280 40.6 -> 28.3, 480x640 24.0 -> 15.0, 120x160 16.8 -> 8.7; smooth textures that move by
+// block, 1088x1920, 75.0 -> 35.7; two unrelated scenes 76.8 -> 68.5; a still picture 76 -> 47.  White noise, where every
+// block is scanned by two or four wavefronts that share its rows, is the slower one on large frames: 1080x1920 75.2 -> 76.7,
+// 995x1906 75.6 -> 79.3, 2160x3840 282 -> 292, 720x1280 40.7 -> 43.2 (480x640: 24.0 -> 17.0).  (A single wavefront a block
+// there, the other one idle: 95 at 1080x1920.)  With every block decided by its bounds a full-HD frame takes 27 us; the rest
+// is the scans of a sixth of the blocks, which come in clusters and are dealt to the compute units by position.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void load_aligned16(const uint32_t *rowp, uint32_t sh, uint32_t (&r)[4])
 {
@@ -267,30 +272,37 @@ __device__ __forceinline__ void rows_of_lanes(uint32_t cl, int lane, uint32_t (&
     for (int j = 0; j < 4; ++j) crow[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((4 * (lane & 15) + j) * 4, (int)cl);
 }
 
-// The full scan of ND candidate rows from d0 on of block wb, whose pixels are `cl` (four per lane): the lowest key, the
-// same for all lanes.
+// The full scan of ND candidate rows from d0 on of block wb, whose pixels are `cl` (four per lane) and, unless that is null,
+// at `block` in memory, in rows of W4 dwords: the lowest key, the same for all lanes.
 template <int R, int ND, int PITCH4>
-__device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl, int wb, int d0, int lane)
+__device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl, const uint32_t *__restrict__ block, int W4,
+                                              int wb, int d0, int lane)
 {
     constexpr int N = 2 * R + 1, NCOL = N < 64 ? N : 64, NLEFT = N - NCOL;
+    static_assert(ND <= 64, "a candidate row per lane");
     // (a value to the compiler: with offsets that it knows it fetches the rows of all steps first, into registers that are
     // not there)
     int pitch = PITCH4;
     asm("" : "+s"(pitch));
     uint32_t c[16][4];                                             // the current block, wave-uniform
+    if (block) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+        for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[i][j] = (uint32_t)__builtin_amdgcn_readlane((int)cl, 4 * i + j);
+            for (int j = 0; j < 4; ++j) c[i][j] = block[i * W4 + j];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[i][j] = (uint32_t)__builtin_amdgcn_readlane((int)cl, 4 * i + j);
+    }
     const int o = 16 * wb + min(lane, NCOL - 1);                   // idle lanes repeat the last column
     const uint32_t sh = (uint32_t)(o & 3);
     const uint32_t *base = lds32 + d0 * pitch + (o >> 2);
     uint32_t acc[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) acc[k] = 0;
     uint32_t lbest = 0xffffffffu;                                  // (sum << 7) | row
 
-    // one window row: block rows i in [ilo, ihi] accumulate into slot (rot - i) & 15;
+    // one window row: block rows i in [ilo, ihi] accumulate into slot (rot - i) & 15, whose sum starts with row 0;
     // then candidate `fin` (if >= 0), which sits in slot (rot + 1) & 15, is complete
     auto step = [&](const uint32_t *rowp, int ilo, int ihi, int rot, int fin) __attribute__((always_inline)) {
         uint32_t r4[4];
@@ -300,13 +312,12 @@ __device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl
             if (i < ilo || i > ihi) continue;
             const int slot = (rot - i) & 15;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[slot] = __builtin_amdgcn_sad_u8(c[i][j], r4[j], acc[slot]);
+            for (int j = 0; j < 4; ++j) acc[slot] = __builtin_amdgcn_sad_u8(c[i][j], r4[j], i + j == 0 ? 0u : acc[slot]);
         }
         if (fin >= 0) {
             const int slot = (rot + 1) & 15;
             const uint32_t key = (acc[slot] << 7) | (uint32_t)fin;
             lbest = key < lbest ? key : lbest;
-            acc[slot] = 0;
         }
     };
     if constexpr (ND < 32) {
@@ -330,7 +341,25 @@ __device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl
             step(base + (ND - 1 + e) * pitch, e, 15, (ND - 1 + e) & 15, ND - 1 + e - 15);
     }
     uint32_t key = lane < NCOL ? ((lbest >> 7) << KEY_SHIFT) | ((uint32_t)(d0 + (int)(lbest & 127u)) * N + (uint32_t)lane) : 0xffffffffu;
-    if (NLEFT > 0 && pitch != 0) {                                 // the last column: sixteen lanes to a candidate, a row each
+    // (the condition on the pitch, always true, keeps this apart from the scan: in one block with it the compiler fetches all
+    // rows first, into registers that are not there)
+    if (NLEFT > 0 && ND > 24 && pitch != 0) {                      // the last column: a candidate row per lane
+        const int ol = 16 * wb + NCOL;
+        const uint32_t sl = (uint32_t)(ol & 3);
+        const int dl = min(lane, ND - 1);                          // (idle lanes repeat the last row)
+        const uint32_t *lp = lds32 + (d0 + dl) * pitch + (ol >> 2);
+        uint32_t a = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            uint32_t r4[4];
+            load_aligned16(lp + i * pitch, sl, r4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(c[i][j], r4[j], a);
+        }
+        a = (a << KEY_SHIFT) | (uint32_t)((d0 + dl) * N + NCOL);
+        key = a < key ? a : key;
+    }
+    if (NLEFT > 0 && ND <= 24 && pitch != 0) {                     // ... sixteen lanes to a candidate, a row each
         uint32_t crow[4];
         rows_of_lanes(cl, lane, crow);
         const int ol = 16 * wb + NCOL;
@@ -544,7 +573,11 @@ __global__ __launch_bounds__(BPW == 4 ? 512 : 256, R == 32 ? 8 : 4) void merit_s
             }
         }
     }
-    if (scan) best = min(best, scan_rows<R, ND, pitch4>(lds32, cl, wb, d0, lane));
+    if (scan) {
+        const bool whole = BPW == 4 && (p.W & 3) == 0 && by * 16 + 16 <= p.H && bx * 16 + 16 <= p.W;
+        const uint32_t *block = whole ? reinterpret_cast<const uint32_t *>(cur + (size_t)by * 16 * p.W + bx * 16) : nullptr;
+        best = min(best, scan_rows<R, ND, pitch4>(lds32, cl, block, p.W >> 2, wb, d0, lane));
+    }
     if (lane == 0) atomicMin(&result[wb], best);
     __syncthreads();
     if (tid >= BPW || bx0 + tid >= p.nbx) return;
