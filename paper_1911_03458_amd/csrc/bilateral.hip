@@ -11,7 +11,8 @@
 // aligned 16-byte loads without a branch.  Any other W >= 4 the same: fp32 rows start on 4-byte
 // boundaries, which is all a 16-byte load or store needs, and the group that the row's end cuts
 // is loaded so that it ends with the row (element by element before: k = 13 on
-// 386x1202 19.0 us -> 17.8, k = 5 on 1000x1501 11.0 -> 10.2, k = 7 on 583x255 6.0 -> 5.3).  A thread makes four outputs of one column, four
+// 386x1202 19.0 us -> 17.8, k = 5 on 1000x1501 11.0 -> 10.2, k = 7 on 583x255 6.0 -> 5.3).
+// Windows of more than 16 taps (shorter ones: merit_bilateral_rows below): a thread makes four outputs of one column, four
 // rows apart: lanes run along the row (conflict-free 4-byte LDS reads) and the four
 // independent chains hide the latency of the exponential.  Five vector instructions per tap:
 // with s = sqrt(|norm| log2 e), the scaled difference d' = center*s - v*s is one fused

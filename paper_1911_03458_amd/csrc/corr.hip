@@ -4,8 +4,8 @@
 // with k = (b, p1, p2, p3, p4 | a1) and the dot product over the channel index a1
 // (Section III-B, Eq. 3).  Output y[b,p1,p2,p3,p4], binary16, fp32 accumulation.
 //
-// A workgroup owns (b, p1, p3, a run of 64 pixels p2): one row of the first tensor and one
-// (displaced) row of the second.  For that pair of rows the layer is a banded matrix product:
+// A workgroup owns (b, p1, p3, a run of 64 pixels p2, or what a narrower image has): one row of
+// the first tensor and one (displaced) row of the second.  For that pair of rows the layer is a banded matrix product:
 // with the pixels p2 as rows, the columns q of the second row as columns and the channels as
 // the reduction axis, D = X1^T X2 holds y[.., p2, p3, p4] at q = p2 + (p4-R)*sd.  Only columns
 // congruent to p2 modulo sd are ever needed, so a block of 16 pixels of one residue class is
