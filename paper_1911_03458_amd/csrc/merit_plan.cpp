@@ -277,7 +277,7 @@ merit_status derive_sad(merit_plan *pl)
         // Four blocks a workgroup share a window and its sums; one block a workgroup, split among four wavefronts, is the
         // finer grain (R = 32, moving scenes, us: 540x960 19.4 against 24.8, 720x1280 27.8 against 34.6, 1080x1440, which has
         // 6120 blocks and takes four, 42.1 against 44.7, 1080x1920 52.7 against 52.2, 1440x2560 86 against 73, 2160x3840 179
-        // against 148; white noise 1080x1440 67.5 against 67.8, 1080x1920 89 against 77)
+        // against 148; white noise 1080x1440 67.5 against 66.6, 1080x1920 89 against 75.4)
         const int64_t bpw = eliminate16 ? 1 : R == 32 && (int64_t)p.nby * p.nbx < 6000 && pl->tile_req[1] <= 0 ? 1 : 4;
         const int64_t c4 = cdiv(bpw * 16 + 2 * R, 4);
         if (fastdiv_ok((16 + 2 * R) * c4, c4)) {

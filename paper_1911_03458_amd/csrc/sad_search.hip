@@ -92,8 +92,11 @@ __device__ __forceinline__ void stage_window16(const SadParams &p, const uint8_t
     static_assert(PITCH4 % 4 == 0 && PITCH4 >= 4 * COLS16, "16-byte rows");
     uint4 v[NU];
     int moved[NU];                                                 // pixels by which the load was moved right
+    // (wavefronts whose further units are all past the last one: none of those)
+    const int first = __builtin_amdgcn_readfirstlane(tid & ~63);
 #pragma unroll
     for (int k = 0; k < NU; ++k) {
+        if (k > 0 && first + NTHREADS * k >= U) break;
         const int u = min(tid + NTHREADS * k, U - 1);
         const int wy = u / COLS16, gx = gx0 + 16 * (u - wy * COLS16);
         const int at = min(max(gx, 0), p.W - 16);
@@ -102,6 +105,7 @@ __device__ __forceinline__ void stage_window16(const SadParams &p, const uint8_t
     }
 #pragma unroll
     for (int k = 0; k < NU; ++k) {
+        if (k > 0 && first + NTHREADS * k >= U) break;
         if (moved[k] != 0) {
             const int n = min(abs(moved[k]), 16);
             uint64_t lo = ((uint64_t)v[k].y << 32) | v[k].x, hi = ((uint64_t)v[k].w << 32) | v[k].z;
@@ -230,19 +234,19 @@ __global__ __launch_bounds__(256) void merit_sad_generic(SadParams p, const uint
 // and its slot restarts for dy + 16.
 // Four blocks a workgroup, a block inside a frame of whole dwords: its pixels come from memory once more, as scalar loads
 // (64 v_readlane less a wavefront; the loads' latency shows on smaller frames, which have the other form).
-// The 65th column at R = 32: its bounds one candidate per lane, its sums too where a wavefront has half of the rows, else
-// sixteen lanes to a candidate.
+// The 65th column at R = 32: its bounds one candidate per lane, its sums too with four blocks a workgroup, else sixteen lanes
+// to a candidate.
 // BPW: blocks per workgroup: four, the rows of a block's candidates split between two wavefronts, or one, split among four
 // (R = 16 as well, on frames of 64 to 1200 blocks: 288x416 11.0 us on the kernel below -> 7.0, 480x640 11.2 -> 9.6).
 // Workgroups go round-robin to the XCDs, not in bands of block rows: a band of sky or water would be the whole work of
 // one of them (1080x1920: 77 us in bands, 53).
 //
 // us a launch, R = 32, full scan (one wavefront a block, in a kernel of its own) -> this: moving scenes with sensor noise,
-// 1080x1920 75.0 -> 51.7, 720x1280 40.6 -> 28.3, 480x640 24.0 -> 15.0, 120x160 16.8 -> 8.7; smooth textures that move by
-// block, 1088x1920, 75.0 -> 35.7; two unrelated scenes 76.8 -> 68.5; a still picture 76 -> 47.  White noise, where every
-// block is scanned by two or four wavefronts that share its rows, is the slower one on large frames: 1080x1920 75.2 -> 76.7,
-// 995x1906 75.6 -> 79.3, 2160x3840 282 -> 292, 720x1280 40.7 -> 43.2 (480x640: 24.0 -> 17.0).  (A single wavefront a block
-// there, the other one idle: 95 at 1080x1920.)  With every block decided by its bounds a full-HD frame takes 27 us; the rest
+// 1080x1920 75.3 -> 51, 720x1280 40.6 -> 27.7, 480x640 24.0 -> 14.9, 120x160 16.8 -> 8.6; smooth textures that move by
+// block, 1088x1920, 75.3 -> 35.7; two unrelated scenes 76.8 -> 68.5; a still picture 76 -> 47.  Where every block is scanned,
+// by two or four wavefronts that share its rows, large frames are slower: white noise 1080x1920 75.4 both, 995x1906 76.0 ->
+// 78.1, 2160x3840 283 -> 287, 540x960 24.3 -> 24.7, 720x1280 40.7 -> 43.4 (480x640: 24.0 -> 16.9); a random texture that
+// moves by block, 1080x1920, 75.5 -> 77.3.  (A single wavefront a block there, the other one idle: 95 at 1080x1920.)  With every block decided by its bounds a full-HD frame takes 27 us; the rest
 // is the scans of a sixth of the blocks, which come in clusters and are dealt to the compute units by position.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void load_aligned16(const uint32_t *rowp, uint32_t sh, uint32_t (&r)[4])
@@ -273,10 +277,11 @@ __device__ __forceinline__ void rows_of_lanes(uint32_t cl, int lane, uint32_t (&
 }
 
 // The full scan of ND candidate rows from d0 on of block wb, whose pixels are `cl` (four per lane) and, unless that is null,
-// at `block` in memory, in rows of W4 dwords: the lowest key, the same for all lanes.
+// at `block` in memory, in rows of W4 dwords: the lowest key, the same for all lanes.  The column past the 64th, where there
+// is one: of these rows (column = 0), of all rows (1), or not (-1).
 template <int R, int ND, int PITCH4>
 __device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl, const uint32_t *__restrict__ block, int W4,
-                                              int wb, int d0, int lane)
+                                              int wb, int d0, int lane, int column)
 {
     constexpr int N = 2 * R + 1, NCOL = N < 64 ? N : 64, NLEFT = N - NCOL;
     static_assert(ND <= 64, "a candidate row per lane");
@@ -343,11 +348,12 @@ __device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl
     uint32_t key = lane < NCOL ? ((lbest >> 7) << KEY_SHIFT) | ((uint32_t)(d0 + (int)(lbest & 127u)) * N + (uint32_t)lane) : 0xffffffffu;
     // (the condition on the pitch, always true, keeps this apart from the scan: in one block with it the compiler fetches all
     // rows first, into registers that are not there)
-    if (NLEFT > 0 && ND > 24 && pitch != 0) {                      // the last column: a candidate row per lane
+    if (NLEFT > 0 && ND > 24 && pitch != 0 && column >= 0) {       // the last column: a candidate row per lane
         const int ol = 16 * wb + NCOL;
         const uint32_t sl = (uint32_t)(ol & 3);
-        const int dl = min(lane, ND - 1);                          // (idle lanes repeat the last row)
-        const uint32_t *lp = lds32 + (d0 + dl) * pitch + (ol >> 2);
+        // (idle lanes repeat the last row; of all rows the 65th is below)
+        const int dl = column > 0 ? lane : d0 + min(lane, ND - 1);
+        const uint32_t *lp = lds32 + dl * pitch + (ol >> 2);
         uint32_t a = 0;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -356,16 +362,17 @@ __device__ __forceinline__ uint32_t scan_rows(const uint32_t *lds32, uint32_t cl
 #pragma unroll
             for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_sad_u8(c[i][j], r4[j], a);
         }
-        a = (a << KEY_SHIFT) | (uint32_t)((d0 + dl) * N + NCOL);
+        a = (a << KEY_SHIFT) | (uint32_t)(dl * N + NCOL);
         key = a < key ? a : key;
     }
-    if (NLEFT > 0 && ND <= 24 && pitch != 0) {                     // ... sixteen lanes to a candidate, a row each
+    if (NLEFT > 0 && pitch != 0 && (ND <= 24 || column > 0)) {     // ... sixteen lanes to a candidate, a row each
         uint32_t crow[4];
         rows_of_lanes(cl, lane, crow);
         const int ol = 16 * wb + NCOL;
+        const int end = ND <= 24 ? d0 + ND : N;
 #pragma unroll 1
-        for (int i = 0; i < ND; i += 4) {
-            const int dy = d0 + min(i + (lane >> 4), ND - 1);
+        for (int i = ND <= 24 ? d0 : N - 1; i < end; i += 4) {
+            const int dy = min(i + (lane >> 4), end - 1);
             uint32_t r4[4], a = 0;
             load_aligned16(lds32 + (dy + (lane & 15)) * pitch + (ol >> 2), (uint32_t)(ol & 3), r4);
 #pragma unroll
@@ -416,14 +423,20 @@ __global__ __launch_bounds__(BPW == 4 ? 512 : 256, R == 32 ? 8 : 4) void merit_s
     uint32_t s4 = __builtin_amdgcn_sad_u8(cl, 0, 0);
     s4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s4, 0x124, 0xf, 0xf, true);          // row_ror:4
     s4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s4, 0x128, 0xf, 0xf, true);          // row_ror:8
-    // (means rounded down; four lanes hold each 4x4 sum)
-    const uint32_t mean = wave_sum_u32(s4) >> 6;                   // of the 4x4 sums
-    const uint32_t coarse = wave_sum_u32(s4 > mean ? s4 - mean : mean - s4) >> 2;
-    const uint32_t fine = wave_sum_u32(__builtin_amdgcn_sad_u8(cl, (s4 >> 4) * 0x01010101u, 0));
-    const bool bounds = coarse >= fine;
-    if (lane == 0) red[wv] = bounds ? 1u : 0u;
+    // (four blocks a workgroup: by one wavefront of a block, for both; with one block, where the chain of a block is the whole
+    // launch, by each: the answer is then there without a trip through LDS, 8.6 against 9.1 us on 120x160)
+    bool bounds = false;
+    if (BPW == 1 || part == 0) {
+        // (means rounded down; four lanes hold each 4x4 sum)
+        const uint32_t mean = wave_sum_u32(s4) >> 6;               // of the 4x4 sums
+        const uint32_t coarse = wave_sum_u32(s4 > mean ? s4 - mean : mean - s4) >> 2;
+        const uint32_t fine = wave_sum_u32(__builtin_amdgcn_sad_u8(cl, (s4 >> 4) * 0x01010101u, 0));
+        bounds = coarse >= fine;
+        if (lane == 0) red[wv] = bounds ? 1u : 0u;
+    }
     if (tid < BPW) result[tid] = 0xffffffffu;
     __syncthreads();
+    if (BPW != 1) bounds = __builtin_amdgcn_readfirstlane((int)red[wb * WPB]) != 0;
 
     const int d0 = min(part * ND, N - ND);                         // first candidate row (the last share overlaps)
     uint32_t best = 0xffffffffu;                                   // wave-uniform (sum << 14) | raster index
@@ -576,7 +589,10 @@ __global__ __launch_bounds__(BPW == 4 ? 512 : 256, R == 32 ? 8 : 4) void merit_s
     if (scan) {
         const bool whole = BPW == 4 && (p.W & 3) == 0 && by * 16 + 16 <= p.H && bx * 16 + 16 <= p.W;
         const uint32_t *block = whole ? reinterpret_cast<const uint32_t *>(cur + (size_t)by * 16 * p.W + bx * 16) : nullptr;
-        best = min(best, scan_rows<R, ND, pitch4>(lds32, cl, block, p.W >> 2, wb, d0, lane));
+        // no block of the workgroup with bounds: both wavefronts of each scan, and one of them takes its last column, four such
+        // wavefronts on four SIMDs (one block a workgroup, one of its four wavefronts: 120x160 6.5 -> 7.8 us; not there)
+        const int column = WPB == 2 && any_bounds == 0 ? (part == ((wb ^ wb >> 1) & 1) ? 1 : -1) : 0;
+        best = min(best, scan_rows<R, ND, pitch4>(lds32, cl, block, p.W >> 2, wb, d0, lane, column));
     }
     if (lane == 0) atomicMin(&result[wb], best);
     __syncthreads();

@@ -17,6 +17,9 @@ def _frames(kind, H, W, rng):
         cur = np.roll(smooth, (5, -9), (0, 1)) + rng.normal(0, 1.5, (H, W))
     elif kind == "noise":                 # never bounded
         ref, cur = rng.integers(0, 256, (2, H, W))
+    elif isinstance(kind, tuple):         # ... with the blocks' matches at one displacement
+        ref = rng.integers(0, 256, (H, W))
+        cur = np.roll(ref, (-kind[0], -kind[1]), (0, 1))
     elif kind == "flat":                  # every candidate ties: the first in scan order
         ref = cur = np.full((H, W), 9)
     elif kind == "stripes":               # coarse, and many exact ties: too many candidates left
@@ -50,6 +53,26 @@ def test_exact(kind, H, W, R, blocks):
     li = plan.launch_info()
     print(kind, H, W, R, li, flush=True)
     assert li["kernel"] == "merit_sad_rowscan16<%d>" % R and li["tile"][1] == blocks
+    _compare(plan, cur, ref, R)
+
+
+def _compare(plan, cur, ref, R):
     sad, mv = mb.merit_sad_search(plan, torch.from_numpy(cur).cuda(), torch.from_numpy(ref).cuda())
     osad, omv = oracle.sad_search(cur, ref, 16, R)
     assert np.array_equal(sad.cpu().numpy(), osad) and np.array_equal(mv.cpu().numpy(), omv)
+    return osad, omv
+
+
+@pytest.mark.parametrize("dy", [-32, -1, 0, 1, 31, 32])
+@pytest.mark.parametrize("dx", [-32, 31, 32])
+@pytest.mark.parametrize("H,W,blocks", [(208, 208, 4), (210, 210, 4), (208, 208, 1)])
+def test_matches_in_the_outer_columns_of_scanned_frames(dy, dx, H, W, blocks):
+    """The 65th column is not a lane's: with four blocks a workgroup one wavefront takes it for all rows of a block."""
+    cur, ref = _frames((dy, dx), H, W, np.random.default_rng(abs(dy * 100 + dx)))
+    plan = mb.merit_plan_sad(H, W, 16, 32)
+    if blocks == 4:
+        plan.set_tile((0, 4))
+    print(dy, dx, H, W, plan.launch_info(), flush=True)
+    assert plan.launch_info()["tile"][1] == blocks
+    osad, omv = _compare(plan, cur, ref, 32)
+    assert (osad == 0).sum() >= 40 and (omv.reshape(-1, 2)[osad.ravel() == 0] == (dy, dx)).all()
