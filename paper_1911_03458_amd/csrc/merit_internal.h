@@ -398,13 +398,20 @@ hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *
 const char *dwconv_kernel_name(const DwParams &p);
 
 // ---- separable filter --------------------------------------------------------------
+// the forms of the separable filter's kernel (see sepfilter.hip), their staged rows at most, the columns of a row-pass unit
+enum SepForm { SEP_TILES = 0, SEP_PERSISTENT = 1, SEP_FEW = 2 };
+constexpr int sep_many(int k) { return k <= 28 ? SEP_TILES : SEP_PERSISTENT; }
+constexpr int sep_rows(int form) { return form == SEP_PERSISTENT ? 96 : 64; }
+constexpr int sep_rc(int form) { return form == SEP_TILES ? 16 : 8; }
+
 struct SepParams {
     int N, H, W, k;
+    int form;
     int c;                 // window offset: tap a reads coordinate p + a - c, c = k/2
     int c4;                // c rounded up to 4: the staged columns start at x0 - c4
     int TH;                // output rows per workgroup (a multiple of 4); 64 columns
     int tiles_y, tiles_x;
-    int PI, PM;            // LDS row pitch (floats) of the staged input and of the row-pass result
+    int PI;                // LDS row pitch (floats) of the staged input and of the row-pass result, which replaces it
     int lds_bytes;
     int wg_per_cu;         // persistent workgroups per compute unit
     FastDiv div_tiles_x, div_tiles_y, div_rh;

@@ -360,22 +360,27 @@ merit_status derive_sep(merit_plan *pl)
     SepParams &p = pl->sep;
     p.N = (int)N; p.H = (int)H; p.W = (int)W; p.k = (int)k; p.c = (int)c;
     p.c4 = (int)round_up(c, 4);
-    // staged rows RH = TH + k - 1: about 64, more for long windows (whose halo rows the row pass
-    // also computes); TH a multiple of 4 (the column pass works on 4 x 4 patches)
-    int64_t rows = k <= 16 ? 64 : 96;                     // the kernel keeps rows / 32 row-pass units per thread
-    if (pl->tile_req[1] > 0) {                            // staged rows per workgroup, at most
-        if (pl->tile_req[1] < k + 3 || pl->tile_req[1] > rows) return MERIT_ERR_UNSUPPORTED;
-        rows = pl->tile_req[1];
-    }
-    const int64_t TH = (rows - k + 1) / 4 * 4;
+    // staged rows RH = TH + k - 1; TH a multiple of 4 (the column pass works on patches of 2 or 4 rows)
+    const int64_t asked = pl->tile_req[1];                // staged rows per workgroup, at most
+    if (asked > 0 && (asked < k + 3 || asked > (k <= 16 ? 64 : 96))) return MERIT_ERR_UNSUPPORTED;
+    auto rows_of = [&](int form) { return asked > 0 && asked < sep_rows(form) ? asked : (int64_t)sep_rows(form); };
+    auto tiles_of = [&](int64_t TH) { return N * cdiv(H, TH) * cdiv(W, 64); };
+    // few tiles: up to three a compute unit (at 480-760 tiles 512 threads are 1-8 % faster, at 960 on k = 30 and at
+    // 1840-2500 otherwise 4-13 % slower).  Where they are fewer than the compute units they are shortened until those are
+    // full, to 16 rows at least: a tile's chain is as long as it is tall (not for short windows, whose chain is the round
+    // trip to memory whatever the height).
+    int64_t TH = (rows_of(SEP_FEW) - k + 1) / 4 * 4;
+    p.form = TH > 0 && tiles_of(TH) <= 768 ? SEP_FEW : sep_many((int)k);
+    if (p.form != SEP_FEW) TH = (rows_of(p.form) - k + 1) / 4 * 4;
+    else if (asked <= 0 && k >= 8)
+        while (TH > 16 && tiles_of(TH - 4) <= 256) TH -= 4;
     const int64_t RH = TH + k - 1;
     p.TH = (int)TH;
     p.tiles_y = (int)cdiv(H, TH);
     p.tiles_x = (int)cdiv(W, 64);
-    // a row-pass unit reads ceil((d + 8 + k - 1) / 4) 16-byte groups from column 8 cg on
-    const int64_t nwr = cdiv((p.c4 - c) + 8 + k - 1, 4);
-    p.PI = (int)(round_up(56 + 4 * nwr, 8) + 4);          // pitches of 4 mod 8 floats: see the kernel
-    p.PM = p.PI;                                          // the row-pass result replaces the staged input
+    // a row-pass unit of rc columns reads ceil((d + rc + k - 1) / 4) 16-byte groups from column rc cg on
+    const int64_t rc = sep_rc(p.form), nwr = cdiv((p.c4 - c) + rc + k - 1, 4);
+    p.PI = (int)(round_up(64 - rc + 4 * nwr, 8) + 4);     // pitches of 4 mod 8 floats: see the kernel
     p.lds_bytes = (int)((RH * p.PI + 8 * cdiv(k, 4)) * 4);
     if (p.lds_bytes > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
     const int64_t grid = N * p.tiles_y * p.tiles_x;
@@ -392,9 +397,9 @@ merit_status derive_sep(merit_plan *pl)
     li.kernel = "merit_sepfilter_tile";
     // persistent grid: the launcher sizes it from the device's CU count (256 on MI355X)
     p.wg_per_cu = (int)(LDS_LIMIT / p.lds_bytes);
-    if (p.wg_per_cu > 8) p.wg_per_cu = 8;
-    li.grid[0] = grid < 256 * p.wg_per_cu ? grid : 256 * p.wg_per_cu; li.grid[1] = 1; li.grid[2] = 1;
-    li.block[0] = 256; li.block[1] = 1; li.block[2] = 1;
+    if (p.wg_per_cu > 4) p.wg_per_cu = 4;
+    li.grid[0] = p.form == SEP_PERSISTENT && grid > 256 * p.wg_per_cu ? 256 * p.wg_per_cu : grid; li.grid[1] = 1; li.grid[2] = 1;
+    li.block[0] = p.form == SEP_FEW ? 512 : 256; li.block[1] = 1; li.block[2] = 1;
     li.lds_bytes = p.lds_bytes;
     li.tile[0] = 1; li.tile[1] = TH; li.tile[2] = 64; li.tile[3] = k; li.tile[4] = k;
     return MERIT_OK;

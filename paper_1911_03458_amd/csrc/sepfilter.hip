@@ -7,12 +7,23 @@
 //
 // A workgroup owns TH x 64 output pixels of one image.  The covering sub-tensor (Section IV-A,
 // Eq. 9: (TH + k - 1) x (64 + k - 1)) is staged in LDS with the clamping resolved there.  A
-// row-pass thread keeps 8 adjacent outputs of one staged row in registers and reads the
-// 8 + k - 1 inputs they need as 16-byte runs; a column-pass thread keeps a 4 x 4 patch and
-// reads k + 3 runs of four columns: 8k and 16k multiply-adds for that many 16-byte reads.
-// In the row pass neighbouring lanes take neighbouring rows; the row pitches are 4 mod 8
-// floats, which spreads the 16-byte accesses of 16 lanes over all banks (the padding layout
-// of Section IV-B).
+// row-pass unit keeps RC adjacent outputs of one staged row in registers and reads the
+// RC + k - 1 inputs they need as 16-byte runs; a column-pass unit keeps a PR x PC patch and
+// reads k + PR - 1 runs of PC columns.  In the row pass neighbouring lanes take neighbouring
+// rows; the row pitches are 4 mod 8 floats, which spreads the 16-byte accesses of 16 lanes over
+// all banks (the padding layout of Section IV-B).
+//
+// Three forms (SepForm, merit_internal.h), chosen by the plan from the window and the number of tiles.  What bounds
+// them: on large frames the multiply-adds (9.9 us of 24 at k = 30 on 4x1080x1920, at the probe's rate), the LDS reads
+// and the memory of a tile one after the other, so they want many workgroups in different phases; on small ones the
+// chain of one tile, so they want it cut into many threads.  us a launch, one persistent form of 256 threads -> these:
+//   TILES       one tile a workgroup, no request ahead: six or seven workgroups a compute unit instead of three
+//               (4x1080x1920: k = 8 15.1 -> 13.6, 12 17.3 -> 15.5, 16 19.7 -> 17.0, 20 22.2 -> 19.4, 24 24.4 -> 21.9)
+//   PERSISTENT  k > 28, where 64 staged rows would be half halo: 96 rows, four workgroups a compute unit that walk the
+//               tiles (k = 30 25.2 -> 24.3; one tile a workgroup 24.4; 64 rows 26.6)
+//   FEW         up to three tiles a compute unit: 512 threads, 2 x 2 patches (2x600x1280: k = 30 9.1 -> 8.3, 20 8.6 ->
+//               7.7, 8 5.7 -> 5.5; 380x936: 30 6.8 -> 4.6, 20 7.0 -> 4.6, 8 4.3 -> 3.9, 3 3.8 -> 3.6), and where the
+//               tiles do not fill the chip shorter ones (624x172: k = 20 6.5 -> 3.7, 4.2 on 44-row tiles; 8 4.0 -> 3.2)
 //
 // The staged columns start at x0 - c4, c4 = k/2 rounded up to 4, so that (for W % 4 == 0) every
 // group of four staged columns is one aligned 16-byte run of the image, entirely inside it or
@@ -31,16 +42,19 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 // K = window length (compile time: every tap index is an immediate, the sliding windows live
 // in renamed registers and no zero tap is multiplied).  RAGGED = W % 4 != 0 (an instance of its
 // own: as a run-time condition it cost the aligned rows 1.5 %)
-template <int K, bool RAGGED>
-__global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(SepParams p, const float *__restrict__ x,
+template <int K, bool RAGGED, int FORM>
+__global__ __launch_bounds__((FORM == SEP_FEW ? 512 : 256), 4) void merit_sepfilter_tile(SepParams p, const float *__restrict__ x,
                                                            const float *__restrict__ kx,
                                                            const float *__restrict__ ky, float *__restrict__ y)
 {
+    constexpr int NT = FORM == SEP_FEW ? 512 : 256, ROWS = sep_rows(FORM), RC = sep_rc(FORM);
+    constexpr int PR = FORM == SEP_FEW ? 2 : 4, PC = FORM == SEP_FEW ? 2 : 4;     // rows and columns of a column-pass patch
+    constexpr bool LONG = K > 8;                                  // one window, or a few rows of a patch, in registers at a time
+    typedef float run __attribute__((ext_vector_type(PC)));
     constexpr int TW = 64;
     constexpr int C = K / 2, C4 = (C + 3) / 4 * 4, D = C4 - C;    // staged column 0 = image column x0 - C4
-    constexpr int NWR = (D + 8 + K - 1 + 3) / 4;                  // 16-byte groups a row-pass unit reads
+    constexpr int NWR = (D + RC + K - 1 + 3) / 4;                 // 16-byte groups a row-pass unit reads
     constexpr int K4 = (K + 3) / 4;
-    constexpr int PR = 4;                                         // rows of a column-pass patch
     extern __shared__ __align__(16) float smem[];
     const int RH = p.TH + K - 1;                          // staged rows
     float *in = smem;                                     // [RH][PI]; later the row-pass result
@@ -70,19 +84,15 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
         wyl[tid] = tid < K ? ky[min(tid, K - 1)] : 0.0f;
     }
     // Staging: every element is a real (clamped) pixel.  A thread owns one 4-column group of
-    // the staged rows r = tid / LPR + (256 / LPR) j; SB rows per batch, every load of a batch
-    // issued before the first LDS write (one memory round trip per batch).
-    constexpr int SB = K <= 16 ? 8 : 12;                  // 8 rows per step: 64 or 96 staged rows at most
+    // the staged rows r = tid / 32 + (NT / 32) j; every load of a tile is issued before its first
+    // LDS write (one memory round trip a tile).
+    constexpr int SB = ROWS / (NT / 32);
     const int P4 = p.PI >> 2, W4 = p.W >> 2;              // P4 <= 32 for every K <= 32
     const bool vec = !RAGGED || p.W >= 4;
     constexpr int lg = 5;                                 // lanes per staged row
     const int cg = tid & ((1 << lg) - 1);
     const bool live = cg < P4;
-    constexpr int rstep = 256 >> lg;
-    // One batch covers a tile, so a workgroup requests its next tile before it computes the
-    // current one: loads, arithmetic and stores of the workgroups of a compute unit overlap
-    // instead of all running in the same phase.
-    const bool pf = vec;
+    constexpr int rstep = NT >> lg;
     float4v pre[SB];
     auto issue = [&](const Tile &T, int r0) {
         const int g4 = ((T.x0 - C4) >> 2) + cg;           // image 4-column group (may be outside)
@@ -134,22 +144,24 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
     // neighbours sat on other XCDs: 1.72 times the image was fetched at k = 30.)
     const int nwg = (int)gridDim.x;
     int t = (int)blockIdx.x, tstep = nwg, tend = ntiles;
-    if (nwg % 8 == 0) {
+    if (FORM != SEP_PERSISTENT) {
+        t = (int)xcd_band_item(blockIdx.x, nwg >> 3, nwg & 7);
+    } else if (nwg % 8 == 0) {
         const int xcd = t & 7, slot = t >> 3;
         t = (int)(((long long)xcd * ntiles) >> 3) + slot;         // slot < nwg / 8 <= the band's length
         tend = (int)(((long long)(xcd + 1) * ntiles) >> 3);
         tstep = nwg >> 3;
     }
-    if (pf) issue(tile_at(t), tid >> lg);                 // t < tend: the grid never exceeds the tile list
-    for (; t < tend; t += tstep) {
+    for (; t < tend; t += tstep) {                        // t < tend at first: the grid never exceeds the tile list
         const Tile T = tile_at(t);
         const int x0 = T.x0, y0 = T.y0;
-        if (pf) {
+        if (vec) {
+            issue(T, tid >> lg);
             commit(T, tid >> lg);
         } else {
             const float *img = x + (size_t)T.n * p.H * p.W;
             const int total = RH * p.PI;
-            for (int e = tid; e < total; e += 256) {
+            for (int e = tid; e < total; e += NT) {
                 const int r = e / p.PI;
                 const int cc = e - r * p.PI;
                 const int gy = min(max(y0 - C + r, 0), p.H - 1);
@@ -158,16 +170,13 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
             }
         }
         __syncthreads();
-        // short windows: the next tile's loads fly during both passes; long windows need the
-        // registers for the row pass and request it before the column pass
-        if (K <= 16 && pf && t + tstep < tend) issue(tile_at(t + tstep), tid >> lg);
 
-        // row pass: unit = (8-column group, staged row), rows fastest; output column j of the
-        // unit = sum_a kx[a] * staged column (8 cg + j + D + a).  The results replace the staged
+        // row pass: unit = (RC-column group, staged row), rows fastest; output column j of the
+        // unit = sum_a kx[a] * staged column (RC cg + j + D + a).  The results replace the staged
         // input in place (columns 0..63 of each row): every unit is computed into registers
         // first, and a barrier separates the last read from the first write.
-        constexpr int RU = K <= 16 ? 2 : 3;               // units per thread: 8 * RH <= 256 * RU
-        float acc[RU][8];
+        constexpr int RU = TW / RC * ROWS / NT;           // units per thread
+        float acc[RU][RC];
         float wx[4 * K4];
 #pragma unroll
         for (int g = 0; g < K4; ++g) {
@@ -176,10 +185,10 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
         }
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
-            const int u = min(tid + 256 * k, (TW / 8) * RH - 1);
+            const int u = min(tid + NT * k, (TW / RC) * RH - 1);
             const int cgr = (int)fdiv((uint32_t)u, p.div_rh);
             const int r = u - cgr * RH;
-            const float *src = in + r * p.PI + 8 * cgr;
+            const float *src = in + r * p.PI + RC * cgr;
             float win[4 * NWR];
 #pragma unroll
             for (int g = 0; g < NWR; ++g) {
@@ -187,15 +196,15 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
                 win[4 * g] = h.x; win[4 * g + 1] = h.y; win[4 * g + 2] = h.z; win[4 * g + 3] = h.w;
             }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[k][j] = 0.0f;
+            for (int j = 0; j < RC; ++j) acc[k][j] = 0.0f;
 #pragma unroll
             for (int a = 0; a < K; ++a)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc[k][j] = fmaf(wx[a], win[j + D + a], acc[k][j]);
+                for (int j = 0; j < RC; ++j) acc[k][j] = fmaf(wx[a], win[j + D + a], acc[k][j]);
             // long windows: one unit's window at a time in registers.  The empty statement
             // consumes the sums and clobbers memory, so these multiply-adds stay above it and
             // the next unit's reads below it.
-            if constexpr (K > 16)
+            if constexpr (LONG && RU > 1)
                 asm volatile("" : "+v"(acc[k][0]), "+v"(acc[k][1]), "+v"(acc[k][2]), "+v"(acc[k][3]),
                                   "+v"(acc[k][4]), "+v"(acc[k][5]), "+v"(acc[k][6]), "+v"(acc[k][7]) : : "memory");
         }
@@ -203,23 +212,20 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
         float *mid = in;                                  // [RH][PI], columns 0..63
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
-            const int u = tid + 256 * k;
-            if (u < (TW / 8) * RH) {
+            const int u = tid + NT * k;
+            if (u < (TW / RC) * RH) {
                 const int cgr = (int)fdiv((uint32_t)u, p.div_rh);
                 const int r = u - cgr * RH;
-                float *dst = mid + r * p.PI + 8 * cgr;
-                float4v o0, o1;
-                o0.x = acc[k][0]; o0.y = acc[k][1]; o0.z = acc[k][2]; o0.w = acc[k][3];
-                o1.x = acc[k][4]; o1.y = acc[k][5]; o1.z = acc[k][6]; o1.w = acc[k][7];
-                *reinterpret_cast<float4v *>(dst) = o0;
-                *reinterpret_cast<float4v *>(dst + 4) = o1;
+                float *dst = mid + r * p.PI + RC * cgr;
+#pragma unroll
+                for (int j = 0; j < RC; j += 4)
+                    *reinterpret_cast<float4v *>(dst + j) = (float4v){acc[k][j], acc[k][j + 1], acc[k][j + 2], acc[k][j + 3]};
             }
         }
         __syncthreads();
-        if (K > 16 && pf && t + tstep < tend) issue(tile_at(t + tstep), tid >> lg);
 
-        // column pass: unit = PR rows x 4 columns, column groups fastest: 16-byte LDS reads and
-        // 16-byte stores.  Row q of the K + PR - 1 rows a unit reads feeds output row i with tap
+        // column pass: unit = PR rows x PC columns, column groups fastest: one LDS read or store
+        // a row.  Row q of the K + PR - 1 rows a unit reads feeds output row i with tap
         // q - i.
         float *out = y + (size_t)T.n * p.H * p.W;
         float wy[4 * K4];
@@ -228,100 +234,90 @@ __global__ __launch_bounds__(256, (K > 16 ? 3 : 1)) void merit_sepfilter_tile(Se
             const float4v w = *reinterpret_cast<const float4v *>(wyl + 4 * g);
             wy[4 * g] = w.x; wy[4 * g + 1] = w.y; wy[4 * g + 2] = w.z; wy[4 * g + 3] = w.w;
         }
-        for (int u = tid; u < (p.TH / PR) * (TW / 4); u += 256) {
-            const int rg = u >> 4, c4 = u & 15;
-            const float *src = mid + (PR * rg) * p.PI + 4 * c4;
-            float4v o[PR];
+        constexpr int CG = TW / PC;
+        for (int u = tid; u < (p.TH / PR) * CG; u += NT) {
+            const int rg = u / CG, cg2 = u % CG;
+            const float *src = mid + (PR * rg) * p.PI + PC * cg2;
+            run o[PR];
 #pragma unroll
-            for (int i = 0; i < PR; ++i) o[i] = (float4v){0.0f, 0.0f, 0.0f, 0.0f};
+            for (int i = 0; i < PR; ++i)
+#pragma unroll
+                for (int j = 0; j < PC; ++j) o[i][j] = 0.0f;
             // QC rows at a time: their reads, then their multiply-adds (for long windows the
-            // scheduler must not pull all K + 3 reads to the front: 4 registers each)
-            constexpr int QC = K > 16 ? 4 : 8;
+            // scheduler must not pull all K + PR - 1 reads to the front: PC registers each)
+            constexpr int QC = LONG ? 16 / PC : 32 / PC;
 #pragma unroll
             for (int q0 = 0; q0 < K + PR - 1; q0 += QC) {
-                float4v v[QC];
+                run v[QC];
 #pragma unroll
                 for (int e = 0; e < QC; ++e)
-                    if (q0 + e < K + PR - 1) v[e] = *reinterpret_cast<const float4v *>(src + (q0 + e) * p.PI);
+                    if (q0 + e < K + PR - 1) v[e] = *reinterpret_cast<const run *>(src + (q0 + e) * p.PI);
 #pragma unroll
                 for (int e = 0; e < QC; ++e) {
                     const int q = q0 + e;
 #pragma unroll
                     for (int i = 0; i < PR; ++i)
-                        if (q < K + PR - 1 && q - i >= 0 && q - i < K) {
-                            o[i].x = fmaf(wy[q - i], v[e].x, o[i].x);
-                            o[i].y = fmaf(wy[q - i], v[e].y, o[i].y);
-                            o[i].z = fmaf(wy[q - i], v[e].z, o[i].z);
-                            o[i].w = fmaf(wy[q - i], v[e].w, o[i].w);
-                        }
+                        if (q < K + PR - 1 && q - i >= 0 && q - i < K)
+#pragma unroll
+                            for (int j = 0; j < PC; ++j) o[i][j] = fmaf(wy[q - i], v[e][j], o[i][j]);
                 }
-                if constexpr (K > 16)
-                    asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]) : : "memory");
+                if constexpr (LONG)
+#pragma unroll
+                    for (int i = 0; i < PR; ++i) asm volatile("" : "+v"(o[i]) : : "memory");
             }
-            const int gx = x0 + 4 * c4;
+            const int gx = x0 + PC * cg2;
 #pragma unroll
             for (int i = 0; i < PR; ++i) {
                 const int gy = y0 + PR * rg + i;
                 if (gy >= p.H) continue;
                 float *dst = out + (size_t)gy * p.W + gx;
                 if (!RAGGED) {
-                    if (gx < p.W) *reinterpret_cast<float4v *>(dst) = o[i];
-                } else if (gx + 3 < p.W) {
-                    __builtin_memcpy(dst, &o[i], 16);
+                    if (gx < p.W) *reinterpret_cast<run *>(dst) = o[i];
+                } else if (gx + PC - 1 < p.W) {
+                    __builtin_memcpy(dst, &o[i], 4 * PC);
                 } else {
-                    if (gx < p.W) dst[0] = o[i].x;
-                    if (gx + 1 < p.W) dst[1] = o[i].y;
-                    if (gx + 2 < p.W) dst[2] = o[i].z;
+#pragma unroll
+                    for (int j = 0; j < PC - 1; ++j)
+                        if (gx + j < p.W) dst[j] = o[i][j];
                 }
             }
         }
+        if (FORM != SEP_PERSISTENT) break;                // one tile a workgroup
         __syncthreads();                                  // the staged tile is free again
     }
 }
 
-template <int K, bool RAGGED>
-static hipError_t launch_sep_rows(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
-                             hipStream_t s, int64_t ntiles, int cus)
+template <int K, bool RAGGED, int FORM>
+static hipError_t launch_sep_form(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
+                                  hipStream_t s, int64_t ntiles)
 {
     static std::atomic<int> raised{0};
-    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_sepfilter_tile<K, RAGGED>), raised);
+    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_sepfilter_tile<K, RAGGED, FORM>), raised);
         e != hipSuccess)
         return e;
-    // Persistent workgroups.  The plan's count per CU is what LDS allows.  Long windows need so
-    // many registers that fewer are resident, and a workgroup beyond the resident ones would
-    // start only when another has finished all of its tiles: there the grid is exactly the
-    // resident count (k = 30 at 4x1080x1920: 768 instead of 1024 workgroups, 30.2 -> 28.1 us).
-    // Short windows keep the plan's count: one tile per workgroup, dealt out as workgroups
-    // retire, measured faster than two rounds over the resident ones (k = 3: 17.2 against 17.9 us).
-    int per_cu = p.wg_per_cu;
-    if (K > 16) {
-        // the last query and its answer in one atomic word (plans of one shape repeat); two
-        // threads with different shapes at worst repeat the query, neither reads the other's answer
-        static std::atomic<uint64_t> last{0};
-        const uint64_t seen = last.load(std::memory_order_relaxed);
-        int answer = (int)(seen & 0xffffffffu);
-        if ((seen >> 32) != (uint64_t)(uint32_t)p.lds_bytes || answer <= 0) {
-            int r = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, merit_sepfilter_tile<K, RAGGED>, 256,
-                                                             (size_t)p.lds_bytes) != hipSuccess || r <= 0)
-                r = 1;
-            answer = r;
-            last.store(((uint64_t)(uint32_t)p.lds_bytes << 32) | (uint32_t)r, std::memory_order_relaxed);
-        }
-        if (answer < per_cu) per_cu = answer;
+    // persistent workgroups: as many as are resident (the registers allow four a compute unit as well)
+    int64_t grid = ntiles;
+    if (FORM == SEP_PERSISTENT) {
+        const int64_t slots = (int64_t)device_cu_count() * p.wg_per_cu;
+        if (grid > slots) grid = slots;
     }
-    const int64_t slots = (int64_t)cus * per_cu;
-    const uint32_t grid = (uint32_t)(ntiles < slots ? ntiles : slots);
-    hipLaunchKernelGGL((merit_sepfilter_tile<K, RAGGED>), dim3(grid), dim3(256), (size_t)p.lds_bytes, s, p, x, kx, ky, y);
+    hipLaunchKernelGGL((merit_sepfilter_tile<K, RAGGED, FORM>), dim3((uint32_t)grid), dim3(FORM == SEP_FEW ? 512 : 256),
+                       (size_t)p.lds_bytes, s, p, x, kx, ky, y);
     return hipGetLastError();
 }
 
 template <int K>
 static hipError_t launch_sep(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
-                             hipStream_t s, int64_t ntiles, int cus)
+                             hipStream_t s, int64_t ntiles)
 {
-    return (p.W & 3) != 0 ? launch_sep_rows<K, true>(p, x, kx, ky, y, s, ntiles, cus)
-                          : launch_sep_rows<K, false>(p, x, kx, ky, y, s, ntiles, cus);
+    constexpr int MANY = sep_many(K);                     // the form on many tiles
+    const bool ragged = (p.W & 3) != 0;
+    if (p.form == SEP_FEW)
+        return ragged ? launch_sep_form<K, true, SEP_FEW>(p, x, kx, ky, y, s, ntiles)
+                      : launch_sep_form<K, false, SEP_FEW>(p, x, kx, ky, y, s, ntiles);
+    if (p.form != MANY) return hipErrorInvalidValue;
+    return ragged ? launch_sep_form<K, true, MANY>(p, x, kx, ky, y, s, ntiles)
+                  : launch_sep_form<K, false, MANY>(p, x, kx, ky, y, s, ntiles);
 }
 
 hipError_t launch_sepfilter(const SepParams &p, const float *x, const float *kx, const float *ky, float *y,
@@ -329,10 +325,8 @@ hipError_t launch_sepfilter(const SepParams &p, const float *x, const float *kx,
 {
     const int64_t ntiles = (int64_t)p.N * p.tiles_y * p.tiles_x;
     if (ntiles == 0) return hipSuccess;
-    // persistent workgroups, p.wg_per_cu per compute unit (256 on MI355X), at most one per tile
-    const int cus = device_cu_count();
     switch (p.k) {
-#define MERIT_SEP_CASE(Kv) case Kv: return launch_sep<Kv>(p, x, kx, ky, y, s, ntiles, cus)
+#define MERIT_SEP_CASE(Kv) case Kv: return launch_sep<Kv>(p, x, kx, ky, y, s, ntiles)
 #define MERIT_SEP_CASE8(B)                                                                           \
     MERIT_SEP_CASE(B + 1); MERIT_SEP_CASE(B + 2); MERIT_SEP_CASE(B + 3); MERIT_SEP_CASE(B + 4);      \
     MERIT_SEP_CASE(B + 5); MERIT_SEP_CASE(B + 6); MERIT_SEP_CASE(B + 7); MERIT_SEP_CASE(B + 8)
