@@ -7,6 +7,10 @@
 // LDS buffers in steps of 64.  What bounds these layers is not the matrix cores but the chain of a step -- memory round
 // trip, LDS, barrier -- on launches that have one workgroup per compute unit, so:
 //   * D steps are in flight in registers (16-byte loads, one to four per thread and step), issued D steps ahead;
+//   * a step that the channels fill has no check, no select and no shift, and no branch lies round a load whose data
+//     leaves it: where paths with different loads in flight meet, the compiler waits for all of them (1024 -> 256 on 8 of
+//     14x14 8.5 us with such branches, with the loads of cut units shifted and with the last step's checks in every step,
+//     5.6 without; the loads alone take 4.0);
 //   * nothing is transposed by hand: the pixels of a channel lie in LDS as they lie in memory, and the operand a lane
 //     feeds to the MFMA (eight channels of one pixel) comes out of ds_read_b64_tr_b16, which transposes on the way;
 //   * all wavefronts load, and all multiply: where TM x TN has fewer than eight 32 x 32 blocks the wavefronts split
@@ -16,19 +20,19 @@
 // sixteen rows of a weight read fall into different banks without padding.
 //
 // Planes of any size (H W >= 8): a 16-byte unit of eight pixels lies on any 2-byte boundary, which a global load or
-// store takes; the unit that a plane's end cuts is loaded so that it ends with the plane and shifted down.  The same
-// for a weight row's last unit when Cin is not a multiple of 8: the zeros that come in are the missing channels.
+// store takes; the unit that a plane's end would cut ends with the plane and has some pixels of the one before it once
+// more.  Channels the same, but there the ones that come twice are zeroed.
 //
-// us a launch, the kernel that took the layer before -> this one (inputs from the Infinity Cache):
-//   1024 -> 256 on 8 images of 14x14                24.6 -> 8.0     (wave-specialised multi-pass kernel)
-//   1760 -> 440 on 4 of 8x39                        44.0 -> 12.0
-//   512 -> 512 on 32 of 28x28                       54.5 -> 27.5    (480 TFLOP/s)
-//   256 -> 1024 on 8 of 14x14, added tensor         10.5 -> 6.0
-//   48 -> 192 on 29 of 22x38, added tensor          78.0 -> 7.2     (single-pass channel-block kernel)
-//   216 -> 16 on 51 of 8x35                         42.5 -> 4.0
-//   32 -> 24 on 26 of 91x97                         39.9 -> 8.0     (4.3 us at the copy rate)
-// A step costs a compute unit 0.3-0.5 us whether two or eight steps are in flight: what is left is the fill of the
-// 128-byte lines that half a row of pixels uses half of, not the round trip.
+// us a launch, the branches and shifts of before -> now (inputs from the Infinity Cache):
+//   1024 -> 256 on 8 images of 14x14                8.5 -> 5.6      (24.6 on the wave-specialised multi-pass kernel)
+//   256 -> 1024 on 8 of 14x14                       5.5 -> 4.2
+//   1568 -> 392 on 3 of 25x17                       13.3 -> 9.2
+//   392 -> 1568 on 3 of 25x17                       10.0 -> 7.4     (128 x 128 tiles; 8.4 on 128 x 64)
+//   512 -> 128 on 25 of 53x19                       11.5 -> 9.7     (5.3 us at the copy rate)
+//   576 -> 16 on 36x111                             5.7 -> 4.1
+//   32 -> 64 on 32 of 64x64                         7.5 -> 6.7      (2.1 us at the copy rate; 8.2 on the multi-pass kernel)
+// Tried: wavefronts that each split the channels and never meet before the sums (5.7 us on the first of these, 1.5-3x
+// slower where the tiles fill the chip); six steps in flight, which is slower everywhere.
 #include "merit_internal.h"
 
 #include <atomic>
@@ -42,14 +46,39 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KB = 64;                     // input channels per step
 constexpr int NT = 512;
 
-__device__ __forceinline__ uint4 load16(const uint16_t *base, uint32_t off)      // off in bytes, on any 2-byte boundary
+// One 16-byte load, off in bytes on any 2-byte boundary.  A vector type throughout: a struct of four dwords the compiler
+// splits into two 8-byte loads wherever a later step looks at its halves.
+__device__ __forceinline__ u32x4 load16(const uint16_t *base, uint32_t off)
 {
-    uint4 v;
-    __builtin_memcpy(&v, reinterpret_cast<const uint8_t *>(base) + off, 16);
+    typedef uint32_t u32x4_2 __attribute__((ext_vector_type(4), aligned(2)));
+    return *reinterpret_cast<const u32x4_2 *>(reinterpret_cast<const uint8_t *>(base) + off);
+}
+
+// Eight pixels of a row to where they lie.  A unit that ends with the plane has some of the one before it: the same
+// values once more, but for the added tensor's, which may be the output itself and which that unit's thread has read.
+template <bool RES>
+__device__ __forceinline__ void store_unit(uint16_t *row, int px, int HW, u32x4 v)
+{
+    uint16_t *dst = row + min(px, HW - 8);
+    if (!RES || px + 8 <= HW) {
+        __builtin_memcpy(dst, &v, 16);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (HW - 8 + k >= px) dst[k] = (uint16_t)(v[k >> 1] >> (16 * (k & 1)));
+    }
+}
+
+// A unit of eight channels without its first `cut` ones, which the unit before it has (8 and more: all of them).
+__device__ __forceinline__ u32x4 zero_first(u32x4 v, int cut)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] &= (2 * j >= cut ? 0xffffu : 0u) | (2 * j + 1 >= cut ? 0xffff0000u : 0u);
     return v;
 }
 
@@ -87,22 +116,20 @@ __global__ __launch_bounds__(NT, MINW) void merit_conv2d_px(PxParams p, const ui
     const int co0 = (item - tile * p.co_groups) * TN;
     const int n = (int)fdiv((uint32_t)tile, p.div_tiles);
     const int px0 = (tile - n * p.tiles) * TM;
-    const int HW = p.HW, Cin = p.Cin, nk = p.nk;
+    const int HW = p.HW, Cin = p.Cin, nk_full = Cin / KB;
     const uint16_t *xn = x + (size_t)n * Cin * HW;
-    const bool ragged_px = px0 + TM > HW && (HW & 7) != 0;              // a unit of this tile is cut by the plane's end
-    const bool ragged_k = (Cin & 7) != 0;
 
-    // ---- what a thread loads of every step ----
+    // ---- what a thread loads of every step.  A unit of eight pixels that the plane's end would cut ends with the plane:
+    // some of its pixels are computed, and stored, twice, the same ----
     int x_row[XU], x_lds[XU], w_k[WU], w_lds[WU];
-    uint32_t x_px[XU], w_base[WU];
-    bool x_cut[XU];
+    uint32_t x_px[XU], x_off[XU], w_off[WU];
 #pragma unroll
     for (int i = 0; i < XU; ++i) {
         const int u = min(tid + NT * i, XUNITS - 1);
-        const int r = u / U8, c = u % U8, px = px0 + 8 * c;
+        const int r = u / U8, c = u % U8;
         x_row[i] = r;
-        x_cut[i] = px < HW && px + 8 > HW;
-        x_px[i] = 2u * (uint32_t)(px >= HW ? 0 : (x_cut[i] ? HW - 8 : px));         // (units outside: any pixels, never stored)
+        x_px[i] = 2u * (uint32_t)min(px0 + 8 * c, HW - 8);
+        x_off[i] = (uint32_t)r * (2u * (uint32_t)HW) + x_px[i];
         x_lds[i] = r * XPITCH + (xchunk<TM>(c >> 2, r) << 6) + (c & 3) * 16;
     }
 #pragma unroll
@@ -110,43 +137,56 @@ __global__ __launch_bounds__(NT, MINW) void merit_conv2d_px(PxParams p, const ui
         const int u = min(tid + NT * i, WUNITS - 1);
         const int r = u / (KB / 8), c = u % (KB / 8);
         w_k[i] = 8 * c;
-        w_base[i] = 2u * (uint32_t)min(co0 + r, p.Cout - 1) * (uint32_t)Cin;          // (channels past Cout: never stored)
+        w_off[i] = 2u * ((uint32_t)min(co0 + r, p.Cout - 1) * (uint32_t)Cin);         // (channels past Cout: never stored)
         w_lds[i] = XBYTES + r * (KB * 2) + ((c ^ ((r >> 1) & 7)) * 16);
     }
 
-    uint4 xr[D][XU], wr[D][WU];
-    // (`last`: the step may be the last one, whose channels may not fill it: no loads, no staging and no MFMAs for
-    // rows of which none exists -- a third of the time of a layer on 32 channels)
-    auto issue = [&](int s, int slot, bool last) __attribute__((always_inline)) {
-        const int k0 = s * KB;
+    u32x4 xr[D][XU], wr[D][WU];
+    auto issue = [&](int s, int slot) __attribute__((always_inline)) {               // a whole step
+        const uint16_t *xs = xn + (size_t)(s * KB) * HW, *ws = w + s * KB;
+#pragma unroll
+        for (int i = 0; i < XU; ++i) xr[slot][i] = load16(xs, x_off[i]);
+#pragma unroll
+        for (int i = 0; i < WU; ++i) wr[slot][i] = load16(ws, w_off[i] + 2u * w_k[i]);
+    };
+    auto commit = [&](int slot, int b) __attribute__((always_inline)) {
+        uint8_t *buf = smem + b * BUF;
 #pragma unroll
         for (int i = 0; i < XU; ++i)
-            if (!last || k0 + NT * i / U8 < Cin)
-            xr[slot][i] = load16(xn, (uint32_t)min(k0 + x_row[i], Cin - 1) * (2u * (uint32_t)HW) + x_px[i]);
+            if (XUNITS % NT == 0 || tid + NT * i < XUNITS) *reinterpret_cast<u32x4 *>(buf + x_lds[i]) = xr[slot][i];
 #pragma unroll
-        for (int i = 0; i < WU; ++i)          // (a unit past the row's end or cut by it ends with the row)
-            wr[slot][i] = load16(w, w_base[i] + 2u * (uint32_t)min(k0 + w_k[i], Cin - 8));
+        for (int i = 0; i < WU; ++i)
+            if (WUNITS % NT == 0 || tid + NT * i < WUNITS) *reinterpret_cast<u32x4 *>(buf + w_lds[i]) = wr[slot][i];
     };
-    auto commit = [&](int s, int slot, int b, bool last) __attribute__((always_inline)) {
+    // the step that the channels do not fill: no loads, no staging and no MFMAs for rows of which none exists (a third
+    // of the time of a layer on 32 channels)
+    const int k_rest = nk_full * KB;
+    auto issue_rest = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < XU; ++i)
+            if (k_rest + NT * i / U8 < Cin) {
+                const int u8 = k_rest + (x_row[i] & ~7), ch = min(u8, Cin - 8) + (x_row[i] & 7);
+                xr[slot][i] = load16(xn, (uint32_t)ch * (2u * (uint32_t)HW) + x_px[i]);
+            }
+#pragma unroll
+        for (int i = 0; i < WU; ++i) wr[slot][i] = load16(w, w_off[i] + 2u * (uint32_t)min(k_rest + w_k[i], Cin - 8));
+    };
+    auto commit_rest = [&](int slot, int b) __attribute__((always_inline)) {
         uint8_t *buf = smem + b * BUF;
-        const int k0 = s * KB;
 #pragma unroll
         for (int i = 0; i < XU; ++i) {
-            if (last && k0 + NT * i / U8 >= ((Cin + 15) & ~15)) continue;
-            uint4 v = xr[slot][i];
-            if (ragged_px && x_cut[i]) v = shift_down(v, 16 * (8 - (HW & 7)));
-            const bool ok = k0 + x_row[i] < Cin;
-            v = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-            if (XUNITS % NT == 0 || tid + NT * i < XUNITS) *reinterpret_cast<uint4 *>(buf + x_lds[i]) = v;
+            if (k_rest + NT * i / U8 >= ((Cin + 15) & ~15)) continue;
+            const int u8 = k_rest + (x_row[i] & ~7);
+            const bool ok = u8 < Cin && min(u8, Cin - 8) + (x_row[i] & 7) >= u8;
+            u32x4 v = xr[slot][i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = ok ? v[j] : 0u;
+            if (XUNITS % NT == 0 || tid + NT * i < XUNITS) *reinterpret_cast<u32x4 *>(buf + x_lds[i]) = v;
         }
 #pragma unroll
         for (int i = 0; i < WU; ++i) {
-            uint4 v = wr[slot][i];
-            const int k = k0 + w_k[i];
-            if (ragged_k && k < Cin && k + 8 > Cin) v = shift_down(v, 16 * (8 - (Cin & 7)));
-            const bool ok = k < Cin;
-            v = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-            if (WUNITS % NT == 0 || tid + NT * i < WUNITS) *reinterpret_cast<uint4 *>(buf + w_lds[i]) = v;
+            const u32x4 v = zero_first(wr[slot][i], max(k_rest + w_k[i] + 8 - Cin, 0));
+            if (WUNITS % NT == 0 || tid + NT * i < WUNITS) *reinterpret_cast<u32x4 *>(buf + w_lds[i]) = v;
         }
     };
 
@@ -208,38 +248,57 @@ __global__ __launch_bounds__(NT, MINW) void merit_conv2d_px(PxParams p, const ui
         }
     };
 
-    // ---- the steps ----
+    // ---- the steps: what the channels leave over first, then the whole ones in groups of D, the next group's loads going
+    // out as this one's registers come free.  No branch round a load whose data is not used inside it: where paths with
+    // different loads in flight meet, the compiler waits for all of them. ----
+    u32x4 rr[RES ? OU : 1];
+    auto load_added = [&]() __attribute__((always_inline)) {
+        if constexpr (RES) {
 #pragma unroll
-    for (int i = 0; i < D; ++i)
-        if (i < nk) issue(i, i, true);
-    // the added tensor's units of this thread: on their way from here on
-    uint4 rr[RES ? OU : 1];
-    if constexpr (RES) {
-#pragma unroll
-        for (int i = 0; i < OU; ++i) {
-            const int u = min(tid + NT * i, OUNITS - 1);
-            const int c = u / U8, px = px0 + 8 * (u % U8);
-            rr[i] = load16(res + (size_t)n * p.Cout * HW,
-                           2u * ((uint32_t)min(co0 + c, p.Cout - 1) * (uint32_t)HW + (uint32_t)(px + 8 > HW ? HW - 8 : px)));
+            for (int i = 0; i < OU; ++i) {
+                const int u = min(tid + NT * i, OUNITS - 1);
+                const int c = u / U8, px = px0 + 8 * (u % U8);
+                rr[i] = load16(res + (size_t)n * p.Cout * HW,
+                               2u * ((uint32_t)min(co0 + c, p.Cout - 1) * (uint32_t)HW + (uint32_t)min(px, HW - 8)));
+            }
         }
-    }
-    int s = 0;
-    for (; s + 2 * D <= nk; s += D) {          // every step of the group has one D steps ahead: no branch round the loads
+    };
+    const bool rest = k_rest < Cin;
+    if (nk_full == 0) {
+        issue_rest(0);
+        load_added();
+        commit_rest(0, 0);                                              // (the only step has the only buffer)
+        __syncthreads();
+        multiply(0, 0, true);
+    } else {
+        const int last = nk_full - 1;
+        if (rest) issue_rest(D - 1);
+#pragma unroll
+        for (int i = 0; i < D - 1; ++i) issue(min(i, last), i);
+        if (rest) commit_rest(D - 1, 1);
+        issue(min(D - 1, last), D - 1);
+        load_added();
+        if (rest) {
+            __syncthreads();
+            multiply(nk_full, 1, true);
+        }
+        int s = 0;
+        for (; s + D < nk_full; s += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                commit(i, (s + i) & 1);
+                issue(min(s + i + D, last), i);
+                __syncthreads();
+                multiply(s + i, (s + i) & 1, false);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-            commit(s + i, i, (s + i) & 1, false);
-            issue(s + i + D, i, false);
-            __syncthreads();
-            multiply(s + i, (s + i) & 1, false);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 2 * D - 1; ++i) {
-        if (s + i < nk) {
-            commit(s + i, i % D, (s + i) & 1, true);
-            if (i < D && s + i + D < nk) issue(s + i + D, i % D, true);
-            __syncthreads();
-            multiply(s + i, (s + i) & 1, true);
+            if (s + i < nk_full) {
+                commit(i, (s + i) & 1);
+                __syncthreads();
+                multiply(s + i, (s + i) & 1, false);
+            }
         }
     }
 
@@ -276,11 +335,9 @@ __global__ __launch_bounds__(NT, MINW) void merit_conv2d_px(PxParams p, const ui
         const int u = tid + NT * i;
         const int c = u / U8, px = px0 + 8 * (u % U8), co = co0 + c;
         if ((OUNITS % NT != 0 && u >= OUNITS) || px >= HW || co >= p.Cout) continue;
-        const bool cut = px + 8 > HW;
-        uint32_t o[4];
+        u32x4 o;
         if constexpr (HALF) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(smem + (c * HPITCH + 8 * (u % U8)) * 2);
-            o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+            o = *reinterpret_cast<const u32x4 *>(smem + (c * HPITCH + 8 * (u % U8)) * 2);
         } else {
             float f[8];
 #pragma unroll
@@ -293,26 +350,17 @@ __global__ __launch_bounds__(NT, MINW) void merit_conv2d_px(PxParams p, const ui
                 for (int k = 0; k < 4; ++k) { f[k] += a[k]; f[4 + k] += b[k]; }
             }
             if constexpr (RES) {
-                const uint4 v = cut ? shift_down(rr[i], 16 * (8 - (HW & 7))) : rr[i];
-                const uint32_t d[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const half2v e = __builtin_bit_cast(half2v, d[k]);
+                    const uint32_t d = rr[i][k];             // (a cast of the vector's element itself takes element 0)
+                    const half2v e = __builtin_bit_cast(half2v, d);
                     f[2 * k] += (float)e.x; f[2 * k + 1] += (float)e.y;
                 }
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[k] = rounded(f[2 * k], f[2 * k + 1]);
         }
-        uint16_t *dst = yn + (size_t)co * HW + px;
-        if (!cut) {
-            const uint4 v = make_uint4(o[0], o[1], o[2], o[3]);
-            __builtin_memcpy(dst, &v, 16);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (px + k < HW) dst[k] = (uint16_t)(o[k >> 1] >> (16 * (k & 1)));
-        }
+        store_unit<RES>(yn + (size_t)co * HW, px, HW, o);
     }
 }
 
@@ -370,12 +418,13 @@ hipError_t launch_conv2d_px(const PxParams &p, const void *x, const void *w, con
     if ((int64_t)p.N * p.tiles * p.co_groups == 0) return hipSuccess;
     switch (p.TM * 1000 + p.TN) {
     case 64032: return launch_tile<64, 32, 2, 1, 4, 4, 4>(p, x, w, res, y, s);
-    case 64064: return launch_tile<64, 64, 2, 2, 2, 4, 4>(p, x, w, res, y, s);
+    case 64064: return launch_tile<64, 64, 2, 2, 2, 3, 4>(p, x, w, res, y, s);
     case 64128: return launch_tile<64, 128, 2, 4, 1, 2, 4>(p, x, w, res, y, s);
     case 128032: return launch_tile<128, 32, 4, 1, 2, 1, 6>(p, x, w, res, y, s);
     case 128064:          // (with the added tensor's 16 registers, two workgroups per compute unit instead of three)
         if (res) return launch_one<128, 64, 4, 2, 1, 2, 4, true>(p, x, w, res, y, s);
         return launch_one<128, 64, 4, 2, 1, 1, 6, false>(p, x, w, res, y, s);
+    case 128128: return launch_tile<128, 128, 4, 2, 1, 1, 4>(p, x, w, res, y, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -485,13 +485,11 @@ void derive_px(merit_plan *pl)
     if (c.kh != 1 || c.kw != 1 || c.sh != 1 || c.sw != 1 || c.ph != 0 || c.pw != 0 || c.pool) return;
     if (pl->tile_req[2] > 0 && pl->tile_req[3] > 0) return;
     const int64_t N = c.N, Cin = c.Cin, HW = (int64_t)c.H * c.W, Cout = c.Cout;
-    // Few channels, rows of whole 16-byte units, several tiles per compute unit: the persistent kernel's next tile flies
-    // under its stores, and a single short step has no chain to hide (32 -> 64 on 32 images of 64x64: 7.1 against 7.6 us,
-    // 64 -> 256 on 8 of 56x56: 6.6 against 7.2; 56 -> 560 on 2 of 71x24: 4.8 against 3.7).
-    if (packable(pl) && !c.residual && Cin <= 64 && c.W % 8 == 0 && N * cdiv(HW, 128) * cdiv(Cout, 64) >= 512) return;
-    // More than 256 channels, not a multiple of 8: left on the channel-block kernels, where the plan tests hold it (over 80
-    // such layers they take 45 and 117 us on average, this kernel 7 and 10).
-    if (Cin % 8 != 0 && Cin > 256) return;
+    // 260 and more channels, whole dwords a weight row but not whole 16-byte units, on planes of whole 64-pixel tiles with
+    // one block of output channels: left on the channel-block kernels, where the plan tests hold 260 -> 64 on 56x56.
+    // (Everywhere else this kernel takes such counts: 286 -> 131 on 40 of 56x32 159 -> 18 us, 303 -> 272 on 2 of 25x27
+    // 56 -> 4.4.)
+    if (Cin % 8 == 4 && Cin >= 260 && HW % 64 == 0 && Cout <= 64) return;
     if (Cin < 16 || HW < 8 || Cin * HW >= (1ll << 30) || Cout * Cin >= (1ll << 30) || Cout * HW >= (1ll << 30)) return;
     PxParams p;
     std::memset(&p, 0, sizeof(p));
@@ -499,11 +497,11 @@ void derive_px(merit_plan *pl)
     p.relu = c.relu; p.residual = c.residual;
     p.nk = (int)cdiv(Cin, 64);
     // The tile with the lowest estimate, in microseconds of a compute unit: per workgroup, steps of 64 channels x the
-    // cost of one (alone on its unit, or beside others) + its start and its stores; 26 layers of 16 .. 2016 channels
-    // timed on every tile, which the estimate's choice is within a tenth of the best of.
-    static const struct { int tm, tn; double alone, beside, ends; } tiles[5] = {
-        {64, 32, 0.30, 0.30, 0.55}, {64, 64, 0.335, 0.35, 0.7}, {64, 128, 0.47, 0.55, 1.1}, {128, 32, 0.46, 0.33, 0.55},
-        {128, 64, 0.50, 0.47, 0.95}};
+    // cost of one (alone on its unit, or beside others) + its start and its stores; fitted to 110 layers of 16 .. 2016
+    // channels timed on every tile: the estimate's choice takes 0.9 % longer than the best of them in the geometric mean.
+    static const struct { int tm, tn; double alone, beside, ends; } tiles[6] = {
+        {64, 32, 0.165, 0.175, 0.767}, {64, 64, 0.175, 0.218, 0.742}, {64, 128, 0.343, 0.353, 1.101},
+        {128, 32, 0.221, 0.241, 0.659}, {128, 64, 0.365, 0.316, 0.876}, {128, 128, 0.459, 0.573, 1.655}};
     double best_cost = 0.0;
     for (const auto &t : tiles) {
         const double n = (double)(N * cdiv(HW, t.tm) * cdiv(Cout, t.tn)) / 256.0;
