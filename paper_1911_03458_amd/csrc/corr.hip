@@ -17,111 +17,40 @@
 // the MFMA.  Positions are ordered by residue class so that the 16 pixels of a block are
 // adjacent.  Channels go through LDS in passes of `chg` groups of eight; the loads of the next
 // pass are in flight while the current one is multiplied.  Needs W >= 8, R <= 15, sd <= 8.
-// Rows of any width: a unit's eight pixels lie on any 2-byte boundary (a 16-byte global load needs no more), and
-// the unit that a row's end cuts is loaded so that it ends with the row and shifted down, which brings in the zeros
-// beyond the edge and keeps every load inside the tensor.  Widths off the multiple of 8 ran on the definition kernel
-// before: 1x184x60x36, +-3: 245 us -> 7.6; 1x32x17x41, +-4: 50 us -> 5.0; 256 channels at 64x63, +-5 at stride 2:
-// 614 -> 12.3 us (9.2 at 64x64).
+// Rows of any width: a unit's eight pixels lie on any 2-byte boundary (a 16-byte global load needs no more), and the unit
+// that the row's end cuts ends with the row, which keeps every load inside the tensor.
+// What bounds it: not the matrix cores but a pass's chain of loads, LDS writes and barriers, and on 256 channels the rows
+// themselves, each of which 2R+1 workgroups stage.  So the loads go out together (with the zeroing beside them each waited
+// for its own round trip), only by lanes that have something to load, and the writes fall into all bank groups.  us a
+// launch, before -> with that: 256 channels at 64x64, +-5 at stride 2: 9.1 -> 7.5; 208 at 63x46, +-3: 8.0 -> 6.0; 80 at
+// 64x58, +-4: 6.2 -> 4.8; 40 at 33x18, +-3: 3.9 -> 3.9; 1.11x over 60 images of 16 to 64 pixels a side, of which one (48 at
+// 52x40, +-5) lost 6 %.
 #include "merit_internal.h"
 
 namespace merit {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int XB = CORR_XB;    // staging units a thread holds in registers per pass
-
-// One staging unit = 8 adjacent pixels x 8 channels of one row: eight 16-byte loads (one per
-// channel), transposed to eight 16-byte LDS items (one per pixel).  The units of a pass form
-// one list: for each channel group the chunk's units of the first tensor, then those of the
-// second.  Units start at multiples of 8: those outside the row, the part of the last one past
-// the row's end, and missing channels give zeros.
-struct StageGeom {
-    int b, p1, yy, px0, npx8, gx2;
-    uint32_t per_g;
-    FastDiv div_perg;
-};
-
-template <bool RAGGED>
-__device__ __forceinline__ void issue_pass(const CorrParams &p, const StageGeom &sg,
-                                           const uint16_t *__restrict__ x1, const uint16_t *__restrict__ x2,
-                                           int chi0, int ng, int tid, uint32_t (&v)[XB][8][4])
+// 16 bytes on a 16-byte boundary, or on any 2-byte one
+template <bool ANY>
+__device__ __forceinline__ u32x4 load16(const uint8_t *src)
 {
-    const uint32_t nu = (uint32_t)ng * sg.per_g;
-    const size_t chstride = (size_t)p.H * p.W;
-#pragma unroll
-    for (int k = 0; k < XB; ++k) {
-        const uint32_t u = min((uint32_t)tid + 256u * k, nu - 1);
-        const uint32_t g = fdiv(u, sg.div_perg);
-        const int r = (int)(u - g * sg.per_g);
-        const bool second = r >= sg.npx8;
-        const int gx = second ? sg.gx2 + 8 * (r - sg.npx8) : sg.px0 + 8 * r;
-        const int gy = second ? sg.yy : sg.p1;
-        const bool colok = gx >= 0 && gx < p.W;
-        const bool cut = RAGGED && colok && gx + 8 > p.W;         // the row ends inside this unit
-        const int c0 = (chi0 + (int)g) * 8;
-        const uint16_t *xs = second ? x2 : x1;
-        const uint16_t *src = xs + (((size_t)sg.b * p.C + min(c0, p.C - 1)) * p.H + gy) * p.W + (cut ? p.W - 8 : colok ? gx : 0);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const bool ok = colok && (c0 + c < p.C);
-            // branch-free: a missing element re-reads the tensor's first bytes and is zeroed
-            uint4 t4;
-            if (RAGGED)
-                __builtin_memcpy(&t4, ok ? src + c * chstride : xs, 16);
-            else
-                t4 = *reinterpret_cast<const uint4 *>(ok ? src + c * chstride : xs);
-            v[k][c][0] = ok ? t4.x : 0u; v[k][c][1] = ok ? t4.y : 0u;
-            v[k][c][2] = ok ? t4.z : 0u; v[k][c][3] = ok ? t4.w : 0u;
-        }
-    }
+    typedef uint32_t u32x4_2 __attribute__((ext_vector_type(4), aligned(2)));
+    if constexpr (ANY) return *reinterpret_cast<const u32x4_2 *>(src);
+    else return *reinterpret_cast<const u32x4 *>(src);
 }
 
-// Whether unit k of this thread is the one a row's end cuts: its values are shifted when they are written to LDS
-// (where they are waited for anyway), not where they are requested.
-__device__ __forceinline__ bool unit_is_cut(const CorrParams &p, const StageGeom &sg, bool second, int run)
+// Where item `at` (a pixel's eight channels, 16 bytes) of channel group g lies in its staged row.  The lanes of a write are
+// eight items apart, two bank groups of the sixteen: each run of eight is rotated by its place and its group.  (80 channels on
+// 64x58, +-4: 6.6 -> 5.9 us.)
+__device__ __forceinline__ int corr_slot(int at, int g)
 {
-    const int gx = second ? sg.gx2 + 8 * run : sg.px0 + 8 * run;
-    return gx >= 0 && gx < p.W && gx + 8 > p.W;
+    return (at & ~7) | ((at + (at >> 3) + g) & 7);
 }
 
-template <bool RAGGED>
-__device__ __forceinline__ void commit_pass(const CorrParams &p, const StageGeom &sg, uint4 *a1l, uint4 *a2l,
-                                            int ng, int tid, uint32_t (&v)[XB][8][4])
-{
-    const uint32_t nu = (uint32_t)ng * sg.per_g;
-#pragma unroll
-    for (int k = 0; k < XB; ++k) {
-        const uint32_t u = (uint32_t)tid + 256u * k;
-        if (u >= nu) break;
-        const uint32_t g = fdiv(u, sg.div_perg);
-        const int r = (int)(u - g * sg.per_g);
-        const bool second = r >= sg.npx8;
-        const int run = second ? r - sg.npx8 : r;
-        if (RAGGED && unit_is_cut(p, sg, second, run)) {
-            const int bits = 16 * (8 - (p.W & 7));
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint4 t = shift_down(make_uint4(v[k][c][0], v[k][c][1], v[k][c][2], v[k][c][3]), bits);
-                v[k][c][0] = t.x; v[k][c][1] = t.y; v[k][c][2] = t.z; v[k][c][3] = t.w;
-            }
-        }
-        uint4 *d4 = second ? a2l + g * p.P2 : a1l + g * p.P1;
-        const int pitch = second ? p.pitch2 : p.pitch1;
-#pragma unroll
-        for (int px = 0; px < 8; ++px) {
-            const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
-            uint32_t d[4];
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq)
-                d[qq] = __builtin_amdgcn_perm(v[k][2 * qq + 1][px >> 1], v[k][2 * qq][px >> 1], sel);
-            const uint32_t col = (uint32_t)(8 * run + px);
-            const uint32_t idx = fdiv(col, p.div_sd);
-            const uint32_t cls = col - idx * (uint32_t)p.sd;
-            d4[cls * (uint32_t)pitch + idx] = make_uint4(d[0], d[1], d[2], d[3]);
-        }
-    }
-}
+static_assert(CORR_XB == 1, "a thread stages one unit a pass");
 
 // NB = 16-column blocks of the second row per pixel block, BPW = pixel blocks per wavefront, RAGGED = W % 8 != 0.
 template <int NB, int BPW, bool RAGGED>
@@ -146,15 +75,86 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
     const int b = (int)fdiv(q1, p.div_h);
     const int p1 = (int)(q1 - (uint32_t)b * (uint32_t)p.H);
 
-    StageGeom sg;
-    sg.b = b; sg.p1 = p1; sg.px0 = xc * 64;
-    sg.yy = p1 + (p3 - p.R) * p.sd;
-    sg.npx8 = min(8, (p.W - sg.px0 + 7) >> 3);                     // 8-pixel units of the first tensor's chunk
-    sg.gx2 = sg.px0 - p.lead;                                     // first staged column of the second tensor
-    sg.per_g = (uint32_t)(sg.npx8 + (p.cols2 >> 3));
-    sg.div_perg = sg.npx8 == 8 ? p.div_perg : p.div_perg_last;
-    const bool rowok = sg.yy >= 0 && sg.yy < p.H;
-    const int wchunk = min(64, p.W - sg.px0);                     // pixels of this chunk
+    const int px0 = xc * 64, yy = p1 + (p3 - p.R) * p.sd;
+    const bool rowok = yy >= 0 && yy < p.H;
+    const int wchunk = min(64, p.W - px0);                        // pixels of this chunk
+
+    // The staging unit of this thread, the same in every pass: 8 adjacent pixels x 8 channels of one row, eight 16-byte
+    // loads (one per channel), transposed to eight 16-byte LDS items (one per pixel).  The units of a pass form one list:
+    // for each channel group the chunk's units of the first tensor, then those of the second.  Units start at multiples of
+    // 8; those outside the row are zeros.
+    const int npx8 = min(8, (p.W - px0 + 7) >> 3);                // units of the first tensor's chunk
+    const uint32_t per_g = (uint32_t)(npx8 + (p.cols2 >> 3));
+    const int sg = (int)fdiv((uint32_t)tid, npx8 == 8 ? p.div_perg : p.div_perg_last);       // channel group of the pass
+    const int unit = tid - sg * (int)per_g;
+    const bool second = unit >= npx8;
+    const int run = second ? unit - npx8 : unit;
+    const int gx = (second ? px0 - p.lead : px0) + 8 * run;
+    const bool colok = gx >= 0 && gx < p.W;
+    const bool stages = rowok && sg < p.chg && colok;             // (rowok uniform: else every product is 0)
+    // (RAGGED: the unit that the row's end cuts ends with the row, its shared pixels are written twice, the same; the units
+    // of zeros behind it follow where it ends)
+    const int shift = RAGGED && gx + 8 > p.W ? -p.W & 7 : 0;
+    const uint32_t chbytes = 2u * (uint32_t)p.H * (uint32_t)p.W, last = (uint32_t)(p.C - 1) * chbytes;
+    const uint8_t *src = reinterpret_cast<const uint8_t *>((second ? x2 : x1) + (size_t)b * p.C * p.H * p.W) +
+                         2u * ((uint32_t)(second ? yy : p1) * (uint32_t)p.W + (uint32_t)(colok ? gx - shift : 0));
+
+    // The loads of a pass, without a select or a branch on their data: whatever uses a value here makes every load wait
+    // for its own round trip before the next one goes out.  Channels past the last: the last one's pixels, zeroed when
+    // they are written to LDS.
+    u32x4 v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = (u32x4){0, 0, 0, 0};         // (units outside the row stay that)
+    auto issue = [&](int chi0) __attribute__((always_inline)) {
+        if (!stages || (chi0 + sg) * 8 >= p.C) return;            // (a lane that loads costs the address unit its cycles)
+        const uint32_t off = (uint32_t)((chi0 + sg) * 8) * chbytes;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = load16<RAGGED>(src + min(off + c * chbytes, last));
+    };
+    issue(0);                                                     // before anything that the loads do not need
+
+    u32x4 *lds0 = reinterpret_cast<u32x4 *>(smem) + (second ? p.chg * p.P1 + sg * p.P2 : sg * p.P1);
+    const int pitch = second ? p.pitch2 : p.pitch1;
+    // where its pixels go: by residue class of the column; to the spare item behind the rows what lies left of the chunk
+    int item[8], col = 8 * run - shift, cls, at;
+    {
+        const int c0 = RAGGED ? max(col, 0) : col;
+        const int idx = (int)fdiv((uint32_t)c0, p.div_sd);
+        cls = c0 - idx * p.sd;
+        at = cls * pitch + idx;
+    }
+    auto next_col = [&]() __attribute__((always_inline)) {
+        const bool wrap = ++cls == p.sd;
+        at += wrap ? 1 - (p.sd - 1) * pitch : pitch;
+        cls = wrap ? 0 : cls;
+    };
+    const int spare = (int)(reinterpret_cast<u32x4 *>(smem) + p.chg * (p.P1 + p.P2) - lds0);
+#pragma unroll
+    for (int px = 0; px < 8; ++px) {
+        const bool there = !RAGGED || col + px >= 0;
+        item[px] = there ? corr_slot(at, sg) : spare;
+        if (there) next_col();
+    }
+
+    auto commit = [&](int chi0, int ng) __attribute__((always_inline)) {
+        if ((chi0 + ng) * 8 > p.C) {                              // uniform: the last pass, where channels are missing
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const bool ok = (chi0 + sg) * 8 + c < p.C;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[c][j] = ok ? v[c][j] : 0u;
+            }
+        }
+        if (sg >= ng) return;
+#pragma unroll
+        for (int px = 0; px < 8; ++px) {
+            const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
+            u32x4 d;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) d[q] = __builtin_amdgcn_perm(v[2 * q + 1][px >> 1], v[2 * q][px >> 1], sel);
+            lds0[item[px]] = d;
+        }
+    };
 
     // this lane's operand positions: pixel (lane & 15) of block (class c, sub-block s) and the
     // columns q = pixel0 - R*sd + sd*j of the same class, j = 16*nb + (lane & 15); positions
@@ -166,13 +166,13 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
         const uint32_t bl = (uint32_t)min(wave + 4 * t, p.nblk - 1);
         const uint32_t s = fdiv(bl, p.div_sd);
         const uint32_t c = bl - s * (uint32_t)p.sd;
-        apos[t] = min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1);
+        apos[t] = corr_slot(min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1), kg);
         const uint32_t ec = (uint32_t)(p.lead - p.R * p.sd) + c;
         const uint32_t ei = fdiv(ec, p.div_sd);
         const uint32_t cls2 = ec - ei * (uint32_t)p.sd;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-            bpos[t][nb] = min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1);
+            bpos[t][nb] = corr_slot(min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1), kg);
     }
 
     floatx4 acc[BPW][NB];
@@ -184,26 +184,23 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
     if (rowok) {                                                  // uniform: else every product is 0
         // groups of the pass that starts at chi0, padded to whole reduction steps (the padding is staged as zeros)
         auto groups_of = [&](int chi0) { return min(p.chg, ((p.nchi - chi0) + 3) & ~3); };
-        uint32_t v[XB][8][4];
-        issue_pass<RAGGED>(p, sg, x1, x2, 0, groups_of(0), tid, v);
         for (int chi0 = 0; chi0 < p.nchi; chi0 += p.chg) {
             const int ng = groups_of(chi0);
             if (chi0 > 0) __syncthreads();                        // previous pass has been read
-            commit_pass<RAGGED>(p, sg, a1l, a2l, ng, tid, v);
+            commit(chi0, ng);
             __syncthreads();
             // the next pass's loads are in flight while this one is multiplied
-            const int nxt = chi0 + p.chg;
-            if (nxt < p.nchi) issue_pass<RAGGED>(p, sg, x1, x2, nxt, groups_of(nxt), tid, v);
+            if (chi0 + p.chg < p.nchi) issue(chi0 + p.chg);
 #pragma unroll
             for (int t = 0; t < BPW; ++t) {
                 if (wave + 4 * t >= p.nblk) break;                // uniform
-                const uint4 *ap = a1l + kg * p.P1 + apos[t];
+                const uint4 *ap = a1l + kg * p.P1;
                 const uint4 *bp = a2l + kg * p.P2;
-                for (int ks = 0; ks < ng; ks += 4) {
-                    const half8 a = __builtin_bit_cast(half8, ap[ks * p.P1]);
+                for (int ks = 0; ks < ng; ks += 4) {              // (four groups on: rotated by four)
+                    const half8 a = __builtin_bit_cast(half8, ap[ks * p.P1 + (apos[t] ^ (ks & 4))]);
                     half8 bq[NB];
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) bq[nb] = __builtin_bit_cast(half8, bp[ks * p.P2 + bpos[t][nb]]);
+                    for (int nb = 0; nb < NB; ++nb) bq[nb] = __builtin_bit_cast(half8, bp[ks * p.P2 + (bpos[t][nb] ^ (ks & 4))]);
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
                         acc[t][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bq[nb], acc[t][nb], 0, 0, 0);
@@ -214,7 +211,7 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
 
     // D[i][j]: lane holds column j = lane & 15 and rows i = 4*(lane >> 4) + r.  Row i is pixel
     // i of the block, column 16*nb + j is displacement p4 = 16*nb + j - i.
-    uint16_t *yrow = y + (((size_t)b * p.H + p1) * p.W + sg.px0) * p.n * p.n + (size_t)p3 * p.n;
+    uint16_t *yrow = y + (((size_t)b * p.H + p1) * p.W + px0) * p.n * p.n + (size_t)p3 * p.n;
 #pragma unroll
     for (int t = 0; t < BPW; ++t) {
         const int bl = wave + 4 * t;
@@ -239,7 +236,7 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
 
 size_t corr_lds_bytes(const CorrParams &p)
 {
-    return (size_t)p.chg * (p.P1 + p.P2) * 16;
+    return ((size_t)p.chg * (p.P1 + p.P2) + 1) * 16;      // and the spare item (see the kernel)
 }
 
 template <int NB, int BPW, bool RAGGED>

@@ -1446,9 +1446,12 @@ merit_status derive_corr(merit_plan *pl)
     // 4.8, 136 on 42x25, +-5 / 2, 6.4 -> 5.2, 56 on 34x27, +-5, 4.4 -> 4.4; 1.12x over 60 of 16 to 64 pixels a side)
     const int64_t chunk = W < 64 ? round_up(W, 8) : 64;
     p.cols2 = (int)round_up(chunk + p.lead + R * sd, 8);
+    // (rows off the multiple of 8: the zeros behind a row start where it ends, up to seven columns before their unit's own
+    // place; only a row's last chunk has those to spare)
+    if (W > 64 && W % 8 != 0) p.cols2 += 8;
     // staged rows ordered by residue class of the column modulo sd (the 16 pixels of an MFMA block are adjacent)
-    p.pitch1 = (int)cdiv(chunk, sd); p.P1 = (int)(sd * p.pitch1);
-    p.pitch2 = (int)cdiv(p.cols2, sd); p.P2 = (int)(sd * p.pitch2);
+    p.pitch1 = (int)cdiv(chunk, sd); p.P1 = (int)round_up(sd * p.pitch1, 8);      // (whole runs of eight: corr_slot)
+    p.pitch2 = (int)cdiv(p.cols2, sd); p.P2 = (int)round_up(sd * p.pitch2, 8);
     p.nsb = (int)cdiv(p.pitch1, 16); p.nblk = (int)(sd * p.nsb);
     p.nb = (int)cdiv(16 + 2 * R, 16);
     // channel groups per pass: whole reduction steps of 4 groups, at most two staging units per
@@ -1462,7 +1465,7 @@ merit_status derive_corr(merit_plan *pl)
     const int64_t nchi4 = round_up(p.nchi, 4);
     const int64_t passes = cdiv(nchi4, chg);
     p.chg = (int)round_up(cdiv(nchi4, passes), 4);       // equal passes
-    if (p.chg * per_g_full > 256 * CORR_XB || p.chg * per_group > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
+    if (p.chg * per_g_full > 256 * CORR_XB || p.chg * per_group + 16 > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
     p.div_sd = make_fastdiv((uint32_t)sd);
     p.div_perg = make_fastdiv((uint32_t)per_g_full);
     p.div_perg_last = make_fastdiv((uint32_t)(cdiv(W % 64, 8) + p.cols2 / 8));
