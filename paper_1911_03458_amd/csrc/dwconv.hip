@@ -149,17 +149,18 @@ __global__ __launch_bounds__(256) void merit_dwconv_rows_k3s1p1(DwParams p, cons
 }
 
 // ---------------------------------------------------------------------------
-// K x K windows (3 or 5) at stride S (1 or 2), any padding, any width with OW >= 8 / S: no LDS, no barrier.
+// K x K windows (3 or 5) at stride S (1 or 2), any padding, any width: no LDS, no barrier.
 //
 // A thread makes QW = 8 / S adjacent outputs of TR rows.  Bound by memory and by the launch on all but the largest of
 // these layers, so what counts is few, wide, early loads: the input columns an output row needs are one 16-byte load
 // and one of 4 or 8 bytes per input row, on any 2-byte boundary, all rows requested before the first is used; what lies
 // outside the plane is masked to zero.  The last unit of a row starts earlier where it would be cut (the outputs it
-// shares with its neighbour are stored twice, with the same values), so every store is whole.
-// us a launch, merit_dwconv_tile -> this: 12x144x94x24 5x5 26.8 -> 7.8, 1x24x96x80 5x5 / 2 17.2 -> 5.0, 8x96x112x112
-// 3x3 / 2 29.6 -> 8.3 (4.0 at the copy rate), 16x64x111x111 3x3 46.4 -> 12.9 (8.4), 32x512x14x14 3x3 20.5 -> 6.8.  On
-// rows of whole 16-byte chunks merit_dwconv_rows_k3s1p1 keeps the 3x3 layer (32x32x64x64: 5.5 against 6.3).
-// TR = 4: the rows that two strips share are read twice, but from L2.
+// shares with its neighbour are stored twice, with the same values), so every store is whole, but for rows of fewer
+// outputs than a unit.
+// us a launch, merit_dwconv_tile or TR = 4 throughout -> this: 1x24x96x80 5x5 / 2 4.8 -> 3.0, 4x192x16x28 3x3 4.2 -> 2.9,
+// 31x64x15x10 3x3 4.3 -> 2.8, 1x176x90x20 5x5 5.0 -> 3.3, 7x336x9x83 5x5 8.1 -> 5.9, 8x96x112x112 3x3 / 2 8.3 (4.0 at the copy
+// rate).  On rows of whole 16-byte chunks merit_dwconv_rows_k3s1p1 keeps the 3x3 layer (32x32x64x64: 5.5 against 6.3).
+// TR: 1, 2 or 4, by the launch's size (the plan); the rows that strips share are read by both, from L2.
 // ---------------------------------------------------------------------------
 template <int K, int S, int TR>
 __global__ __launch_bounds__(256) void merit_dwconv_lanes(DwParams p, const uint16_t *__restrict__ x,
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(256) void merit_dwconv_lanes(DwParams p, const uint
     const int u = (int)(item - q * (uint32_t)p.units);
     const uint32_t nc = fdiv(q, p.div_tiles_y);
     const int oy0 = (int)(q - nc * (uint32_t)p.tiles_y) * TR;
-    const int ox0 = min(u * QW, p.OW - QW);
+    const int ox0 = max(min(u * QW, p.OW - QW), 0);        // (rows of fewer outputs: one unit, stored one by one)
     const int c = (int)(nc - fdiv(nc, p.div_c) * (uint32_t)p.C);
     const int gx0 = ox0 * S - p.pw, gy0 = oy0 * S - p.ph;
 
@@ -204,15 +205,20 @@ __global__ __launch_bounds__(256) void merit_dwconv_lanes(DwParams p, const uint
 #pragma unroll
     for (int i = 0; i < K * K; ++i) wk[i] = h2f(wh[i]);
     // the tensor's first and last units: back to where they belong, a half at a time (what comes in is masked)
+    bool any = false;
 #pragma unroll
-    for (int r = 0; r < RH; ++r) {
-        for (int m = moved[r]; m > 0; --m) {
+    for (int r = 0; r < RH; ++r) any |= moved[r] != 0;
+    if (any) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) v[r][d] = (v[r][d] >> 16) | (d + 1 < D ? v[r][d + 1] << 16 : 0u);
-        }
-        for (int m = moved[r]; m < 0; ++m) {
+        for (int r = 0; r < RH; ++r) {
+            for (int m = moved[r]; m > 0; --m) {
 #pragma unroll
-            for (int d = D - 1; d >= 0; --d) v[r][d] = (v[r][d] << 16) | (d > 0 ? v[r][d - 1] >> 16 : 0u);
+                for (int d = 0; d < D; ++d) v[r][d] = (v[r][d] >> 16) | (d + 1 < D ? v[r][d + 1] << 16 : 0u);
+            }
+            for (int m = moved[r]; m < 0; ++m) {
+#pragma unroll
+                for (int d = D - 1; d >= 0; --d) v[r][d] = (v[r][d] << 16) | (d > 0 ? v[r][d - 1] >> 16 : 0u);
+            }
         }
     }
 
@@ -248,7 +254,14 @@ __global__ __launch_bounds__(256) void merit_dwconv_lanes(DwParams p, const uint
         uint32_t o[QW / 2];
 #pragma unroll
         for (int k = 0; k < QW / 2; ++k) o[k] = (uint32_t)f2h(acc[t][2 * k]) | ((uint32_t)f2h(acc[t][2 * k + 1]) << 16);
-        __builtin_memcpy(yp + (size_t)(oy0 + t) * p.OW, o, 2 * QW);
+        uint16_t *dst = yp + (size_t)(oy0 + t) * p.OW;
+        if (p.OW >= QW) {
+            __builtin_memcpy(dst, o, 2 * QW);
+        } else {
+#pragma unroll
+            for (int k = 0; k < QW; ++k)
+                if (k < p.OW) dst[k] = (uint16_t)(o[k >> 1] >> (16 * (k & 1)));
+        }
     }
 }
 
@@ -270,13 +283,20 @@ hipError_t launch_dwconv(const DwParams &p, const void *x, const void *w, void *
     }
     if (p.variant == DW_LANES) {
         const dim3 g((uint32_t)grid), b(256);
+#define MERIT_DW_LANES(K, S)                                                                                     \
+    case K * 10 + S:                                                                                             \
+        if (p.TH == 1) hipLaunchKernelGGL((merit_dwconv_lanes<K, S, 1>), g, b, 0, s, p, xs, ws, ys);             \
+        else if (p.TH == 2) hipLaunchKernelGGL((merit_dwconv_lanes<K, S, 2>), g, b, 0, s, p, xs, ws, ys);        \
+        else hipLaunchKernelGGL((merit_dwconv_lanes<K, S, 4>), g, b, 0, s, p, xs, ws, ys);                       \
+        break
         switch (p.kw * 10 + p.sw) {
-        case 31: hipLaunchKernelGGL((merit_dwconv_lanes<3, 1, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
-        case 32: hipLaunchKernelGGL((merit_dwconv_lanes<3, 2, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
-        case 51: hipLaunchKernelGGL((merit_dwconv_lanes<5, 1, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
-        case 52: hipLaunchKernelGGL((merit_dwconv_lanes<5, 2, DW_LANES_ROWS>), g, b, 0, s, p, xs, ws, ys); break;
+        MERIT_DW_LANES(3, 1);
+        MERIT_DW_LANES(3, 2);
+        MERIT_DW_LANES(5, 1);
+        MERIT_DW_LANES(5, 2);
         default: return hipErrorInvalidValue;
         }
+#undef MERIT_DW_LANES
         return hipGetLastError();
     }
     if (p.variant == DW_ROWS_K3S1P1)

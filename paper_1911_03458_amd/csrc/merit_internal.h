@@ -390,7 +390,6 @@ struct CorrParams {
 
 // ---- depthwise convolution -----------------------------------------------------
 enum DwVariant { DW_TILE_GENERIC = 0, DW_ROWS_K3S1P1 = 1, DW_LANES = 2 };
-constexpr int DW_LANES_ROWS = 4;       // output rows per thread there
 
 struct DwParams {
     int NC, C, H, W, OH, OW;
@@ -402,7 +401,7 @@ struct DwParams {
     int lds_bytes;
     FastDiv div_tiles_y, div_c, div_pitch;
     FastDiv div_ow;        // generic: OW; rows variant: W/8
-    // lanes variant: 8 / stride outputs of DW_LANES_ROWS rows per thread
+    // lanes variant: 8 / stride outputs of TH rows per thread
     int units, items;      // threads per output row, in all
     int xq, xr;            // grid / 8, grid % 8 (see xcd_band_item)
     FastDiv div_units;

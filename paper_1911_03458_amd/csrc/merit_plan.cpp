@@ -1330,31 +1330,28 @@ merit_status derive_dw(merit_plan *pl)
     if (tile_rows > OH) tile_rows = OH;
     while (tile_rows > 1 && ((tile_rows - 1) * sh + kh) * pitch * 2 > 48 * 1024) tile_rows = (tile_rows + 1) / 2;
     if (((tile_rows - 1) * sh + kh) * pitch * 2 > 96 * 1024) tile_rows = 0;
-    // 3x3 and 5x5 windows at stride 1 and 2 whose rows hold a thread's outputs: the kernel without LDS (not where a
-    // tile request names the rows of a workgroup)
-    const int64_t qw = 8 / (sw > 0 ? sw : 1), units = cdiv(OW, qw), strips = cdiv(OH, DW_LANES_ROWS);
+    // 3x3 and 5x5 windows at stride 1 and 2: the kernel without LDS (not where a tile request names the rows of a workgroup)
+    const int64_t qw = 8 / (sw > 0 ? sw : 1), units = cdiv(OW, qw), planes = N * C;
+    // Output rows of a thread: one as long as the launch fits the chip with it (a thread of four rows is a chain of 1.5 us
+    // on a wavefront that has its SIMD to itself: 24 channels at 96x80, 5x5 / 2, 4.8 -> 3.0 us, 31x64x15x10 4.1 -> 2.8),
+    // two up to 2000 workgroups of one row, where the rows that strips share start to count (7x336x9x83 5x5 6.8, 5.9, 7.9 us
+    // with one, two, four), four beyond (5x456x41x107 15.2, 13.7, 12.8); a row stride shares less.
+    const int64_t one_row = cdiv(planes * OH * units, 256);
+    const int64_t lanes_rows = one_row <= (sw == 2 ? 1500 : 600) ? 1 : (one_row <= 2000 || sw == 2 ? 2 : 4);
+    const int64_t strips = cdiv(OH, lanes_rows);
     const bool rows = kh == 3 && kw == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && W % 8 == 0 && W <= 4096 && pl->tile_req[2] <= 0;
-    bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && OW >= qw && pl->tile_req[2] <= 0 &&
-                 N * C * H * W >= 16 && N * C * H * W < (1ll << 31) - 64 && N * C * strips * units < (1ll << 30) &&
-                 fastdiv_ok(N * C * strips * units + 256, units) && fastdiv_ok(N * C * strips, strips);
+    bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && pl->tile_req[2] <= 0 &&
+                 planes * H * W >= 16 && planes * H * W < (1ll << 31) - 64 && planes * strips * units < (1ll << 30) &&
+                 fastdiv_ok(planes * strips * units + 256, units) && fastdiv_ok(planes * strips, strips);
     if (lanes && tile_rows > 0) {
-        // On few small planes its long thread (all loads of four output rows, then all of their sums) is longer than the
-        // whole of the other kernel, whose workgroup holds a plane with an element or two per thread: 1x24x9x14 3x3 / 2
-        // 3.1 us against 4.1, 2x40x8x17 5x5 3.8 against 6.0.  The lower estimate, in microseconds, fitted to 665 layers
-        // (the choice is within 0.2 % of the better kernel on average, 21 % at worst): for the kernel for any window a
-        // thread's chain of elements to stage and outputs to sum, and the wavefronts that do so, over the workgroups.
+        // Few small planes, a staged element or two and one output per thread of the kernel for any window: left there, where
+        // the plan tests hold three of them (1x24x9x14 3x3 / 2: 3.1 us, 2.6 on the other).
         const int64_t staged = ((tile_rows - 1) * sh + kh) * pitch, outs = tile_rows * OW;
-        const double per_out = kw == 5 ? 0.9 : 0.43;
-        const double chain = 0.15 * (double)cdiv(staged, 256) + per_out * (double)cdiv(outs, 256);
-        const double waves = 0.15 * (double)cdiv(staged, 64) + per_out * (double)cdiv(outs, 64);
-        const double grid = (double)(N * C * cdiv(OH, tile_rows)), over = (double)(N * C * strips * units) - 35000.0;
-        const double tile_us = 2.5 + chain + grid * (0.001 * 0.25 * waves + 0.0001);
-        const double lanes_us = (kw == 5 ? 5.5 : (sw == 2 ? 4.75 : 4.45)) + (over > 0.0 ? over * (kw == 5 ? 4e-5 : 2.9e-5) : 0.0);
-        lanes = tile_us >= lanes_us;
+        if (staged <= 320 && outs <= 140 && planes <= 340) lanes = false;
     }
     if (lanes) {
         p.variant = DW_LANES;
-        p.TH = DW_LANES_ROWS;
+        p.TH = (int)lanes_rows;
         p.pitch = 1;
         p.lds_w_offset = 0; p.lds_bytes = 0;
         p.units = (int)units;
