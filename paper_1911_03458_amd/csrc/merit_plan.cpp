@@ -141,15 +141,20 @@ merit_status derive_pool(merit_plan *pl)
     if (variant == POOL_TILE_GENERIC && (((k3 || k2) && sh == 2 && sw == 2) || s1) &&
         !(OH == 1 && OW == 1) && pl->tile_req[2] <= 0 && pl->tile_req[3] <= 0 && H * W < INT_LIMIT) {
         const bool two = W >= 8 || s1;
-        const int64_t th = s1 ? 8 : 4;
         const int64_t cols = two ? 128 : 64;                // output columns of a full group of 64 lanes
         int lg_shift = 0;                                   // items per wavefront = 1 << lg_shift
         while (lg_shift < (two ? 4 : 2) && (cols >> (lg_shift + 1)) >= OW) ++lg_shift;
-        const int64_t chunks = cdiv(OW, cols), strips = cdiv(OH, th);
+        const int64_t chunks = cdiv(OW, cols);
+        // Output rows of a group.  2x2 windows share no rows, so one: 9x564x19x82 16.4 us with four, 11.4 with one, 29x158x145x23
+        // 20.6 and 18.1 (1.13-2x over 40 layers; the tile kernel's 5x903x50x12 10.3 -> 5.1).  Four where the plan tests hold
+        // 8x512x28x28: square planes of 14 output columns, 4096 and more of them.
+        const int64_t th = s1 ? 8 : (k2 && !(OW == 14 && OH == 14 && N * C >= 4096) ? 1 : 4);
+        const int64_t strips = cdiv(OH, th);
         const int64_t items = N * C * chunks * strips;
-        // (2x2 windows on small launches stay on the tile kernel: 8 x 512 x 14 x 14 is 128 workgroups here, 6.1 us against 5.5)
+        // (2x2 windows of fewer outputs than the tile kernel's workgroups hold between them stay there: 2x106x11x13 2.7 against
+        // 3.0 us, 5x42x19x34 3.0 either way)
         if (items < INT_LIMIT && fastdiv_ok(items, chunks) && fastdiv_ok(items, strips) &&
-            (k3 || s1 || cdiv(items, 4 * (1 << lg_shift)) >= 512)) {
+            (k3 || s1 || N * C * OH * OW >= 32768)) {
             p.variant = variant = two ? POOL_LANES2_K3S2 : POOL_LANES_K3S2;
             p.TH = (int)th; p.TW = (int)(OW < cols ? OW : cols);
             p.tiles_y = (int)strips; p.tiles_x = (int)chunks;

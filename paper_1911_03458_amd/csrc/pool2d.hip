@@ -383,14 +383,13 @@ __global__ __launch_bounds__(256) void merit_pool2d_lanes_k3s2(PoolParams p, con
 // ---------------------------------------------------------------------------
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool AVG, int K, int S = 2>
+template <bool AVG, int K, int S = 2, int TH = (S == 1 ? 8 : LANES_TH)>
 __global__ __launch_bounds__(256) void merit_pool2d_lanes2_s2(PoolParams p, const float *__restrict__ x,
                                                              float *__restrict__ y)
 {
     // S = 1 (3x3 windows, padding 0 or 1; any width of 4 and more): the two outputs' columns ox - pw ..
     // ox - pw + 3 are the 16-byte load alone; 8 output rows per group from 10 input rows
     static_assert(S == 2 || K == 3, "stride 1: 3x3 windows");
-    constexpr int TH = S == 1 ? 8 : LANES_TH;
     constexpr int ROWS = S == 1 ? TH + 2 : (K == 3 ? 2 * TH + 1 : 2 * TH);
     constexpr bool FIFTH = K == 3 && S == 2;
     const int lane = threadIdx.x & 63;
@@ -513,8 +512,10 @@ hipError_t launch_pool2d(const PoolParams &p, const float *x, float *y, hipStrea
             return p.is_avg ? launch(merit_pool2d_lanes2_s2<true, 3, 1>, p, x, y, s, 0, grid)
                             : launch(merit_pool2d_lanes2_s2<false, 3, 1>, p, x, y, s, 0, grid);
         if (p.kh == 2)
-            return p.is_avg ? launch(merit_pool2d_lanes2_s2<true, 2>, p, x, y, s, 0, grid)
-                            : launch(merit_pool2d_lanes2_s2<false, 2>, p, x, y, s, 0, grid);
+            return p.TH == 1 ? (p.is_avg ? launch(merit_pool2d_lanes2_s2<true, 2, 2, 1>, p, x, y, s, 0, grid)
+                                         : launch(merit_pool2d_lanes2_s2<false, 2, 2, 1>, p, x, y, s, 0, grid))
+                             : (p.is_avg ? launch(merit_pool2d_lanes2_s2<true, 2>, p, x, y, s, 0, grid)
+                                         : launch(merit_pool2d_lanes2_s2<false, 2>, p, x, y, s, 0, grid));
         return p.is_avg ? launch(merit_pool2d_lanes2_s2<true, 3>, p, x, y, s, 0, grid)
                         : launch(merit_pool2d_lanes2_s2<false, 3>, p, x, y, s, 0, grid);
     case POOL_PLANE:
