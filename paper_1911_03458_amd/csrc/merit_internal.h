@@ -50,20 +50,6 @@ __device__ __forceinline__ uint32_t xcd_band_item(uint32_t hw_id, int xq, int xr
     return xcd * (uint32_t)xq + min(xcd, (uint32_t)xr) + slot;
 }
 
-// The kernel-argument block is read with scalar loads where its values are first needed, a memory trip after the other;
-// touching each of its 64-byte lines with the first instructions fetches them side by side.  BYTES: what the kernel's
-// arguments take.
-template <int BYTES>
-__device__ __forceinline__ void touch_kernel_arguments()
-{
-    typedef const uint32_t __attribute__((address_space(4))) *kernarg_ptr;
-    kernarg_ptr ka = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-    uint32_t warm = ka[0];
-#pragma unroll
-    for (int i = 1; i < (BYTES + 63) / 64; ++i) warm ^= ka[16 * i];
-    asm volatile("" ::"s"(warm));
-}
-
 // v moved down by `bits` (a multiple of 16, 0 < bits < 128) with zeros behind it: the 16 bytes of a load that ends with its
 // row, where the unit that the row's end cuts wants them.
 __device__ __forceinline__ uint4 shift_down(uint4 v, int bits)
