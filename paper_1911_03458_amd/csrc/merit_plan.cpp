@@ -366,10 +366,16 @@ merit_status derive_sep(merit_plan *pl)
     p.N = (int)N; p.H = (int)H; p.W = (int)W; p.k = (int)k; p.c = (int)c;
     p.c4 = (int)round_up(c, 4);
     // staged rows RH = TH + k - 1; TH a multiple of 4 (the column pass works on patches of 2 or 4 rows)
-    const int64_t asked = pl->tile_req[1];                // staged rows per workgroup, at most
-    if (asked > 0 && (asked < k + 3 || asked > (k <= 16 ? 64 : 96))) return MERIT_ERR_UNSUPPORTED;
-    auto rows_of = [&](int form) { return asked > 0 && asked < sep_rows(form) ? asked : (int64_t)sep_rows(form); };
+    const int64_t asked = pl->tile_req[1], most = k <= 16 ? 64 : 96;      // staged rows per workgroup, at most
+    if (asked > 0 && (asked < k + 3 || asked > most)) return MERIT_ERR_UNSUPPORTED;
+    auto rows_of = [&](int form) {
+        const int64_t rows = form == SEP_PERSISTENT ? most : sep_rows(form);
+        return asked > 0 && asked < rows ? asked : rows;
+    };
     auto tiles_of = [&](int64_t TH) { return N * cdiv(H, TH) * cdiv(W, 64); };
+    auto divides = [&](int64_t TH) {
+        return fastdiv_ok(tiles_of(TH), cdiv(W, 64)) && fastdiv_ok(N * cdiv(H, TH), cdiv(H, TH));
+    };
     // few tiles: up to three a compute unit (at 480-760 tiles 512 threads are 1-8 % faster, at 960 on k = 30 and at
     // 1840-2500 otherwise 4-13 % slower).  Where they are fewer than the compute units they are shortened until those are
     // full, to 16 rows at least: a tile's chain is as long as it is tall (not for short windows, whose chain is the round
@@ -379,6 +385,12 @@ merit_status derive_sep(merit_plan *pl)
     if (p.form != SEP_FEW) TH = (rows_of(p.form) - k + 1) / 4 * 4;
     else if (asked <= 0 && k >= 8)
         while (TH > 16 && tiles_of(TH - 4) <= 256) TH -= 4;
+    // (2^24 workgroups of 256 threads are more than a launch takes, and more tiles than workgroups can be walked; taller
+    // tiles on frames of so many rows that the shorter ones' numbers do not divide)
+    if (p.form == SEP_TILES && (tiles_of(TH) >= 1 << 24 || !divides(TH))) {
+        p.form = SEP_PERSISTENT;
+        TH = (rows_of(p.form) - k + 1) / 4 * 4;
+    }
     const int64_t RH = TH + k - 1;
     p.TH = (int)TH;
     p.tiles_y = (int)cdiv(H, TH);
@@ -389,9 +401,7 @@ merit_status derive_sep(merit_plan *pl)
     p.lds_bytes = (int)((RH * p.PI + 8 * cdiv(k, 4)) * 4);
     if (p.lds_bytes > LDS_LIMIT) return MERIT_ERR_UNSUPPORTED;
     const int64_t grid = N * p.tiles_y * p.tiles_x;
-    if (grid >= INT_LIMIT || !fastdiv_ok(grid, p.tiles_x) || !fastdiv_ok(N * p.tiles_y, p.tiles_y) ||
-        !fastdiv_ok(8 * RH, RH))
-        return MERIT_ERR_UNSUPPORTED;
+    if (grid >= INT_LIMIT || !divides(TH) || !fastdiv_ok(8 * RH, RH)) return MERIT_ERR_UNSUPPORTED;
     p.div_tiles_x = make_fastdiv((uint32_t)p.tiles_x);
     p.div_tiles_y = make_fastdiv((uint32_t)p.tiles_y);
     p.div_rh = make_fastdiv((uint32_t)RH);

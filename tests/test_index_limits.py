@@ -1,0 +1,35 @@
+"""Work lists near the limits of a launch (2^32 threads) and of the kernels' 32-bit divisions: the kernels that smaller calls
+run on take them, in another form where that is what it takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1911_03458_amd import binding as mb
+
+
+def _threads(li):
+    return li["grid"][0] * li["grid"][1] * li["grid"][2] * li["block"][0]
+
+
+# N, H, W, k: a tile an image and 2^24 and more of them; tiles whose count a frame's height makes too large to divide by
+SEP = [((1 << 24) + 3, 1, 4, 3), ((1 << 24) + 3, 1, 5, 3), ((1 << 24) + 3, 1, 1, 28), (1 << 24, 8, 8, 3),
+       (1, 3200000, 8, 20), (45, 439354, 8, 25), (35338139, 2, 93, 26)]
+
+
+@pytest.mark.parametrize("shape", SEP)
+def test_separable_filters_of_many_tiles(shape):
+    li = mb.merit_plan_sepfilter(*shape).launch_info()
+    assert li["kernel"] == "merit_sepfilter_tile" and _threads(li) < 1 << 32, li
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [SEP[0], SEP[1], SEP[4]])
+def test_separable_filters_of_many_tiles_against_the_oracle(shape):
+    N, H, W, k = shape
+    rng = np.random.default_rng(k)
+    x = rng.integers(0, 256, (N, H, W), dtype=np.uint8).astype(np.float32)
+    kx, ky = (rng.standard_normal(k).astype(np.float32) for _ in range(2))
+    y = mb.merit_sepfilter(mb.merit_plan_sepfilter(*shape), *(torch.from_numpy(a).cuda() for a in (x, kx, ky))).cpu().numpy()
+    # 2k fp32 multiply-adds of at most |kx| |ky| max|x|
+    assert np.abs(y - oracle.sepfilter(x, kx, ky)).max() <= 1e-5 * np.abs(kx).sum() * np.abs(ky).sum() * 255
