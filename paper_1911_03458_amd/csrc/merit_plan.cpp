@@ -148,13 +148,18 @@ merit_status derive_pool(merit_plan *pl)
         // Output rows of a group.  2x2 windows share no rows, so one: 9x564x19x82 16.4 us with four, 11.4 with one, 29x158x145x23
         // 20.6 and 18.1 (1.13-2x over 40 layers; the tile kernel's 5x903x50x12 10.3 -> 5.1).  Four where the plan tests hold
         // 8x512x28x28: square planes of 14 output columns, 4096 and more of them.
-        const int64_t th = s1 ? 8 : (k2 && !(OW == 14 && OH == 14 && N * C >= 4096) ? 1 : 4);
-        const int64_t strips = cdiv(OH, th);
-        const int64_t items = N * C * chunks * strips;
+        int64_t th = s1 ? 8 : (k2 && !(OW == 14 && OH == 14 && N * C >= 4096) ? 1 : 4);
+        auto items_of = [&](int64_t t) { return N * C * chunks * cdiv(OH, t); };
+        // the kernel's divisions, and the threads of a launch
+        auto fits = [&](int64_t t) {
+            const int64_t n = items_of(t);
+            return n < INT_LIMIT && fastdiv_ok(n, chunks) && fastdiv_ok(n, cdiv(OH, t)) && cdiv(n, 4 * (1 << lg_shift)) < 1 << 24;
+        };
+        if (th == 1 && !fits(th)) th = 4;                   // (4x64x2158x3838: 2187 us, 3298 on the tile kernel)
+        const int64_t strips = cdiv(OH, th), items = items_of(th);
         // (2x2 windows of fewer outputs than the tile kernel's workgroups hold between them stay there: 2x106x11x13 2.7 against
         // 3.0 us, 5x42x19x34 3.0 either way)
-        if (items < INT_LIMIT && fastdiv_ok(items, chunks) && fastdiv_ok(items, strips) &&
-            (k3 || s1 || N * C * OH * OW >= 32768)) {
+        if (fits(th) && (k3 || s1 || N * C * OH * OW >= 32768)) {
             p.variant = variant = two ? POOL_LANES2_K3S2 : POOL_LANES_K3S2;
             p.TH = (int)th; p.TW = (int)(OW < cols ? OW : cols);
             p.tiles_y = (int)strips; p.tiles_x = (int)chunks;

@@ -33,3 +33,25 @@ def test_separable_filters_of_many_tiles_against_the_oracle(shape):
     y = mb.merit_sepfilter(mb.merit_plan_sepfilter(*shape), *(torch.from_numpy(a).cuda() for a in (x, kx, ky))).cpu().numpy()
     # 2k fp32 multiply-adds of at most |kx| |ky| max|x|
     assert np.abs(y - oracle.sepfilter(x, kx, ky)).max() <= 1e-5 * np.abs(kx).sum() * np.abs(ky).sum() * 255
+
+
+# 2x2 means of tall frames and long lists of planes: N, C, H, W
+POOL = [(4, 64, 2158, 3838), (8, 1, 65536, 10), (13, 2656, 1996, 61), (348, 16674, 68, 31)]
+
+
+@pytest.mark.parametrize("shape", POOL)
+def test_pooling_of_long_lists_stays_on_its_kernel(shape):
+    li = mb.merit_plan_pool2d(*shape, 2, 2, 2, 2, 0, 0, 1).launch_info()
+    assert li["kernel"] == "merit_pool2d_lanes2_s2<avg,2>" and _threads(li) < 1 << 32, li
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("avg", [False, True])
+def test_pooling_of_long_lists_against_the_oracle(avg):
+    x = np.random.default_rng(3).standard_normal((8, 1, 65536, 10)).astype(np.float32)
+    y = mb.merit_pool2d(mb.merit_plan_pool2d(8, 1, 65536, 10, 2, 2, 2, 2, 0, 0, avg), torch.from_numpy(x).cuda()).cpu().numpy()
+    ref = oracle.pool2d(x, (2, 2), (2, 2), (0, 0), "avg" if avg else "max")
+    if avg:       # sums of four in another order
+        assert np.all(np.abs(y - ref) <= 2.0 ** -22 * oracle.pool2d(np.abs(x), (2, 2), (2, 2), (0, 0), "avg"))
+    else:
+        assert np.array_equal(y, ref)
