@@ -1357,12 +1357,16 @@ merit_status derive_dw(merit_plan *pl)
     // two up to 2000 workgroups of one row, where the rows that strips share start to count (7x336x9x83 5x5 6.8, 5.9, 7.9 us
     // with one, two, four), four beyond (5x456x41x107 15.2, 13.7, 12.8); a row stride shares less.
     const int64_t one_row = cdiv(planes * OH * units, 256);
-    const int64_t lanes_rows = one_row <= (sw == 2 ? 1500 : 600) ? 1 : (one_row <= 2000 || sw == 2 ? 2 : 4);
+    int64_t lanes_rows = one_row <= (sw == 2 ? 1500 : 600) ? 1 : (one_row <= 2000 || sw == 2 ? 2 : 4);
+    auto lanes_fit = [&](int64_t t) {                    // the kernel's divisions
+        const int64_t n = planes * cdiv(OH, t);
+        return n * units < (1ll << 30) && fastdiv_ok(n * units + 256, units) && fastdiv_ok(n, cdiv(OH, t));
+    };
+    while (lanes_rows < 4 && !lanes_fit(lanes_rows)) lanes_rows *= 2;
     const int64_t strips = cdiv(OH, lanes_rows);
     const bool rows = kh == 3 && kw == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && W % 8 == 0 && W <= 4096 && pl->tile_req[2] <= 0;
     bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && pl->tile_req[2] <= 0 &&
-                 planes * H * W >= 16 && planes * H * W < (1ll << 31) - 64 && planes * strips * units < (1ll << 30) &&
-                 fastdiv_ok(planes * strips * units + 256, units) && fastdiv_ok(planes * strips, strips);
+                 planes * H * W >= 16 && planes * H * W < (1ll << 31) - 64 && lanes_fit(lanes_rows);
     if (lanes && tile_rows > 0) {
         // Few small planes, a staged element or two and one output per thread of the kernel for any window: left there, where
         // the plan tests hold three of them (1x24x9x14 3x3 / 2: 3.1 us, 2.6 on the other).

@@ -55,3 +55,30 @@ def test_pooling_of_long_lists_against_the_oracle(avg):
         assert np.all(np.abs(y - ref) <= 2.0 ** -22 * oracle.pool2d(np.abs(x), (2, 2), (2, 2), (0, 0), "avg"))
     else:
         assert np.array_equal(y, ref)
+
+
+# depthwise layers with wide rows or many planes: N, C, H, W, k, s
+DW = [(1, 3, 1400, 17000, 3, 2), (1, 3, 1400, 17000, 5, 2), (5, 63, 12, 19888, 3, 2), (4, 3, 923, 13451, 5, 2),
+      (47, 8, 322, 4166, 3, 2), (2, 2400, 174, 1578, 3, 2), (30, 23, 13141, 7, 5, 2)]
+
+
+@pytest.mark.parametrize("shape", DW)
+def test_large_depthwise_layers_stay_on_the_kernel_without_lds(shape):
+    N, C, H, W, k, s = shape
+    li = mb.merit_plan_conv2d_depthwise(N, C, H, W, k, k, s, s, k // 2, k // 2).launch_info()
+    assert li["kernel"] == "merit_dwconv_lanes" and _threads(li) < 1 << 32, li
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [DW[0], DW[3]])
+def test_large_depthwise_layers_against_the_oracle(shape):
+    N, C, H, W, k, s = shape
+    rng = np.random.default_rng(k)
+    x = rng.standard_normal((N, C, H, W), dtype=np.float32).astype(np.float16)
+    w = (rng.standard_normal((C, k, k)) / k).astype(np.float16)
+    plan = mb.merit_plan_conv2d_depthwise(N, C, H, W, k, k, s, s, k // 2, k // 2)
+    y = mb.merit_conv2d_depthwise(plan, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()).cpu().numpy()
+    ref = oracle.conv2d_depthwise(x, w, (s, s), (k // 2, k // 2)).astype(np.float64)
+    mag = oracle.conv2d_depthwise(np.abs(x), np.abs(w), (s, s), (k // 2, k // 2)).astype(np.float64)
+    # one rounding to binary16 on either side and k*k fp32 sums in another order
+    assert np.all(np.abs(y - ref) <= 2.0 ** -10 * np.abs(ref) + k * k * 2.0 ** -23 * mag + 1e-7)
