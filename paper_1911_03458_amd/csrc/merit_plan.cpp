@@ -532,7 +532,8 @@ void derive_px(merit_plan *pl)
     }
     p.tiles = (int)cdiv(HW, p.TM); p.co_groups = (int)cdiv(Cout, p.TN);
     const int64_t grid = N * p.tiles * p.co_groups;
-    if (grid >= (1ll << 30) || !fastdiv_ok(grid, p.co_groups) || !fastdiv_ok(N * p.tiles, p.tiles)) return;
+    // (2^23 workgroups of 512 threads are more than a launch takes: the general planner's kernels walk their tiles)
+    if (grid >= (1ll << 23) || !fastdiv_ok(grid, p.co_groups) || !fastdiv_ok(N * p.tiles, p.tiles)) return;
     p.xq = (int)(grid / 8); p.xr = (int)(grid % 8);
     p.div_cog = make_fastdiv((uint32_t)p.co_groups);
     p.div_tiles = make_fastdiv((uint32_t)p.tiles);

@@ -82,3 +82,30 @@ def test_large_depthwise_layers_against_the_oracle(shape):
     mag = oracle.conv2d_depthwise(np.abs(x), np.abs(w), (s, s), (k // 2, k // 2)).astype(np.float64)
     # one rounding to binary16 on either side and k*k fp32 sums in another order
     assert np.all(np.abs(y - ref) <= 2.0 ** -10 * np.abs(ref) + k * k * 2.0 ** -23 * mag + 1e-7)
+
+
+# 1x1 layers on millions of images: N, Cin, H, W, Cout
+PX = [((1 << 23) + 1, 16, 1, 8, 40), (1 << 23, 40, 2, 8, 48), (5812858, 643, 1, 8, 399)]
+
+
+@pytest.mark.parametrize("shape", PX)
+def test_1x1_layers_on_millions_of_images(shape):
+    li = mb.merit_plan_conv2d(*shape, 1, 1, 1, 1, 0, 0).launch_info()
+    assert li["kernel"] in ("merit_conv2d_chws", "merit_conv2d_chblock", "merit_conv2d_chpass") and _threads(li) < 1 << 32, li
+
+
+@pytest.mark.gpu
+def test_1x1_layers_on_millions_of_images_against_the_oracle():
+    N, Cin, H, W, Cout = PX[0]
+    rng = np.random.default_rng(2)
+    some = rng.standard_normal((1001, Cin, H, W)).astype(np.float16)        # the batch repeats these
+    w = (rng.standard_normal((Cout, Cin, 1, 1)) / 4).astype(np.float16)
+    x = torch.from_numpy(some).cuda()[torch.arange(N, device="cuda") % 1001]
+    y = mb.merit_conv2d(mb.merit_plan_conv2d(N, Cin, H, W, Cout, 1, 1, 1, 1, 0, 0), x, torch.from_numpy(w).cuda())
+    ref = torch.from_numpy(oracle.conv2d(some, w, (1, 1), (0, 0)).astype(np.float32)).cuda()
+    mag = torch.from_numpy(oracle.conv2d(np.abs(some), np.abs(w), (1, 1), (0, 0)).astype(np.float32)).cuda()
+    for i in range(0, N, 1001 * 1024):
+        got = y[i:i + 1001 * 1024].float()
+        j = torch.arange(i, i + len(got), device="cuda") % 1001
+        # one rounding to binary16 on either side and fp32 sums of Cin products in another order
+        assert bool(((got - ref[j]).abs() <= 2.0 ** -10 * ref[j].abs() + (Cin + 2) * 2.0 ** -23 * mag[j] + 1e-7).all())
