@@ -385,8 +385,9 @@ merit_status derive_sep(merit_plan *pl)
     // 1840-2500 otherwise 4-13 % slower).  Where they are fewer than the compute units they are shortened until those are
     // full, to 16 rows at least: a tile's chain is as long as it is tall (not for short windows, whose chain is the round
     // trip to memory whatever the height).
+    // A request for more rows than those two forms stage names the third.
     int64_t TH = (rows_of(SEP_FEW) - k + 1) / 4 * 4;
-    p.form = TH > 0 && tiles_of(TH) <= 768 ? SEP_FEW : sep_many((int)k);
+    p.form = asked > sep_rows(SEP_FEW) ? SEP_PERSISTENT : TH > 0 && tiles_of(TH) <= 768 ? SEP_FEW : sep_many((int)k);
     if (p.form != SEP_FEW) TH = (rows_of(p.form) - k + 1) / 4 * 4;
     else if (asked <= 0 && k >= 8)
         while (TH > 16 && tiles_of(TH - 4) <= 256) TH -= 4;

@@ -21,7 +21,7 @@
 //               (4x1080x1920: k = 8 15.1 -> 13.6, 12 17.3 -> 15.5, 16 19.7 -> 17.0, 20 22.2 -> 19.4, 24 24.4 -> 21.9)
 //   PERSISTENT  k > 28, where 64 staged rows would be half halo: 96 rows, four workgroups a compute unit that walk the
 //               tiles (k = 30 25.2 -> 24.3; one tile a workgroup 24.4; 64 rows 26.6); and any window on more tiles than
-//               a launch has workgroups
+//               a launch has workgroups, or on request of more than 64 staged rows
 //   FEW         up to three tiles a compute unit: 512 threads, 2 x 2 patches (2x600x1280: k = 30 9.1 -> 8.3, 20 8.6 ->
 //               7.7, 8 5.7 -> 5.5; 380x936: 30 6.8 -> 4.6, 20 7.0 -> 4.6, 8 4.3 -> 3.9, 3 3.8 -> 3.6), and where the
 //               tiles do not fill the chip shorter ones (624x172: k = 20 6.5 -> 3.7, 4.2 on 44-row tiles; 8 4.0 -> 3.2)
