@@ -22,7 +22,20 @@ CASES = [
     (24, 248, 7, 18, 992),     # 128 x 128 tiles
     (25, 130, 53, 19, 520),
     (1, 260, 8, 16, 128),      # whole tiles, channels off the 8
+    (17, 173, 2, 5, 585),      # 64 x 64 tiles
+    (17, 211, 3, 3, 981),      # 64 x 128
+    (23, 130, 6, 23, 222),     # 128 x 64
 ]
+
+
+def _tile(li, W):
+    return next(t for t in (64, 128) if -(-t // W) == li["tile"][2]), li["tile"][1]
+
+
+@pytest.mark.parametrize("make", [mb.merit_plan_conv2d, mb.merit_plan_conv2d_residual])
+def test_the_cases_reach_every_tile(make):
+    tiles = {_tile(make(N, Cin, H, W, Cout, 1, 1, 1, 1, 0, 0).launch_info(), W) for N, Cin, H, W, Cout in CASES}
+    assert tiles == {(64, 32), (64, 64), (64, 128), (128, 32), (128, 64), (128, 128)}
 
 
 @pytest.mark.parametrize("residual", [False, True])

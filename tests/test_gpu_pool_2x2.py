@@ -49,3 +49,23 @@ def test_against_the_oracle(case, avg):
         assert np.all(np.abs(y.cpu().numpy() - ref) <= 2.0 ** -22 * mag)
     else:
         assert np.array_equal(y.cpu().numpy(), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(30, 300, 9, 9), (2, 34, 57, 85), (8, 512, 28, 28)])
+def test_nan_and_infinities_stay_in_their_windows(case):
+    """A maximum passes over NaN unless it is all there is, a mean with one is one; the windows beside are as without."""
+    N, C, H, W = case
+    x = np.random.default_rng(7).standard_normal((N, C, H, W)).astype(np.float32)
+    x[::2, 1, 0, 3], x[:, 2, 2:4, 2:4], x[:, 3, 4, 5], x[0, :, 6, 7], x[1, :, 6, 6] = np.nan, np.nan, np.inf, -np.inf, np.finfo(np.float32).min
+    win = x[:, :, :H // 2 * 2, :W // 2 * 2].reshape(N, C, H // 2, 2, W // 2, 2)
+    dx = torch.from_numpy(x).cuda()
+    top = mb.merit_pool2d(mb.merit_plan_pool2d(N, C, H, W, 2, 2, 2, 2, 0, 0, 0), dx).cpu().numpy()
+    want = np.fmax(np.fmax(win[:, :, :, 0, :, 0], win[:, :, :, 0, :, 1]), np.fmax(win[:, :, :, 1, :, 0], win[:, :, :, 1, :, 1]))
+    assert np.array_equal(top, want, equal_nan=True) and np.isnan(top[:, 2, 1, 1]).all()
+    mean = mb.merit_pool2d(mb.merit_plan_pool2d(N, C, H, W, 2, 2, 2, 2, 0, 0, 1), dx).cpu().numpy()
+    want = win.astype(np.float64).mean(axis=(3, 5)).astype(np.float32)
+    finite = np.isfinite(want)
+    assert np.array_equal(mean[~finite], want[~finite], equal_nan=True)
+    mag = np.abs(win).astype(np.float64).mean(axis=(3, 5))[finite]
+    assert np.all(np.abs(mean[finite] - want[finite]) <= 2.0 ** -22 * mag)   # three roundings of at most 2^-24 of the magnitudes' sum

@@ -24,7 +24,7 @@ def test_separable_filters_of_many_tiles(shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", [SEP[0], SEP[1], SEP[4]])
+@pytest.mark.parametrize("shape", [SEP[0], SEP[1], SEP[4], ((1 << 24) + 3, 1, 4, 1), ((1 << 24) + 3, 1, 5, 9), ((1 << 24) + 3, 1, 4, 16)])
 def test_separable_filters_of_many_tiles_against_the_oracle(shape):
     N, H, W, k = shape
     rng = np.random.default_rng(k)
