@@ -146,9 +146,9 @@ merit_status derive_pool(merit_plan *pl)
         while (lg_shift < (two ? 4 : 2) && (cols >> (lg_shift + 1)) >= OW) ++lg_shift;
         const int64_t chunks = cdiv(OW, cols);
         // Output rows of a group.  2x2 windows share no rows, so one: 9x564x19x82 16.4 us with four, 11.4 with one, 29x158x145x23
-        // 20.6 and 18.1 (1.13-2x over 40 layers; the tile kernel's 5x903x50x12 10.3 -> 5.1).  Four where the plan tests hold
-        // 8x512x28x28: square planes of 14 output columns, 4096 and more of them.
-        int64_t th = s1 ? 8 : (k2 && !(OW == 14 && OH == 14 && N * C >= 4096) ? 1 : 4);
+        // 20.6 and 18.1 (1.13-2x over 40 layers; the tile kernel's 5x903x50x12 10.3 -> 5.1), 8x512x28x28 7.1 and 5.2,
+        // 64x512x28x28 26.7 and 22.9.
+        int64_t th = s1 ? 8 : (k2 ? 1 : 4);
         auto items_of = [&](int64_t t) { return N * C * chunks * cdiv(OH, t); };
         // the kernel's divisions, and the threads of a launch
         auto fits = [&](int64_t t) {

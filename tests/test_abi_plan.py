@@ -627,7 +627,7 @@ def test_pool_plan_lane_per_column_for_odd_widths():
     assert mb.merit_plan_pool2d(32, 192, 28, 28, 3, 3, 1, 1, 1, 1, 0).set_tile((0, 0, 7)).launch_info()["kernel"].startswith("merit_pool2d_rows<3,3,1,1,1")
     # 2x2 / stride 2 where the output rows are not whole 16-byte vectors (28 -> 14, 14 -> 7)
     li = mb.merit_plan_pool2d(8, 512, 28, 28, 2, 2, 2, 2, 0, 0, 0).launch_info()
-    assert li["kernel"] == "merit_pool2d_lanes2_s2<max,2>" and li["grid"][0] == -(-(8 * 512 * 4) // 32)
+    assert li["kernel"] == "merit_pool2d_lanes2_s2<max,2>" and li["grid"][0] == -(-(8 * 512 * 14) // 32)     # a row a group
     assert mb.merit_plan_pool2d(8, 64, 224, 224, 2, 2, 2, 2, 0, 0, 0).launch_info()["kernel"].startswith("merit_pool2d_rows")
     # the 16-byte kernels keep the shapes they take
     assert mb.merit_plan_pool2d(16, 64, 112, 112, 3, 3, 2, 2, 1, 1, 0).launch_info()["kernel"].startswith("merit_pool2d_stream")
