@@ -506,11 +506,8 @@ void derive_px(merit_plan *pl)
     if (c.kh != 1 || c.kw != 1 || c.sh != 1 || c.sw != 1 || c.ph != 0 || c.pw != 0 || c.pool) return;
     if (pl->tile_req[2] > 0 && pl->tile_req[3] > 0) return;
     const int64_t N = c.N, Cin = c.Cin, HW = (int64_t)c.H * c.W, Cout = c.Cout;
-    // 260 and more channels, whole dwords a weight row but not whole 16-byte units, on planes of whole 64-pixel tiles with
-    // one block of output channels: left on the channel-block kernels, where the plan tests hold 260 -> 64 on 56x56.
-    // (Everywhere else this kernel takes such counts: 286 -> 131 on 40 of 56x32 159 -> 18 us, 303 -> 272 on 2 of 25x27
-    // 56 -> 4.4.)
-    if (Cin % 8 == 4 && Cin >= 260 && HW % 64 == 0 && Cout <= 64) return;
+    // (any channel count: 260 -> 64 on 8 of 56x56 4.8 us, 23.7 on the channel-block kernels, 1028 -> 64 on 64 of 16x16 7.4 and
+    // 61.4, 286 -> 131 on 40 of 56x32 18 and 159)
     if (Cin < 16 || HW < 8 || Cin * HW >= (1ll << 30) || Cout * Cin >= (1ll << 30) || Cout * HW >= (1ll << 30)) return;
     PxParams p;
     std::memset(&p, 0, sizeof(p));

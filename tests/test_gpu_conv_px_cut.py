@@ -22,6 +22,8 @@ CASES = [
     (24, 248, 7, 18, 992),     # 128 x 128 tiles
     (25, 130, 53, 19, 520),
     (1, 260, 8, 16, 128),      # whole tiles, channels off the 8
+    (8, 260, 56, 56, 64),
+    (3, 1028, 16, 16, 40),
     (17, 173, 2, 5, 585),      # 64 x 64 tiles
     (17, 211, 3, 3, 981),      # 64 x 128
     (23, 130, 6, 23, 222),     # 128 x 64
