@@ -1367,10 +1367,11 @@ merit_status derive_dw(merit_plan *pl)
     bool lanes = !rows && kh == kw && (kw == 3 || kw == 5) && sh == sw && (sw == 1 || sw == 2) && pl->tile_req[2] <= 0 &&
                  planes * H * W >= 16 && planes * H * W < (1ll << 31) - 64 && lanes_fit(lanes_rows);
     if (lanes && tile_rows > 0) {
-        // Few small planes, a staged element or two and one output per thread of the kernel for any window: left there, where
-        // the plan tests hold three of them (1x24x9x14 3x3 / 2: 3.1 us, 2.6 on the other).
-        const int64_t staged = ((tile_rows - 1) * sh + kh) * pitch, outs = tile_rows * OW;
-        if (staged <= 320 && outs <= 140 && planes <= 340) lanes = false;
+        // 5x5 windows at stride 1 on small planes of odd width: the kernel for any window, with an output a thread.  Rows on
+        // every second 2-byte boundary cost the other 0.4 us (2x14x18x7 3.43 against 3.84 us, 2x40x8x17 3.49, 3.72, 4x31x8x21
+        // 3.57, 3.75, 8x70x11x7 3.77, 3.68; on even widths 3.4 to 4.1 against 3.2 to 3.5).  Elsewhere over 260 small layers
+        // it takes 0.96 to 1.83 of the other's time, 1.1 on average (1x24x9x14 3x3 / 2 2.75 against 2.67).
+        if (kw == 5 && sw == 1 && W % 2 == 1 && tile_rows * OW <= 256 && planes <= 512) lanes = false;
     }
     if (lanes) {
         p.variant = DW_LANES;
