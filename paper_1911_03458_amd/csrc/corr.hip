@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
     const int run = second ? unit - npx8 : unit;
     const int gx = (second ? px0 - p.lead : px0) + 8 * run;
     const bool colok = gx >= 0 && gx < p.W;
-    const bool stages = rowok && sg < p.chg && colok;             // (rowok uniform: else every product is 0)
+    const bool stages = rowok && sg < p.chg && colok;
     // (RAGGED: the unit that the row's end cuts ends with the row, its shared pixels are written twice, the same; the units
     // of zeros behind it follow where it ends)
     const int shift = RAGGED && gx + 8 > p.W ? -p.W & 7 : 0;
@@ -113,75 +113,78 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
     };
     issue(0);                                                     // before anything that the loads do not need
 
-    u32x4 *lds0 = reinterpret_cast<u32x4 *>(smem) + (second ? p.chg * p.P1 + sg * p.P2 : sg * p.P1);
-    const int pitch = second ? p.pitch2 : p.pitch1;
-    // where its pixels go: by residue class of the column; to the spare item behind the rows what lies left of the chunk
-    int item[8], col = 8 * run - shift, cls, at;
-    {
-        const int c0 = RAGGED ? max(col, 0) : col;
-        const int idx = (int)fdiv((uint32_t)c0, p.div_sd);
-        cls = c0 - idx * p.sd;
-        at = cls * pitch + idx;
-    }
-    auto next_col = [&]() __attribute__((always_inline)) {
-        const bool wrap = ++cls == p.sd;
-        at += wrap ? 1 - (p.sd - 1) * pitch : pitch;
-        cls = wrap ? 0 : cls;
-    };
-    const int spare = (int)(reinterpret_cast<u32x4 *>(smem) + p.chg * (p.P1 + p.P2) - lds0);
-#pragma unroll
-    for (int px = 0; px < 8; ++px) {
-        const bool there = !RAGGED || col + px >= 0;
-        item[px] = there ? corr_slot(at, sg) : spare;
-        if (there) next_col();
-    }
-
-    auto commit = [&](int chi0, int ng) __attribute__((always_inline)) {
-        if ((chi0 + ng) * 8 > p.C) {                              // uniform: the last pass, where channels are missing
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const bool ok = (chi0 + sg) * 8 + c < p.C;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[c][j] = ok ? v[c][j] : 0u;
-            }
-        }
-        if (sg >= ng) return;
-#pragma unroll
-        for (int px = 0; px < 8; ++px) {
-            const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
-            u32x4 d;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) d[q] = __builtin_amdgcn_perm(v[2 * q + 1][px >> 1], v[2 * q][px >> 1], sel);
-            lds0[item[px]] = d;
-        }
-    };
-
-    // this lane's operand positions: pixel (lane & 15) of block (class c, sub-block s) and the
-    // columns q = pixel0 - R*sd + sd*j of the same class, j = 16*nb + (lane & 15); positions
-    // past the staged ones are clamped (their products are never stored)
     const int l16 = lane & 15, kg = lane >> 4;
-    int apos[BPW], bpos[BPW][NB];
-#pragma unroll
-    for (int t = 0; t < BPW; ++t) {
-        const uint32_t bl = (uint32_t)min(wave + 4 * t, p.nblk - 1);
-        const uint32_t s = fdiv(bl, p.div_sd);
-        const uint32_t c = bl - s * (uint32_t)p.sd;
-        apos[t] = corr_slot(min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1), kg);
-        const uint32_t ec = (uint32_t)(p.lead - p.R * p.sd) + c;
-        const uint32_t ei = fdiv(ec, p.div_sd);
-        const uint32_t cls2 = ec - ei * (uint32_t)p.sd;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            bpos[t][nb] = corr_slot(min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1), kg);
-    }
-
     floatx4 acc[BPW][NB];
 #pragma unroll
     for (int t = 0; t < BPW; ++t)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[t][nb] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    if (rowok) {                                                  // uniform: else every product is 0
+    // (uniform: else every product is 0, and the workgroup has only zeros to store.  What the staging needs is computed
+    // inside: before the branch it was a cost of every displaced row beside the image as well, 3x16x16x82, +-8 / 3, 7.7 us
+    // against 7.3, 4x55x9x93, +-6 / 3, 5.8 against 5.5.  The loads are not: inside they go out later, 4 to 16 % slower.)
+    if (rowok) {
+        u32x4 *lds0 = reinterpret_cast<u32x4 *>(smem) + (second ? p.chg * p.P1 + sg * p.P2 : sg * p.P1);
+        const int pitch = second ? p.pitch2 : p.pitch1;
+        // where its pixels go: by residue class of the column; to the spare item behind the rows what lies left of the chunk
+        int item[8], col = 8 * run - shift, cls, at;
+        {
+            const int c0 = RAGGED ? max(col, 0) : col;
+            const int idx = (int)fdiv((uint32_t)c0, p.div_sd);
+            cls = c0 - idx * p.sd;
+            at = cls * pitch + idx;
+        }
+        auto next_col = [&]() __attribute__((always_inline)) {
+            const bool wrap = ++cls == p.sd;
+            at += wrap ? 1 - (p.sd - 1) * pitch : pitch;
+            cls = wrap ? 0 : cls;
+        };
+        const int spare = (int)(reinterpret_cast<u32x4 *>(smem) + p.chg * (p.P1 + p.P2) - lds0);
+#pragma unroll
+        for (int px = 0; px < 8; ++px) {
+            const bool there = !RAGGED || col + px >= 0;
+            item[px] = there ? corr_slot(at, sg) : spare;
+            if (there) next_col();
+        }
+
+        auto commit = [&](int chi0, int ng) __attribute__((always_inline)) {
+            if ((chi0 + ng) * 8 > p.C) {                              // uniform: the last pass, where channels are missing
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const bool ok = (chi0 + sg) * 8 + c < p.C;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[c][j] = ok ? v[c][j] : 0u;
+                }
+            }
+            if (sg >= ng) return;
+#pragma unroll
+            for (int px = 0; px < 8; ++px) {
+                const uint32_t sel = (px & 1) ? 0x07060302u : 0x05040100u;
+                u32x4 d;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) d[q] = __builtin_amdgcn_perm(v[2 * q + 1][px >> 1], v[2 * q][px >> 1], sel);
+                lds0[item[px]] = d;
+            }
+        };
+
+        // this lane's operand positions: pixel (lane & 15) of block (class c, sub-block s) and the
+        // columns q = pixel0 - R*sd + sd*j of the same class, j = 16*nb + (lane & 15); positions
+        // past the staged ones are clamped (their products are never stored)
+        int apos[BPW], bpos[BPW][NB];
+#pragma unroll
+        for (int t = 0; t < BPW; ++t) {
+            const uint32_t bl = (uint32_t)min(wave + 4 * t, p.nblk - 1);
+            const uint32_t s = fdiv(bl, p.div_sd);
+            const uint32_t c = bl - s * (uint32_t)p.sd;
+            apos[t] = corr_slot(min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1), kg);
+            const uint32_t ec = (uint32_t)(p.lead - p.R * p.sd) + c;
+            const uint32_t ei = fdiv(ec, p.div_sd);
+            const uint32_t cls2 = ec - ei * (uint32_t)p.sd;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                bpos[t][nb] = corr_slot(min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1), kg);
+        }
+
         // groups of the pass that starts at chi0, padded to whole reduction steps (the padding is staged as zeros)
         auto groups_of = [&](int chi0) { return min(p.chg, ((p.nchi - chi0) + 3) & ~3); };
         for (int chi0 = 0; chi0 < p.nchi; chi0 += p.chg) {
