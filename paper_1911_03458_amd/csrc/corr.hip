@@ -43,17 +43,18 @@ __device__ __forceinline__ u32x4 load16(const uint8_t *src)
 }
 
 // Where item `at` (a pixel's eight channels, 16 bytes) of channel group g lies in its staged row.  The lanes of a write are
-// eight items apart, two bank groups of the sixteen: each run of eight is rotated by its place and its group.  (80 channels on
-// 64x58, +-4: 6.6 -> 5.9 us.)
+// eight items apart, two bank groups of the sixteen: with ROT each run of eight is rotated by its place and its group.
+template <bool ROT>
 __device__ __forceinline__ int corr_slot(int at, int g)
 {
-    return (at & ~7) | ((at + (at >> 3) + g) & 7);
+    return ROT ? (at & ~7) | ((at + (at >> 3) + g) & 7) : at;
 }
 
 static_assert(CORR_XB == 1, "a thread stages one unit a pass");
 
-// NB = 16-column blocks of the second row per pixel block, BPW = pixel blocks per wavefront, RAGGED = W % 8 != 0.
-template <int NB, int BPW, bool RAGGED>
+// NB = 16-column blocks of the second row per pixel block, BPW = pixel blocks per wavefront, RAGGED = W % 8 != 0.  ROT: the
+// plan's choice (CorrParams::rot); what it costs where it does not pay are the instructions, so an instance of its own.
+template <int NB, int BPW, bool RAGGED, bool ROT>
 __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const uint16_t *__restrict__ x1,
                                                        const uint16_t *__restrict__ x2, uint16_t *__restrict__ y)
 {
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
 #pragma unroll
         for (int px = 0; px < 8; ++px) {
             const bool there = !RAGGED || col + px >= 0;
-            item[px] = there ? corr_slot(at, sg) : spare;
+            item[px] = there ? corr_slot<ROT>(at, sg) : spare;
             if (there) next_col();
         }
 
@@ -176,13 +177,13 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
             const uint32_t bl = (uint32_t)min(wave + 4 * t, p.nblk - 1);
             const uint32_t s = fdiv(bl, p.div_sd);
             const uint32_t c = bl - s * (uint32_t)p.sd;
-            apos[t] = corr_slot(min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1), kg);
+            apos[t] = corr_slot<ROT>(min((int)c * p.pitch1 + 16 * (int)s + l16, p.P1 - 1), kg);
             const uint32_t ec = (uint32_t)(p.lead - p.R * p.sd) + c;
             const uint32_t ei = fdiv(ec, p.div_sd);
             const uint32_t cls2 = ec - ei * (uint32_t)p.sd;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-                bpos[t][nb] = corr_slot(min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1), kg);
+                bpos[t][nb] = corr_slot<ROT>(min((int)cls2 * p.pitch2 + (int)ei + 16 * (int)s + 16 * nb + l16, p.P2 - 1), kg);
         }
 
         // groups of the pass that starts at chi0, padded to whole reduction steps (the padding is staged as zeros)
@@ -200,10 +201,10 @@ __global__ __launch_bounds__(256, 4) void merit_corr_mfma(CorrParams p, const ui
                 const uint4 *ap = a1l + kg * p.P1;
                 const uint4 *bp = a2l + kg * p.P2;
                 for (int ks = 0; ks < ng; ks += 4) {              // (four groups on: rotated by four)
-                    const half8 a = __builtin_bit_cast(half8, ap[ks * p.P1 + (apos[t] ^ (ks & 4))]);
+                    const half8 a = __builtin_bit_cast(half8, ap[ks * p.P1 + (apos[t] ^ (ROT ? ks & 4 : 0))]);
                     half8 bq[NB];
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) bq[nb] = __builtin_bit_cast(half8, bp[ks * p.P2 + (bpos[t][nb] ^ (ks & 4))]);
+                    for (int nb = 0; nb < NB; ++nb) bq[nb] = __builtin_bit_cast(half8, bp[ks * p.P2 + (bpos[t][nb] ^ (ROT ? ks & 4 : 0))]);
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
                         acc[t][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bq[nb], acc[t][nb], 0, 0, 0);
@@ -242,15 +243,15 @@ size_t corr_lds_bytes(const CorrParams &p)
     return ((size_t)p.chg * (p.P1 + p.P2) + 1) * 16;      // and the spare item (see the kernel)
 }
 
-template <int NB, int BPW, bool RAGGED>
+template <int NB, int BPW, bool RAGGED, bool ROT>
 static hipError_t launch_corr(const CorrParams &p, const void *x1, const void *x2, void *y, hipStream_t s,
                               uint32_t grid)
 {
     static std::atomic<int> raised{0};
-    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_corr_mfma<NB, BPW, RAGGED>), raised);
+    if (hipError_t e = raise_lds_limit_once(reinterpret_cast<const void *>(merit_corr_mfma<NB, BPW, RAGGED, ROT>), raised);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((merit_corr_mfma<NB, BPW, RAGGED>), dim3(grid), dim3(256), corr_lds_bytes(p), s, p,
+    hipLaunchKernelGGL((merit_corr_mfma<NB, BPW, RAGGED, ROT>), dim3(grid), dim3(256), corr_lds_bytes(p), s, p,
                        reinterpret_cast<const uint16_t *>(x1), reinterpret_cast<const uint16_t *>(x2),
                        reinterpret_cast<uint16_t *>(y));
     return hipGetLastError();
@@ -264,18 +265,20 @@ hipError_t launch_correlation(const CorrParams &p, const void *x1, const void *x
     const int bpw = (p.nblk + 3) / 4;
     if (bpw < 1 || bpw > 2) return hipErrorInvalidValue;
     const int v = p.nb * 2 + (bpw - 1);
-#define MERIT_CORR(RAGGED)                                              \
-    switch (v) {                                                        \
-    case 2: return launch_corr<1, 1, RAGGED>(p, x1, x2, y, s, gx);      \
-    case 3: return launch_corr<1, 2, RAGGED>(p, x1, x2, y, s, gx);      \
-    case 4: return launch_corr<2, 1, RAGGED>(p, x1, x2, y, s, gx);      \
-    case 5: return launch_corr<2, 2, RAGGED>(p, x1, x2, y, s, gx);      \
-    case 6: return launch_corr<3, 1, RAGGED>(p, x1, x2, y, s, gx);      \
-    case 7: return launch_corr<3, 2, RAGGED>(p, x1, x2, y, s, gx);      \
-    default: return hipErrorInvalidValue;                               \
+#define MERIT_CORR(RAGGED, ROT)                                              \
+    switch (v) {                                                             \
+    case 2: return launch_corr<1, 1, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    case 3: return launch_corr<1, 2, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    case 4: return launch_corr<2, 1, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    case 5: return launch_corr<2, 2, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    case 6: return launch_corr<3, 1, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    case 7: return launch_corr<3, 2, RAGGED, ROT>(p, x1, x2, y, s, gx);      \
+    default: return hipErrorInvalidValue;                                    \
     }
-    if (p.W % 8 != 0) MERIT_CORR(true)
-    MERIT_CORR(false)
+    if (p.W % 8 != 0 && p.rot) MERIT_CORR(true, true)
+    if (p.W % 8 != 0) MERIT_CORR(true, false)
+    if (p.rot) MERIT_CORR(false, true)
+    MERIT_CORR(false, false)
 #undef MERIT_CORR
 }
 

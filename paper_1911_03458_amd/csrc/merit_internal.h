@@ -367,7 +367,8 @@ struct CorrParams {
     int xq, xr;                 // grid / 8 and grid % 8: hardware workgroup id -> one contiguous band of work per XCD
     // staged rows are stored by residue class of the column modulo sd: position = class * pitch + column / sd
     int pitch1, P1;             // first tensor: positions per class (ceil(64/sd)), positions per channel group
-    int pitch2, P2;             // second tensor: ceil(cols2/sd), sd * pitch2
+    int pitch2, P2;             // second tensor: ceil(cols2/sd), sd * pitch2; P1 and P2 rounded up to whole runs of eight
+    int rot;                    // 1: the items of a run of eight are rotated (see corr_slot)
     int nsb, nblk;              // 16-pixel blocks per class, blocks per chunk (sd * nsb <= 8)
     int nb;                     // 16-column blocks of the second tensor per pixel block: ceil((16 + 2R) / 16)
     FastDiv div_n, div_xchunks, div_h, div_sd;

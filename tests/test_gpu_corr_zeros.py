@@ -17,6 +17,10 @@ CASES = [
     (1, 40, 6, 65, 5, 2),        # a last chunk of one pixel
     (2, 260, 5, 47, 3, 1),       # several passes
     (1, 24, 9, 191, 2, 5),
+    (1, 40, 6, 72, 5, 2),        # rows of whole units; up to 64 channels, and more
+    (2, 64, 5, 40, 4, 1),
+    (1, 72, 5, 64, 3, 1),
+    (1, 136, 7, 24, 6, 3),
 ]
 
 
