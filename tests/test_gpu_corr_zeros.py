@@ -42,3 +42,21 @@ def test_zeros(case):
     keep = np.broadcast_to((p1 != H // 2)[None, :, None, :, None], ref.shape)
     mag = oracle.correlation(np.abs(x1), np.abs(x2), R, sd).astype(np.float64)
     assert np.all((np.abs(y - ref) <= 2.0 ** -10 * np.abs(ref) + (C + 2) * 2.0 ** -23 * mag + 1e-7)[keep])
+
+
+@pytest.mark.parametrize("R,sd", [(1, 1), (3, 2), (5, 2), (2, 3), (3, 8), (9, 7), (15, 1)])
+def test_the_last_columns_of_a_chunk_before_the_last(R, sd):
+    """Rows of two and three chunks that end anywhere inside a unit: every column that a product needs is staged, whatever the
+    workgroup's LDS held before (infinities, from the call before)."""
+    C, H = 24, 6
+    rng = np.random.default_rng(R)
+    for W in [w for w in range(65, 137) if w % 8] + [191, 193]:
+        x1, x2 = (rng.standard_normal((1, C, H, W)).astype(np.float16) for _ in range(2))
+        plan = mb.merit_plan_correlation(1, C, H, W, R, sd)
+        assert plan.launch_info()["kernel"] == "merit_corr_mfma"
+        mb.merit_correlation(plan, *(torch.full((1, C, H, W), float("inf"), device="cuda").half() for _ in range(2)))
+        y = mb.merit_correlation(plan, torch.from_numpy(x1).cuda(), torch.from_numpy(x2).cuda()).cpu().numpy().astype(np.float64)
+        ref = oracle.correlation(x1, x2, R, sd).astype(np.float64)
+        mag = oracle.correlation(np.abs(x1), np.abs(x2), R, sd).astype(np.float64)
+        # one rounding to binary16 and fp32 sums of C products in another order
+        assert np.all(np.abs(y - ref) <= 2.0 ** -10 * np.abs(ref) + (C + 2) * 2.0 ** -23 * mag + 1e-7), W
