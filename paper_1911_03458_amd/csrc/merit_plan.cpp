@@ -1354,9 +1354,11 @@ merit_status derive_dw(merit_plan *pl)
     // Output rows of a thread: one as long as the launch fits the chip with it (a thread of four rows is a chain of 1.5 us
     // on a wavefront that has its SIMD to itself: 24 channels at 96x80, 5x5 / 2, 4.8 -> 3.0 us, 31x64x15x10 4.1 -> 2.8),
     // two up to 2000 workgroups of one row, where the rows that strips share start to count (7x336x9x83 5x5 6.8, 5.9, 7.9 us
-    // with one, two, four), four beyond (5x456x41x107 15.2, 13.7, 12.8); a row stride shares less.
-    const int64_t one_row = cdiv(planes * OH * units, 256);
-    int64_t lanes_rows = one_row <= (sw == 2 ? 1500 : 600) ? 1 : (one_row <= 2000 || sw == 2 ? 2 : 4);
+    // with one, two, four), four beyond (5x456x41x107 15.2, 13.7, 12.8).  A row stride shares fewer: two up to 4000
+    // workgroups of 5x5 windows (4x928x179x24 11.4 us, 12.1 with four; 181x10x192x57 16.7, 14.2; 16x501x73x665 305, 257), up
+    // to 15000 of 3x3 ones (11x341x251x22 15.2, 17.2; 60x5x317x762 36.4, 33.4; 95x60x143x126 51.4, 46.6).
+    const int64_t one_row = cdiv(planes * OH * units, 256), two_rows = sw == 1 ? 2000 : (kw == 5 ? 4000 : 15000);
+    int64_t lanes_rows = one_row <= (sw == 2 ? 1500 : 600) ? 1 : (one_row <= two_rows ? 2 : 4);
     auto lanes_fit = [&](int64_t t) {                    // the kernel's divisions
         const int64_t n = planes * cdiv(OH, t);
         return n * units < (1ll << 30) && fastdiv_ok(n * units + 256, units) && fastdiv_ok(n, cdiv(OH, t));

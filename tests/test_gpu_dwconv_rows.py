@@ -20,11 +20,23 @@ CASES = [
     (200, 3, 25, 5, 5, 1, 2, 2, 1),
     (200, 3, 33, 5, 3, 2, 1, 1, 1),       # three
     (1, 400, 2, 3, 5, 2, 4, 4, 1),
+    (41, 530, 13, 54, 5, 2, 2, 2, 4),     # four rows at stride 2, the last strip of three
 ]
 
 
 @pytest.mark.parametrize("case", CASES)
 def test_the_rows_of_a_thread(case):
+    _rows_of_a_thread(case)
+
+
+# large layers at stride 2, to either side of the lines (the plan alone)
+@pytest.mark.parametrize("case", [(4, 928, 179, 24, 5, 2, 2, 2, 2), (181, 10, 192, 57, 5, 2, 0, 0, 4), (11, 341, 251, 22, 3, 2, 1, 1, 2),
+                                  (60, 5, 317, 762, 3, 2, 1, 1, 4)])
+def test_the_rows_of_a_thread_at_stride_2(case):
+    _rows_of_a_thread(case)
+
+
+def _rows_of_a_thread(case):
     N, C, H, W, k, s, ph, pw, rows = case
     li = mb.merit_plan_conv2d_depthwise(N, C, H, W, k, k, s, s, ph, pw).launch_info()
     assert li["kernel"] == "merit_dwconv_lanes" and li["tile"][2] == rows, li
