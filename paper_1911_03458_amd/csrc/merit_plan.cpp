@@ -147,8 +147,13 @@ merit_status derive_pool(merit_plan *pl)
         const int64_t chunks = cdiv(OW, cols);
         // Output rows of a group.  2x2 windows share no rows, so one: 9x564x19x82 16.4 us with four, 11.4 with one, 29x158x145x23
         // 20.6 and 18.1 (1.13-2x over 40 layers; the tile kernel's 5x903x50x12 10.3 -> 5.1), 8x512x28x28 7.1 and 5.2,
-        // 64x512x28x28 26.7 and 22.9.
-        int64_t th = s1 ? 8 : (k2 ? 1 : 4);
+        // 64x512x28x28 26.7 and 22.9.  Four on the largest launches, 200000 wavefronts of one row and more, where a group's
+        // lanes have outputs for three quarters of them at most: 38x157x94x262 162 us, 189 with one, 1x311x1638x347 157 and
+        // 177, 204x15x705x34 87 and 97 (51x194x60x754, all lanes at work, 470 and 400; 203x284x228x10, 16 groups a
+        // wavefront, 170 and 149).
+        const int64_t row_waves = N * C * chunks * OH >> lg_shift;
+        const bool four = k2 && row_waves >= 200000 && lg_shift < 4 && 4 * OW <= 3 * chunks * (cols >> lg_shift);
+        int64_t th = s1 ? 8 : (k2 && !four ? 1 : 4);
         auto items_of = [&](int64_t t) { return N * C * chunks * cdiv(OH, t); };
         // the kernel's divisions, and the threads of a launch
         auto fits = [&](int64_t t) {

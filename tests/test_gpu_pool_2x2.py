@@ -22,7 +22,11 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES)
+# large launches, to either side of the line (the plan alone)
+LARGE = [(38, 157, 94, 262, 4), (204, 15, 705, 34, 4), (51, 194, 60, 754, 1), (203, 284, 228, 10, 1), (100, 15, 705, 34, 1)]
+
+
+@pytest.mark.parametrize("case", CASES + LARGE)
 def test_rows_of_a_group(case):
     N, C, H, W, rows = case
     li = mb.merit_plan_pool2d(N, C, H, W, 2, 2, 2, 2, 0, 0, 1).launch_info()
