@@ -21,10 +21,10 @@
 // that the row's end cuts ends with the row, which keeps every load inside the tensor.
 // What bounds it: not the matrix cores but a pass's chain of loads, LDS writes and barriers, and on 256 channels the rows
 // themselves, each of which 2R+1 workgroups stage.  So the loads go out together (with the zeroing beside them each waited
-// for its own round trip), only by lanes that have something to load, and the writes fall into all bank groups.  us a
-// launch, before -> with that: 256 channels at 64x64, +-5 at stride 2: 9.1 -> 7.5; 208 at 63x46, +-3: 8.0 -> 6.0; 80 at
-// 64x58, +-4: 6.2 -> 4.8; 40 at 33x18, +-3: 3.9 -> 3.9; 1.11x over 60 images of 16 to 64 pixels a side, of which one (48 at
-// 52x40, +-5) lost 6 %.
+// for its own round trip), only by lanes that have something to load, and on many channels the writes fall into all bank
+// groups.  us a launch of 20 in a graph, before -> with that: 256 channels at 64x64, +-5 at stride 2: 9.0 -> 7.3; 208 at
+// 63x46, +-3: 7.8 -> 5.9; 80 at 64x58, +-4: 6.1 -> 5.0; 48 at 52x40, +-5: 4.6 -> 4.4; 40 at 33x18, +-3: 3.8 -> 3.8; 1.12x
+// over 400 images of 8 to 150 pixels a side, of which six (the shortest launches, 3.5 us) lost 4 to 6 %.
 #include "merit_internal.h"
 
 namespace merit {

@@ -1485,8 +1485,8 @@ merit_status derive_corr(merit_plan *pl)
     p.pitch2 = (int)cdiv(p.cols2, sd); p.P2 = (int)round_up(sd * p.pitch2, 8);
     p.nsb = (int)cdiv(p.pitch1, 16); p.nblk = (int)(sd * p.nsb);
     p.nb = (int)cdiv(16 + 2 * R, 16);
-    // channel groups per pass: whole reduction steps of 4 groups, at most two staging units per
-    // thread, and about 40 KB so that four workgroups share a CU's LDS (measured best)
+    // channel groups per pass: whole reduction steps of 4 groups, at most CORR_XB staging units (one) per
+    // thread, and at most CORR_LDS_KB of them, so that several workgroups share a CU's LDS
     const int64_t per_g_full = chunk / 8 + p.cols2 / 8;
     const int64_t per_group = ((int64_t)p.P1 + p.P2) * 16;
     int64_t chg = (CORR_LDS_KB * 1024) / per_group;

@@ -16,15 +16,17 @@
 // Three forms (SepForm, merit_internal.h), chosen by the plan from the window and the number of tiles.  What bounds
 // them: on large frames the multiply-adds (9.9 us of 24 at k = 30 on 4x1080x1920, at the probe's rate), the LDS reads
 // and the memory of a tile one after the other, so they want many workgroups in different phases; on small ones the
-// chain of one tile, so they want it cut into many threads.  us a launch, one persistent form of 256 threads -> these:
+// chain of one tile, so they want it cut into many threads.  us a launch (18 in a graph, over three sets of buffers), one
+// persistent form of 256 threads that requested its next tile -> these:
 //   TILES       one tile a workgroup, no request ahead: six or seven workgroups a compute unit instead of three
-//               (4x1080x1920: k = 8 15.1 -> 13.6, 12 17.3 -> 15.5, 16 19.7 -> 17.0, 20 22.2 -> 19.4, 24 24.4 -> 21.9)
+//               (4x1080x1920: k = 3 12.7 -> 12.3, 8 14.9 -> 13.7, 12 17.0 -> 15.1, 16 19.4 -> 16.8, 20 21.7 -> 19.2, 24
+//               23.7 -> 21.6, 28 25.5 -> 25.3)
 //   PERSISTENT  k > 28, where 64 staged rows would be half halo: 96 rows, four workgroups a compute unit that walk the
-//               tiles (k = 30 25.2 -> 24.3; one tile a workgroup 24.4; 64 rows 26.6); and any window on more tiles than
+//               tiles (k = 30 23.7 -> 23.4, 32 24.5 -> 24.3; 64 rows 10 % more); and any window on more tiles than
 //               a launch has workgroups, or on request of more than 64 staged rows
-//   FEW         up to three tiles a compute unit: 512 threads, 2 x 2 patches (2x600x1280: k = 30 9.1 -> 8.3, 20 8.6 ->
-//               7.7, 8 5.7 -> 5.5; 380x936: 30 6.8 -> 4.6, 20 7.0 -> 4.6, 8 4.3 -> 3.9, 3 3.8 -> 3.6), and where the
-//               tiles do not fill the chip shorter ones (624x172: k = 20 6.5 -> 3.7, 4.2 on 44-row tiles; 8 4.0 -> 3.2)
+//   FEW         up to three tiles a compute unit: 512 threads, 2 x 2 patches (2x600x1280: k = 30 8.6 -> 7.9, 20 8.1 ->
+//               7.2; 380x936: 30 6.8 -> 4.4, 8 4.3 -> 3.6), and where the tiles do not fill the chip shorter ones
+//               (624x172: k = 20 6.6 -> 3.8, 0.5 more on 44-row tiles)
 //
 // The staged columns start at x0 - c4, c4 = k/2 rounded up to 4, so that (for W % 4 == 0) every
 // group of four staged columns is one aligned 16-byte run of the image, entirely inside it or

@@ -1139,8 +1139,9 @@ def test_sepfilter(mb, N, H, W, k, tile):
 
 @pytest.mark.parametrize("k", range(1, 33))
 def test_sepfilter_every_window_length(mb, k):
-    """Every window length is a kernel instantiation of its own (taps and windows unrolled):
-    each is checked on an image of three column tiles, the last ragged, two tiles down."""
+    """Every window length is a kernel instantiation of its own (taps and windows unrolled), one of
+    each form: here that of small frames, on an image of three column tiles, the last ragged, two
+    tiles down; test_gpu_sep_lengths.py has those of large frames."""
     N, H, W = 2, 101, 136
     rng = np.random.default_rng(4000 + k)
     x = rng.uniform(0, 255, (N, H, W)).astype(np.float32)
