@@ -1377,8 +1377,10 @@ merit_status derive_dw(merit_plan *pl)
         // 5x5 windows at stride 1 on small planes of odd width: the kernel for any window, with an output a thread.  Rows on
         // every second 2-byte boundary cost the other 0.4 us (2x14x18x7 3.43 against 3.84 us, 2x40x8x17 3.49, 3.72, 4x31x8x21
         // 3.57, 3.75, 8x70x11x7 3.77, 3.68; on even widths 3.4 to 4.1 against 3.2 to 3.5).  Elsewhere over 260 small layers
-        // it takes 0.96 to 1.83 of the other's time, 1.1 on average (1x24x9x14 3x3 / 2 2.75 against 2.67).
-        if (kw == 5 && sw == 1 && W % 2 == 1 && tile_rows * OW <= 256 && planes <= 512) lanes = false;
+        // it takes 0.96 to 1.83 of the other's time, 1.1 on average (1x24x9x14 3x3 / 2 2.75 against 2.67).  So with one and two
+        // columns, most of whose loaded units lie outside the row (1x95x29x1 5x5 / 2 3.46 against 4.21, 8x10x26x2 5x5 3.46,
+        // 4.07; 0.94 over 88 of them, 1.1 to 4 times the other's time from 1000 planes on).
+        if (planes <= 512 && (W <= 2 || (kw == 5 && sw == 1 && W % 2 == 1 && tile_rows * OW <= 256))) lanes = false;
     }
     if (lanes) {
         p.variant = DW_LANES;

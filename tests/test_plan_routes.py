@@ -106,6 +106,8 @@ def test_launch_info_names_the_kernel_that_runs():
     ((12, 144, 94, 24, 5, 5, 1, 1, 2, 2), "merit_dwconv_lanes"),    # 26.8, 7.8
     ((32, 512, 14, 14, 3, 3, 1, 1, 1, 1), "merit_dwconv_lanes"),    # 20.5, 6.8
     ((1, 8, 8, 4096, 3, 3, 1, 1, 0, 0), "merit_dwconv_lanes"),
+    ((8, 10, 26, 2, 5, 5, 1, 1, 2, 2), "merit_dwconv_tile"),        # 3.5, 4.1 on the other
+    ((1, 95, 29, 1, 5, 5, 2, 2, 2, 2), "merit_dwconv_tile"),        # 3.5, 4.2
 ])
 def test_depthwise_layers_take_the_faster_kernel(shape, kernel):
     assert mb.merit_plan_conv2d_depthwise(*shape).launch_info()["kernel"] == kernel
